@@ -14,6 +14,7 @@
 #include "decode_kernels.h"
 #include "prefill_kernels.h"
 #include "step_kernel.h"
+#include "prefill_gemm.h"
 #include "decode_batch_kernels.h"
 #include "sample_kernels.h"
 #include "train_kernels.h"
@@ -81,6 +82,9 @@ struct first_ctx {
   void *p_x = nullptr, *p_a = nullptr, *p_z = nullptr;
   bf16 *p_qh = nullptr, *p_ql = nullptr, *p_kc = nullptr, *p_vt = nullptr;   // matrix-core prefill attention operands
   bf16 *p_xh = nullptr, *p_xl = nullptr, *p_ah = nullptr, *p_al = nullptr, *p_zh = nullptr, *p_zl = nullptr;   // split activations (bf16 models)
+  bool w_aligned = false;                 // every matrix starts on 16 bytes (bf16 models): what k_pgemm's loads need
+  float* pg_part = nullptr;               // k_pgemm: partial tiles of the slices of K, 2 num_cu tiles of 64 x 128
+  unsigned* pg_cnt = nullptr;             //          arrival counters per tile (zero between launches)
   int p_tp = 0;                           // key pitch of p_vt / rows of p_kc (max_seq_len padded to the key tile)
   int prefill_flash = 1;                  // FIRST_OPT_PREFILL_ATTN
   float2* p_cs = nullptr;
@@ -627,32 +631,116 @@ int launch_gemm(first_ctx* c, hipStream_t st, int dtype, const void* A, const vo
   return FIRST_OK;
 }
 
-int launch_gemm_hl(first_ctx* c, hipStream_t st, const bf16* Ah, const bf16* Al, const void* W, float* C, int M, int N, int K,
-                   int acc) {
-  dim3 grid((N + GB_N - 1) / GB_N, (M + GB_M - 1) / GB_M);
-  if (M > GB_MS && (int)(grid.x * grid.y) <= device_cus()) {   // at most one 128-row tile per compute unit: use 64-row tiles
-    dim3 gs(grid.x, (M + GB_MS - 1) / GB_MS);
-    hipLaunchKernelGGL(k_gemm_nt_bf16_hl_s, gs, dim3(WG), 0, st, Ah, Al, reinterpret_cast<const bf16*>(W), C, M, N, K, acc);
-    HIPCHK(c, hipGetLastError());
-    return FIRST_OK;
+// Tile and number of K slices of a k_pgemm launch.  The estimate (in us) is fixed cost + K steps times the time of a step, summed
+// over the rounds the grid takes on the chip, fitted to a sweep over M = 16 .. 4000 and the projections of the 8B, 3B and 1B
+// geometries with weights that no cache holds (within 2 % of the best of all choices on average, 18 % at worst).  What the
+// numbers say: 128 x 256 does most work per operand byte (1.76 us per step of 8.4 Mflop on a compute unit) and wins once
+// it fills the chip in whole rounds; 64 x 256 with K shared by two groups of waves gives every compute unit a tile where
+// 128 x 256 would leave half of them idle (1024 x 4096 x 14336: 219 us against 323); a prompt of a few dozen rows is a
+// stream of weights, which takes 32-row tiles and K cut into slices until every compute unit has work (16 x 4096 x 14336:
+// 22 us with 6 slices, 67 with one).  Slices cost a trip of the partial tiles through memory, so they are not used beyond
+// two workgroups a compute unit.
+struct PgTile { int bm, bn, occ; double fix, full, one, red, red_ks, red_wg; };
+constexpr PgTile PG_TILES[4] = {{128, 256, 1, 9.3, 1.76, 1.29, 0, 0, 0},
+                                {64, 256, 1, 9.0, 1.05, 0.77, 0, 0, 0},
+                                {64, 128, 2, 3.5, 1.06, 0.79, 1.7, 0.8, 2.9},
+                                {32, 128, 2, 4.3, 0.69, 0.43, 0.6, 0.33, 1.2}};
+struct PgPlan { int tile = 0, ks = 1, gm = 0, gn = 0; };
+
+PgPlan pg_plan(int M, std::initializer_list<int> Ns, int K, bool gu, int num_cu) {
+  PgPlan best;
+  double best_t = 1e30;
+  const int steps = (K + PG_BK - 1) / PG_BK;
+  for (int t = 0; t < 4; ++t) {
+    const PgTile& T = PG_TILES[t];
+    const int cols = gu ? T.bn / 2 : T.bn, gm = (M + T.bm - 1) / T.bm;
+    int gn = 0;
+    for (int N : Ns) gn += (N + cols - 1) / cols;
+    for (int ks : {1, 2, 3, 4, 6, 8, 12}) {
+      const long long wgs = (long long)gm * gn * ks;
+      if (ks > 1 && (T.occ == 1 || wgs > 2 * num_cu || ks > steps)) break;
+      const long long rem = wgs % (num_cu * T.occ);
+      const bool pair = T.occ == 2 && rem > num_cu;               // the last round puts two workgroups on a compute unit
+      const double st = (steps + ks - 1) / ks;
+      double us = T.fix + st * (T.full * (wgs / (num_cu * T.occ) + (pair ? 1 : 0)) + T.one * (rem > 0 && !pair ? 1 : 0));
+      if (ks > 1) us += T.red + T.red_ks * ks + (wgs > num_cu ? T.red_wg * wgs / (2 * num_cu) : 0);
+      if (us < best_t) { best_t = us; best.tile = t; best.ks = ks; best.gm = gm; best.gn = gn; }
+    }
   }
-  hipLaunchKernelGGL(k_gemm_nt_bf16_hl, grid, dim3(WG), 0, st, Ah, Al, reinterpret_cast<const bf16*>(W), C, M, N, K, acc);
+  return best;
+}
+
+template <int BM, int BN, int WGM, int WGN, int KG, int S, bool GU, bool SPLIT>
+constexpr size_t pg_lds() { return (size_t)S * (2 * BM + BN) * PG_BK * 2; }
+template <bool GU>
+void launch_pgemm(hipStream_t st, const PgPlan& plan, const PgArgs& P) {
+  const dim3 grid((unsigned)(plan.gm * plan.gn * plan.ks));
+  switch (plan.tile) {
+    case 0: hipLaunchKernelGGL((k_pgemm<128, 256, 2, 4, 1, 2, GU, false>), grid, dim3(512), (pg_lds<128, 256, 2, 4, 1, 2, GU, false>()), st, P); break;
+    case 1: hipLaunchKernelGGL((k_pgemm<64, 256, 1, 4, 2, 3, GU, false>), grid, dim3(512), (pg_lds<64, 256, 1, 4, 2, 3, GU, false>()), st, P); break;
+    case 2: hipLaunchKernelGGL((k_pgemm<64, 128, 1, 4, 1, 2, GU, true>), grid, dim3(256), (pg_lds<64, 128, 1, 4, 1, 2, GU, true>()), st, P); break;
+    default: hipLaunchKernelGGL((k_pgemm<32, 128, 1, 4, 1, 3, GU, true>), grid, dim3(256), (pg_lds<32, 128, 1, 4, 1, 3, GU, true>()), st, P); break;
+  }
+}
+template <bool GU>
+hipError_t pg_set_lds() {
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pgemm<128, 256, 2, 4, 1, 2, GU, false>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)pg_lds<128, 256, 2, 4, 1, 2, GU, false>());
+  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pgemm<64, 256, 1, 4, 2, 3, GU, false>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)pg_lds<64, 256, 1, 4, 2, 3, GU, false>());
+  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pgemm<64, 128, 1, 4, 1, 2, GU, true>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)pg_lds<64, 128, 1, 4, 1, 2, GU, true>());
+  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pgemm<32, 128, 1, 4, 1, 3, GU, true>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)pg_lds<32, 128, 1, 4, 1, 3, GU, true>());
+  return e;
+}
+// k_pgemm's loads start on 16 bytes (K is a multiple of 8) and address a tile's rows with 31 bits.
+bool pg_fits(const first_ctx* c, int K) { return c->w_aligned && K <= (1 << 21); }
+
+PgArgs pg_args(const first_ctx* c, const PgPlan& plan, const bf16* Ah, const bf16* Al, int M, int K, int acc) {
+  PgArgs P{};
+  P.Ah = Ah; P.Al = Al; P.M = M; P.K = K; P.accumulate = acc; P.gm = plan.gm; P.gn = plan.gn; P.ks = plan.ks;
+  P.part = c->pg_part; P.cnt = c->pg_cnt;
+  return P;
+}
+
+// Up to three projections of the same split activations in one launch.
+int launch_gemm_hl_seg(first_ctx* c, hipStream_t st, const bf16* Ah, const bf16* Al, int M, int K, int acc, std::initializer_list<GemmSeg> list) {
+  if (pg_fits(c, K)) {
+    const GemmSeg* g = list.begin();
+    const PgPlan plan = list.size() == 3 ? pg_plan(M, {g[0].N, g[1].N, g[2].N}, K, false, c->num_cu) : pg_plan(M, {g[0].N}, K, false, c->num_cu);
+    PgArgs P = pg_args(c, plan, Ah, Al, M, K, acc);
+    for (const GemmSeg& s : list) P.seg[P.nseg++] = PgSeg{s.W, s.C, s.N, (s.N + PG_TILES[plan.tile].bn - 1) / PG_TILES[plan.tile].bn};
+    launch_pgemm<false>(st, plan, P);
+  } else {
+    GemmSegs segs{};
+    int blocks = 0;
+    for (const GemmSeg& g : list) {
+      GemmSeg s = g;
+      s.blocks = (g.N + GB_N - 1) / GB_N;
+      blocks += s.blocks;
+      segs.s[segs.n++] = s;
+    }
+    hipLaunchKernelGGL(k_gemm_nt_bf16_hl_seg, dim3(blocks, (M + GB_M - 1) / GB_M), dim3(WG), 0, st, Ah, Al, segs, M, K, acc);
+  }
   HIPCHK(c, hipGetLastError());
   return FIRST_OK;
 }
 
-// Up to three projections of the same split activations in one launch.
-int launch_gemm_hl_seg(first_ctx* c, hipStream_t st, const bf16* Ah, const bf16* Al, int M, int K, int acc,
-                       std::initializer_list<GemmSeg> list) {
-  GemmSegs segs{};
-  int blocks = 0;
-  for (const GemmSeg& g : list) {
-    GemmSeg s = g;
-    s.blocks = (g.N + GB_N - 1) / GB_N;
-    blocks += s.blocks;
-    segs.s[segs.n++] = s;
+int launch_gemm_hl(first_ctx* c, hipStream_t st, const bf16* Ah, const bf16* Al, const void* W, float* C, int M, int N, int K,
+                   int acc) {
+  return launch_gemm_hl_seg(c, st, Ah, Al, M, K, acc, {GemmSeg{reinterpret_cast<const bf16*>(W), C, N, 0}});
+}
+
+// Gate and up with SiLU(gate) * up in the epilogue, written split for the down projection.
+int launch_gemm_hl_gu(first_ctx* c, hipStream_t st, const bf16* Ah, const bf16* Al, const void* Wg, const void* Wu, bf16* zh, bf16* zl,
+                      int M, int F, int K) {
+  if (pg_fits(c, K)) {
+    const PgPlan plan = pg_plan(M, {F}, K, true, c->num_cu);
+    PgArgs P = pg_args(c, plan, Ah, Al, M, K, 0);
+    P.nseg = 1; P.seg[0] = PgSeg{reinterpret_cast<const bf16*>(Wg), nullptr, F, plan.gn}; P.Wu = reinterpret_cast<const bf16*>(Wu);
+    P.zh = zh; P.zl = zl;
+    launch_pgemm<true>(st, plan, P);
+  } else {
+    hipLaunchKernelGGL(k_gemm_nt_bf16_hl_gu, dim3((F + GB_N / 2 - 1) / (GB_N / 2), (M + GB_M - 1) / GB_M), dim3(WG), 0, st, Ah, Al,
+                       reinterpret_cast<const bf16*>(Wg), reinterpret_cast<const bf16*>(Wu), zh, zl, M, F, K);
   }
-  hipLaunchKernelGGL(k_gemm_nt_bf16_hl_seg, dim3(blocks, (M + GB_M - 1) / GB_M), dim3(WG), 0, st, Ah, Al, segs, M, K, acc);
   HIPCHK(c, hipGetLastError());
   return FIRST_OK;
 }
@@ -750,9 +838,7 @@ int prefill_one(first_ctx* c, int b, const int* ids, int T, float* hidden_out, f
     hipLaunchKernelGGL(k_rmsnorm_router<float>, dim3((T + WAVES - 1) / WAVES), dim3(WG), 0, st, c->p_H, l.g_mlp,
                        (const float*)nullptr, x, (float*)nullptr, T, D, d.rms_eps, hl ? c->p_xh : nullptr, hl ? c->p_xl : nullptr);
     if (hl) {        // SiLU(gate) * up in the GEMM's epilogue, written split for the down projection
-      hipLaunchKernelGGL(k_gemm_nt_bf16_hl_gu, dim3((F + GB_N / 2 - 1) / (GB_N / 2), (T + GB_M - 1) / GB_M), dim3(WG), 0, st, c->p_xh,
-                         c->p_xl, (const bf16*)l.wg, (const bf16*)l.wu, c->p_zh, c->p_zl, T, F, D);
-      HIPCHK(c, hipGetLastError());
+      if ((rc = launch_gemm_hl_gu(c, st, c->p_xh, c->p_xl, l.wg, l.wu, c->p_zh, c->p_zl, T, F, D))) return rc;
     } else {
       if ((rc = gemm(x, c->p_xh, c->p_xl, l.wg, c->p_g, F, D, 0))) return rc;
       if ((rc = gemm(x, c->p_xh, c->p_xl, l.wu, c->p_u, F, D, 0))) return rc;
@@ -918,6 +1004,13 @@ int first_create(const first_model_desc* desc, const first_weights* w, void* hip
   A(dev_alloc(c, &c->d_tagstate, (size_t)B * 8));
   A(dev_alloc(c, &c->d_layers, L)); A(dev_alloc(c, &c->d_done, (size_t)c->num_cu)); A(dev_alloc(c, &c->d_err, 4));
   A(dev_alloc(c, &c->d_tdbg, (size_t)(4 * L + 1) * SK_TSLOTS));
+  if (d.dtype == FIRST_DTYPE_BF16) {
+    A(dev_alloc(c, &c->pg_part, (size_t)2 * c->num_cu * 64 * 128)); A(dev_alloc(c, &c->pg_cnt, (size_t)2 * c->num_cu));
+    uintptr_t bits = reinterpret_cast<uintptr_t>(c->lm_head);
+    for (const LayerPtrs& l : c->layers)
+      for (const void* p : {l.wq, l.wk, l.wv, l.wo, l.wg, l.wu, l.wd}) bits |= reinterpret_cast<uintptr_t>(p);
+    c->w_aligned = bits % 16 == 0;
+  }
   if (rc == FIRST_OK) {
     std::vector<double> theta(c->half);
     for (int i = 0; i < c->half; ++i) theta[i] = std::pow((double)d.rope_base, -2.0 * i / d.head_dim);
@@ -925,6 +1018,11 @@ int first_create(const first_model_desc* desc, const first_weights* w, void* hip
     if (e == hipSuccess) e = hipMemset(c->d_attn_cnt, 0, (size_t)B * d.n_kv_heads * sizeof(unsigned));
     if (e == hipSuccess) e = hipMemset(c->d_head_cnt, 0, B * sizeof(unsigned));
     if (e == hipSuccess) e = hipMemset(c->d_len, 0, B * sizeof(int));
+    if (e == hipSuccess && c->pg_cnt) {
+      e = hipMemset(c->pg_cnt, 0, (size_t)2 * c->num_cu * sizeof(unsigned));
+      if (e == hipSuccess) e = pg_set_lds<false>();
+      if (e == hipSuccess) e = pg_set_lds<true>();
+    }
     if (e == hipSuccess) e = hipMemset(c->d_err, 0, 4 * sizeof(int));
     if (e == hipSuccess) e = reset_tagged_exchange(c);
     c->step_ok = step_kernel_fits(c);

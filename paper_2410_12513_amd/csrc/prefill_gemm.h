@@ -1,0 +1,325 @@
+// The projections of the prompt pass on the matrix cores: C[M, N] = (Ah + Al)[M, K] . W[N, K]^T with activations split
+// into two bf16 parts (see k_gemm_nt_bf16_split) and bf16 weights, fp32 accumulation.
+//
+// Both parts meet the same weight tile, so a K step costs 2 BM + BN rows of operands and 4 BM BN BK flops.  What bounds it
+// is the matrix cores once operands arrive without costing registers or instructions: a K step of 64 goes from global
+// memory straight into LDS (buffer loads with an LDS destination, 16 bytes a lane; the descriptor covers the tile's rows, so
+// rows past the end read as zeros and nothing is clamped), two steps in the ring, one barrier per step.  A row is 128 bytes
+// in LDS; its eight 16-byte chunks are permuted by (row / 2) % 8 - on the way in through the address each lane fetches - so
+// that the 32 rows a wave reads at one K offset spread over all banks.
+//
+// Measured, weights cold (matrix-core work, twice the useful flops): 1024 x 28672 x 4096 (gate + up of the 8B geometry) 425 us =
+// 1130 TFLOP/s with 128 x 256 tiles, 571 us with the earlier kernel (four waves of 64 x 64, operands through registers);
+// 1024 x 4096 x 14336 (down) 219 us = 1100 TFLOP/s with 64 x 256 tiles, 325 us before; the library's plain bf16 product of
+// the first shape runs at 1156 TFLOP/s, of 8192^3 at 1301.
+#pragma once
+#include "step_kernel.h"
+
+namespace first {
+
+constexpr int PG_BK = 64;                       // K step: one row of a tile is 128 bytes
+
+// 16 bytes per lane from (descriptor base + voff + soff) to LDS byte lds_off + 16 * lane.  No register is written: nothing
+// for the compiler to reuse too early; pg_wait / pg_barrier order it.
+typedef int i32x4_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void pg_load_lds(uint32_t lds_off, uint32_t voff, i32x4_t rsrc, uint32_t soff) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds_off), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+}
+__device__ __forceinline__ i32x4_t pg_rsrc(const void* p, uint32_t bytes) {
+  const uint64_t a = reinterpret_cast<uint64_t>(p);
+  i32x4_t r;
+  r[0] = __builtin_amdgcn_readfirstlane((int)(uint32_t)a);
+  r[1] = __builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32) & 0xffff);
+  r[2] = __builtin_amdgcn_readfirstlane((int)bytes);
+  r[3] = 0x00020000;
+  return r;
+}
+template <int N> __device__ __forceinline__ void pg_wait() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+__device__ __forceinline__ int pg_chunk(int row, int chunk) { return chunk ^ ((row >> 1) & 7); }
+
+// One launch: up to three weight matrices applied to the same activations, their column tiles one after the other.
+struct PgSeg { const bf16* W; float* C; int N; int tiles; };        // tiles = column tiles of this matrix
+struct PgArgs {
+  const bf16 *Ah, *Al;
+  PgSeg seg[3];
+  int nseg, M, K, accumulate;
+  const bf16* Wu;               // gate/up launch: seg[0].W = gate, this = up, N = d_ffn
+  bf16 *zh, *zl;                //   SiLU(gate) * up, split, [M, N]
+  int gm, gn;                   // row tiles, column tiles of all matrices together
+  int ks;                       // slices of K (1: none); more than one only in the shapes instantiated with SPLIT
+  float* part;                  // partial tiles of the slices, arrival counters per tile (zero between launches)
+  unsigned* cnt;
+};
+
+// BM x BN tile; KG groups of WGM x WGN waves over it, each group taking its share of every K step (KG = 2 gives a tile
+// that has a compute unit to itself a second wave per SIMD without smaller wave tiles: 64 KB of sums cross LDS at the end).
+// S: K steps in the LDS ring (three where they fit: with weights from HBM a third step in flight took 1024 x 4096 x 14336
+// from 266 to 223 us; two 64 x 128 workgroups on a compute unit hide each other's waits and have 64 KB each).
+// GU: the tile's BN weight rows are 32 (16 where a wave tile is 32 wide) gate rows and as many up rows in turn, so that
+// a gate value and its up value sit in the same lane (in lanes 16 apart).
+template <int BM, int BN, int WGM, int WGN, int KG, int S, bool GU, bool SPLIT>
+__global__ void __launch_bounds__(KG * WGM * WGN * 64, 2) k_pgemm(PgArgs P) {
+  constexpr int NW = KG * WGM * WGN, TM = BM / WGM, TN = BN / WGN, IM = TM / 32, JN = TN / 32, BK = PG_BK;
+  constexpr int IA = BM / 8 / NW, IB = BN / 8 / NW;        // 1 KB loads per wave and K step: each half of A; B
+  constexpr int GI = JN >= 2 ? 32 : 16;                    // gate / up interleave
+  static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0 && TM % 32 == 0 && TN % 32 == 0, "tile shape");
+  static_assert(!(SPLIT && KG > 1), "one of the two");
+  constexpr int STG = (2 * BM + BN) * BK * 2;              // LDS bytes of a K step
+  extern __shared__ __align__(16) char pg_smem[];
+  __shared__ int last_flag;
+  const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) void*)pg_smem;
+  const int tid = threadIdx.x, wave = uni(tid >> 6), lane = tid & 63;
+  const int K = P.K, M = P.M;
+
+  // Workgroup -> tile.  Consecutive workgroups go to the eight XCDs in turn; each XCD gets a contiguous run of tiles, in
+  // groups of eight row tiles with the row tiles of a column next to each other: what runs on an XCD at a time is a
+  // compact block of tiles whose operands its L2 holds (at 16384 x 28672 x 4096 column-major runs of all 128 row
+  // tiles cost 5 to 50 %, depending on the tile).
+  int id = blockIdx.x;
+  {
+    const int total = gridDim.x, per = total / 8, rem = total % 8, x = id % 8;
+    id = x * per + min(x, rem) + id / 8;
+  }
+  const int slice = SPLIT ? id % P.ks : 0;
+  if (SPLIT) id /= P.ks;
+  const int tile = id;
+  constexpr int GR = 8;
+  const int grp = id / (GR * P.gn), in = id - grp * GR * P.gn, grn = min(GR, P.gm - grp * GR);
+  const int m0 = (grp * GR + in % grn) * BM;
+  int ct = in / grn, si = 0;
+  if (!GU)
+    while (si + 1 < P.nseg && ct >= P.seg[si].tiles) { ct -= P.seg[si].tiles; ++si; }
+  const bf16* const W = P.seg[si].W;
+  float* const C = P.seg[si].C;
+  const int N = P.seg[si].N;
+  const int n0 = ct * (GU ? BN / 2 : BN);
+  const int rowsA = min(BM, M - m0), rowsB = min(GU ? BN / 2 : BN, N - n0);
+  const i32x4_t rh = pg_rsrc(P.Ah + (size_t)m0 * K, (uint32_t)rowsA * K * 2);
+  const i32x4_t rl = pg_rsrc(P.Al + (size_t)m0 * K, (uint32_t)rowsA * K * 2);
+  const i32x4_t rb = pg_rsrc(W + (size_t)n0 * K, (uint32_t)rowsB * K * 2);
+  const i32x4_t ru = GU ? pg_rsrc(P.Wu + (size_t)n0 * K, (uint32_t)rowsB * K * 2) : rb;
+
+  // byte offset of this lane's chunk in each of the wave's loads; lane -> (row of eight, slot), slot holds chunk pg_chunk
+  uint32_t va[IA], vb[IB];
+  const int lrow = lane >> 3;
+#pragma unroll
+  for (int i = 0; i < IA; ++i) {
+    const int r = (wave * IA + i) * 8 + lrow;
+    va[i] = (uint32_t)r * K * 2 + pg_chunk(r, lane & 7) * 16;
+  }
+#pragma unroll
+  for (int i = 0; i < IB; ++i) {
+    const int r = (wave * IB + i) * 8 + lrow;
+    const int src = GU ? (r / (2 * GI)) * GI + r % GI : r;               // (a load's eight rows lie in one block of gate or of up rows)
+    vb[i] = (uint32_t)src * K * 2 + pg_chunk(r, lane & 7) * 16;
+  }
+  const int nsteps = (K + BK - 1) / BK;
+  const int s0 = SPLIT ? nsteps * slice / P.ks : 0, s1 = SPLIT ? nsteps * (slice + 1) / P.ks : nsteps;
+  const int tail_chunks = (K % BK) / 8;                                   // chunks of the last step that exist (0: all)
+  auto issue = [&](int step) __attribute__((always_inline)) {
+    const uint32_t b = lds0 + (uint32_t)((step - s0) % S) * STG, so = (uint32_t)step * BK * 2;
+    const bool cut = tail_chunks != 0 && step == nsteps - 1;
+    auto off = [&](uint32_t v, int r) __attribute__((always_inline)) {   // past the row's end: out of the descriptor's range, reads as zeros
+      return cut && pg_chunk(r, lane & 7) >= tail_chunks ? 0x7ffffff0u : v;
+    };
+#pragma unroll
+    for (int i = 0; i < IA; ++i) {
+      const uint32_t v = off(va[i], (wave * IA + i) * 8 + lrow);
+      pg_load_lds(b + (wave * IA + i) * 1024, v, rh, so);
+      pg_load_lds(b + BM * BK * 2 + (wave * IA + i) * 1024, v, rl, so);
+    }
+#pragma unroll
+    for (int i = 0; i < IB; ++i) {
+      const int r8 = (wave * IB + i) * 8;
+      const bool up = GU && (r8 / GI) % 2 == 1;
+      const i32x4_t rs = up ? ru : rb;
+      pg_load_lds(b + 2 * BM * BK * 2 + (wave * IB + i) * 1024, off(vb[i], r8 + lrow), rs, so);
+    }
+  };
+  constexpr int NL = 2 * IA + IB;
+
+  floatx16_t acc[IM][JN];
+#pragma unroll
+  for (int i = 0; i < IM; ++i)
+#pragma unroll
+    for (int j = 0; j < JN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+  const int kg = wave / (WGM * WGN), w4 = wave % (WGM * WGN);
+  const int wm = (w4 / WGN) * TM, wn = (w4 % WGN) * TN;
+  const int lr = lane & 31, lg = lane >> 5;
+#pragma unroll
+  for (int s = 0; s < S - 1; ++s)
+    if (s0 + s < s1) issue(s0 + s);
+  for (int s = s0; s < s1; ++s) {
+    if (S == 2 || s + S - 2 >= s1) pg_wait<0>(); else pg_wait<NL * (S - 2)>();
+    lds_barrier();                             // step s is in LDS for every wave, and everyone is through with step s - 1
+    if (s + S - 1 < s1) issue(s + S - 1);
+    const char* base = pg_smem + ((s - s0) % S) * STG;
+    const char *sAh = base, *sAl = base + BM * BK * 2, *sB = base + 2 * BM * BK * 2;
+#pragma unroll
+    for (int kq = 0; kq < BK / KG; kq += 16) {
+      const int c = (kq + kg * (BK / KG)) / 8 + lg;
+      bf16x8_t ah[IM], al[IM], b[JN];
+#pragma unroll
+      for (int i = 0; i < IM; ++i) {
+        const int r = wm + i * 32 + lr, o = r * BK * 2 + pg_chunk(r, c) * 16;
+        ah[i] = *reinterpret_cast<const bf16x8_t*>(sAh + o);
+        al[i] = *reinterpret_cast<const bf16x8_t*>(sAl + o);
+      }
+#pragma unroll
+      for (int j = 0; j < JN; ++j) {
+        const int r = wn + j * 32 + lr;
+        b[j] = *reinterpret_cast<const bf16x8_t*>(sB + r * BK * 2 + pg_chunk(r, c) * 16);
+      }
+      // low halves first, then high halves: two products into the same accumulator are never issued back to back
+#pragma unroll
+      for (int i = 0; i < IM; ++i)
+#pragma unroll
+        for (int j = 0; j < JN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[i], b[j], acc[i][j], 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < IM; ++i)
+#pragma unroll
+        for (int j = 0; j < JN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[i], b[j], acc[i][j], 0, 0, 0);
+    }
+  }
+
+  if constexpr (KG == 2) {                     // the second group's sums reach the first through the operand LDS
+    static_assert((size_t)(NW / 2) * IM * JN * 4096 <= (size_t)S * STG, "sums fit the ring");
+    float* red = reinterpret_cast<float*>(pg_smem) + (size_t)w4 * IM * JN * 1024 + lane;
+    lds_barrier();
+    if (kg == 1) {
+#pragma unroll
+      for (int i = 0; i < IM; ++i)
+#pragma unroll
+        for (int j = 0; j < JN; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) red[((i * JN + j) * 16 + r) * 64] = acc[i][j][r];
+    }
+    lds_barrier();
+    if (kg == 1) return;
+#pragma unroll
+    for (int i = 0; i < IM; ++i)
+#pragma unroll
+      for (int j = 0; j < JN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] += red[((i * JN + j) * 16 + r) * 64];
+  }
+  if constexpr (SPLIT) {
+    // Slices of K: every workgroup stores its partial tile (accumulator order, 16 bytes a lane, write-through), counts
+    // itself in, and the last one adds the slices in slice order - the sum does not depend on who is last.
+    if (P.ks > 1) {
+      constexpr size_t WF = (size_t)IM * JN * 1024;                      // floats of one wave's partial tile
+      // (Stores the compiler knows, so that it sees that they read what the last MFMA is still writing, and without a scalar
+      // offset: with one it takes the data registers for free at once, and overwriting them in the next instruction put
+      // wrong values into one of the four words now and then.)
+      const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
+          uni(P.part + (((size_t)tile * P.ks + slice) * NW + wave) * WF), (short)0, (int)(WF * 4), 0x00020000);
+#pragma unroll
+      for (int i = 0; i < IM; ++i)
+#pragma unroll
+        for (int j = 0; j < JN; ++j)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const u32x4_t v = {__float_as_uint(acc[i][j][4 * q]), __float_as_uint(acc[i][j][4 * q + 1]),
+                               __float_as_uint(acc[i][j][4 * q + 2]), __float_as_uint(acc[i][j][4 * q + 3])};
+            __builtin_amdgcn_raw_buffer_store_b128(v, rw, ((i * JN + j) * 4 + q) * 1024 + lane * 16, 0, 17);   // sc0 sc1
+          }
+      pg_wait<0>();
+      __syncthreads();
+      if (tid == 0) {
+        const unsigned old = __hip_atomic_fetch_add(P.cnt + tile, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int last = old == (unsigned)(P.ks - 1);
+        if (last) __hip_atomic_store(P.cnt + tile, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        last_flag = last;
+      }
+      __syncthreads();
+      if (!last_flag) return;
+      const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+          uni(P.part + (size_t)tile * P.ks * NW * WF), (short)0, (int)((size_t)P.ks * NW * WF * 4), 0x00020000);
+#pragma unroll
+      for (int i = 0; i < IM; ++i)
+#pragma unroll
+        for (int j = 0; j < JN; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+#pragma unroll 2
+      for (int q = 0; q < P.ks; ++q) {
+        const int so = (int)(((size_t)q * NW + wave) * WF * 4);
+#pragma unroll
+        for (int i = 0; i < IM; ++i)
+#pragma unroll
+          for (int j = 0; j < JN; ++j)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+              const u32x4_t x = __builtin_amdgcn_raw_buffer_load_b128(rs, ((i * JN + j) * 4 + v) * 1024 + lane * 16, so, 17);   // sc0 sc1
+#pragma unroll
+              for (int e = 0; e < 4; ++e) acc[i][j][4 * v + e] += __uint_as_float(x[e]);
+            }
+      }
+    }
+  }
+
+  // D layout of the 32x32 MFMA: lane -> column (lane & 31); register r -> row 8 (r / 4) + 4 (lane / 32) + r % 4
+  if constexpr (GU) {
+    auto put = [&](int row, int col, float g, float u) __attribute__((always_inline)) {
+      if (row >= M || col >= N) return;
+      const float z = siluf(g) * u;
+      const bf16 h = from_f32<bf16>(z);
+      P.zh[(size_t)row * N + col] = h;
+      P.zl[(size_t)row * N + col] = from_f32<bf16>(z - to_f32(h));
+    };
+#pragma unroll
+    for (int i = 0; i < IM; ++i) {
+      if constexpr (JN >= 2) {
+#pragma unroll
+        for (int j = 0; j < JN; j += 2)
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            put(m0 + wm + i * 32 + 8 * (r >> 2) + 4 * lg + (r & 3), n0 + (wn + j * 32) / 2 + lr, acc[i][j][r], acc[i][j + 1][r]);
+      } else {                                 // columns 0..15 gate, 16..31 up: each half finishes eight of the sixteen rows
+#pragma unroll
+        for (int r = 0; r < 16; r += 2) {
+          const bool hi = (lane & 16) != 0;
+          const float give = hi ? acc[i][0][r] : acc[i][0][r + 1], keep = hi ? acc[i][0][r + 1] : acc[i][0][r];
+          const float got = __shfl_xor(give, 16, 64);
+          const int rr = hi ? r + 1 : r;
+          put(m0 + wm + i * 32 + 8 * (rr >> 2) + 4 * lg + (rr & 3), n0 + wn / 2 + (lane & 15), hi ? got : keep, hi ? keep : got);
+        }
+      }
+    }
+  } else {
+    // What is added to is requested as a whole before any of it is used: a load, a wait and a store per element were up to
+    // 64 memory round trips in a row, 50 to 80 us of the 4096 x 14336 projection of 1024 rows.
+    float old[IM][JN][16];
+    if (P.accumulate) {
+#pragma unroll
+      for (int i = 0; i < IM; ++i)
+#pragma unroll
+        for (int j = 0; j < JN; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            old[i][j][r] = C[(size_t)min(m0 + wm + i * 32 + 8 * (r >> 2) + 4 * lg + (r & 3), M - 1) * N + min(n0 + wn + j * 32 + lr, N - 1)];
+    } else {
+#pragma unroll
+      for (int i = 0; i < IM; ++i)
+#pragma unroll
+        for (int j = 0; j < JN; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) old[i][j][r] = 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < IM; ++i)
+#pragma unroll
+      for (int j = 0; j < JN; ++j) {
+        const int col = n0 + wn + j * 32 + lr;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int row = m0 + wm + i * 32 + 8 * (r >> 2) + 4 * lg + (r & 3);
+          if (row < M && col < N) C[(size_t)row * N + col] = old[i][j][r] + acc[i][j][r];
+        }
+      }
+  }
+}
+
+}  // namespace first

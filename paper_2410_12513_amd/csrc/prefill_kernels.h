@@ -485,21 +485,6 @@ __device__ __forceinline__ void gemm_nt_bf16_hl_tile(const bf16* __restrict__ Ah
     }
 }
 
-__global__ void __launch_bounds__(WG) k_gemm_nt_bf16_hl(const bf16* __restrict__ Ah, const bf16* __restrict__ Al,
-                                                        const bf16* __restrict__ W, float* __restrict__ C, int M, int N,
-                                                        int K, int accumulate) {
-  gemm_nt_bf16_hl_tile<GB_M, GB_N, 2, 2>(Ah, Al, W, C, M, N, K, accumulate, blockIdx.y * GB_M, blockIdx.x * GB_N);
-}
-
-// The same with 64-row tiles, for shapes whose 128 x 128 tiles would leave every compute unit a single workgroup
-// (one wave per SIMD, nothing to overlap a barrier or a load with): twice the workgroups, two per compute unit.
-constexpr int GB_MS = 64;
-__global__ void __launch_bounds__(WG) k_gemm_nt_bf16_hl_s(const bf16* __restrict__ Ah, const bf16* __restrict__ Al,
-                                                          const bf16* __restrict__ W, float* __restrict__ C, int M, int N,
-                                                          int K, int accumulate) {
-  gemm_nt_bf16_hl_tile<GB_MS, GB_N, 2, 2>(Ah, Al, W, C, M, N, K, accumulate, blockIdx.y * GB_MS, blockIdx.x * GB_N);
-}
-
 // Several weight matrices applied to the same activations in one launch (Q, K and V; gate and up): the column
 // blocks of the segments follow each other in blockIdx.x, each segment with its own matrix, output and width.
 // A matrix of 1024 rows alone is 64 workgroups at 1024 tokens - a quarter of the compute units; together the
