@@ -487,6 +487,75 @@ template <typename WT> __global__ void __launch_bounds__(WG) k_head(DecParams p)
   phase_head<WT>(p, blockIdx.x, gridDim.x, smem_f);
 }
 
+// RMSNorm(h; g_final) of the sequences blockIdx.x .., in the order k_head_rows stages them: the same arithmetic as the LM
+// head's own prologue.  x [n][D].
+template <typename WT>
+__global__ void __launch_bounds__(WG) k_head_norm(DecParams p, float* __restrict__ x) {
+  extern __shared__ __align__(16) float smem_f[];
+  stage_x<Vec<WT>::N>(smem_f, smem_f + p.D, p.h + (size_t)blockIdx.x * p.D, p.D, p.g_final, p.eps);
+  for (int k = threadIdx.x; k < p.D; k += WG) x[(size_t)blockIdx.x * p.D + k] = smem_f[k];
+}
+
+// logits of NS sequences b0 .. in ONE pass over the LM head (the prompts of a batch): the normed fp32 vectors stand in LDS, a
+// wave takes four rows at a time and multiplies them with all of them.  Same fp32 products and the same order of
+// additions per sequence as phase_head.  Bound: HBM, the matrix once per NS sequences instead of once per sequence;
+// sixteen waves share the staged vectors, since with 96 KB of them a compute unit has room for one workgroup only
+// (128256 x 3072, eight sequences: 8 x 193 us one by one, 670 with four waves, 182 with sixteen).
+constexpr int HR_THREADS = 1024, HR_WAVES = HR_THREADS / 64;
+template <typename WT, int NS>
+__global__ void __launch_bounds__(HR_THREADS) k_head_rows(DecParams p, const float* __restrict__ x, int b0, int n) {
+  extern __shared__ __align__(16) float smem_f[];
+  constexpr int VEC = Vec<WT>::N, R = 4;
+  const int D = p.D, lane = threadIdx.x & 63;
+  for (int j = 0; j < NS; ++j)
+    for (int k = threadIdx.x * 4; k < D; k += HR_THREADS * 4)
+      *reinterpret_cast<float4*>(smem_f + (size_t)j * D + k) = *reinterpret_cast<const float4*>(x + (size_t)(b0 + min(j, n - 1)) * D + k);
+  __syncthreads();
+  const WT* W = reinterpret_cast<const WT*>(p.lm_head);
+  const int full = D / (64 * VEC), ktail = full * 64 * VEC + lane * VEC;
+  for (int r0 = (blockIdx.x * HR_WAVES + (threadIdx.x >> 6)) * R; r0 < p.V; r0 += gridDim.x * HR_WAVES * R) {
+    const WT* rp[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) rp[i] = W + (size_t)min(r0 + i, p.V - 1) * D;
+    float acc[R][NS];
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+      for (int j = 0; j < NS; ++j) acc[i][j] = 0.f;
+    auto step = [&](int k) __attribute__((always_inline)) {
+      float wv[R][VEC];
+#pragma unroll
+      for (int i = 0; i < R; ++i) load_vec(rp[i] + k, wv[i]);
+#pragma unroll
+      for (int j = 0; j < NS; ++j) {
+        const float* xs = smem_f + (size_t)j * D;
+        float xv[VEC];
+        if (VEC == 8) {
+          const float4 a = *reinterpret_cast<const float4*>(xs + ((k >> 3) << 2)), b = *reinterpret_cast<const float4*>(xs + (D >> 1) + ((k >> 3) << 2));
+          xv[0] = a.x; xv[1] = a.y; xv[2] = a.z; xv[3] = a.w;
+          xv[4 % VEC] = b.x; xv[5 % VEC] = b.y; xv[6 % VEC] = b.z; xv[7 % VEC] = b.w;
+        } else {
+          const float4 a = *reinterpret_cast<const float4*>(xs + k);
+          xv[0] = a.x; xv[1] = a.y; xv[2] = a.z; xv[3] = a.w;
+        }
+#pragma unroll
+        for (int i = 0; i < R; ++i)
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) acc[i][j] = fmaf(wv[i][e], xv[e], acc[i][j]);
+      }
+    };
+    for (int c = 0; c < full; ++c) step((c * 64 + lane) * VEC);
+    if (ktail < D) step(ktail);
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+      for (int j = 0; j < NS; ++j) {
+        const float s = wave_sum(acc[i][j]);
+        if (lane == 0 && j < n && r0 + i < p.V) p.logits[(size_t)(b0 + j) * p.V + r0 + i] = s;
+      }
+  }
+}
+
 // Stand-alone mat-vec (unit tests and kernel-level roofline): y (+)= W x.
 template <typename WT> __global__ void __launch_bounds__(WG)
 k_gemv(const WT* __restrict__ W, const float* __restrict__ x, float* __restrict__ y, int n, int K, int accumulate) {

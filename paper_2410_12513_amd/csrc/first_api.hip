@@ -15,6 +15,7 @@
 #include "prefill_kernels.h"
 #include "step_kernel.h"
 #include "prefill_gemm.h"
+#include "prefill_attn.h"
 #include "decode_batch_kernels.h"
 #include "sample_kernels.h"
 #include "train_kernels.h"
@@ -83,9 +84,13 @@ struct first_ctx {
   bf16 *p_qh = nullptr, *p_ql = nullptr, *p_kc = nullptr, *p_vt = nullptr;   // matrix-core prefill attention operands
   bf16 *p_xh = nullptr, *p_xl = nullptr, *p_ah = nullptr, *p_al = nullptr, *p_zh = nullptr, *p_zl = nullptr;   // split activations (bf16 models)
   bool w_aligned = false;                 // every matrix starts on 16 bytes (bf16 models): what k_pgemm's loads need
-  float* pg_part = nullptr;               // k_pgemm: partial tiles of the slices of K, 2 num_cu tiles of 64 x 128
+  float* pg_part = nullptr;               // k_pgemm: partial tiles of the slices of K, four for each of at most num_cu tiles of 64 x 128
   unsigned* pg_cnt = nullptr;             //          arrival counters per tile (zero between launches)
-  int p_tp = 0;                           // key pitch of p_vt / rows of p_kc (max_seq_len padded to the key tile)
+  int p_rows = 0;                         // rows of the prefill workspace: prompts of a batch go through it in groups of at most this many rows
+  int p_tp = 0;                           // padded rows of p_kc / p_vt (every prompt of a group starts at a multiple of PACK_PAD)
+  int* d_off = nullptr;                   // [max_batch + 1] first row of every prompt of the call, behind the last one the total; then the
+                                          // same in padded rows (uploaded together with the page tables, right behind them)
+  std::vector<int> h_off;                 // their host copy
   int prefill_flash = 1;                  // FIRST_OPT_PREFILL_ATTN
   float2* p_cs = nullptr;
   // soft-skip forward (first_soft_forward; allocated at its first call)
@@ -104,7 +109,7 @@ struct first_ctx {
   int kv_slots = 0, slices_used = 0;
   std::vector<int> layer_slice;
   std::vector<std::vector<uint8_t>> has_kv;   // [seq][layer]: the sequence's prompt KV of that layer was stored
-  uint8_t* h_keep = nullptr;                  // pinned: one router decision read back per layer while eliding
+  uint8_t* h_keep = nullptr;                  // pinned: the group's router decisions of a layer, read back while eliding
   hipEvent_t ev_keep = nullptr;
   // persistent whole-step kernel (bf16, one live sequence)
   LayerDev* d_layers = nullptr;
@@ -633,22 +638,32 @@ int launch_gemm(first_ctx* c, hipStream_t st, int dtype, const void* A, const vo
 
 // Tile and number of K slices of a k_pgemm launch.  The estimate (in us) is fixed cost + K steps times the time of a step, summed
 // over the rounds the grid takes on the chip, fitted to a sweep over M = 16 .. 4000 and the projections of the 8B, 3B and 1B
-// geometries with weights that no cache holds (within 2 % of the best of all choices on average, 18 % at worst).  What the
+// geometries with weights that no cache holds (within 1 % of the best of all choices on average, 15 % at worst).  What the
 // numbers say: 128 x 256 does most work per operand byte (1.76 us per step of 8.4 Mflop on a compute unit) and wins once
-// it fills the chip in whole rounds; 64 x 256 with K shared by two groups of waves gives every compute unit a tile where
-// 128 x 256 would leave half of them idle (1024 x 4096 x 14336: 219 us against 323); a prompt of a few dozen rows is a
+// it fills the chip in whole rounds; 64 x 256 gives every compute unit a tile where 128 x 256 would leave half of them
+// idle (1024 x 4096 x 14336: 233 us against 323; 260 with 64 x 128); a prompt of a few dozen rows is a
 // stream of weights, which takes 32-row tiles and K cut into slices until every compute unit has work (16 x 4096 x 14336:
-// 22 us with 6 slices, 67 with one).  Slices cost a trip of the partial tiles through memory, so they are not used beyond
+// 28 us with four slices, 67 with one).  Slices cost a trip of the partial tiles through memory, so they are not used beyond
 // two workgroups a compute unit.
 struct PgTile { int bm, bn, occ; double fix, full, one, red, red_ks, red_wg; };
 constexpr PgTile PG_TILES[4] = {{128, 256, 1, 9.3, 1.76, 1.29, 0, 0, 0},
-                                {64, 256, 1, 9.0, 1.05, 0.77, 0, 0, 0},
-                                {64, 128, 2, 3.5, 1.06, 0.79, 1.7, 0.8, 2.9},
-                                {32, 128, 2, 4.3, 0.69, 0.43, 0.6, 0.33, 1.2}};
-struct PgPlan { int tile = 0, ks = 1, gm = 0, gn = 0; };
+                                {64, 256, 1, 6.5, 1.07, 0.83, 0, 0, 0},
+                                {64, 128, 2, 3.3, 1.15, 0.78, 1.9, 0.3, 3.2},
+                                {32, 128, 2, 4.3, 0.75, 0.46, 0.8, 0.2, 0}};
+struct PgPlan { int tile = 0, ks = 1, gm = 0, gn = 0, seg = 1; };
+
+// Segments of K (see k_pgemm): four where a launch over few rows would leave compute units without a tile - fewer than 64
+// column tiles - and K is long enough to be worth cutting (eight steps a segment).  A property of the matrices alone, so that a prompt's results do
+// not depend on what shares its launch.
+int pg_segments(std::initializer_list<int> Ns, int K, bool gu) {
+  int cols = 0;
+  for (int N : Ns) cols += N;
+  return !gu && cols <= 8192 && K >= 32 * PG_BK ? 4 : 1;
+}
 
 PgPlan pg_plan(int M, std::initializer_list<int> Ns, int K, bool gu, int num_cu) {
   PgPlan best;
+  best.seg = pg_segments(Ns, K, gu);
   double best_t = 1e30;
   const int steps = (K + PG_BK - 1) / PG_BK;
   for (int t = 0; t < 4; ++t) {
@@ -656,9 +671,9 @@ PgPlan pg_plan(int M, std::initializer_list<int> Ns, int K, bool gu, int num_cu)
     const int cols = gu ? T.bn / 2 : T.bn, gm = (M + T.bm - 1) / T.bm;
     int gn = 0;
     for (int N : Ns) gn += (N + cols - 1) / cols;
-    for (int ks : {1, 2, 3, 4, 6, 8, 12}) {
+    for (int ks : {1, 2, 4}) {
       const long long wgs = (long long)gm * gn * ks;
-      if (ks > 1 && (T.occ == 1 || wgs > 2 * num_cu || ks > steps)) break;
+      if (ks > 1 && (T.occ == 1 || best.seg == 1 || wgs > 2 * num_cu)) break;
       const long long rem = wgs % (num_cu * T.occ);
       const bool pair = T.occ == 2 && rem > num_cu;               // the last round puts two workgroups on a compute unit
       const double st = (steps + ks - 1) / ks;
@@ -670,28 +685,26 @@ PgPlan pg_plan(int M, std::initializer_list<int> Ns, int K, bool gu, int num_cu)
   return best;
 }
 
-template <int BM, int BN, int WGM, int WGN, int KG, int S, bool GU, bool SPLIT>
-constexpr size_t pg_lds() { return (size_t)S * (2 * BM + BN) * PG_BK * 2; }
-template <bool GU>
-void launch_pgemm(hipStream_t st, const PgPlan& plan, const PgArgs& P) {
+template <int BM, int BN, int S> constexpr int pg_lds() { return S * (2 * BM + BN) * PG_BK * 2; }
+template <bool GU, int SEG>
+void launch_pgemm_seg(hipStream_t st, const PgPlan& plan, const PgArgs& P) {
   const dim3 grid((unsigned)(plan.gm * plan.gn * plan.ks));
-  switch (plan.tile) {
-    case 0: hipLaunchKernelGGL((k_pgemm<128, 256, 2, 4, 1, 2, GU, false>), grid, dim3(512), (pg_lds<128, 256, 2, 4, 1, 2, GU, false>()), st, P); break;
-    case 1: hipLaunchKernelGGL((k_pgemm<64, 256, 1, 4, 2, 3, GU, false>), grid, dim3(512), (pg_lds<64, 256, 1, 4, 2, 3, GU, false>()), st, P); break;
-    case 2: hipLaunchKernelGGL((k_pgemm<64, 128, 1, 4, 1, 2, GU, true>), grid, dim3(256), (pg_lds<64, 128, 1, 4, 1, 2, GU, true>()), st, P); break;
-    default: hipLaunchKernelGGL((k_pgemm<32, 128, 1, 4, 1, 3, GU, true>), grid, dim3(256), (pg_lds<32, 128, 1, 4, 1, 3, GU, true>()), st, P); break;
-  }
+  if (plan.tile == 0) hipLaunchKernelGGL((k_pgemm<128, 256, 2, 4, 2, GU, false, SEG>), grid, dim3(512), (pg_lds<128, 256, 2>()), st, P);
+  else if (plan.tile == 2) hipLaunchKernelGGL((k_pgemm<64, 128, 1, 4, 2, GU, true, SEG>), grid, dim3(256), (pg_lds<64, 128, 2>()), st, P);
+  else if (plan.tile == 3) hipLaunchKernelGGL((k_pgemm<32, 128, 1, 4, 3, GU, true, SEG>), grid, dim3(256), (pg_lds<32, 128, 3>()), st, P);
+  else hipLaunchKernelGGL((k_pgemm<64, 256, 2, 4, 3, GU, false, SEG>), grid, dim3(512), (pg_lds<64, 256, 3>()), st, P);
 }
-template <bool GU>
+template <bool GU, int SEG>
 hipError_t pg_set_lds() {
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pgemm<128, 256, 2, 4, 1, 2, GU, false>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)pg_lds<128, 256, 2, 4, 1, 2, GU, false>());
-  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pgemm<64, 256, 1, 4, 2, 3, GU, false>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)pg_lds<64, 256, 1, 4, 2, 3, GU, false>());
-  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pgemm<64, 128, 1, 4, 1, 2, GU, true>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)pg_lds<64, 128, 1, 4, 1, 2, GU, true>());
-  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pgemm<32, 128, 1, 4, 1, 3, GU, true>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)pg_lds<32, 128, 1, 4, 1, 3, GU, true>());
+  auto set = [](const void* fn, int lds) { return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds); };
+  hipError_t e = set(reinterpret_cast<const void*>(&k_pgemm<128, 256, 2, 4, 2, GU, false, SEG>), pg_lds<128, 256, 2>());
+  if (e == hipSuccess) e = set(reinterpret_cast<const void*>(&k_pgemm<64, 128, 1, 4, 2, GU, true, SEG>), pg_lds<64, 128, 2>());
+  if (e == hipSuccess) e = set(reinterpret_cast<const void*>(&k_pgemm<32, 128, 1, 4, 3, GU, true, SEG>), pg_lds<32, 128, 3>());
+  if (e == hipSuccess) e = set(reinterpret_cast<const void*>(&k_pgemm<64, 256, 2, 4, 3, GU, false, SEG>), pg_lds<64, 256, 3>());
   return e;
 }
-// k_pgemm's loads start on 16 bytes (K is a multiple of 8) and address a tile's rows with 31 bits.
-bool pg_fits(const first_ctx* c, int K) { return c->w_aligned && K <= (1 << 21); }
+// k_pgemm's loads start on 16 bytes (K is a multiple of 8), and it addresses the rows of a tile with 31 bits.
+bool pg_fits(const first_ctx* c, int N, int K) { return c->w_aligned && K <= (1 << 21) && N <= (1 << 21); }
 
 PgArgs pg_args(const first_ctx* c, const PgPlan& plan, const bf16* Ah, const bf16* Al, int M, int K, int acc) {
   PgArgs P{};
@@ -702,12 +715,12 @@ PgArgs pg_args(const first_ctx* c, const PgPlan& plan, const bf16* Ah, const bf1
 
 // Up to three projections of the same split activations in one launch.
 int launch_gemm_hl_seg(first_ctx* c, hipStream_t st, const bf16* Ah, const bf16* Al, int M, int K, int acc, std::initializer_list<GemmSeg> list) {
-  if (pg_fits(c, K)) {
-    const GemmSeg* g = list.begin();
+  const GemmSeg* g = list.begin();
+  if (pg_fits(c, std::max({g[0].N, g[list.size() / 2].N, g[list.size() - 1].N}), K)) {
     const PgPlan plan = list.size() == 3 ? pg_plan(M, {g[0].N, g[1].N, g[2].N}, K, false, c->num_cu) : pg_plan(M, {g[0].N}, K, false, c->num_cu);
     PgArgs P = pg_args(c, plan, Ah, Al, M, K, acc);
     for (const GemmSeg& s : list) P.seg[P.nseg++] = PgSeg{s.W, s.C, s.N, (s.N + PG_TILES[plan.tile].bn - 1) / PG_TILES[plan.tile].bn};
-    launch_pgemm<false>(st, plan, P);
+    if (plan.seg == 4) launch_pgemm_seg<false, 4>(st, plan, P); else launch_pgemm_seg<false, 1>(st, plan, P);
   } else {
     GemmSegs segs{};
     int blocks = 0;
@@ -731,12 +744,12 @@ int launch_gemm_hl(first_ctx* c, hipStream_t st, const bf16* Ah, const bf16* Al,
 // Gate and up with SiLU(gate) * up in the epilogue, written split for the down projection.
 int launch_gemm_hl_gu(first_ctx* c, hipStream_t st, const bf16* Ah, const bf16* Al, const void* Wg, const void* Wu, bf16* zh, bf16* zl,
                       int M, int F, int K) {
-  if (pg_fits(c, K)) {
+  if (pg_fits(c, F, K)) {
     const PgPlan plan = pg_plan(M, {F}, K, true, c->num_cu);
     PgArgs P = pg_args(c, plan, Ah, Al, M, K, 0);
     P.nseg = 1; P.seg[0] = PgSeg{reinterpret_cast<const bf16*>(Wg), nullptr, F, plan.gn}; P.Wu = reinterpret_cast<const bf16*>(Wu);
     P.zh = zh; P.zl = zl;
-    launch_pgemm<true>(st, plan, P);
+    launch_pgemm_seg<true, 1>(st, plan, P);
   } else {
     hipLaunchKernelGGL(k_gemm_nt_bf16_hl_gu, dim3((F + GB_N / 2 - 1) / (GB_N / 2), (M + GB_M - 1) / GB_M), dim3(WG), 0, st, Ah, Al,
                        reinterpret_cast<const bf16*>(Wg), reinterpret_cast<const bf16*>(Wu), zh, zl, M, F, K);
@@ -745,32 +758,36 @@ int launch_gemm_hl_gu(first_ctx* c, hipStream_t st, const bf16* Ah, const bf16* 
   return FIRST_OK;
 }
 
-// Prompt attention on the matrix cores: operand preparation (query split, key gather, value
-// transpose out of the cache pages) and the tiled kernel.
-void launch_attn_flash(first_ctx* c, hipStream_t st, const bf16* pool, const int* pt, int T) {
+// Prompt attention of a group on the matrix cores.
+template <int HD>
+void launch_attn_prompt(first_ctx* c, hipStream_t st, bf16* pool, const PromptPack& pk, int padded, int T_min, int T_max) {
   const first_model_desc& d = c->d;
-  const size_t nq_all = (size_t)T * c->nq;
-  hipLaunchKernelGGL(k_split_bf16, dim3((unsigned)std::min<size_t>((nq_all + WG - 1) / WG, 16384)), dim3(WG), 0, st, c->p_q,
-                     c->p_qh, c->p_ql, nq_all);
-  hipLaunchKernelGGL(k_kv_gather, dim3((T + 31) / 32, d.n_kv_heads), dim3(WG), 0, st, pool, c->page_elems, pt, c->p_kc,
-                     c->p_vt, T, c->p_tp, d.n_kv_heads, d.head_dim, d.kv_page_tokens);
-  const dim3 grid((T + WAVES * FA_QW - 1) / (WAVES * FA_QW), d.n_q_heads);
-  if (d.head_dim == 128)
-    hipLaunchKernelGGL(k_attn_flash<128>, grid, dim3(WG), 0, st, c->p_qh, c->p_ql, c->p_kc, c->p_vt, c->p_ah, c->p_al, T, c->p_tp,
-                       d.n_q_heads, d.n_kv_heads);
-  else
-    hipLaunchKernelGGL(k_attn_flash<64>, grid, dim3(WG), 0, st, c->p_qh, c->p_ql, c->p_kc, c->p_vt, c->p_ah, c->p_al, T, c->p_tp,
-                       d.n_q_heads, d.n_kv_heads);
+  const float qscale = 1.0f / std::sqrt((float)d.head_dim);
+  hipLaunchKernelGGL(k_rope_split<HD>, dim3(padded / 32, d.n_q_heads + 2 * d.n_kv_heads), dim3(WG), 0, st, c->p_q, c->p_k, c->p_v, c->p_cs, pk,
+                     pool, c->page_elems, c->p_qh, c->p_ql, c->p_kc, c->p_vt, d.n_q_heads, d.n_kv_heads, padded, d.kv_page_tokens, qscale);
+  // 64 queries a workgroup and the keys shared by two waves for the shorter prompts, 128 queries a workgroup for the others
+  // (chosen by the prompt's own length: what shares the launch does not change a prompt's bits)
+  const int wide = padded / 128 * d.n_q_heads;
+  if (T_max >= FA_WIDE_FROM)
+    hipLaunchKernelGGL((k_attn_prompt<HD, 4, 1>), dim3(wide), dim3(WG), 4 * FA_TILE * HD * 2, st, c->p_qh, c->p_ql, c->p_kc, c->p_vt, c->p_ah,
+                       c->p_al, pk, padded, d.n_q_heads, d.n_kv_heads);
+  if (T_min < FA_WIDE_FROM)
+    hipLaunchKernelGGL((k_attn_prompt<HD, 2, 2>), dim3(2 * wide), dim3(WG), 4 * FA_TILE * HD * 2, st, c->p_qh, c->p_ql, c->p_kc, c->p_vt,
+                       c->p_ah, c->p_al, pk, padded, d.n_q_heads, d.n_kv_heads);
 }
 
-// Prefill of one sequence: T prompt tokens at ids, all layers, routers scored on the way.
+// Prompt pass of sequences b0 .. b0 + n - 1, whose ids follow each other at ids: all layers on the packed rows, routers scored on
+// the way.  soft: the soft-skip pass (training side).
 template <typename WT>
-int prefill_one(first_ctx* c, int b, const int* ids, int T, float* hidden_out, float* logits_out, int* token_out,
-                bool soft = false) {
+int prefill_group(first_ctx* c, int b0, int n, const int* ids, float* hidden_out, bool soft = false) {
   const first_model_desc& d = c->d;
   hipStream_t st = c->stream;
-  const int D = d.d_model, F = d.d_ffn, L = d.n_layers, hd = d.head_dim, P = d.kv_page_tokens;
-  const int* pt = c->d_page_table + (size_t)b * c->max_pages;
+  const int D = d.d_model, F = d.d_ffn, L = d.n_layers, hd = d.head_dim, P = d.kv_page_tokens, Bm = d.max_batch;
+  const int* h_off = c->h_off.data() + b0;
+  const int R = h_off[n] - h_off[0], padded = h_off[Bm + 1 + n] - h_off[Bm + 1];
+  int T_max = 0, T_min = R;
+  for (int j = 0; j < n; ++j) { T_max = std::max(T_max, h_off[j + 1] - h_off[j]); T_min = std::min(T_min, h_off[j + 1] - h_off[j]); }
+  const PromptPack pk{c->d_off + b0, c->d_off + Bm + 1 + b0, n, b0, c->d_page_table, c->max_pages};
   const int QB = std::max(1, 64 / c->G);
   const float qscale = 1.0f / std::sqrt((float)hd);
   const size_t kpitch = (size_t)hd * sizeof(WT) + 4;
@@ -779,30 +796,30 @@ int prefill_one(first_ctx* c, int b, const int* ids, int T, float* hidden_out, f
   float* x = reinterpret_cast<float*>(c->p_x);
   float* a = reinterpret_cast<float*>(c->p_a);
   float* z = reinterpret_cast<float*>(c->p_z);
+  const bool hl = d.dtype == FIRST_DTYPE_BF16;   // activations leave their producers split for the matrix cores
+  float* rho = c->d_rho + (size_t)b0 * L;
+  uint8_t* mask = c->d_mask + (size_t)b0 * L;
 
-  hipLaunchKernelGGL(k_embed_rows<WT>, dim3(T), dim3(WG), 0, st, ids, reinterpret_cast<const WT*>(c->embed), c->p_H, D,
-                     d.vocab);
-  hipLaunchKernelGGL(k_rope_table, dim3((T * c->half + WG - 1) / WG), dim3(WG), 0, st, c->d_theta, c->p_cs, T, c->half);
+  hipLaunchKernelGGL(k_embed_rows<WT>, dim3(R), dim3(WG), 0, st, ids, reinterpret_cast<const WT*>(c->embed), c->p_H, D, d.vocab);
+  hipLaunchKernelGGL(k_rope_table, dim3((T_max * c->half + WG - 1) / WG), dim3(WG), 0, st, c->d_theta, c->p_cs, T_max, c->half);
   for (int i = 0; i < L; ++i) {
     const LayerPtrs& l = c->layers[i];
     // router i reads the stream entering layer i, in the same pass as the attention norm
-    const bool hl = d.dtype == FIRST_DTYPE_BF16;   // activations leave their producers split for the matrix cores
-    hipLaunchKernelGGL(k_rmsnorm_router<float>, dim3((T + WAVES - 1) / WAVES), dim3(WG), 0, st, c->p_H, l.g_attn,
-                       c->router + (size_t)i * D, x, c->p_sig, T, D, d.rms_eps, hl ? c->p_xh : nullptr, hl ? c->p_xl : nullptr);
-    hipLaunchKernelGGL(k_router_reduce, dim3(1), dim3(WG), 0, st, c->p_sig, T, c->d_rho + (size_t)b * L + i,
-                       c->d_mask + (size_t)b * L + i);
+    hipLaunchKernelGGL(k_rmsnorm_router<float>, dim3((R + WAVES - 1) / WAVES), dim3(WG), 0, st, c->p_H, l.g_attn,
+                       c->router + (size_t)i * D, x, c->p_sig, R, D, d.rms_eps, hl ? c->p_xh : nullptr, hl ? c->p_xl : nullptr);
+    hipLaunchKernelGGL(k_router_reduce, dim3(n), dim3(WG), 0, st, c->p_sig, pk.off, rho + i, mask + i, L);
     if (soft)            // the stream entering the layer, for H = Hprev + rho (phi(Hprev))
-      HIPCHK(c, hipMemcpyAsync(c->p_Hs, c->p_H, (size_t)T * D * sizeof(float), hipMemcpyDeviceToDevice, st));
-    if (c->kv_elide && !soft) {   // the decision is known before the layer stores anything (Section 4.1): fetch it while Q/K/V run
-      HIPCHK(c, hipMemcpyAsync(c->h_keep, c->d_mask + (size_t)b * L + i, 1, hipMemcpyDeviceToHost, st));
+      HIPCHK(c, hipMemcpyAsync(c->p_Hs, c->p_H, (size_t)R * D * sizeof(float), hipMemcpyDeviceToDevice, st));
+    if (c->kv_elide && !soft) {   // the decisions are known before the layer stores anything (Section 4.1): fetch them while Q/K/V run
+      HIPCHK(c, hipMemcpy2DAsync(c->h_keep, 1, mask + i, L, 1, n, hipMemcpyDeviceToHost, st));
       HIPCHK(c, hipEventRecord(c->ev_keep, st));
     }
     int rc;
     auto gemm = [&](const float* A32, const bf16* Ah, const bf16* Al, const void* W, float* C, int N, int K, int acc) {
-      return hl ? launch_gemm_hl(c, st, Ah, Al, W, C, T, N, K, acc) : launch_gemm(c, st, d.dtype, A32, W, C, T, N, K, acc, true);
+      return hl ? launch_gemm_hl(c, st, Ah, Al, W, C, R, N, K, acc) : launch_gemm(c, st, d.dtype, A32, W, C, R, N, K, acc, true);
     };
     if (hl) {
-      if ((rc = launch_gemm_hl_seg(c, st, c->p_xh, c->p_xl, T, D, 0,
+      if ((rc = launch_gemm_hl_seg(c, st, c->p_xh, c->p_xl, R, D, 0,
                                    {GemmSeg{(const bf16*)l.wq, c->p_q, c->nq, 0}, GemmSeg{(const bf16*)l.wk, c->p_k, c->nkv, 0},
                                     GemmSeg{(const bf16*)l.wv, c->p_v, c->nkv, 0}})))
         return rc;
@@ -811,56 +828,117 @@ int prefill_one(first_ctx* c, int b, const int* ids, int T, float* hidden_out, f
       if ((rc = gemm(x, c->p_xh, c->p_xl, l.wk, c->p_k, c->nkv, D, 0))) return rc;
       if ((rc = gemm(x, c->p_xh, c->p_xl, l.wv, c->p_v, c->nkv, D, 0))) return rc;
     }
-    if (c->kv_elide && !soft) {
-      HIPCHK(c, hipEventSynchronize(c->ev_keep));
-      if (*c->h_keep && c->layer_slice[i] < 0) {
+    if (c->kv_elide && !soft) HIPCHK(c, hipEventSynchronize(c->ev_keep));
+    for (int j = 0; j < n; ++j) {
+      if (c->kv_elide && !soft && c->h_keep[j] && c->layer_slice[i] < 0) {
         if (c->slices_used >= c->kv_slots)
           return fail(c, FIRST_ERR_CAPACITY, "first_prefill_route: the routers keep more layers than kv_layer_slots");
         c->layer_slice[i] = c->slices_used++;
       }
+      c->has_kv[b0 + j][i] = c->layer_slice[i] >= 0;   // stored from the first sequence on that keeps the layer
     }
-    c->has_kv[b][i] = c->layer_slice[i] >= 0;
     WT* pool = reinterpret_cast<WT*>(kv_base(c, i));   // a layer without a slice lends its prompt K/V to the scratch slice
-    hipLaunchKernelGGL(k_rope_kvwrite<WT>, dim3(T), dim3(WG), 0, st, c->p_q, c->p_k, c->p_v, c->p_cs, pt, pool,
-                       c->page_elems, d.n_q_heads, d.n_kv_heads, hd, P, qscale);
-    if (c->p_qh && c->prefill_flash) {
-      launch_attn_flash(c, st, reinterpret_cast<const bf16*>(pool), pt, T);
-    } else {
-      hipLaunchKernelGGL((k_attn_prefill<float, WT>), dim3((T + QB - 1) / QB, d.n_kv_heads), dim3(WG), lds_attn, st, c->p_q, a,
-                         pt, pool, c->page_elems, T, d.n_q_heads, d.n_kv_heads, hd, P, QB);
+    bool flash = false;
+    if constexpr (sizeof(WT) == 2) {
+      flash = c->p_qh && c->prefill_flash;
+      if (flash && hd == 128) launch_attn_prompt<128>(c, st, pool, pk, padded, T_min, T_max);
+      else if (flash) launch_attn_prompt<64>(c, st, pool, pk, padded, T_min, T_max);
+    }
+    if (!flash) {
+      hipLaunchKernelGGL(k_rope_kvwrite<WT>, dim3(R), dim3(WG), 0, st, c->p_q, c->p_k, c->p_v, c->p_cs, pk, pool,
+                         c->page_elems, d.n_q_heads, d.n_kv_heads, hd, P, qscale);
+      for (int j = 0; j < n; ++j) {
+        const int T = h_off[j + 1] - h_off[j];
+        const size_t row = (size_t)(h_off[j] - h_off[0]) * c->nq;
+        hipLaunchKernelGGL((k_attn_prefill<float, WT>), dim3((T + QB - 1) / QB, d.n_kv_heads), dim3(WG), lds_attn, st, c->p_q + row, a + row,
+                           c->d_page_table + (size_t)(b0 + j) * c->max_pages, pool, c->page_elems, T, d.n_q_heads, d.n_kv_heads, hd, P, QB);
+      }
       if (hl) {
-        const size_t n = (size_t)T * c->nq;
-        hipLaunchKernelGGL(k_split_bf16, dim3((unsigned)std::min<size_t>((n + WG - 1) / WG, 16384)), dim3(WG), 0, st, a, c->p_ah,
-                           c->p_al, n);
+        const size_t cnt = (size_t)R * c->nq;
+        hipLaunchKernelGGL(k_split_bf16, dim3((unsigned)std::min<size_t>((cnt + WG - 1) / WG, 16384)), dim3(WG), 0, st, a, c->p_ah,
+                           c->p_al, cnt);
       }
     }
     if ((rc = gemm(a, c->p_ah, c->p_al, l.wo, c->p_H, D, c->nq, 1))) return rc;
-    hipLaunchKernelGGL(k_rmsnorm_router<float>, dim3((T + WAVES - 1) / WAVES), dim3(WG), 0, st, c->p_H, l.g_mlp,
-                       (const float*)nullptr, x, (float*)nullptr, T, D, d.rms_eps, hl ? c->p_xh : nullptr, hl ? c->p_xl : nullptr);
+    hipLaunchKernelGGL(k_rmsnorm_router<float>, dim3((R + WAVES - 1) / WAVES), dim3(WG), 0, st, c->p_H, l.g_mlp,
+                       (const float*)nullptr, x, (float*)nullptr, R, D, d.rms_eps, hl ? c->p_xh : nullptr, hl ? c->p_xl : nullptr);
     if (hl) {        // SiLU(gate) * up in the GEMM's epilogue, written split for the down projection
-      if ((rc = launch_gemm_hl_gu(c, st, c->p_xh, c->p_xl, l.wg, l.wu, c->p_zh, c->p_zl, T, F, D))) return rc;
+      if ((rc = launch_gemm_hl_gu(c, st, c->p_xh, c->p_xl, l.wg, l.wu, c->p_zh, c->p_zl, R, F, D))) return rc;
     } else {
       if ((rc = gemm(x, c->p_xh, c->p_xl, l.wg, c->p_g, F, D, 0))) return rc;
       if ((rc = gemm(x, c->p_xh, c->p_xl, l.wu, c->p_u, F, D, 0))) return rc;
+      const unsigned sm_grid = (unsigned)std::min<size_t>(((size_t)R * F + WG - 1) / WG, 65536);
+      hipLaunchKernelGGL(k_silu_mul<float>, dim3(sm_grid), dim3(WG), 0, st, c->p_g, c->p_u, z, (size_t)R * F);
     }
-    const unsigned sm_grid = (unsigned)std::min<size_t>(((size_t)T * F + WG - 1) / WG, 65536);
-    if (!hl) hipLaunchKernelGGL(k_silu_mul<float>, dim3(sm_grid), dim3(WG), 0, st, c->p_g, c->p_u, z, (size_t)T * F);
     if ((rc = gemm(z, c->p_zh, c->p_zl, l.wd, c->p_H, D, F, 1))) return rc;
-    if (soft)
-      hipLaunchKernelGGL(k_soft_blend, dim3((unsigned)std::min<size_t>(((size_t)T * D + WG - 1) / WG, 4096)), dim3(WG), 0, st,
-                         c->p_H, c->p_Hs, c->d_rho + (size_t)b * L + i, (size_t)T * D);
+    if (soft) hipLaunchKernelGGL(k_soft_blend, dim3(R), dim3(WG), 0, st, c->p_H, c->p_Hs, rho + i, L, pk.off, n, D);
   }
-  if (soft) {
+  if (!soft)         // last positions -> decode residual slots (+ optional copy out)
+    hipLaunchKernelGGL(k_last_rows, dim3(n), dim3(WG), 0, st, c->p_H, pk.off, c->d_h + (size_t)b0 * D,
+                       hidden_out ? hidden_out + (size_t)b0 * D : nullptr, c->d_len + b0, D);
+  HIPCHK(c, hipGetLastError());
+  return FIRST_OK;
+}
+
+// First-token logits and tokens of sequences 0 .. B - 1 from their residual slots.  One sequence: the decode head.  More: one
+// pass over the LM head for up to eight of them (as many as have room in LDS), argmax over the logits.
+constexpr size_t HEAD_ROWS_LDS = 128 * 1024;
+template <typename WT, int NS>
+void launch_head_rows(first_ctx* c, DecParams p, int b0, int n) {
+  const size_t lds = (size_t)NS * c->d.d_model * sizeof(float);
+  const int need = (c->d.vocab + 4 * HR_WAVES - 1) / (4 * HR_WAVES);
+  hipLaunchKernelGGL((k_head_rows<WT, NS>), dim3(std::min(need, c->num_cu)), dim3(HR_THREADS), lds, c->stream, p,
+                     reinterpret_cast<const float*>(c->p_x), b0, n);
+}
+template <typename WT>
+int enqueue_first_tokens(first_ctx* c, int B, float* logits_out, int* token_out) {
+  DecParams p = base_params(c, 0, 1);
+  const int fit = (int)(HEAD_ROWS_LDS / sizeof(float) / c->d.d_model);
+  if (B == 1 || fit < 2) {
+    for (int b = 0; b < B; ++b) { p.b = b; enqueue_head<WT>(c, p, logits_out, token_out, 0); }
     HIPCHK(c, hipGetLastError());
     return FIRST_OK;
   }
-  // last position -> decode residual slot of this sequence (+ optional copy out), first token
-  hipLaunchKernelGGL(k_copy_f32, dim3((D + WG - 1) / WG), dim3(WG), 0, st, c->p_H + (size_t)(T - 1) * D,
-                     c->d_h + (size_t)b * D, hidden_out ? hidden_out + (size_t)b * D : nullptr, D);
-  hipLaunchKernelGGL(k_set_int, dim3(1), dim3(1), 0, st, c->d_len + b, T);
-  DecParams p = base_params(c, b, 1);
-  enqueue_head<WT>(c, p, logits_out, token_out, 0);
+  p.logits = logits_out ? logits_out : c->d_logits_own; p.token_out = token_out;
+  hipLaunchKernelGGL(k_head_norm<WT>, dim3(B), dim3(WG), ((size_t)c->d.d_model + WAVES) * sizeof(float), c->stream, p, reinterpret_cast<float*>(c->p_x));
+  for (int b = 0; b < B;) {
+    const int n = std::min(B - b, fit >= 8 ? 8 : fit >= 4 ? 4 : 2);
+    if (n > 4) launch_head_rows<WT, 8>(c, p, b, n);
+    else if (n > 2) launch_head_rows<WT, 4>(c, p, b, n);
+    else launch_head_rows<WT, 2>(c, p, b, n);
+    b += n;
+  }
+  if (token_out)
+    for (int b = 0; b < B; b += BATCH_SLOTS) {
+      BatchParams P{};
+      P.d = p; P.logits_all = p.logits;
+      for (int j = b; j < std::min(B, b + BATCH_SLOTS); ++j) P.seqs.id[P.seqs.n++] = j;
+      hipLaunchKernelGGL(k_argmax_part_b, dim3(P.seqs.n, ARG_CHUNKS), dim3(WG), 0, c->stream, P);
+      hipLaunchKernelGGL(k_argmax_final_b, dim3(P.seqs.n), dim3(64), 0, c->stream, P, 0);
+    }
   HIPCHK(c, hipGetLastError());
+  return FIRST_OK;
+}
+
+// Sequences that go through the layers together: as many as follow each other from b0 and fit the workspace.
+int group_size(const first_ctx* c, const int* lens, int B, int b0) {
+  int n = 1, rows = lens[b0];
+  while (b0 + n < B && rows + lens[b0 + n] <= c->p_rows) rows += lens[b0 + n++];
+  return n;
+}
+
+// Page tables and row offsets of the call's prompts, in one upload; the stream is idle when it returns.
+int upload_prompt_tables(first_ctx* c, const int* lens, int B) {
+  const int Bm = c->d.max_batch;
+  c->h_off.assign((size_t)2 * (Bm + 1), 0);
+  for (int b = 0; b < B; ++b) {
+    c->h_off[b + 1] = c->h_off[b] + lens[b];
+    c->h_off[Bm + 1 + b + 1] = c->h_off[Bm + 1 + b] + (lens[b] + PACK_PAD - 1) / PACK_PAD * PACK_PAD;
+  }
+  std::vector<int> all(c->h_page_table);
+  all.insert(all.end(), c->h_off.begin(), c->h_off.end());
+  HIPCHK(c, hipMemcpyAsync(c->d_page_table, all.data(), all.size() * sizeof(int), hipMemcpyHostToDevice, c->stream));
+  HIPCHK(c, hipStreamSynchronize(c->stream));     // the host tables may now be edited again
   return FIRST_OK;
 }
 
@@ -927,7 +1005,9 @@ int first_create(const first_model_desc* desc, const first_weights* w, void* hip
   c->n_pages = c->max_pages * d.max_batch;
   c->page_elems = (size_t)2 * d.n_kv_heads * d.kv_page_tokens * d.head_dim;
 
-  const int B = d.max_batch, L = d.n_layers, T = d.max_seq_len;
+  // Rows of the prefill workspace: the longest prompt, and for batches up to 4096 rows together (at 2000 rows the projections
+  // have reached their rate: 1160 TFLOP/s of 1180 at 4000 on the 8B shape's gate / up; 240 KB of workspace a row there).
+  const int B = d.max_batch, L = d.n_layers, T = c->p_rows = (int)std::max<long long>(d.max_seq_len, std::min<long long>((long long)B * d.max_seq_len, 4096));
   int rc = FIRST_OK;
   auto A = [&](int r) { if (rc == FIRST_OK) rc = r; };
   c->kv_elide = d.kv_layer_slots > 0 && d.kv_layer_slots < L;
@@ -936,11 +1016,12 @@ int first_create(const first_model_desc* desc, const first_weights* w, void* hip
   reset_layer_slices(c);
   A(dev_alloc(c, &c->kv_pool, (size_t)(c->kv_slots + (c->kv_elide ? 1 : 0)) * kv_slice_bytes(c)));
   if (c->kv_elide && rc == FIRST_OK) {
-    if (hipHostMalloc(reinterpret_cast<void**>(&c->h_keep), 64, hipHostMallocDefault) != hipSuccess ||
+    if (hipHostMalloc(reinterpret_cast<void**>(&c->h_keep), std::max(64, B), hipHostMallocDefault) != hipSuccess ||
         hipEventCreateWithFlags(&c->ev_keep, hipEventDisableTiming) != hipSuccess)
       rc = fail(c, FIRST_ERR_HIP, "first_create: pinned byte / event for the router decisions");
   }
-  A(dev_alloc(c, &c->d_page_table, (size_t)B * c->max_pages));
+  A(dev_alloc(c, &c->d_page_table, (size_t)B * c->max_pages + 2 * (B + 1)));
+  c->d_off = c->d_page_table + (size_t)B * c->max_pages;
   A(dev_alloc(c, &c->d_len, B)); A(dev_alloc(c, &c->d_kept, (size_t)B * L)); A(dev_alloc(c, &c->d_nkept, B));
   A(dev_alloc(c, &c->d_mask, (size_t)B * L)); A(dev_alloc(c, &c->d_rho, (size_t)B * L));
   A(dev_alloc(c, &c->d_theta, c->half));
@@ -956,19 +1037,20 @@ int first_create(const first_model_desc* desc, const first_weights* w, void* hip
     A(dev_alloc(c, &c->p_g, (size_t)T * d.d_ffn)); A(dev_alloc(c, &c->p_u, (size_t)T * d.d_ffn));
   }
   A(dev_alloc(c, &c->p_sig, T)); A(dev_alloc(c, &c->p_cs, (size_t)T * c->half));
-  A(dev_alloc(c, reinterpret_cast<char**>(&c->p_x), (size_t)T * d.d_model * 4));
+  // (bf16 models write the normed stream and the MLP activation split: fp32 copies hold the last positions' norm only / nothing)
+  A(dev_alloc(c, reinterpret_cast<char**>(&c->p_x), (size_t)(d.dtype == FIRST_DTYPE_BF16 ? B : T) * d.d_model * 4));
   A(dev_alloc(c, reinterpret_cast<char**>(&c->p_a), (size_t)T * c->nq * 4));
   if (d.dtype == FIRST_DTYPE_BF16) {
     A(dev_alloc(c, &c->p_xh, (size_t)T * d.d_model)); A(dev_alloc(c, &c->p_xl, (size_t)T * d.d_model));
     A(dev_alloc(c, &c->p_ah, (size_t)T * c->nq)); A(dev_alloc(c, &c->p_al, (size_t)T * c->nq));
     A(dev_alloc(c, &c->p_zh, (size_t)T * d.d_ffn)); A(dev_alloc(c, &c->p_zl, (size_t)T * d.d_ffn));
   }
-  c->p_tp = (T + FA_KT - 1) / FA_KT * FA_KT;
+  c->p_tp = (T / PACK_PAD + 1 + B) * PACK_PAD;
   if (d.dtype == FIRST_DTYPE_BF16 && (d.head_dim == 64 || d.head_dim == 128)) {
     A(dev_alloc(c, &c->p_qh, (size_t)T * c->nq)); A(dev_alloc(c, &c->p_ql, (size_t)T * c->nq));
     A(dev_alloc(c, &c->p_kc, (size_t)c->p_tp * c->nkv)); A(dev_alloc(c, &c->p_vt, (size_t)c->p_tp * c->nkv));
   }
-  A(dev_alloc(c, reinterpret_cast<char**>(&c->p_z), (size_t)T * d.d_ffn * 4));
+  if (d.dtype != FIRST_DTYPE_BF16) A(dev_alloc(c, reinterpret_cast<char**>(&c->p_z), (size_t)T * d.d_ffn * 4));
   c->xpitch = (std::max(std::max(d.d_model, c->nq), d.d_ffn) + 31) / 32 * 32;
   if (B > 1) {
     A(dev_alloc(c, &c->d_xh, (size_t)BATCH_SLOTS * c->xpitch)); A(dev_alloc(c, &c->d_xl, (size_t)BATCH_SLOTS * c->xpitch));
@@ -1005,7 +1087,7 @@ int first_create(const first_model_desc* desc, const first_weights* w, void* hip
   A(dev_alloc(c, &c->d_layers, L)); A(dev_alloc(c, &c->d_done, (size_t)c->num_cu)); A(dev_alloc(c, &c->d_err, 4));
   A(dev_alloc(c, &c->d_tdbg, (size_t)(4 * L + 1) * SK_TSLOTS));
   if (d.dtype == FIRST_DTYPE_BF16) {
-    A(dev_alloc(c, &c->pg_part, (size_t)2 * c->num_cu * 64 * 128)); A(dev_alloc(c, &c->pg_cnt, (size_t)2 * c->num_cu));
+    A(dev_alloc(c, &c->pg_part, (size_t)4 * c->num_cu * 64 * 128)); A(dev_alloc(c, &c->pg_cnt, (size_t)2 * c->num_cu));
     uintptr_t bits = reinterpret_cast<uintptr_t>(c->lm_head);
     for (const LayerPtrs& l : c->layers)
       for (const void* p : {l.wq, l.wk, l.wv, l.wo, l.wg, l.wu, l.wd}) bits |= reinterpret_cast<uintptr_t>(p);
@@ -1020,8 +1102,11 @@ int first_create(const first_model_desc* desc, const first_weights* w, void* hip
     if (e == hipSuccess) e = hipMemset(c->d_len, 0, B * sizeof(int));
     if (e == hipSuccess && c->pg_cnt) {
       e = hipMemset(c->pg_cnt, 0, (size_t)2 * c->num_cu * sizeof(unsigned));
-      if (e == hipSuccess) e = pg_set_lds<false>();
-      if (e == hipSuccess) e = pg_set_lds<true>();
+      if (e == hipSuccess) e = pg_set_lds<false, 1>();
+      if (e == hipSuccess) e = pg_set_lds<false, 4>();
+      if (e == hipSuccess) e = pg_set_lds<true, 1>();
+      for (const void* fn : {reinterpret_cast<const void*>(&k_attn_prompt<128, 4, 1>), reinterpret_cast<const void*>(&k_attn_prompt<128, 2, 2>)})
+        if (e == hipSuccess) e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * FA_TILE * 128 * 2);
     }
     if (e == hipSuccess) e = hipMemset(c->d_err, 0, 4 * sizeof(int));
     if (e == hipSuccess) e = reset_tagged_exchange(c);
@@ -1039,6 +1124,12 @@ int first_create(const first_model_desc* desc, const first_weights* w, void* hip
     if (e == hipSuccess && B > 1 && d.dtype == FIRST_DTYPE_BF16 && d_batch_fits(c)) e = make_tiled_copies(c);
     if (e == hipSuccess) e = hipMemset(c->d_mask, 0, (size_t)B * L);
     if (e == hipSuccess) e = hipMemset(c->d_page_table, 0, (size_t)B * c->max_pages * sizeof(int));
+#define FIRST_HEAD_ATTR(WT)                                                                                                     \
+  for (const void* fn : {reinterpret_cast<const void*>(&k_head_rows<WT, 2>), reinterpret_cast<const void*>(&k_head_rows<WT, 4>),  \
+                         reinterpret_cast<const void*>(&k_head_rows<WT, 8>)})                                                     \
+    if (e == hipSuccess) e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)HEAD_ROWS_LDS + 256);
+    FIRST_HEAD_ATTR(bf16) FIRST_HEAD_ATTR(float)
+#undef FIRST_HEAD_ATTR
     // the prefill attention kernels stage more than 64 KB of LDS for head_dim 128
     if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_prefill<float, bf16>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
@@ -1095,20 +1186,19 @@ int first_prefill_route(first_ctx* c, int32_t B, const int32_t* ids, const int32
   for (int b = 0; b < B; ++b)
     for (int need = (lens[b] + P - 1) / P; c->seq_npages[b] < need;)
       if (alloc_page(c, b) < 0) return fail(c, FIRST_ERR_CAPACITY, "first_prefill_route: out of KV pages");
-  HIPCHK(c, hipMemcpyAsync(c->d_page_table, c->h_page_table.data(), c->h_page_table.size() * sizeof(int),
-                           hipMemcpyHostToDevice, c->stream));
-  HIPCHK(c, hipStreamSynchronize(c->stream));     // the host table may now be edited again
-  size_t off = 0;
-  for (int b = 0; b < B; ++b) {
-    const int rc = c->d.dtype == FIRST_DTYPE_BF16
-                       ? prefill_one<bf16>(c, b, ids + off, lens[b], hidden_out, logits_out, token_out)
-                       : prefill_one<float>(c, b, ids + off, lens[b], hidden_out, logits_out, token_out);
-    if (rc) return rc;
-    off += lens[b];
-    c->hlen[b] = lens[b];
+  int rc = upload_prompt_tables(c, lens, B);
+  if (rc) return rc;
+  const bool bf = c->d.dtype == FIRST_DTYPE_BF16;
+  for (int b = 0; b < B;) {
+    const int n = group_size(c, lens, B, b);
+    const int32_t* at = ids + c->h_off[b];
+    if ((rc = bf ? prefill_group<bf16>(c, b, n, at, hidden_out) : prefill_group<float>(c, b, n, at, hidden_out))) return rc;
+    b += n;
   }
+  if ((rc = bf ? enqueue_first_tokens<bf16>(c, B, logits_out, token_out) : enqueue_first_tokens<float>(c, B, logits_out, token_out))) return rc;
+  for (int b = 0; b < B; ++b) c->hlen[b] = lens[b];
   c->B = B;
-  int rc = compact_masks(c);
+  rc = compact_masks(c);
   if (rc) return rc;
   std::vector<uint8_t> hm((size_t)B * L);
   HIPCHK(c, hipMemcpyAsync(hm.data(), c->d_mask, hm.size(), hipMemcpyDeviceToHost, c->stream));
@@ -1476,7 +1566,7 @@ int first_kv_usage(first_ctx* c, int64_t* pool_bytes, int32_t* layer_slots, int3
   return FIRST_OK;
 }
 
-constexpr int SOFT_ROWS = 128;   // positions whose logits are formed at a time in first_soft_forward
+constexpr int SOFT_ROWS = 1024;  // positions whose logits are formed at a time in first_soft_forward (128 left the LM head's GEMM a quarter of its rate)
 
 int first_soft_forward(first_ctx* c, int32_t B, const int32_t* ids, const int32_t* lens, const int32_t* targets, float lambda,
                        float alpha, float* rho_out, float* terms_out, float* hidden_out) {
@@ -1491,9 +1581,9 @@ int first_soft_forward(first_ctx* c, int32_t B, const int32_t* ids, const int32_
   const int L = d.n_layers, P = d.kv_page_tokens, D = d.d_model, V = d.vocab;
   hipStream_t st = c->stream;
   if (!c->p_Hs) {
-    int rc = dev_alloc(c, &c->p_Hs, (size_t)d.max_seq_len * D);
-    if (rc == FIRST_OK) rc = dev_alloc(c, &c->p_lg, (size_t)SOFT_ROWS * V);
-    if (rc == FIRST_OK) rc = dev_alloc(c, &c->p_ce, (size_t)d.max_seq_len);
+    int rc = dev_alloc(c, &c->p_Hs, (size_t)c->p_rows * D);
+    if (rc == FIRST_OK) rc = dev_alloc(c, &c->p_lg, (size_t)std::min(SOFT_ROWS, c->p_rows) * V);
+    if (rc == FIRST_OK) rc = dev_alloc(c, &c->p_ce, (size_t)c->p_rows);
     if (rc != FIRST_OK) { c->p_Hs = nullptr; return rc; }
   }
   release_sequences(c);
@@ -1502,33 +1592,31 @@ int first_soft_forward(first_ctx* c, int32_t B, const int32_t* ids, const int32_
   for (int b = 0; b < B; ++b)
     for (int need = (lens[b] + P - 1) / P; c->seq_npages[b] < need;)
       if (alloc_page(c, b) < 0) return fail(c, FIRST_ERR_CAPACITY, "first_soft_forward: out of KV pages");
-  HIPCHK(c, hipMemcpyAsync(c->d_page_table, c->h_page_table.data(), c->h_page_table.size() * sizeof(int),
-                           hipMemcpyHostToDevice, st));
-  HIPCHK(c, hipStreamSynchronize(st));
+  int rc = upload_prompt_tables(c, lens, B);
+  if (rc) return rc;
   const bool hl = d.dtype == FIRST_DTYPE_BF16;
-  size_t off = 0;
-  for (int b = 0; b < B; ++b) {
-    const int T = lens[b];
-    int rc = hl ? prefill_one<bf16>(c, b, ids + off, T, nullptr, nullptr, nullptr, true)
-                : prefill_one<float>(c, b, ids + off, T, nullptr, nullptr, nullptr, true);
-    if (rc) return rc;
+  for (int b = 0; b < B;) {
+    const int n = group_size(c, lens, B, b);
+    const size_t off = c->h_off[b];
+    const int R = c->h_off[b + n] - c->h_off[b];
+    if ((rc = hl ? prefill_group<bf16>(c, b, n, ids + off, nullptr, true) : prefill_group<float>(c, b, n, ids + off, nullptr, true))) return rc;
     if (hidden_out)
-      HIPCHK(c, hipMemcpyAsync(hidden_out + off * D, c->p_H, (size_t)T * D * sizeof(float), hipMemcpyDeviceToDevice, st));
+      HIPCHK(c, hipMemcpyAsync(hidden_out + off * D, c->p_H, (size_t)R * D * sizeof(float), hipMemcpyDeviceToDevice, st));
     // logits of every position = W_lm . RMSNorm(H_L; g_final), SOFT_ROWS positions at a time, then their cross entropy
     float* x = reinterpret_cast<float*>(c->p_x);
-    hipLaunchKernelGGL(k_rmsnorm_router<float>, dim3((T + WAVES - 1) / WAVES), dim3(WG), 0, st, c->p_H, c->g_final,
-                       (const float*)nullptr, x, (float*)nullptr, T, D, d.rms_eps, hl ? c->p_xh : nullptr, hl ? c->p_xl : nullptr);
-    for (int r0 = 0; r0 < T; r0 += SOFT_ROWS) {
-      const int rows = std::min(SOFT_ROWS, T - r0);
+    hipLaunchKernelGGL(k_rmsnorm_router<float>, dim3((R + WAVES - 1) / WAVES), dim3(WG), 0, st, c->p_H, c->g_final,
+                       (const float*)nullptr, x, (float*)nullptr, R, D, d.rms_eps, hl ? c->p_xh : nullptr, hl ? c->p_xl : nullptr);
+    for (int r0 = 0; r0 < R; r0 += SOFT_ROWS) {
+      const int rows = std::min(SOFT_ROWS, R - r0);
       rc = hl ? launch_gemm_hl(c, st, c->p_xh + (size_t)r0 * D, c->p_xl + (size_t)r0 * D, c->lm_head, c->p_lg, rows, V, D, 0)
               : launch_gemm(c, st, d.dtype, x + (size_t)r0 * D, c->lm_head, c->p_lg, rows, V, D, 0, true);
       if (rc) return rc;
       hipLaunchKernelGGL(k_ce_rows, dim3(rows), dim3(WG), 0, st, c->p_lg, targets + off + r0, c->p_ce + r0, V);
     }
-    hipLaunchKernelGGL(k_loss_terms, dim3(1), dim3(WG), 0, st, c->p_ce, targets + off, T, V, c->d_rho + (size_t)b * L, L,
+    hipLaunchKernelGGL(k_loss_terms, dim3(n), dim3(WG), 0, st, c->p_ce, targets + off, c->d_off + b, V, c->d_rho + (size_t)b * L, L,
                        c->router, (size_t)L * D, lambda, alpha, terms_out + (size_t)b * 4);
     HIPCHK(c, hipGetLastError());
-    off += T;
+    b += n;
   }
   if (rho_out) HIPCHK(c, hipMemcpyAsync(rho_out, c->d_rho, (size_t)B * L * sizeof(float), hipMemcpyDeviceToDevice, st));
   HIPCHK(c, hipStreamSynchronize(st));

@@ -23,6 +23,9 @@ constexpr int PG_BK = 64;                       // K step: one row of a tile is 
 // for the compiler to reuse too early; pg_wait / pg_barrier order it.
 typedef int i32x4_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void pg_load_lds(uint32_t lds_off, uint32_t voff, i32x4_t rsrc, uint32_t soff) {
+  // (uniform by construction; said again for the compiler, which does not see it through every loop)
+  lds_off = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_off);
+  soff = (uint32_t)__builtin_amdgcn_readfirstlane((int)soff);
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds_off), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
 }
 __device__ __forceinline__ i32x4_t pg_rsrc(const void* p, uint32_t bytes) {
@@ -46,24 +49,27 @@ struct PgArgs {
   const bf16* Wu;               // gate/up launch: seg[0].W = gate, this = up, N = d_ffn
   bf16 *zh, *zl;                //   SiLU(gate) * up, split, [M, N]
   int gm, gn;                   // row tiles, column tiles of all matrices together
-  int ks;                       // slices of K (1: none); more than one only in the shapes instantiated with SPLIT
+  int ks;                       // slices of K: 1, 2 or 4 (more than one with SPLIT and SEG = 4 only)
   float* part;                  // partial tiles of the slices, arrival counters per tile (zero between launches)
   unsigned* cnt;
 };
 
-// BM x BN tile; KG groups of WGM x WGN waves over it, each group taking its share of every K step (KG = 2 gives a tile
-// that has a compute unit to itself a second wave per SIMD without smaller wave tiles: 64 KB of sums cross LDS at the end).
-// S: K steps in the LDS ring (three where they fit: with weights from HBM a third step in flight took 1024 x 4096 x 14336
-// from 266 to 223 us; two 64 x 128 workgroups on a compute unit hide each other's waits and have 64 KB each).
+// The order of additions does not depend on M, nor on the tile: a row of the result is the same bits whatever prompts share
+// the launch.  With SEG = 4 (a property of the matrix, see pg_segments) K is four segments of whole steps, each summed
+// from zero, added in order; slices of K take whole segments, and the upper half's two travel apart.
+//
+// BM x BN tile, WGM x WGN waves.  S: K steps in the LDS ring (three where they fit: with weights from HBM a third step in
+// flight took 1024 x 4096 x 14336 from 266 to 223 us; two 64 x 128 workgroups on a compute unit hide each other's waits
+// and have 64 KB each).
 // GU: the tile's BN weight rows are 32 (16 where a wave tile is 32 wide) gate rows and as many up rows in turn, so that
 // a gate value and its up value sit in the same lane (in lanes 16 apart).
-template <int BM, int BN, int WGM, int WGN, int KG, int S, bool GU, bool SPLIT>
-__global__ void __launch_bounds__(KG * WGM * WGN * 64, 2) k_pgemm(PgArgs P) {
-  constexpr int NW = KG * WGM * WGN, TM = BM / WGM, TN = BN / WGN, IM = TM / 32, JN = TN / 32, BK = PG_BK;
+template <int BM, int BN, int WGM, int WGN, int S, bool GU, bool SPLIT, int SEG>
+__global__ void __launch_bounds__(WGM * WGN * 64, 2) k_pgemm(PgArgs P) {
+  constexpr int NW = WGM * WGN, TM = BM / WGM, TN = BN / WGN, IM = TM / 32, JN = TN / 32, BK = PG_BK;
   constexpr int IA = BM / 8 / NW, IB = BN / 8 / NW;        // 1 KB loads per wave and K step: each half of A; B
   constexpr int GI = JN >= 2 ? 32 : 16;                    // gate / up interleave
   static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0 && TM % 32 == 0 && TN % 32 == 0, "tile shape");
-  static_assert(!(SPLIT && KG > 1), "one of the two");
+  static_assert(SEG == 1 || SEG == 4, "segments of K");
   constexpr int STG = (2 * BM + BN) * BK * 2;              // LDS bytes of a K step
   extern __shared__ __align__(16) char pg_smem[];
   __shared__ int last_flag;
@@ -113,8 +119,10 @@ __global__ void __launch_bounds__(KG * WGM * WGN * 64, 2) k_pgemm(PgArgs P) {
     const int src = GU ? (r / (2 * GI)) * GI + r % GI : r;               // (a load's eight rows lie in one block of gate or of up rows)
     vb[i] = (uint32_t)src * K * 2 + pg_chunk(r, lane & 7) * 16;
   }
+  // segments of this workgroup and their steps
   const int nsteps = (K + BK - 1) / BK;
-  const int s0 = SPLIT ? nsteps * slice / P.ks : 0, s1 = SPLIT ? nsteps * (slice + 1) / P.ks : nsteps;
+  const int g0 = SPLIT ? SEG * slice / P.ks : 0, g1 = SPLIT && SEG > 1 ? SEG * (slice + 1) / P.ks : SEG;
+  const int s0 = nsteps * g0 / SEG, s1 = nsteps * g1 / SEG;
   const int tail_chunks = (K % BK) / 8;                                   // chunks of the last step that exist (0: all)
   auto issue = [&](int step) __attribute__((always_inline)) {
     const uint32_t b = lds0 + (uint32_t)((step - s0) % S) * STG, so = (uint32_t)step * BK * 2;
@@ -138,93 +146,94 @@ __global__ void __launch_bounds__(KG * WGM * WGN * 64, 2) k_pgemm(PgArgs P) {
   };
   constexpr int NL = 2 * IA + IB;
 
-  floatx16_t acc[IM][JN];
-#pragma unroll
-  for (int i = 0; i < IM; ++i)
-#pragma unroll
-    for (int j = 0; j < JN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-  const int kg = wave / (WGM * WGN), w4 = wave % (WGM * WGN);
-  const int wm = (w4 / WGN) * TM, wn = (w4 % WGN) * TN;
+  floatx16_t acc[IM][JN], tot[SEG > 1 ? IM : 1][JN];
+  const int wm = (wave / WGN) * TM, wn = (wave % WGN) * TN;
   const int lr = lane & 31, lg = lane >> 5;
 #pragma unroll
   for (int s = 0; s < S - 1; ++s)
     if (s0 + s < s1) issue(s0 + s);
-  for (int s = s0; s < s1; ++s) {
-    if (S == 2 || s + S - 2 >= s1) pg_wait<0>(); else pg_wait<NL * (S - 2)>();
-    lds_barrier();                             // step s is in LDS for every wave, and everyone is through with step s - 1
-    if (s + S - 1 < s1) issue(s + S - 1);
-    const char* base = pg_smem + ((s - s0) % S) * STG;
-    const char *sAh = base, *sAl = base + BM * BK * 2, *sB = base + 2 * BM * BK * 2;
-#pragma unroll
-    for (int kq = 0; kq < BK / KG; kq += 16) {
-      const int c = (kq + kg * (BK / KG)) / 8 + lg;
-      bf16x8_t ah[IM], al[IM], b[JN];
-#pragma unroll
-      for (int i = 0; i < IM; ++i) {
-        const int r = wm + i * 32 + lr, o = r * BK * 2 + pg_chunk(r, c) * 16;
-        ah[i] = *reinterpret_cast<const bf16x8_t*>(sAh + o);
-        al[i] = *reinterpret_cast<const bf16x8_t*>(sAl + o);
-      }
-#pragma unroll
-      for (int j = 0; j < JN; ++j) {
-        const int r = wn + j * 32 + lr;
-        b[j] = *reinterpret_cast<const bf16x8_t*>(sB + r * BK * 2 + pg_chunk(r, c) * 16);
-      }
-      // low halves first, then high halves: two products into the same accumulator are never issued back to back
-#pragma unroll
-      for (int i = 0; i < IM; ++i)
-#pragma unroll
-        for (int j = 0; j < JN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[i], b[j], acc[i][j], 0, 0, 0);
-#pragma unroll
-      for (int i = 0; i < IM; ++i)
-#pragma unroll
-        for (int j = 0; j < JN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[i], b[j], acc[i][j], 0, 0, 0);
-    }
-  }
-
-  if constexpr (KG == 2) {                     // the second group's sums reach the first through the operand LDS
-    static_assert((size_t)(NW / 2) * IM * JN * 4096 <= (size_t)S * STG, "sums fit the ring");
-    float* red = reinterpret_cast<float*>(pg_smem) + (size_t)w4 * IM * JN * 1024 + lane;
-    lds_barrier();
-    if (kg == 1) {
-#pragma unroll
-      for (int i = 0; i < IM; ++i)
-#pragma unroll
-        for (int j = 0; j < JN; ++j)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) red[((i * JN + j) * 16 + r) * 64] = acc[i][j][r];
-    }
-    lds_barrier();
-    if (kg == 1) return;
+  // the upper half of K on its own: its two segments are added to the lower half's sum one after the other
+  const bool apart = SPLIT && P.ks == 2 && slice == 1;
+  for (int sg = g0; sg < g1; ++sg) {
 #pragma unroll
     for (int i = 0; i < IM; ++i)
 #pragma unroll
       for (int j = 0; j < JN; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][j][r] += red[((i * JN + j) * 16 + r) * 64];
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    const int e1 = nsteps * (sg + 1) / SEG;
+    for (int s = nsteps * sg / SEG; s < e1; ++s) {
+      if (S == 2 || s + S - 2 >= s1) pg_wait<0>(); else pg_wait<NL * (S - 2)>();
+      lds_barrier();                           // step s is in LDS for every wave, and everyone is through with step s - 1
+      if (s + S - 1 < s1) issue(s + S - 1);
+      const char* base = pg_smem + ((s - s0) % S) * STG;
+      const char *sAh = base, *sAl = base + BM * BK * 2, *sB = base + 2 * BM * BK * 2;
+#pragma unroll
+      for (int kk = 0; kk < BK; kk += 16) {
+        const int c = kk / 8 + lg;
+        bf16x8_t ah[IM], al[IM], b[JN];
+#pragma unroll
+        for (int i = 0; i < IM; ++i) {
+          const int r = wm + i * 32 + lr, o = r * BK * 2 + pg_chunk(r, c) * 16;
+          ah[i] = *reinterpret_cast<const bf16x8_t*>(sAh + o);
+          al[i] = *reinterpret_cast<const bf16x8_t*>(sAl + o);
+        }
+#pragma unroll
+        for (int j = 0; j < JN; ++j) {
+          const int r = wn + j * 32 + lr;
+          b[j] = *reinterpret_cast<const bf16x8_t*>(sB + r * BK * 2 + pg_chunk(r, c) * 16);
+        }
+        // low halves first, then high halves: two products into the same accumulator are never issued back to back
+#pragma unroll
+        for (int i = 0; i < IM; ++i)
+#pragma unroll
+          for (int j = 0; j < JN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[i], b[j], acc[i][j], 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < IM; ++i)
+#pragma unroll
+          for (int j = 0; j < JN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[i], b[j], acc[i][j], 0, 0, 0);
+      }
+    }
+    if constexpr (SEG > 1) {                   // what the segments of this workgroup come to so far
+      if (sg == g0) {
+#pragma unroll
+        for (int i = 0; i < IM; ++i)
+#pragma unroll
+          for (int j = 0; j < JN; ++j) tot[i][j] = acc[i][j];
+      } else if (!apart) {
+#pragma unroll
+        for (int i = 0; i < IM; ++i)
+#pragma unroll
+          for (int j = 0; j < JN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) tot[i][j][r] += acc[i][j][r];
+      }
+    }
   }
-  if constexpr (SPLIT) {
-    // Slices of K: every workgroup stores its partial tile (accumulator order, 16 bytes a lane, write-through), counts
-    // itself in, and the last one adds the slices in slice order - the sum does not depend on who is last.
+  if constexpr (SPLIT && SEG > 1) {
+    // Slices of K (two or four): every workgroup stores its partial tile (accumulator order, 16 bytes a lane, write-through),
+    // counts itself in, and the last one adds the slices as the segments are added - the sum does not depend on who is last.
     if (P.ks > 1) {
       constexpr size_t WF = (size_t)IM * JN * 1024;                      // floats of one wave's partial tile
       // (Stores the compiler knows, so that it sees that they read what the last MFMA is still writing, and without a scalar
       // offset: with one it takes the data registers for free at once, and overwriting them in the next instruction put
       // wrong values into one of the four words now and then.)
-      const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
-          uni(P.part + (((size_t)tile * P.ks + slice) * NW + wave) * WF), (short)0, (int)(WF * 4), 0x00020000);
+      auto put = [&](const floatx16_t (&from)[IM][JN], int slot) __attribute__((always_inline)) {
+        const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(uni(P.part + (((size_t)tile * 4 + slot) * NW + wave) * WF), (short)0,
+                                                                            (int)(WF * 4), 0x00020000);
 #pragma unroll
-      for (int i = 0; i < IM; ++i)
+        for (int i = 0; i < IM; ++i)
 #pragma unroll
-        for (int j = 0; j < JN; ++j)
+          for (int j = 0; j < JN; ++j)
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const u32x4_t v = {__float_as_uint(acc[i][j][4 * q]), __float_as_uint(acc[i][j][4 * q + 1]),
-                               __float_as_uint(acc[i][j][4 * q + 2]), __float_as_uint(acc[i][j][4 * q + 3])};
-            __builtin_amdgcn_raw_buffer_store_b128(v, rw, ((i * JN + j) * 4 + q) * 1024 + lane * 16, 0, 17);   // sc0 sc1
-          }
+            for (int q = 0; q < 4; ++q) {
+              const u32x4_t v = {__float_as_uint(from[i][j][4 * q]), __float_as_uint(from[i][j][4 * q + 1]),
+                                 __float_as_uint(from[i][j][4 * q + 2]), __float_as_uint(from[i][j][4 * q + 3])};
+              __builtin_amdgcn_raw_buffer_store_b128(v, rw, ((i * JN + j) * 4 + q) * 1024 + lane * 16, 0, 17);   // sc0 sc1
+            }
+      };
+      put(tot, slice);
+      if (apart) put(acc, 2);
       pg_wait<0>();
       __syncthreads();
       if (tid == 0) {
@@ -235,17 +244,10 @@ __global__ void __launch_bounds__(KG * WGM * WGN * 64, 2) k_pgemm(PgArgs P) {
       }
       __syncthreads();
       if (!last_flag) return;
-      const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-          uni(P.part + (size_t)tile * P.ks * NW * WF), (short)0, (int)((size_t)P.ks * NW * WF * 4), 0x00020000);
-#pragma unroll
-      for (int i = 0; i < IM; ++i)
-#pragma unroll
-        for (int j = 0; j < JN; ++j)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-#pragma unroll 2
-      for (int q = 0; q < P.ks; ++q) {
-        const int so = (int)(((size_t)q * NW + wave) * WF * 4);
+      const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(uni(P.part + (size_t)tile * 4 * NW * WF), (short)0,
+                                                                          (int)(4 * NW * WF * 4), 0x00020000);
+      auto get = [&](floatx16_t (&to)[IM][JN], int slot) __attribute__((always_inline)) {
+        const int so = (int)(((size_t)slot * NW + wave) * WF * 4);
 #pragma unroll
         for (int i = 0; i < IM; ++i)
 #pragma unroll
@@ -254,10 +256,30 @@ __global__ void __launch_bounds__(KG * WGM * WGN * 64, 2) k_pgemm(PgArgs P) {
             for (int v = 0; v < 4; ++v) {
               const u32x4_t x = __builtin_amdgcn_raw_buffer_load_b128(rs, ((i * JN + j) * 4 + v) * 1024 + lane * 16, so, 17);   // sc0 sc1
 #pragma unroll
-              for (int e = 0; e < 4; ++e) acc[i][j][4 * v + e] += __uint_as_float(x[e]);
+              for (int e = 0; e < 4; ++e) to[i][j][4 * v + e] = __uint_as_float(x[e]);
             }
-      }
+      };
+      floatx16_t p1[IM][JN], p2[IM][JN];
+      get(tot, 0);
+      get(p1, 1);
+      get(p2, 2);
+      if (P.ks == 4) get(acc, 3);
+#pragma unroll
+      for (int i = 0; i < IM; ++i)
+#pragma unroll
+        for (int j = 0; j < JN; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            tot[i][j][r] = (tot[i][j][r] + p1[i][j][r]) + p2[i][j][r];
+            if (P.ks == 4) tot[i][j][r] += acc[i][j][r];
+          }
     }
+  }
+  if constexpr (SEG > 1) {
+#pragma unroll
+    for (int i = 0; i < IM; ++i)
+#pragma unroll
+      for (int j = 0; j < JN; ++j) acc[i][j] = tot[i][j];
   }
 
   // D layout of the 32x32 MFMA: lane -> column (lane & 31); register r -> row 8 (r / 4) + 4 (lane / 32) + r % 4
@@ -289,8 +311,15 @@ __global__ void __launch_bounds__(KG * WGM * WGN * 64, 2) k_pgemm(PgArgs P) {
       }
     }
   } else {
-    // What is added to is requested as a whole before any of it is used: a load, a wait and a store per element were up to
-    // 64 memory round trips in a row, 50 to 80 us of the 4096 x 14336 projection of 1024 rows.
+    // Through a descriptor that ends with the tile's last row: rows past M (and, by an offset out of its range, columns past N)
+    // read as zeros and are not written, without a branch per element.  What is added to is requested as a whole before any
+    // of it is used: a load, a wait and a store per element were up to 64 memory round trips in a row, 50 to 80 us of the
+    // 4096 x 14336 projection of 1024 rows.
+    const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(uni(C + (size_t)m0 * N), (short)0, rowsA * N * 4, 0x00020000);
+    auto at = [&](int i, int j, int r) __attribute__((always_inline)) {
+      const int col = n0 + wn + j * 32 + lr, row = wm + i * 32 + 8 * (r >> 2) + 4 * lg + (r & 3);
+      return col < N ? (row * N + col) * 4 : 0x7ffffffc;
+    };
     float old[IM][JN][16];
     if (P.accumulate) {
 #pragma unroll
@@ -298,8 +327,7 @@ __global__ void __launch_bounds__(KG * WGM * WGN * 64, 2) k_pgemm(PgArgs P) {
 #pragma unroll
         for (int j = 0; j < JN; ++j)
 #pragma unroll
-          for (int r = 0; r < 16; ++r)
-            old[i][j][r] = C[(size_t)min(m0 + wm + i * 32 + 8 * (r >> 2) + 4 * lg + (r & 3), M - 1) * N + min(n0 + wn + j * 32 + lr, N - 1)];
+          for (int r = 0; r < 16; ++r) old[i][j][r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rc, at(i, j, r), 0, 0));
     } else {
 #pragma unroll
       for (int i = 0; i < IM; ++i)
@@ -311,14 +339,9 @@ __global__ void __launch_bounds__(KG * WGM * WGN * 64, 2) k_pgemm(PgArgs P) {
 #pragma unroll
     for (int i = 0; i < IM; ++i)
 #pragma unroll
-      for (int j = 0; j < JN; ++j) {
-        const int col = n0 + wn + j * 32 + lr;
+      for (int j = 0; j < JN; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int row = m0 + wm + i * 32 + 8 * (r >> 2) + 4 * lg + (r & 3);
-          if (row < M && col < N) C[(size_t)row * N + col] = old[i][j][r] + acc[i][j][r];
-        }
-      }
+        for (int r = 0; r < 16; ++r) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(old[i][j][r] + acc[i][j][r]), rc, at(i, j, r), 0, 0);
   }
 }
 

@@ -1,19 +1,22 @@
 // Training-side forward pieces (Section 4.1: soft skip and the loss terms; Section 4.2: LoRA
 // merged into the weights for inference).  Forward values only.
 #pragma once
-#include "common.h"
+#include "prefill_kernels.h"
 
 namespace first {
 
-// Soft skip of one layer for one sequence: H = Hprev + rho * (H - Hprev), where Hprev is the
-// stream that entered the layer, H holds Hprev + phi(Hprev) on entry, and rho is the router's
-// score of Hprev (device scalar).
+// Soft skip of one layer for the prompts of a group: H = Hprev + rho * (H - Hprev), where Hprev is the stream that entered
+// the layer, H holds Hprev + phi(Hprev) on entry, and rho is the router's score of Hprev (rho[j * stride] for prompt j).
+// grid = rows.
 __global__ void __launch_bounds__(WG) k_soft_blend(float* __restrict__ H, const float* __restrict__ Hprev,
-                                                   const float* __restrict__ rho, size_t n) {
-  const float r = *rho;
-  for (size_t i = (size_t)blockIdx.x * WG + threadIdx.x; i < n; i += (size_t)gridDim.x * WG) {
-    const float p = Hprev[i];
-    H[i] = fmaf(r, H[i] - p, p);
+                                                   const float* __restrict__ rho, int stride, const int* __restrict__ off, int n, int D) {
+  const float r = rho[(size_t)pack_find(off, n, blockIdx.x) * stride];
+  const size_t row = (size_t)blockIdx.x * D;
+  for (int i = threadIdx.x * 4; i < D; i += WG * 4) {
+    const float4 p = *reinterpret_cast<const float4*>(Hprev + row + i);
+    float4 h = *reinterpret_cast<const float4*>(H + row + i);
+    h.x = fmaf(r, h.x - p.x, p.x); h.y = fmaf(r, h.y - p.y, p.y); h.z = fmaf(r, h.z - p.z, p.z); h.w = fmaf(r, h.w - p.w, p.w);
+    *reinterpret_cast<float4*>(H + row + i) = h;
   }
 }
 
@@ -44,30 +47,40 @@ __global__ void __launch_bounds__(WG) k_ce_rows(const float* __restrict__ logits
   if (threadIdx.x == 0) ce[j] = m + logf(tot) - row[t];
 }
 
-// The loss terms of one sequence (Section 4.1), one workgroup, fixed summation order:
+// The loss terms (Section 4.1), one workgroup per prompt of the group, fixed summation order:
 //   terms[0] = L_CE  = mean of ce[j] over the positions with a target (0 when there is none)
 //   terms[1] = L_Reg = sum over all router weights of w^2
 //   terms[2] = L_PP  = sum_i rho[i]
 //   terms[3] = L_CE + lambda * L_Reg + alpha * L_PP
-__global__ void __launch_bounds__(WG) k_loss_terms(const float* __restrict__ ce, const int* __restrict__ targets, int T, int V,
-                                                   const float* __restrict__ rho, int L, const float* __restrict__ router,
+__global__ void __launch_bounds__(WG) k_loss_terms(const float* __restrict__ ce, const int* __restrict__ targets, const int* __restrict__ off,
+                                                   int V, const float* __restrict__ rho, int L, const float* __restrict__ router,
                                                    size_t n_router, float lambda, float alpha, float* __restrict__ terms) {
   __shared__ float red[WAVES];
-  float s = 0.f, cnt = 0.f, q = 0.f;
+  const int row0 = off[blockIdx.x] - off[0], T = off[blockIdx.x + 1] - off[blockIdx.x];
+  ce += row0; targets += row0; rho += (size_t)blockIdx.x * L; terms += (size_t)blockIdx.x * 4;
+  float s = 0.f, cnt = 0.f, q = 0.f, pp = 0.f;
   for (int j = threadIdx.x; j < T; j += WG) {
     const int t = targets[j];
     if (t >= 0 && t < V) { s += ce[j]; cnt += 1.f; }
   }
-  for (size_t i = threadIdx.x; i < n_router; i += WG) q = fmaf(router[i], router[i], q);
+  // (n_router = L * D is a multiple of 8; eight 16-byte loads in flight per thread)
+  for (size_t i0 = threadIdx.x * 4; i0 < n_router; i0 += WG * 32) {
+    float4 w[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) w[u] = *reinterpret_cast<const float4*>(router + min(i0 + (size_t)u * WG * 4, n_router - 4));
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (i0 + (size_t)u * WG * 4 < n_router) { q = fmaf(w[u].x, w[u].x, q); q = fmaf(w[u].y, w[u].y, q); q = fmaf(w[u].z, w[u].z, q); q = fmaf(w[u].w, w[u].w, q); }
+  }
+  for (int i = threadIdx.x; i < L; i += WG) pp += rho[i];
   const float ce_sum = block_sum(s, red);
   const float n = block_sum(cnt, red);
   const float reg = block_sum(q, red);
+  const float rho_sum = block_sum(pp, red);
   if (threadIdx.x == 0) {
-    float pp = 0.f;
-    for (int i = 0; i < L; ++i) pp += rho[i];
     const float l_ce = n > 0.f ? __fdiv_rn(ce_sum, n) : 0.f;
-    terms[0] = l_ce; terms[1] = reg; terms[2] = pp;
-    terms[3] = l_ce + lambda * reg + alpha * pp;
+    terms[0] = l_ce; terms[1] = reg; terms[2] = rho_sum;
+    terms[3] = l_ce + lambda * reg + alpha * rho_sum;
   }
 }
 

@@ -1,0 +1,81 @@
+"""Prompts of a batch share their launches: every prompt's results must be the bits it has alone, whatever shares the launch
+(tile, K slices and wave groups of the projections change with the rows; both attention kernels in one group), and the
+attention kernels agree with the plain one at the edges of their tiles."""
+import pytest
+import torch
+
+from oracle import first_oracle as O
+from synth import make_prompt, make_router, make_weights
+from synth.generators import ModelDesc, to_device
+from tests.gpu_util import logits_close
+
+# a down projection in four segments of K (d_ffn >= 2048), both head dimensions
+HD64 = ModelDesc(2, 512, 8, 2, 64, 2048, 700)
+HD128 = ModelDesc(2, 512, 6, 2, 128, 2304, 701)
+
+
+def _run(desc, w, r, prompts, max_seq_len, slots=0, flash=1):
+    import paper_2410_12513_amd as P
+    B = len(prompts)
+    ctx = P.FirstContext(desc, w, r, max_batch=B, max_seq_len=max_seq_len, kv_layer_slots=slots)
+    ctx.set_option(7, flash)
+    out = dict(rho=torch.zeros(B, desc.n_layers, device="cuda"), hidden=torch.zeros(B, desc.d_model, device="cuda"),
+               logits=torch.zeros(B, desc.vocab, device="cuda"), token=torch.zeros(B, dtype=torch.int32, device="cuda"))
+    ctx.prefill_route(torch.cat(prompts).cuda(), [p.numel() for p in prompts], **out)
+    out = {k: v.cpu() for k, v in out.items()}
+    out["kv"] = [[tuple(t.cpu() for t in ctx.kv_read(b, i, 0, p.numel())) for i in range(desc.n_layers)] for b, p in enumerate(prompts)] if not slots else None
+    assert [ctx.seq_len(b) for b in range(B)] == [p.numel() for p in prompts]
+    ctx.close()
+    return out
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("desc", [HD64, HD128])
+def test_prompts_in_a_group_have_the_bits_they_have_alone(desc):
+    # 4096 rows of workspace: the prompts go through in two groups, the first with both attention kernels
+    lens = (2100, 5, 64, 129, 1100, 63, 2048, 300, 1)
+    w, r = make_weights(desc, 5), make_router(desc, 5)
+    wg, rg = to_device(w, "cuda"), r.cuda()
+    prompts = [make_prompt(desc.vocab, n, 50 + i) for i, n in enumerate(lens)]
+    got = _run(desc, wg, rg, prompts, 2200)
+    for b, p in enumerate(prompts):
+        one = _run(desc, wg, rg, [p], 2200)
+        for k in ("rho", "hidden", "logits", "token"):
+            assert torch.equal(one[k][0], got[k][b]), (k, lens[b])
+        for i in range(desc.n_layers):
+            assert torch.equal(one["kv"][0][i][0], got["kv"][b][i][0]) and torch.equal(one["kv"][0][i][1], got["kv"][b][i][1])
+    for b in (1, 3, 5, 7, 8):
+        st = O.prefill_route(desc, w, r, prompts[b])
+        ok, ma, rel = logits_close(got["logits"][b], st.logits, desc.dtype)
+        assert ok and float((got["rho"][b] - st.rho).abs().max()) <= 5e-4, (lens[b], ma, rel)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("desc,lens", [(HD64, (32, 33, 95, 128)), (HD128, (65, 191, 1)), (HD128, (2047, 2049)), (HD64, (2176, 40))])
+def test_prompt_attention_agrees_with_the_plain_kernel(desc, lens):
+    w, r = to_device(make_weights(desc, 6), "cuda"), make_router(desc, 6).cuda()
+    prompts = [make_prompt(desc.vocab, n, 60 + i) for i, n in enumerate(lens)]
+    a, b = _run(desc, w, r, prompts, max(lens) + 8), _run(desc, w, r, prompts, max(lens) + 8, flash=0)
+    # probabilities carry 16 bits into the second product and queries 16 into the first; K, V of the second layer may round
+    # to the other neighbouring bf16 (2^-9 of a value): the stream stays within 1.5e-3
+    for k in ("hidden", "logits"):
+        assert float((a[k] - b[k]).norm() / b[k].norm()) <= 1.5e-3
+
+
+@pytest.mark.gpu
+def test_group_with_elided_layers_matches_one_without():
+    desc = HD64
+    w, r = to_device(make_weights(desc, 7), "cuda"), make_router(desc, 7)
+    r[0] = 1.0           # a router that adds up the embedding: some prompts keep the first layer, others do not
+    r = r.cuda()
+    prompts = [make_prompt(desc.vocab, n, 70 + i) for i, n in enumerate((40, 130, 17, 64))]
+    full = _run(desc, w, r, prompts, 160)
+    import paper_2410_12513_amd as P
+    kept = (full["rho"] >= 0.5).any(0)
+    try:
+        part = _run(desc, w, r, prompts, 160, slots=1)
+        assert int(kept.sum()) <= 1
+        for k in ("rho", "hidden", "logits", "token"):
+            assert torch.equal(full[k], part[k])
+    except P.FirstError as e:
+        assert e.code == -3 and int(kept.sum()) > 1
