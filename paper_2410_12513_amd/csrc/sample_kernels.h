@@ -7,9 +7,9 @@
 //   p_j ~ exp((l_j - l_max) / T) over the candidates, summed in descending-logit order;
 //   result = the first candidate whose cumulative weight exceeds u * total.
 //
-// Two stages: every workgroup of k_topk_part selects the top k of its 2048 logits (k rounds
-// of "largest element after the previous one", values in registers); k_topk_sample merges the
-// per-chunk lists of one sequence the same way and draws.  All fp32, fixed order.
+// Two stages: every wave of k_topk_part selects the top k of its 512 logits (k rounds of "the largest key left", keys in
+// registers, no barrier), the workgroup merges its four lists by rank; k_topk_sample does the same with the lists of one
+// sequence and draws.  All fp32, fixed order.
 #pragma once
 #include "common.h"
 
@@ -28,88 +28,128 @@ __device__ __forceinline__ bool cand_before(const Cand& a, const Cand& b) {
   return a.v > b.v || (a.v == b.v && a.i < b.i);
 }
 
-// The first candidate in order over the whole workgroup (every thread contributes one);
-// red: SMP_THREADS / 64 entries of LDS.  Returns it in every thread.
-__device__ __forceinline__ Cand wg_first(Cand c, Cand* red) {
+// The order as an unsigned key: a comes before b iff key(a) > key(b).  Upper word: the logit's bits in ascending order (-0 counts
+// as 0), lower word: ~index.  0: no candidate (a NaN is none either).
+__device__ __forceinline__ unsigned long long cand_key(float v, int i) {
+  const uint32_t u = __float_as_uint(v + 0.f);
+  const uint32_t o = (u & 0x80000000u) ? ~u : u | 0x80000000u;
+  return i == SMP_NONE || v != v ? 0ull : ((unsigned long long)o << 32) | (uint32_t)~i;
+}
+__device__ __forceinline__ Cand cand_of(unsigned long long key) {
+  const uint32_t o = (uint32_t)(key >> 32);
+  return key == 0ull ? Cand{-INFINITY, SMP_NONE} : Cand{__uint_as_float((o & 0x80000000u) ? o & 0x7fffffffu : ~o), (int)~(uint32_t)key};
+}
+// Largest value over the wave (DPP: quads, half rows, rows, then the two row broadcasts of gfx9), in every lane.
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+#define FIRST_DPP_MAX(CTRL, ROWS) v = max(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, ROWS, 0xf, false))
+  FIRST_DPP_MAX(0xB1, 0xf); FIRST_DPP_MAX(0x4E, 0xf); FIRST_DPP_MAX(0x141, 0xf); FIRST_DPP_MAX(0x140, 0xf);
+  FIRST_DPP_MAX(0x142, 0xa); FIRST_DPP_MAX(0x143, 0xc);
+#undef FIRST_DPP_MAX
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+// list[0 .. k) = the k largest of the wave's keys, in order (0 behind the last one).  Takes them out of e.
+__device__ __forceinline__ void wave_top(unsigned long long (&e)[SMP_VPT], int k, unsigned long long* list) {
+  for (int r = 0; r < k; ++r) {
+    unsigned long long best = e[0];
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const Cand d{__shfl_xor(c.v, o, 64), __shfl_xor(c.i, o, 64)};
-    if (cand_before(d, c)) c = d;
+    for (int j = 1; j < SMP_VPT; ++j) best = e[j] > best ? e[j] : best;
+    const uint32_t hi = wave_max_u32((uint32_t)(best >> 32));
+    const uint32_t lo = wave_max_u32((uint32_t)(best >> 32) == hi ? (uint32_t)best : 0u);
+    const unsigned long long first = ((unsigned long long)hi << 32) | lo;
+#pragma unroll
+    for (int j = 0; j < SMP_VPT; ++j)
+      if (e[j] == first) e[j] = 0ull;
+    if ((threadIdx.x & 63) == 0) list[r] = first;
   }
-  const int wave = threadIdx.x >> 6;
-  __syncthreads();                                      // red may still be read from the round before
-  if ((threadIdx.x & 63) == 0) red[wave] = c;
+}
+// top[0 .. k) = the k largest of the n keys (all different but for the zeros): a key's place is the number of larger ones.
+__device__ __forceinline__ void rank_merge(const unsigned long long* keys, int n, int k, unsigned long long* top) {
+  if ((int)threadIdx.x < k) top[threadIdx.x] = 0ull;
   __syncthreads();
-  Cand r = red[0];
-  for (int w = 1; w < SMP_THREADS / 64; ++w)
-    if (cand_before(red[w], r)) r = red[w];
-  return r;
+  for (int i = threadIdx.x; i < n; i += SMP_THREADS) {
+    const unsigned long long x = keys[i];
+    int before = 0;
+    for (int j = 0; j < n; ++j) before += keys[j] > x;
+    if (x != 0ull && before < k) top[before] = x;
+  }
+  __syncthreads();
 }
 
-// The draw: top[0..k) in order (SMP_NONE beyond the vocabulary), u in [0, 1).  One thread; every path that samples ends
-// in this function, so that they take the same decision on the same candidates.
-__device__ __forceinline__ int smp_draw(const Cand* top, int k, float temperature, float u) {
+// The draw: top[0..k) in order (SMP_NONE beyond the vocabulary), weight(j) = exp((l_j - l_max) / T), u in [0, 1).  One thread;
+// every path that samples ends in this function, so that they take the same decision on the same candidates.
+template <typename Weight>
+__device__ __forceinline__ int smp_pick(const Cand* top, int k, float u, Weight weight) {
   int kk = 0;
   while (kk < k && top[kk].i != SMP_NONE) ++kk;
-  const float lmax = top[0].v;
   float total = 0.f;
-  for (int j = 0; j < kk; ++j) total += expf((top[j].v - lmax) / temperature);
+  for (int j = 0; j < kk; ++j) total += weight(j);
   const float target = u * total;
   float cum = 0.f;
   int pick = kk > 0 ? top[kk - 1].i : 0;
   for (int j = 0; j < kk; ++j) {
-    cum += expf((top[j].v - lmax) / temperature);
+    cum += weight(j);
     if (cum > target) { pick = top[j].i; break; }
   }
   return pick;
 }
+__device__ __forceinline__ float smp_weight(const Cand& c, const Cand& best, float temperature) { return expf((c.v - best.v) / temperature); }
+__device__ __forceinline__ int smp_draw(const Cand* top, int k, float temperature, float u) {
+  return smp_pick(top, k, u, [=](int j) { return smp_weight(top[j], top[0], temperature); });
+}
 
 // Stage 1.  grid (chunks, sequences).  part[(seq * chunks + chunk) * k + r] = r-th candidate of the chunk.
+// Latency, not bandwidth (16 x 128256 logits, k = 10: 24.6 us with a barrier pair and an LDS reduction per candidate,
+// 10.9 now; 8 MB).
 __global__ void __launch_bounds__(SMP_THREADS) k_topk_part(const float* __restrict__ logits, int V, int k, Cand* __restrict__ part) {
-  __shared__ Cand red[SMP_THREADS / 64];
+  __shared__ unsigned long long lists[(SMP_THREADS / 64) * SMP_KMAX], top[SMP_KMAX];
   const int tid = threadIdx.x, chunk = blockIdx.x, seq = blockIdx.y;
   const float* row = logits + (size_t)seq * V;
-  Cand e[SMP_VPT];
+  float v[SMP_VPT];
+#pragma unroll
+  for (int j = 0; j < SMP_VPT; ++j) v[j] = row[min(chunk * SMP_CHUNK + j * SMP_THREADS + tid, V - 1)];
+  unsigned long long e[SMP_VPT];
 #pragma unroll
   for (int j = 0; j < SMP_VPT; ++j) {
     const int idx = chunk * SMP_CHUNK + j * SMP_THREADS + tid;
-    e[j] = idx < V ? Cand{row[idx], idx} : Cand{-INFINITY, SMP_NONE};
+    e[j] = idx < V ? cand_key(v[j], idx) : 0ull;
   }
-  Cand last{INFINITY, -1};
-  Cand* out = part + ((size_t)seq * gridDim.x + chunk) * k;
-  for (int r = 0; r < k; ++r) {
-    Cand best{-INFINITY, SMP_NONE};
-#pragma unroll
-    for (int j = 0; j < SMP_VPT; ++j)
-      if (e[j].i != SMP_NONE && cand_before(last, e[j]) && cand_before(e[j], best)) best = e[j];
-    best = wg_first(best, red);
-    if (tid == 0) out[r] = best;
-    last = best.i == SMP_NONE ? Cand{-INFINITY, SMP_NONE} : best;   // nothing left: nothing comes after
-  }
+  wave_top(e, k, lists + (tid >> 6) * k);
+  rank_merge(lists, (SMP_THREADS / 64) * k, k, top);       // (begins with a barrier)
+  if (tid < k) part[((size_t)seq * gridDim.x + chunk) * k + tid] = cand_of(top[tid]);
 }
 
-// Stage 2.  grid (sequences).  n = chunks * k candidates of the sequence.
+// Stage 2.  grid (sequences).  n = chunks * k candidates of the sequence, 2048 at a time (17.4 us before at n = 630, 9.9 now).
 __global__ void __launch_bounds__(SMP_THREADS) k_topk_sample(const Cand* __restrict__ part, int n, int k, float temperature,
                                                             const float* __restrict__ uniforms, int* __restrict__ token_out,
                                                             int* __restrict__ cand_out) {
-  __shared__ Cand red[SMP_THREADS / 64];
-  __shared__ Cand top[SMP_KMAX];
+  __shared__ unsigned long long lists[(SMP_THREADS / 64 + 1) * SMP_KMAX], top[SMP_KMAX];
+  __shared__ Cand first[SMP_KMAX];
+  __shared__ float weight[SMP_KMAX];
   const int tid = threadIdx.x, seq = blockIdx.x;
   const Cand* c = part + (size_t)seq * n;
-  Cand last{INFINITY, -1};
-  for (int r = 0; r < k; ++r) {
-    Cand best{-INFINITY, SMP_NONE};
-    for (int j = tid; j < n; j += SMP_THREADS) {
-      const Cand x = c[j];
-      if (x.i != SMP_NONE && cand_before(last, x) && cand_before(x, best)) best = x;
+  const float u = uniforms[seq];
+  if (tid < k) top[tid] = 0ull;
+  for (int base = 0; base < n; base += SMP_CHUNK) {
+    unsigned long long e[SMP_VPT];
+#pragma unroll
+    for (int j = 0; j < SMP_VPT; ++j) {
+      const int at = base + j * SMP_THREADS + tid;
+      const Cand x = c[min(at, n - 1)];
+      e[j] = at < n ? cand_key(x.v, x.i) : 0ull;
     }
-    best = wg_first(best, red);
-    if (tid == 0) top[r] = best;
-    last = best.i == SMP_NONE ? Cand{-INFINITY, SMP_NONE} : best;
+    wave_top(e, k, lists + (tid >> 6) * k);
+    if (tid < k) lists[(SMP_THREADS / 64) * k + tid] = top[tid];          // what the candidates before these came to
+    __syncthreads();
+    rank_merge(lists, (SMP_THREADS / 64 + 1) * k, k, top);
+  }
+  if (tid < k) {
+    const Cand t = cand_of(top[tid]);
+    first[tid] = t;
+    weight[tid] = smp_weight(t, cand_of(top[0]), temperature);           // (side by side; one thread adds them up)
+    if (cand_out != nullptr) cand_out[(size_t)seq * k + tid] = t.i == SMP_NONE ? -1 : t.i;
   }
   __syncthreads();
-  if (tid < k && cand_out != nullptr) cand_out[(size_t)seq * k + tid] = top[tid].i == SMP_NONE ? -1 : top[tid].i;
-  if (tid == 0) token_out[seq] = smp_draw(top, k, temperature, uniforms[seq]);
+  if (tid == 0) token_out[seq] = smp_pick(first, k, u, [&](int j) { return weight[j]; });
 }
 
 }  // namespace first
