@@ -232,6 +232,8 @@ __device__ __forceinline__ void phase_attn(const DecParams& p, int g, int s, cha
   const int chunk = ((tiles + S - 1) / S) << 6;
   const int k_begin = s * chunk;
   const int k_end = min(nkeys, k_begin + chunk);
+  const int live = (nkeys + chunk - 1) / chunk;            // splits that have keys: the others take no part, one alone needs no merge
+  if (s >= live) return;
   const int nq = p.Hq * hd, nkv = p.Hkv * hd;
   const float* qkv = p.qkv + (size_t)b * (nq + 2 * nkv);
   const float2* cs = p.rope_cs + (size_t)b * half;
@@ -240,8 +242,7 @@ __device__ __forceinline__ void phase_attn(const DecParams& p, int g, int s, cha
   const size_t head_off = (size_t)g * P * hd;             // within the K (or V) half of a page
   const size_t v_off = (size_t)p.Hkv * P * hd;            // V half follows the K half
 
-  const bool active = k_begin < k_end;
-  if (active) {
+  {
     // rotate q of this group's heads (pre-scaled by 1/sqrt(hd))
     for (int i = tid; i < G * half; i += WG) {
       const int hq = i / half, d = i - hq * half;
@@ -277,30 +278,35 @@ __device__ __forceinline__ void phase_attn(const DecParams& p, int g, int s, cha
 
   const int vec_per_key = hd / VEC;
   for (int t0 = k_begin; t0 < k_end; t0 += 64) {
-    // stage 64 keys of K (padded rows) and V
-    for (int i = tid; i < 64 * vec_per_key; i += WG) {
-      const int j = i / vec_per_key, c = (i - j * vec_per_key) * VEC;
-      const int key = t0 + j;
-      uint4 kv4 = make_uint4(0, 0, 0, 0), vv4 = make_uint4(0, 0, 0, 0);
-      bool fresh = false;
-      if (key < k_end) {
-        if (key == pos) fresh = true;
-        else {
-          const size_t base = (size_t)pt[key / P] * p.page_elems + head_off + (size_t)(key % P) * hd + c;
-          kv4 = *reinterpret_cast<const uint4*>(pool + base);
-          vv4 = *reinterpret_cast<const uint4*>(pool + base + v_off);
-        }
-      }
-      if (fresh) {
+    // stage 64 keys of K (padded rows) and V; four 16-byte pieces of each per thread at a time, all page lookups before the
+    // first key is requested and all requests before the first store (one after the other they were eight round trips)
+    for (int i0 = tid; i0 < 64 * vec_per_key; i0 += 4 * WG) {
+      const KVT* src[4];
+      uint4 kv4[4], vv4[4];
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) {
-          *reinterpret_cast<KVT*>(kt + j * kpitch + (c + e) * sizeof(KVT)) = from_f32<KVT>(knew[c + e]);
-          vt[j * hd + c + e] = from_f32<KVT>(vnew[c + e]);
+      for (int u = 0; u < 4; ++u) {
+        const int i = min(i0 + u * WG, 64 * vec_per_key - 1), j = i / vec_per_key, c = (i - j * vec_per_key) * VEC;
+        const int key = min(t0 + j, k_end - 1);
+        src[u] = pool + (size_t)pt[key / P] * p.page_elems + head_off + (size_t)(key % P) * hd + c;
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) { kv4[u] = *reinterpret_cast<const uint4*>(src[u]); vv4[u] = *reinterpret_cast<const uint4*>(src[u] + v_off); }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int i = i0 + u * WG, j = i / vec_per_key, c = (i - j * vec_per_key) * VEC;
+        if (i >= 64 * vec_per_key) break;
+        if (t0 + j == pos) {                               // the new key may not have reached memory yet: from LDS
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) {
+            *reinterpret_cast<KVT*>(kt + j * kpitch + (c + e) * sizeof(KVT)) = from_f32<KVT>(knew[c + e]);
+            vt[j * hd + c + e] = from_f32<KVT>(vnew[c + e]);
+          }
+        } else {
+          const bool in = t0 + j < k_end;
+          uint32_t* kd = reinterpret_cast<uint32_t*>(kt + j * kpitch + c * sizeof(KVT));
+          kd[0] = in ? kv4[u].x : 0u; kd[1] = in ? kv4[u].y : 0u; kd[2] = in ? kv4[u].z : 0u; kd[3] = in ? kv4[u].w : 0u;
+          *reinterpret_cast<uint4*>(vt + j * hd + c) = in ? vv4[u] : make_uint4(0, 0, 0, 0);
         }
-      } else {
-        uint32_t* kd = reinterpret_cast<uint32_t*>(kt + j * kpitch + c * sizeof(KVT));
-        kd[0] = kv4.x; kd[1] = kv4.y; kd[2] = kv4.z; kd[3] = kv4.w;
-        *reinterpret_cast<uint4*>(vt + j * hd + c) = vv4;
       }
     }
     __syncthreads();
@@ -314,12 +320,14 @@ __device__ __forceinline__ void phase_attn(const DecParams& p, int g, int s, cha
         const char* krow = kt + lane * kpitch;
         const float* q = qs + hq * hd;
         if (sizeof(KVT) == 2) {
+#pragma unroll 16
           for (int d = 0; d < hd; d += 2) {
             const uint32_t w2 = *reinterpret_cast<const uint32_t*>(krow + d * 2);
             sc = fmaf(q[d], __uint_as_float(w2 << 16), sc);
             sc = fmaf(q[d + 1], __uint_as_float(w2 & 0xffff0000u), sc);
           }
         } else {
+#pragma unroll 32
           for (int d = 0; d < hd; ++d) sc = fmaf(q[d], *reinterpret_cast<const float*>(krow + d * 4), sc);
         }
         if (lane >= jn) sc = -INFINITY;
@@ -330,17 +338,38 @@ __device__ __forceinline__ void phase_attn(const DecParams& p, int g, int s, cha
         l[hi] = l[hi] * corr + wave_sum(pj);
         o0[hi] *= corr; o1[hi] *= corr;
         m[hi] = mn;
-        // o += p_j * V[j]; lane owns dims lane and lane+64
-        for (int j = 0; j < jn; ++j) {
-          const float pb = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(pj), j));
-          if (lane < hd) o0[hi] = fmaf(pb, to_f32(vt[j * hd + lane]), o0[hi]);
-          if (lane + 64 < hd) o1[hi] = fmaf(pb, to_f32(vt[j * hd + lane + 64]), o1[hi]);
+        // o += p_j * V[j]; lane owns dims lane and lane+64 (hd = 64 or 128)
+        if (hd > 64) {
+#pragma unroll 8
+          for (int j = 0; j < jn; ++j) {
+            const float pb = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(pj), j));
+            o0[hi] = fmaf(pb, to_f32(vt[j * hd + lane]), o0[hi]);
+            o1[hi] = fmaf(pb, to_f32(vt[j * hd + lane + 64]), o1[hi]);
+          }
+        } else {
+#pragma unroll 16
+          for (int j = 0; j < jn; ++j) {
+            const float pb = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(pj), j));
+            o0[hi] = fmaf(pb, to_f32(vt[j * 64 + lane]), o0[hi]);
+          }
         }
       }
     }
     __syncthreads();
   }
 
+  if (live == 1) {                                         // all keys were here
+#pragma unroll
+    for (int hi = 0; hi < MAXH; ++hi) {
+      const int hq = wave + hi * WAVES;
+      if (hq < G) {
+        float* out = p.attn + (size_t)b * nq + (g * G + hq) * hd;
+        if (lane < hd) out[lane] = o0[hi] / l[hi];
+        if (lane + 64 < hd) out[lane + 64] = o1[hi] / l[hi];
+      }
+    }
+    return;
+  }
   // partial results of this split
 #pragma unroll
   for (int hi = 0; hi < MAXH; ++hi) {
@@ -362,7 +391,7 @@ __device__ __forceinline__ void phase_attn(const DecParams& p, int g, int s, cha
   __syncthreads();
   if (tid == 0) {
     const unsigned old = atomicAdd(&p.attn_cnt[b * p.Hkv + g], 1u);
-    const int last = (old == (unsigned)(S - 1));
+    const int last = (old == (unsigned)(live - 1));
     if (last) p.attn_cnt[b * p.Hkv + g] = 0u;
     *flag = last;
   }
@@ -377,9 +406,9 @@ __device__ __forceinline__ void phase_attn(const DecParams& p, int g, int s, cha
         const float* pml = p.part_ml + ((size_t)b * p.Hq + H) * S_MAX * 2;
         const float* po = p.part_o + ((size_t)b * p.Hq + H) * S_MAX * hd;
         float M = -INFINITY;
-        for (int t = 0; t < S; ++t) M = fmaxf(M, __builtin_nontemporal_load(pml + 2 * t));
+        for (int t = 0; t < live; ++t) M = fmaxf(M, __builtin_nontemporal_load(pml + 2 * t));
         float den = 0.f, a0 = 0.f, a1 = 0.f;
-        for (int t = 0; t < S; ++t) {
+        for (int t = 0; t < live; ++t) {
           const float mt = __builtin_nontemporal_load(pml + 2 * t);
           const float lt = __builtin_nontemporal_load(pml + 2 * t + 1);
           if (lt > 0.f) {

@@ -627,6 +627,14 @@ int launch_gemm(first_ctx* c, hipStream_t st, int dtype, const void* A, const vo
     dim3 grid((N + GB_N - 1) / GB_N, (M + GB_M - 1) / GB_M);
     hipLaunchKernelGGL(k_gemm_nt_bf16, grid, dim3(WG), 0, st, reinterpret_cast<const bf16*>(A),
                        reinterpret_cast<const bf16*>(W), C, M, N, K, acc);
+  } else if ((long long)((N + 63) / 64) * ((M + 63) / 64) < device_cus()) {
+    // fewer 64 x 64 tiles than compute units: 32 x 32 tiles, or 16 x 16 ones while those do not fill the chip either
+    if ((long long)((N + 31) / 32) * ((M + 31) / 32) >= device_cus())
+      hipLaunchKernelGGL(k_gemm_nt_f32_small<2>, dim3((N + 31) / 32, (M + 31) / 32), dim3(WG), 0, st, reinterpret_cast<const float*>(A),
+                         reinterpret_cast<const float*>(W), C, M, N, K, acc);
+    else
+      hipLaunchKernelGGL(k_gemm_nt_f32_small<1>, dim3((N + 15) / 16, (M + 15) / 16), dim3(WG), 0, st, reinterpret_cast<const float*>(A),
+                         reinterpret_cast<const float*>(W), C, M, N, K, acc);
   } else {
     dim3 grid((N + 63) / 64, (M + 63) / 64);
     hipLaunchKernelGGL(k_gemm_nt_f32, grid, dim3(WG), 0, st, reinterpret_cast<const float*>(A),
@@ -788,7 +796,6 @@ int prefill_group(first_ctx* c, int b0, int n, const int* ids, float* hidden_out
   int T_max = 0, T_min = R;
   for (int j = 0; j < n; ++j) { T_max = std::max(T_max, h_off[j + 1] - h_off[j]); T_min = std::min(T_min, h_off[j + 1] - h_off[j]); }
   const PromptPack pk{c->d_off + b0, c->d_off + Bm + 1 + b0, n, b0, c->d_page_table, c->max_pages};
-  const int QB = std::max(1, 64 / c->G);
   const float qscale = 1.0f / std::sqrt((float)hd);
   const size_t kpitch = (size_t)hd * sizeof(WT) + 4;
   const size_t lds_attn = (size_t)64 * hd * sizeof(float) + 64 * kpitch + (size_t)64 * hd * sizeof(WT);
@@ -849,6 +856,10 @@ int prefill_group(first_ctx* c, int b0, int n, const int* ids, float* hidden_out
                          c->page_elems, d.n_q_heads, d.n_kv_heads, hd, P, qscale);
       for (int j = 0; j < n; ++j) {
         const int T = h_off[j + 1] - h_off[j];
+        // queries a workgroup: as many as its LDS holds, fewer while that leaves compute units without one (down to a row a wave)
+        int QB = std::max(1, 64 / c->G);
+        while (QB * c->G > WAVES && (T + QB - 1) / QB * d.n_kv_heads < c->num_cu) QB /= 2;
+        QB = std::max(1, QB);
         const size_t row = (size_t)(h_off[j] - h_off[0]) * c->nq;
         hipLaunchKernelGGL((k_attn_prefill<float, WT>), dim3((T + QB - 1) / QB, d.n_kv_heads), dim3(WG), lds_attn, st, c->p_q + row, a + row,
                            c->d_page_table + (size_t)(b0 + j) * c->max_pages, pool, c->page_elems, T, d.n_q_heads, d.n_kv_heads, hd, P, QB);
