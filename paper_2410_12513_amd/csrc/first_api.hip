@@ -953,6 +953,29 @@ int upload_prompt_tables(first_ctx* c, const int* lens, int B) {
   return FIRST_OK;
 }
 
+// Dynamic LDS limits of the prompt pass's kernels: a property of the loaded code, set once per device.
+hipError_t prefill_attributes() {
+  static std::mutex m;
+  static bool done[STATIC_SCRATCH_MAX_DEV] = {};
+  int dev = -1;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  std::lock_guard<std::mutex> lock(m);
+  const bool known = dev >= 0 && dev < STATIC_SCRATCH_MAX_DEV;
+  if (known && done[dev]) return hipSuccess;
+  if (e == hipSuccess) e = pg_set_lds<false, 1>();
+  if (e == hipSuccess) e = pg_set_lds<false, 4>();
+  if (e == hipSuccess) e = pg_set_lds<true, 1>();
+  for (const void* fn : {reinterpret_cast<const void*>(&k_attn_prompt<128, 4, 1>), reinterpret_cast<const void*>(&k_attn_prompt<128, 2, 2>)})
+    if (e == hipSuccess) e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * FA_TILE * 128 * 2);
+  for (const void* fn : {reinterpret_cast<const void*>(&k_head_rows<bf16, 2>), reinterpret_cast<const void*>(&k_head_rows<bf16, 4>),
+                         reinterpret_cast<const void*>(&k_head_rows<bf16, 8>), reinterpret_cast<const void*>(&k_head_rows<float, 2>),
+                         reinterpret_cast<const void*>(&k_head_rows<float, 4>), reinterpret_cast<const void*>(&k_head_rows<float, 8>)})
+    if (e == hipSuccess) e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)HEAD_ROWS_LDS);
+  if (e == hipSuccess && known) done[dev] = true;
+  return e;
+}
+
 int compact_masks(first_ctx* c) {
   hipLaunchKernelGGL(k_compact, dim3(c->d.max_batch), dim3(64), 0, c->stream, c->d_mask, c->d.n_layers, c->d_kept,
                      c->d_nkept);
@@ -1111,14 +1134,8 @@ int first_create(const first_model_desc* desc, const first_weights* w, void* hip
     if (e == hipSuccess) e = hipMemset(c->d_attn_cnt, 0, (size_t)B * d.n_kv_heads * sizeof(unsigned));
     if (e == hipSuccess) e = hipMemset(c->d_head_cnt, 0, B * sizeof(unsigned));
     if (e == hipSuccess) e = hipMemset(c->d_len, 0, B * sizeof(int));
-    if (e == hipSuccess && c->pg_cnt) {
-      e = hipMemset(c->pg_cnt, 0, (size_t)2 * c->num_cu * sizeof(unsigned));
-      if (e == hipSuccess) e = pg_set_lds<false, 1>();
-      if (e == hipSuccess) e = pg_set_lds<false, 4>();
-      if (e == hipSuccess) e = pg_set_lds<true, 1>();
-      for (const void* fn : {reinterpret_cast<const void*>(&k_attn_prompt<128, 4, 1>), reinterpret_cast<const void*>(&k_attn_prompt<128, 2, 2>)})
-        if (e == hipSuccess) e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * FA_TILE * 128 * 2);
-    }
+    if (e == hipSuccess && c->pg_cnt) e = hipMemset(c->pg_cnt, 0, (size_t)2 * c->num_cu * sizeof(unsigned));
+    if (e == hipSuccess) e = prefill_attributes();
     if (e == hipSuccess) e = hipMemset(c->d_err, 0, 4 * sizeof(int));
     if (e == hipSuccess) e = reset_tagged_exchange(c);
     c->step_ok = step_kernel_fits(c);
@@ -1135,12 +1152,6 @@ int first_create(const first_model_desc* desc, const first_weights* w, void* hip
     if (e == hipSuccess && B > 1 && d.dtype == FIRST_DTYPE_BF16 && d_batch_fits(c)) e = make_tiled_copies(c);
     if (e == hipSuccess) e = hipMemset(c->d_mask, 0, (size_t)B * L);
     if (e == hipSuccess) e = hipMemset(c->d_page_table, 0, (size_t)B * c->max_pages * sizeof(int));
-#define FIRST_HEAD_ATTR(WT)                                                                                                     \
-  for (const void* fn : {reinterpret_cast<const void*>(&k_head_rows<WT, 2>), reinterpret_cast<const void*>(&k_head_rows<WT, 4>),  \
-                         reinterpret_cast<const void*>(&k_head_rows<WT, 8>)})                                                     \
-    if (e == hipSuccess) e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)HEAD_ROWS_LDS + 256);
-    FIRST_HEAD_ATTR(bf16) FIRST_HEAD_ATTR(float)
-#undef FIRST_HEAD_ATTR
     // the prefill attention kernels stage more than 64 KB of LDS for head_dim 128
     if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_prefill<float, bf16>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
@@ -1648,6 +1659,21 @@ int first_lora_merge(void* hip_stream, int32_t dtype, void* W, const float* A, c
   const int rows_per_wg = std::min(64, std::max(2 * LM_RG, ((n + want_y - 1) / want_y + 2 * LM_RG - 1) / (2 * LM_RG) * (2 * LM_RG)));
   const dim3 grid(chunks, (n + rows_per_wg - 1) / rows_per_wg);
   const size_t lds = ((size_t)r * LM_COLS + (size_t)rows_per_wg * r) * sizeof(float);
+  if (r <= 8) {            // A in registers; about eight workgroups per CU, at least 16 rows each
+    const int want = std::max(1, (8 * device_cus() + chunks - 1) / chunks);
+    const int rows = std::min(64, std::max(4 * LM_RG, ((n + want - 1) / want + 2 * LM_RG - 1) / (2 * LM_RG) * (2 * LM_RG)));
+    const dim3 g(chunks, (n + rows - 1) / rows);
+    if (g.y <= 65535) {
+      if (dtype == FIRST_DTYPE_BF16)
+        hipLaunchKernelGGL(k_lora_merge_small<bf16>, g, dim3(WG), 0, st, reinterpret_cast<bf16*>(W), A, Bm, n, k, r, scale, rows);
+      else
+        hipLaunchKernelGGL(k_lora_merge_small<float>, g, dim3(WG), 0, st, reinterpret_cast<float*>(W), A, Bm, n, k, r, scale, rows);
+      const hipError_t es = hipGetLastError();
+      if (es == hipSuccess) return FIRST_OK;
+      g_create_error = std::string("first_lora_merge: ") + hipGetErrorString(es);
+      return FIRST_ERR_HIP;
+    }
+  }
   hipError_t e;
   if (dtype == FIRST_DTYPE_BF16) {
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_lora_merge<bf16>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
