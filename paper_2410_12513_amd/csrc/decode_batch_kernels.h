@@ -128,11 +128,51 @@ __global__ void __launch_bounds__(WG) k_xsplit(BatchParams P, int src, int K, in
   }
 }
 
-// h = E[token] and the rotation table of the position, for slot blockIdx.x.
-__global__ void __launch_bounds__(WG) k_embed_b(BatchParams P) {
-  DecParams p = P.d;
-  p.b = P.seqs.id[blockIdx.x];
-  phase_embed<bf16>(p);
+// Start of a step for slot blockIdx.x.  blockIdx.y = 0: h = E[token] and, with a gain, the first norm op's input as k_xsplit
+// would leave it (same sums in the same order) - sixteen elements of the row requested at a time; blockIdx.y = 1: the
+// rotation table of the position (fp64 sines, beside the embedding instead of behind it).  10 + 8 us in two launches
+// before, 6.5 now (4096 wide).
+__global__ void __launch_bounds__(WG) k_embed_b(BatchParams P, const float* gain) {
+  __shared__ float red[WAVES];
+  const DecParams& p = P.d;
+  const int j = blockIdx.x, b = P.seqs.id[j];
+  if (blockIdx.y == 1) {
+    const int pos = p.len[b];
+    for (int i = threadIdx.x; i < p.hd / 2; i += WG) {
+      const double a = (double)pos * p.theta[i];
+      p.rope_cs[(size_t)b * (p.hd / 2) + i] = make_float2((float)cos(a), (float)sin(a));
+    }
+    return;
+  }
+  const int tok = min(max(p.tokens[b], 0), p.V - 1), D = p.D;
+  const bf16* row = reinterpret_cast<const bf16*>(p.embed) + (size_t)tok * D;
+  float ss = 0.f;
+  for (int k0 = threadIdx.x; k0 < D; k0 += 16 * WG) {
+    float v[16], g[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      const int k = min(k0 + u * WG, D - 1);
+      v[u] = to_f32(row[k]);
+      g[u] = gain ? gain[k] : 0.f;
+    }
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      const int k = k0 + u * WG;
+      if (k >= D) break;
+      p.h[(size_t)b * D + k] = v[u];
+      if (gain) {
+        ss = fmaf(v[u], v[u], ss);
+        const float x = v[u] * g[u];
+        const bf16 hi = from_f32<bf16>(x);
+        P.xh[bg_aidx(j, k)] = hi;
+        P.xl[bg_aidx(j, k)] = from_f32<bf16>(x - to_f32(hi));
+      }
+    }
+  }
+  if (gain) {
+    const float tot = block_sum(ss, red);
+    if (threadIdx.x == 0) P.rinv[j] = 1.0f / sqrtf(tot / (float)D + p.eps);
+  }
 }
 
 // Decode attention of (split, KV head, slot).
@@ -983,43 +1023,56 @@ __global__ void __launch_bounds__(GW * 64) k_bgemv_g(BatchParams P, int N, int K
   }
 }
 
-// Greedy token, stage 1: candidate of chunk blockIdx.y of slot blockIdx.x's logits row.
+// Greedy token: candidate of chunk blockIdx.y of slot blockIdx.x's logits row; the last chunk of a slot to finish takes the
+// lowest index among the best candidates and advances the sequence length.  (Eight logits of a thread in flight, one
+// launch: 9.4 us for 4 x 128256, 5.6 + 4 and a gap in two launches before.)
 constexpr int ARG_CHUNKS = 64;
-__global__ void __launch_bounds__(WG) k_argmax_part_b(BatchParams P) {
+__global__ void __launch_bounds__(WG) k_argmax_b(BatchParams P, int advance) {
   __shared__ Best wbest[WAVES];
+  __shared__ int last_flag;
   const DecParams& p = P.d;
   const int b = P.seqs.id[blockIdx.x], tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const float* lg = P.logits_all + (size_t)b * p.V;
   const int per = (p.V + ARG_CHUNKS - 1) / ARG_CHUNKS, r0 = blockIdx.y * per, r1 = min(p.V, r0 + per);
   Best best{-INFINITY, 0x7fffffff};
-  for (int r = r0 + tid; r < r1; r += WG) {
-    const Best c{lg[r], r};
-    if (better(c, best)) best = c;
-  }
+  for (int i0 = r0 + tid; i0 < r1; i0 += 8 * WG) {
+    float v[8];
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const Best c{__shfl_xor(best.v, o, 64), __shfl_xor(best.i, o, 64)};
-    if (better(c, best)) best = c;
+    for (int u = 0; u < 8; ++u) v[u] = lg[min(i0 + u * WG, r1 - 1)];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const Best c{v[u], i0 + u * WG};
+      if (c.i < r1 && better(c, best)) best = c;
+    }
   }
+  auto wave_best = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      const Best c{__shfl_xor(best.v, o, 64), __shfl_xor(best.i, o, 64)};
+      if (better(c, best)) best = c;
+    }
+  };
+  wave_best();
   if (lane == 0) wbest[wave] = best;
   __syncthreads();
   if (tid == 0) {
     for (int wv = 1; wv < WAVES; ++wv)
       if (better(wbest[wv], best)) best = wbest[wv];
-    p.arg_part[(size_t)b * ARG_MAX_WG + blockIdx.y] = best;
+    Best* mine = p.arg_part + (size_t)b * ARG_MAX_WG + blockIdx.y;
+    __hip_atomic_store(&mine->v, best.v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&mine->i, best.i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    vm_wait_all();
+    const unsigned old = __hip_atomic_fetch_add(p.head_cnt + b, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int last = old == (unsigned)(ARG_CHUNKS - 1);
+    if (last) __hip_atomic_store(p.head_cnt + b, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    last_flag = last;
   }
-}
-
-// Stage 2: lowest index among the best candidates; advances the sequence length.
-__global__ void __launch_bounds__(64) k_argmax_final_b(BatchParams P, int advance) {
-  const DecParams& p = P.d;
-  const int b = P.seqs.id[blockIdx.x], lane = threadIdx.x;
-  Best best = lane < ARG_CHUNKS ? p.arg_part[(size_t)b * ARG_MAX_WG + lane] : Best{-INFINITY, 0x7fffffff};
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const Best c{__shfl_xor(best.v, o, 64), __shfl_xor(best.i, o, 64)};
-    if (better(c, best)) best = c;
-  }
+  __syncthreads();
+  if (!last_flag || wave != 0) return;
+  const Best* ap = p.arg_part + (size_t)b * ARG_MAX_WG + lane;          // one chunk per lane
+  static_assert(ARG_CHUNKS == 64, "one chunk per lane");
+  best = Best{__hip_atomic_load(&ap->v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), __hip_atomic_load(&ap->i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)};
+  wave_best();
   if (lane == 0) {
     if (p.token_out) p.token_out[b] = best.i;
     if (advance) p.len[b] += 1;
