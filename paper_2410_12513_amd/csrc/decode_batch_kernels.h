@@ -158,14 +158,15 @@ __global__ void __launch_bounds__(WG) k_embed_b(BatchParams P, const float* gain
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
       const int k = k0 + u * WG;
-      if (k >= D) break;
-      p.h[(size_t)b * D + k] = v[u];
-      if (gain) {
-        ss = fmaf(v[u], v[u], ss);
-        const float x = v[u] * g[u];
-        const bf16 hi = from_f32<bf16>(x);
-        P.xh[bg_aidx(j, k)] = hi;
-        P.xl[bg_aidx(j, k)] = from_f32<bf16>(x - to_f32(hi));
+      if (k < D) {
+        p.h[(size_t)b * D + k] = v[u];
+        if (gain) {
+          ss = fmaf(v[u], v[u], ss);
+          const float x = v[u] * g[u];
+          const bf16 hi = from_f32<bf16>(x);
+          P.xh[bg_aidx(j, k)] = hi;
+          P.xl[bg_aidx(j, k)] = from_f32<bf16>(x - to_f32(hi));
+        }
       }
     }
   }

@@ -338,19 +338,20 @@ __device__ __forceinline__ void phase_attn(const DecParams& p, int g, int s, cha
         l[hi] = l[hi] * corr + wave_sum(pj);
         o0[hi] *= corr; o1[hi] *= corr;
         m[hi] = mn;
-        // o += p_j * V[j]; lane owns dims lane and lane+64 (hd = 64 or 128)
-        if (hd > 64) {
-#pragma unroll 8
-          for (int j = 0; j < jn; ++j) {
-            const float pb = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(pj), j));
-            o0[hi] = fmaf(pb, to_f32(vt[j * hd + lane]), o0[hi]);
-            o1[hi] = fmaf(pb, to_f32(vt[j * hd + lane + 64]), o1[hi]);
+        // o += p_j * V[j]; lane owns dims lane and lane+64 (hd = 64 or 128).  Eight keys at a time, their values requested
+        // together: past jn the weights and the staged values are zeros
+        for (int j0 = 0; j0 < jn; j0 += 8) {
+          float v0[8], v1[8];
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            v0[j] = to_f32(vt[(j0 + j) * hd + lane]);
+            v1[j] = hd > 64 ? to_f32(vt[(j0 + j) * hd + lane + 64]) : 0.f;
           }
-        } else {
-#pragma unroll 16
-          for (int j = 0; j < jn; ++j) {
-            const float pb = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(pj), j));
-            o0[hi] = fmaf(pb, to_f32(vt[j * 64 + lane]), o0[hi]);
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            const float pb = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(pj), j0 + j));
+            o0[hi] = fmaf(pb, v0[j], o0[hi]);
+            o1[hi] = fmaf(pb, v1[j], o1[hi]);
           }
         }
       }

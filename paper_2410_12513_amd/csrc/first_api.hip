@@ -794,6 +794,18 @@ void launch_attn_prompt(first_ctx* c, hipStream_t st, bf16* pool, const PromptPa
                        c->p_ah, c->p_al, pk, padded, d.n_q_heads, d.n_kv_heads);
 }
 
+// x = RMSNorm of the rows of p_H (split for bf16 models), with a router's sigmoid of every row beside it.  A workgroup per row
+// once each of its threads has two pieces, a wave per row below that.
+void launch_rmsnorm(first_ctx* c, hipStream_t st, const float* gain, const float* router, float* sig, int R, bool hl) {
+  const int D = c->d.d_model;
+  float* x = reinterpret_cast<float*>(c->p_x);
+  bf16 *xh = hl ? c->p_xh : nullptr, *xl = hl ? c->p_xl : nullptr;
+  if (D >= 8 * WG)
+    hipLaunchKernelGGL(k_rmsnorm_router_wide<float>, dim3(R), dim3(WG), 0, st, c->p_H, gain, router, x, sig, D, c->d.rms_eps, xh, xl);
+  else
+    hipLaunchKernelGGL(k_rmsnorm_router<float>, dim3((R + WAVES - 1) / WAVES), dim3(WG), 0, st, c->p_H, gain, router, x, sig, R, D, c->d.rms_eps, xh, xl);
+}
+
 // Prompt pass of sequences b0 .. b0 + n - 1, whose ids follow each other at ids: all layers on the packed rows, routers scored on
 // the way.  soft: the soft-skip pass (training side).
 template <typename WT>
@@ -816,15 +828,16 @@ int prefill_group(first_ctx* c, int b0, int n, const int* ids, float* hidden_out
   const bool hl = d.dtype == FIRST_DTYPE_BF16;   // activations leave their producers split for the matrix cores
   float* rho = c->d_rho + (size_t)b0 * L;
   uint8_t* mask = c->d_mask + (size_t)b0 * L;
+  const bool per_layer = soft || c->kv_elide;    // a router's score is needed before the next layer
 
   hipLaunchKernelGGL(k_embed_rows<WT>, dim3(R), dim3(WG), 0, st, ids, reinterpret_cast<const WT*>(c->embed), c->p_H, D, d.vocab);
   hipLaunchKernelGGL(k_rope_table, dim3((T_max * c->half + WG - 1) / WG), dim3(WG), 0, st, c->d_theta, c->p_cs, T_max, c->half);
   for (int i = 0; i < L; ++i) {
     const LayerPtrs& l = c->layers[i];
     // router i reads the stream entering layer i, in the same pass as the attention norm
-    hipLaunchKernelGGL(k_rmsnorm_router<float>, dim3((R + WAVES - 1) / WAVES), dim3(WG), 0, st, c->p_H, l.g_attn,
-                       c->router + (size_t)i * D, x, c->p_sig, R, D, d.rms_eps, hl ? c->p_xh : nullptr, hl ? c->p_xl : nullptr);
-    hipLaunchKernelGGL(k_router_reduce, dim3(n), dim3(WG), 0, st, c->p_sig, pk.off, rho + i, mask + i, L);
+    launch_rmsnorm(c, st, l.g_attn, c->router + (size_t)i * D, c->p_sig + (per_layer ? 0 : (size_t)i * c->p_rows), R, hl);
+    if (per_layer)
+      hipLaunchKernelGGL(k_router_reduce, dim3(n, 1), dim3(WG), 0, st, c->p_sig, (size_t)0, pk.off, rho + i, mask + i, L);
     if (soft)            // the stream entering the layer, for H = Hprev + rho (phi(Hprev))
       HIPCHK(c, hipMemcpyAsync(c->p_Hs, c->p_H, (size_t)R * D * sizeof(float), hipMemcpyDeviceToDevice, st));
     if (c->kv_elide && !soft) {   // the decisions are known before the layer stores anything (Section 4.1): fetch them while Q/K/V run
@@ -881,8 +894,7 @@ int prefill_group(first_ctx* c, int b0, int n, const int* ids, float* hidden_out
       }
     }
     if ((rc = gemm(a, c->p_ah, c->p_al, l.wo, c->p_H, D, c->nq, 1))) return rc;
-    hipLaunchKernelGGL(k_rmsnorm_router<float>, dim3((R + WAVES - 1) / WAVES), dim3(WG), 0, st, c->p_H, l.g_mlp,
-                       (const float*)nullptr, x, (float*)nullptr, R, D, d.rms_eps, hl ? c->p_xh : nullptr, hl ? c->p_xl : nullptr);
+    launch_rmsnorm(c, st, l.g_mlp, nullptr, nullptr, R, hl);
     if (hl) {        // SiLU(gate) * up in the GEMM's epilogue, written split for the down projection
       if ((rc = launch_gemm_hl_gu(c, st, c->p_xh, c->p_xl, l.wg, l.wu, c->p_zh, c->p_zl, R, F, D))) return rc;
     } else {
@@ -894,6 +906,8 @@ int prefill_group(first_ctx* c, int b0, int n, const int* ids, float* hidden_out
     if ((rc = gemm(z, c->p_zh, c->p_zl, l.wd, c->p_H, D, F, 1))) return rc;
     if (soft) hipLaunchKernelGGL(k_soft_blend, dim3(R), dim3(WG), 0, st, c->p_H, c->p_Hs, rho + i, L, pk.off, n, D);
   }
+  if (!per_layer)    // all routers' scores of all prompts in one launch
+    hipLaunchKernelGGL(k_router_reduce, dim3(n, L), dim3(WG), 0, st, c->p_sig, (size_t)c->p_rows, pk.off, rho, mask, L);
   if (!soft)         // last positions -> decode residual slots (+ optional copy out)
     hipLaunchKernelGGL(k_last_rows, dim3(n), dim3(WG), 0, st, c->p_H, pk.off, c->d_h + (size_t)b0 * D,
                        hidden_out ? hidden_out + (size_t)b0 * D : nullptr, c->d_len + b0, D);
@@ -1079,7 +1093,7 @@ int first_create(const first_model_desc* desc, const first_weights* w, void* hip
   if (d.dtype != FIRST_DTYPE_BF16) {   // (bf16 models form SiLU(gate) * up in the GEMM's epilogue: no fp32 gate / up matrices)
     A(dev_alloc(c, &c->p_g, (size_t)T * d.d_ffn)); A(dev_alloc(c, &c->p_u, (size_t)T * d.d_ffn));
   }
-  A(dev_alloc(c, &c->p_sig, T)); A(dev_alloc(c, &c->p_cs, (size_t)T * c->half));
+  A(dev_alloc(c, &c->p_sig, (size_t)T * L)); A(dev_alloc(c, &c->p_cs, (size_t)T * c->half));
   // (bf16 models write the normed stream and the MLP activation split: fp32 copies hold the last positions' norm only / nothing)
   A(dev_alloc(c, reinterpret_cast<char**>(&c->p_x), (size_t)(d.dtype == FIRST_DTYPE_BF16 ? B : T) * d.d_model * 4));
   A(dev_alloc(c, reinterpret_cast<char**>(&c->p_a), (size_t)T * c->nq * 4));
@@ -1635,8 +1649,7 @@ int first_soft_forward(first_ctx* c, int32_t B, const int32_t* ids, const int32_
       HIPCHK(c, hipMemcpyAsync(hidden_out + off * D, c->p_H, (size_t)R * D * sizeof(float), hipMemcpyDeviceToDevice, st));
     // logits of every position = W_lm . RMSNorm(H_L; g_final), SOFT_ROWS positions at a time, then their cross entropy
     float* x = reinterpret_cast<float*>(c->p_x);
-    hipLaunchKernelGGL(k_rmsnorm_router<float>, dim3((R + WAVES - 1) / WAVES), dim3(WG), 0, st, c->p_H, c->g_final,
-                       (const float*)nullptr, x, (float*)nullptr, R, D, d.rms_eps, hl ? c->p_xh : nullptr, hl ? c->p_xl : nullptr);
+    launch_rmsnorm(c, st, c->g_final, nullptr, nullptr, R, hl);
     for (int r0 = 0; r0 < R; r0 += SOFT_ROWS) {
       const int rows = std::min(SOFT_ROWS, R - r0);
       rc = hl ? launch_gemm_hl(c, st, c->p_xh + (size_t)r0 * D, c->p_xl + (size_t)r0 * D, c->lm_head, c->p_lg, rows, V, D, 0)

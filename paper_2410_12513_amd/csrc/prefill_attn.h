@@ -19,18 +19,6 @@ constexpr int FA_TILE = 64;              // keys per tile of kc / vt
 constexpr int FA_WIDE_FROM = 2048;       // prompts of at least this many tokens: 128 queries a workgroup
 constexpr float LOG2E = 1.4426950408889634f;
 
-typedef __attribute__((__vector_size__(2 * sizeof(float)))) float float2v_t;
-typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2_t;
-// two fp32 -> two bf16 (nearest even) in one register, low half first
-__device__ __forceinline__ uint32_t pk_bf16(float a, float b) {
-  const float2v_t v = {a, b};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
-}
-// hi = bf16(x), lo = bf16(x - hi) for a pair
-__device__ __forceinline__ void split_pair(float a, float b, uint32_t& hi, uint32_t& lo) {
-  hi = pk_bf16(a, b);
-  lo = pk_bf16(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xffff0000u));
-}
 // x in both halves of the wave -> (value of lane % 32 in the lower half, in the upper half)
 __device__ __forceinline__ void both_halves(float x, float& lower, float& upper) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
@@ -238,10 +226,12 @@ __global__ void __launch_bounds__(WG, 2) k_attn_prompt(const bf16* __restrict__ 
       m = mn;
     }
     const float m2e = m * LOG2E;
+    float ls[4] = {0.f, 0.f, 0.f, 0.f};                    // the tile's sum first: a long prompt's l is thousands of terms
 #pragma unroll
     for (int u = 0; u < NS; ++u)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) { S[u][r] = __builtin_amdgcn_exp2f(fmaf(S[u][r], LOG2E, -m2e)); l += S[u][r]; }
+      for (int r = 0; r < 16; ++r) { S[u][r] = __builtin_amdgcn_exp2f(fmaf(S[u][r], LOG2E, -m2e)); ls[r & 3] += S[u][r]; }
+    l += (ls[0] + ls[1]) + (ls[2] + ls[3]);
     // O^T += V^T P^T: k-step s2 uses accumulator registers 8 s2 .. 8 s2 + 7 of P as they are
 #pragma unroll
     for (int s2 = 0; s2 < 2 * NS; ++s2) {

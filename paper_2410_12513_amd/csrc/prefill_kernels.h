@@ -8,6 +8,19 @@ namespace first {
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16_t;
 
+typedef __attribute__((__vector_size__(2 * sizeof(float)))) float float2v_t;
+typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2_t;
+// two fp32 -> two bf16 (nearest even) in one register, low half first
+__device__ __forceinline__ uint32_t pk_bf16(float a, float b) {
+  const float2v_t v = {a, b};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
+}
+// hi = bf16(x), lo = bf16(x - hi) for a pair
+__device__ __forceinline__ void split_pair(float a, float b, uint32_t& hi, uint32_t& lo) {
+  hi = pk_bf16(a, b);
+  lo = pk_bf16(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xffff0000u));
+}
+
 // Prompts go through the layers in groups, packed row after row.
 // The prompts of one group: rows off[j] - off[0] .. of sequence b0 + j, padded rows from poff[j] - poff[0].
 struct PromptPack {
@@ -103,14 +116,73 @@ __global__ void __launch_bounds__(WG) k_rmsnorm_router(const float* __restrict__
   }
 }
 
-// rho = mean_t sig[t] (fixed summation order); mask = (rho >= 0.5).  One workgroup per prompt of the group: rows off[j] - off[0] ..,
-// results of prompt j at rho / mask + j * stride.  (A thread requests eight of its values before it adds the first: one
+// The same with a workgroup per token, for rows long enough to give every thread several pieces: at 1024 tokens a wave per
+// token is one wave per SIMD, and reads the row twice.  The first 4096 elements of the row stay in registers between the
+// sums and the scaling.  Bound: HBM / latency (1024 x 4096, 33 MB: 18 -> 12 us).
+template <typename XT>
+__global__ void __launch_bounds__(WG) k_rmsnorm_router_wide(const float* __restrict__ H, const float* __restrict__ gain,
+                                                            const float* __restrict__ rw, XT* __restrict__ x, float* __restrict__ sig,
+                                                            int D, float eps, bf16* __restrict__ xh, bf16* __restrict__ xl) {
+  __shared__ float2 red[WAVES];
+  constexpr int RB = 4;
+  const int t = blockIdx.x, tid = threadIdx.x;
+  const float* row = H + (size_t)t * D;
+  float4 v[RB];
+  float ss = 0.f, dot = 0.f;
+  auto add = [&](const float4& a, const float4& w) __attribute__((always_inline)) {
+    ss = fmaf(a.x, a.x, ss); ss = fmaf(a.y, a.y, ss); ss = fmaf(a.z, a.z, ss); ss = fmaf(a.w, a.w, ss);
+    dot = fmaf(a.x, w.x, dot); dot = fmaf(a.y, w.y, dot); dot = fmaf(a.z, w.z, dot); dot = fmaf(a.w, w.w, dot);
+  };
+  const float4 zero = make_float4(0, 0, 0, 0);
+  {
+    float4 w[RB];
+#pragma unroll
+    for (int u = 0; u < RB; ++u) {
+      const int k = tid * 4 + u * WG * 4;
+      v[u] = k < D ? *reinterpret_cast<const float4*>(row + k) : zero;
+      w[u] = rw && k < D ? *reinterpret_cast<const float4*>(rw + k) : zero;
+    }
+#pragma unroll
+    for (int u = 0; u < RB; ++u) add(v[u], w[u]);
+  }
+  for (int k = tid * 4 + RB * WG * 4; k < D; k += WG * 4) add(*reinterpret_cast<const float4*>(row + k), rw ? *reinterpret_cast<const float4*>(rw + k) : zero);
+  ss = wave_sum(ss); dot = wave_sum(dot);
+  if ((tid & 63) == 0) red[tid >> 6] = make_float2(ss, dot);
+  __syncthreads();
+  ss = 0.f; dot = 0.f;
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) { ss += red[w].x; dot += red[w].y; }
+  const float r = 1.0f / sqrtf(ss / (float)D + eps);
+  auto put = [&](int k, const float4& a) __attribute__((always_inline)) {
+    const float4 g = *reinterpret_cast<const float4*>(gain + k);
+    const float y[4] = {a.x * g.x * r, a.y * g.y * r, a.z * g.z * r, a.w * g.w * r};
+    if (xh) {                                      // split for the matrix cores: y = hi + lo
+      uint2 hi, lo;
+      split_pair(y[0], y[1], hi.x, lo.x); split_pair(y[2], y[3], hi.y, lo.y);
+      *reinterpret_cast<uint2*>(xh + (size_t)t * D + k) = hi;
+      *reinterpret_cast<uint2*>(xl + (size_t)t * D + k) = lo;
+    } else {
+      XT* o = x + (size_t)t * D + k;
+      o[0] = from_f32<XT>(y[0]); o[1] = from_f32<XT>(y[1]); o[2] = from_f32<XT>(y[2]); o[3] = from_f32<XT>(y[3]);
+    }
+  };
+#pragma unroll
+  for (int u = 0; u < RB; ++u) {
+    const int k = tid * 4 + u * WG * 4;
+    if (k < D) put(k, v[u]);
+  }
+  for (int k = tid * 4 + RB * WG * 4; k < D; k += WG * 4) put(k, *reinterpret_cast<const float4*>(row + k));
+  if (rw && tid == 0) sig[t] = sigmoidf(dot);
+}
+
+// rho = mean_t sig[t] (fixed summation order); mask = (rho >= 0.5).  One workgroup per prompt j of the group (blockIdx.x; rows
+// off[j] - off[0] .. of sig) and layer i (blockIdx.y; sig + i * sig_pitch); results at rho / mask + j * stride + i.  (A thread requests eight of its values before it adds the first: one
 // after the other took 20 us at 16384 tokens.)
-__global__ void __launch_bounds__(WG) k_router_reduce(const float* __restrict__ sig, const int* __restrict__ off,
+__global__ void __launch_bounds__(WG) k_router_reduce(const float* __restrict__ sig, size_t sig_pitch, const int* __restrict__ off,
                                                       float* __restrict__ rho, uint8_t* __restrict__ mask, int stride) {
   __shared__ float red[WAVES];
   const int j = blockIdx.x, T = off[j + 1] - off[j];
-  sig += off[j] - off[0];
+  sig += blockIdx.y * sig_pitch + (off[j] - off[0]);
   float s = 0.f;
   for (int t0 = threadIdx.x; t0 < T; t0 += 8 * WG) {
     float v[8];
@@ -123,8 +195,8 @@ __global__ void __launch_bounds__(WG) k_router_reduce(const float* __restrict__ 
   const float tot = block_sum(s, red);
   if (threadIdx.x == 0) {
     const float r = __fdiv_rn(tot, (float)T);
-    rho[(size_t)j * stride] = r;
-    mask[(size_t)j * stride] = (r >= 0.5f) ? 1 : 0;
+    rho[(size_t)j * stride + blockIdx.y] = r;
+    mask[(size_t)j * stride + blockIdx.y] = (r >= 0.5f) ? 1 : 0;
   }
 }
 
