@@ -530,7 +530,7 @@ __global__ void __launch_bounds__(WG) k_head_norm(DecParams p, float* __restrict
 // wave takes four rows at a time and multiplies them with all of them.  Same fp32 products and the same order of
 // additions per sequence as phase_head.  Bound: HBM, the matrix once per NS sequences instead of once per sequence;
 // sixteen waves share the staged vectors, since with 96 KB of them a compute unit has room for one workgroup only
-// (128256 x 3072, eight sequences: 8 x 193 us one by one, 670 with four waves, 182 with sixteen).
+// (128256 x 3072, eight sequences: 8 x 193 us one by one, 670 with four waves, 182 with sixteen, 160 with the next weights on their way).
 constexpr int HR_THREADS = 1024, HR_WAVES = HR_THREADS / 64;
 template <typename WT, int NS>
 __global__ void __launch_bounds__(HR_THREADS) k_head_rows(DecParams p, const float* __restrict__ x, int b0, int n) {
@@ -552,10 +552,20 @@ __global__ void __launch_bounds__(HR_THREADS) k_head_rows(DecParams p, const flo
     for (int i = 0; i < R; ++i)
 #pragma unroll
       for (int j = 0; j < NS; ++j) acc[i][j] = 0.f;
+    u32x4_t raw[R], nxt[R];                                // this chunk's weights, the next one's on their way
+    auto fetch = [&](u32x4_t (&v)[R], int k) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < R; ++i) v[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(rp[i] + k));
+    };
     auto step = [&](int k) __attribute__((always_inline)) {
       float wv[R][VEC];
 #pragma unroll
-      for (int i = 0; i < R; ++i) load_vec(rp[i] + k, wv[i]);
+      for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          if (VEC == 8) { wv[i][(2 * e) % VEC] = __uint_as_float(raw[i][e] << 16); wv[i][(2 * e + 1) % VEC] = __uint_as_float(raw[i][e] & 0xffff0000u); }
+          else wv[i][e] = __uint_as_float(raw[i][e]);
+        }
 #pragma unroll
       for (int j = 0; j < NS; ++j) {
         const float* xs = smem_f + (size_t)j * D;
@@ -574,7 +584,14 @@ __global__ void __launch_bounds__(HR_THREADS) k_head_rows(DecParams p, const flo
           for (int e = 0; e < VEC; ++e) acc[i][j] = fmaf(wv[i][e], xv[e], acc[i][j]);
       }
     };
-    for (int c = 0; c < full; ++c) step((c * 64 + lane) * VEC);
+    fetch(raw, min(lane * VEC, D - VEC));
+    for (int c = 0; c < full; ++c) {
+      const int k = (c * 64 + lane) * VEC;
+      fetch(nxt, min(k + 64 * VEC, D - VEC));              // (past the row's end: a piece it has, not used)
+      step(k);
+#pragma unroll
+      for (int i = 0; i < R; ++i) raw[i] = nxt[i];
+    }
     if (ktail < D) step(ktail);
 #pragma unroll
     for (int i = 0; i < R; ++i)

@@ -40,6 +40,8 @@ __device__ __forceinline__ int pack_find(const int* o, int n, int row) {
   return lo;
 }
 
+__device__ __forceinline__ float4 keep4(float4 v, bool in) { return make_float4(in ? v.x : 0.f, in ? v.y : 0.f, in ? v.z : 0.f, in ? v.w : 0.f); }
+
 // H[t] = E[ids[t]] widened to fp32.  grid = T.
 template <typename WT>
 __global__ void __launch_bounds__(WG) k_embed_rows(const int* __restrict__ ids, const WT* __restrict__ E,
@@ -139,13 +141,18 @@ __global__ void __launch_bounds__(WG) k_rmsnorm_router_wide(const float* __restr
 #pragma unroll
     for (int u = 0; u < RB; ++u) {
       const int k = tid * 4 + u * WG * 4;
-      v[u] = k < D ? *reinterpret_cast<const float4*>(row + k) : zero;
-      w[u] = rw && k < D ? *reinterpret_cast<const float4*>(rw + k) : zero;
+      v[u] = keep4(*reinterpret_cast<const float4*>(row + min(k, D - 4)), k < D);
+      w[u] = zero;
+      if (rw) w[u] = keep4(*reinterpret_cast<const float4*>(rw + min(k, D - 4)), k < D);
     }
 #pragma unroll
     for (int u = 0; u < RB; ++u) add(v[u], w[u]);
   }
-  for (int k = tid * 4 + RB * WG * 4; k < D; k += WG * 4) add(*reinterpret_cast<const float4*>(row + k), rw ? *reinterpret_cast<const float4*>(rw + k) : zero);
+  for (int k = tid * 4 + RB * WG * 4; k < D; k += WG * 4) {
+    float4 w = zero;
+    if (rw) w = *reinterpret_cast<const float4*>(rw + k);
+    add(*reinterpret_cast<const float4*>(row + k), w);
+  }
   ss = wave_sum(ss); dot = wave_sum(dot);
   if ((tid & 63) == 0) red[tid >> 6] = make_float2(ss, dot);
   __syncthreads();
@@ -681,9 +688,10 @@ __global__ void __launch_bounds__(WG) k_gemm_nt_f32_small(const float* __restric
 #pragma unroll
     for (int u = 0; u < TT; ++u) {                         // 16 rows of 16 pieces per round
       const int row = u * 16 + ty, k = k0 + tx * 4;
-      const float4 zero = make_float4(0, 0, 0, 0);
-      ra[u] = k < K && m0 + row < M ? *reinterpret_cast<const float4*>(A + (size_t)(m0 + row) * K + k) : zero;
-      rb[u] = k < K && n0 + row < N ? *reinterpret_cast<const float4*>(W + (size_t)(n0 + row) * K + k) : zero;
+      // (a piece that exists is loaded whatever happens and zeroed afterwards: choosing between a load and a constant makes
+      // the compiler choose between two addresses, one of them in scratch memory)
+      ra[u] = keep4(*reinterpret_cast<const float4*>(A + (size_t)min(m0 + row, M - 1) * K + min(k, K - 4)), k < K && m0 + row < M);
+      rb[u] = keep4(*reinterpret_cast<const float4*>(W + (size_t)min(n0 + row, N - 1) * K + min(k, K - 4)), k < K && n0 + row < N);
     }
   };
   float acc[TT][TT] = {};

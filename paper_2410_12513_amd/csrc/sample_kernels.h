@@ -75,26 +75,38 @@ __device__ __forceinline__ void rank_merge(const unsigned long long* keys, int n
   __syncthreads();
 }
 
-// The draw: top[0..k) in order (SMP_NONE beyond the vocabulary), weight(j) = exp((l_j - l_max) / T), u in [0, 1).  One thread;
-// every path that samples ends in this function, so that they take the same decision on the same candidates.
-template <typename Weight>
-__device__ __forceinline__ int smp_pick(const Cand* top, int k, float u, Weight weight) {
+// The draw: top[0..k) in order (SMP_NONE beyond the vocabulary), u in [0, 1).  One thread.  smp_draw forms the weights as it
+// goes (the persistent kernel's single lane), smp_pick takes them ready (formed side by side by the lanes of
+// k_topk_sample): the same values, the same sums, the same decision.
+__device__ __forceinline__ float smp_weight(const Cand& c, const Cand& best, float temperature) { return expf((c.v - best.v) / temperature); }
+__device__ __forceinline__ int smp_draw(const Cand* top, int k, float temperature, float u) {
   int kk = 0;
   while (kk < k && top[kk].i != SMP_NONE) ++kk;
+  const float lmax = top[0].v;
   float total = 0.f;
-  for (int j = 0; j < kk; ++j) total += weight(j);
+  for (int j = 0; j < kk; ++j) total += expf((top[j].v - lmax) / temperature);
   const float target = u * total;
   float cum = 0.f;
   int pick = kk > 0 ? top[kk - 1].i : 0;
   for (int j = 0; j < kk; ++j) {
-    cum += weight(j);
+    cum += expf((top[j].v - lmax) / temperature);
     if (cum > target) { pick = top[j].i; break; }
   }
   return pick;
 }
-__device__ __forceinline__ float smp_weight(const Cand& c, const Cand& best, float temperature) { return expf((c.v - best.v) / temperature); }
-__device__ __forceinline__ int smp_draw(const Cand* top, int k, float temperature, float u) {
-  return smp_pick(top, k, u, [=](int j) { return smp_weight(top[j], top[0], temperature); });
+__device__ __forceinline__ int smp_pick(const Cand* top, const float* weight, int k, float u) {
+  int kk = 0;
+  while (kk < k && top[kk].i != SMP_NONE) ++kk;
+  float total = 0.f;
+  for (int j = 0; j < kk; ++j) total += weight[j];
+  const float target = u * total;
+  float cum = 0.f;
+  int pick = kk > 0 ? top[kk - 1].i : 0;
+  for (int j = 0; j < kk; ++j) {
+    cum += weight[j];
+    if (cum > target) { pick = top[j].i; break; }
+  }
+  return pick;
 }
 
 // Stage 1.  grid (chunks, sequences).  part[(seq * chunks + chunk) * k + r] = r-th candidate of the chunk.
@@ -149,7 +161,7 @@ __global__ void __launch_bounds__(SMP_THREADS) k_topk_sample(const Cand* __restr
     if (cand_out != nullptr) cand_out[(size_t)seq * k + tid] = t.i == SMP_NONE ? -1 : t.i;
   }
   __syncthreads();
-  if (tid == 0) token_out[seq] = smp_pick(first, k, u, [&](int j) { return weight[j]; });
+  if (tid == 0) token_out[seq] = smp_pick(first, weight, k, u);
 }
 
 }  // namespace first
