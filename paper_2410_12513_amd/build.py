@@ -21,8 +21,10 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
 # written later, so a destination it spills and hands to another value is overwritten when the load lands.  Bytes of
 # scratch per lane each kernel may use (k_attn_tiles_b: a handful of loop-invariant values the compiler parks there under
 # the kernel's 128-register cap; asm_check.py verifies that no in-flight destination is among them, or is touched in any
-# other way; "k_bgemv" covers k_bgemv and k_bgemv_g):
-SCRATCH_LIMITS = {"k_step": 0, "k_attn_tiles_b": 32, "k_attn_mfma_b": 0, "k_bgemv": 0, "k_gemm_nt_bf16_hl": 0}
+# other way; "k_bgemv" covers k_bgemv and k_bgemv_g).  k_pgemm and k_attn_prompt load straight into LDS and wait by
+# counting the loads behind the one they need: a reload from scratch would be counted among them.
+SCRATCH_LIMITS = {"k_step": 0, "k_attn_tiles_b": 32, "k_attn_mfma_b": 0, "k_bgemv": 0, "k_gemm_nt_bf16_hl": 0,
+                  "k_pgemm": 0, "k_attn_prompt": 0}
 
 
 def kernel_resources(remarks: str) -> dict:
