@@ -1094,8 +1094,9 @@ int first_create(const first_model_desc* desc, const first_weights* w, void* hip
     A(dev_alloc(c, &c->p_g, (size_t)T * d.d_ffn)); A(dev_alloc(c, &c->p_u, (size_t)T * d.d_ffn));
   }
   A(dev_alloc(c, &c->p_sig, (size_t)T * L)); A(dev_alloc(c, &c->p_cs, (size_t)T * c->half));
-  // (bf16 models write the normed stream and the MLP activation split: fp32 copies hold the last positions' norm only / nothing)
-  A(dev_alloc(c, reinterpret_cast<char**>(&c->p_x), (size_t)(d.dtype == FIRST_DTYPE_BF16 ? B : T) * d.d_model * 4));
+  // (bf16 models write the normed stream and the MLP activation split: fp32 copies hold the last positions' norm only / nothing.
+  // The last positions are a row for each of up to max_batch prompts, which can be more than a group has rows.)
+  A(dev_alloc(c, reinterpret_cast<char**>(&c->p_x), (size_t)(d.dtype == FIRST_DTYPE_BF16 ? B : std::max(T, B)) * d.d_model * 4));
   A(dev_alloc(c, reinterpret_cast<char**>(&c->p_a), (size_t)T * c->nq * 4));
   if (d.dtype == FIRST_DTYPE_BF16) {
     A(dev_alloc(c, &c->p_xh, (size_t)T * d.d_model)); A(dev_alloc(c, &c->p_xl, (size_t)T * d.d_model));

@@ -79,3 +79,22 @@ def test_group_with_elided_layers_matches_one_without():
             assert torch.equal(full[k], part[k])
     except P.FirstError as e:
         assert e.code == -3 and int(kept.sum()) > 1
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+def test_more_prompts_than_workspace_rows(dtype):
+    """The last positions of a call are a row per prompt beside the rows of a group: 4200 prompts of one token in a context whose
+    prompt pass takes 4096 rows.  Every prompt is one of 37, whose results a context with room for them all gives."""
+    desc = ModelDesc(1, 64, 2, 1, 64, 72, 37, dtype=dtype)
+    w, r = to_device(make_weights(desc, 8), "cuda"), make_router(desc, 8).cuda()
+    one = _run(desc, w, r, [torch.tensor([t], dtype=torch.int32) for t in range(37)], 2)
+    ids = make_prompt(desc.vocab, 4200, 80)
+    import paper_2410_12513_amd as P
+    ctx = P.FirstContext(desc, w, r, max_batch=4200, max_seq_len=2)
+    out = dict(rho=torch.zeros(4200, 1, device="cuda"), hidden=torch.zeros(4200, 64, device="cuda"),
+               logits=torch.zeros(4200, 37, device="cuda"), token=torch.zeros(4200, dtype=torch.int32, device="cuda"))
+    ctx.prefill_route(ids.cuda(), [1] * 4200, **out)
+    ctx.close()
+    for k, v in out.items():
+        assert torch.equal(v.cpu(), one[k][ids.long()]), k
