@@ -19,14 +19,15 @@ namespace first {
 
 constexpr int PG_BK = 64;                       // K step: one row of a tile is 128 bytes
 
-// 16 bytes per lane from (descriptor base + voff + soff) to LDS byte lds_off + 16 * lane.  No register is written: nothing
-// for the compiler to reuse too early; pg_wait / pg_barrier order it.
+// 16 bytes per lane from (descriptor base + voff + soff) to LDS byte lds_off + 16 * lane.  No vector register is written: nothing
+// for the compiler to reuse too early; pg_wait / lds_barrier order it.  The LDS offset travels in m0, as an operand: it is the
+// compiler that writes the register, so it knows (m0 written in the asm text would be a write it knows nothing of).
 typedef int i32x4_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void pg_load_lds(uint32_t lds_off, uint32_t voff, i32x4_t rsrc, uint32_t soff) {
   // (uniform by construction; said again for the compiler, which does not see it through every loop)
   lds_off = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_off);
   soff = (uint32_t)__builtin_amdgcn_readfirstlane((int)soff);
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds_off), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+  asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"{m0}"(lds_off), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
 }
 __device__ __forceinline__ i32x4_t pg_rsrc(const void* p, uint32_t bytes) {
   const uint64_t a = reinterpret_cast<uint64_t>(p);

@@ -1,5 +1,8 @@
 """The kernels that keep loads in flight through inline asm must not let go of a load's destination register before
 the wait that covers the load (paper_2410_12513_amd/asm_check.py): a check of the library's own assembly, on the CPU."""
+import os
+import re
+
 from paper_2410_12513_amd import asm_check
 
 
@@ -87,3 +90,20 @@ def test_no_kernel_of_the_library_touches_a_load_destination_in_flight():
     assert all(n >= 1 for n in seen.values()), seen          # the walk must not be blind: every family of kernels is found
     hits = asm_check.touched_in_flight(asm)
     assert not hits, hits[:5]
+
+
+def test_loads_into_lds_take_their_offset_as_an_operand():
+    """m0 carries the LDS offset of a load into LDS, and it also serves the compiler (register indexing, loads of its own).  It is
+    reserved, so an asm statement cannot name it as overwritten: it has to be an operand, which the compiler writes itself."""
+    csrc = os.path.dirname(asm_check.SRC)
+    loads = 0
+    for name in sorted(os.listdir(csrc)):
+        with open(os.path.join(csrc, name)) as fh:
+            text = fh.read()
+        for m in re.finditer(r"\basm\s+volatile\s*\((.*?)\);", text, re.S):
+            code = m.group(1)
+            assert not re.search(r"\bm0\s*,", code), (name, code)            # m0 as a destination
+            if re.search(r"buffer_load\S*[^\"]*\blds\b", code):
+                assert '"{m0}"' in code, (name, code)
+                loads += 1
+    assert loads >= 1
