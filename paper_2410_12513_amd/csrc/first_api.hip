@@ -83,7 +83,6 @@ struct first_ctx {
   void *p_x = nullptr, *p_a = nullptr, *p_z = nullptr;
   bf16 *p_qh = nullptr, *p_ql = nullptr, *p_kc = nullptr, *p_vt = nullptr;   // matrix-core prefill attention operands
   bf16 *p_xh = nullptr, *p_xl = nullptr, *p_ah = nullptr, *p_al = nullptr, *p_zh = nullptr, *p_zl = nullptr;   // split activations (bf16 models)
-  bool w_aligned = false;                 // every matrix starts on 16 bytes (bf16 models): what k_pgemm's loads need
   float* pg_part = nullptr;               // k_pgemm: partial tiles of the slices of K, four for each of at most num_cu tiles of 64 x 128
   unsigned* pg_cnt = nullptr;             //          arrival counters per tile (zero between launches)
   int p_rows = 0;                         // rows of the prefill workspace: prompts of a batch go through it in groups of at most this many rows
@@ -721,8 +720,9 @@ hipError_t pg_set_lds() {
   if (e == hipSuccess) e = set(reinterpret_cast<const void*>(&k_pgemm<64, 256, 2, 4, 3, GU, false, SEG>), pg_lds<64, 256, 3>());
   return e;
 }
-// k_pgemm's loads start on 16 bytes (K is a multiple of 8), and it addresses the rows of a tile with 31 bits.
-bool pg_fits(const first_ctx* c, int N, int K) { return c->w_aligned && K <= (1 << 21) && N <= (1 << 21); }
+// k_pgemm's loads start on 16 bytes (K is a multiple of 8, so the first row decides), and it addresses the rows of a tile with
+// 31 bits.
+bool pg_fits(const void* W, int N, int K) { return reinterpret_cast<uintptr_t>(W) % 16 == 0 && K <= (1 << 21) && N <= (1 << 21); }
 
 PgArgs pg_args(const first_ctx* c, const PgPlan& plan, const bf16* Ah, const bf16* Al, int M, int K, int acc) {
   PgArgs P{};
@@ -734,12 +734,15 @@ PgArgs pg_args(const first_ctx* c, const PgPlan& plan, const bf16* Ah, const bf1
 // Up to three projections of the same split activations in one launch.
 int launch_gemm_hl_seg(first_ctx* c, hipStream_t st, const bf16* Ah, const bf16* Al, int M, int K, int acc, std::initializer_list<GemmSeg> list) {
   const GemmSeg* g = list.begin();
-  if (pg_fits(c, std::max({g[0].N, g[list.size() / 2].N, g[list.size() - 1].N}), K)) {
+  bool fits = true;
+  for (const GemmSeg& s : list) fits = fits && pg_fits(s.W, s.N, K);
+  if (fits) {
     const PgPlan plan = list.size() == 3 ? pg_plan(M, {g[0].N, g[1].N, g[2].N}, K, false, c->num_cu) : pg_plan(M, {g[0].N}, K, false, c->num_cu);
     PgArgs P = pg_args(c, plan, Ah, Al, M, K, acc);
     for (const GemmSeg& s : list) P.seg[P.nseg++] = PgSeg{s.W, s.C, s.N, (s.N + PG_TILES[plan.tile].bn - 1) / PG_TILES[plan.tile].bn};
     if (plan.seg == 4) launch_pgemm_seg<false, 4>(st, plan, P); else launch_pgemm_seg<false, 1>(st, plan, P);
   } else {
+    // (matrices off 16 bytes)  at most one 128-row tile per compute unit: 64-row tiles, as long as the rows need more than one
     GemmSegs segs{};
     int blocks = 0;
     for (const GemmSeg& g : list) {
@@ -748,7 +751,11 @@ int launch_gemm_hl_seg(first_ctx* c, hipStream_t st, const bf16* Ah, const bf16*
       blocks += s.blocks;
       segs.s[segs.n++] = s;
     }
-    hipLaunchKernelGGL(k_gemm_nt_bf16_hl_seg, dim3(blocks, (M + GB_M - 1) / GB_M), dim3(WG), 0, st, Ah, Al, segs, M, K, acc);
+    const int tiles = (M + GB_M - 1) / GB_M;
+    if (M > GB_MS && blocks * tiles <= c->num_cu)
+      hipLaunchKernelGGL(k_gemm_nt_bf16_hl_seg_s, dim3(blocks, (M + GB_MS - 1) / GB_MS), dim3(WG), 0, st, Ah, Al, segs, M, K, acc);
+    else
+      hipLaunchKernelGGL(k_gemm_nt_bf16_hl_seg, dim3(blocks, tiles), dim3(WG), 0, st, Ah, Al, segs, M, K, acc);
   }
   HIPCHK(c, hipGetLastError());
   return FIRST_OK;
@@ -762,7 +769,7 @@ int launch_gemm_hl(first_ctx* c, hipStream_t st, const bf16* Ah, const bf16* Al,
 // Gate and up with SiLU(gate) * up in the epilogue, written split for the down projection.
 int launch_gemm_hl_gu(first_ctx* c, hipStream_t st, const bf16* Ah, const bf16* Al, const void* Wg, const void* Wu, bf16* zh, bf16* zl,
                       int M, int F, int K) {
-  if (pg_fits(c, F, K)) {
+  if (pg_fits(Wg, F, K) && pg_fits(Wu, F, K)) {
     const PgPlan plan = pg_plan(M, {F}, K, true, c->num_cu);
     PgArgs P = pg_args(c, plan, Ah, Al, M, K, 0);
     P.nseg = 1; P.seg[0] = PgSeg{reinterpret_cast<const bf16*>(Wg), nullptr, F, plan.gn}; P.Wu = reinterpret_cast<const bf16*>(Wu);
@@ -1146,10 +1153,6 @@ int first_create(const first_model_desc* desc, const first_weights* w, void* hip
   A(dev_alloc(c, &c->d_tdbg, (size_t)(4 * L + 1) * SK_TSLOTS));
   if (d.dtype == FIRST_DTYPE_BF16) {
     A(dev_alloc(c, &c->pg_part, (size_t)4 * c->num_cu * 64 * 128)); A(dev_alloc(c, &c->pg_cnt, (size_t)2 * c->num_cu));
-    uintptr_t bits = reinterpret_cast<uintptr_t>(c->lm_head);
-    for (const LayerPtrs& l : c->layers)
-      for (const void* p : {l.wq, l.wk, l.wv, l.wo, l.wg, l.wu, l.wd}) bits |= reinterpret_cast<uintptr_t>(p);
-    c->w_aligned = bits % 16 == 0;
   }
   if (rc == FIRST_OK) {
     std::vector<double> theta(c->half);
