@@ -282,7 +282,8 @@ int first_kv_usage(first_ctx *ctx, int64_t *pool_bytes, int32_t *layer_slots, in
  *   hidden_out DEV  fp32  [sum(lens), D]  H_L of every position (may be NULL)
  * Uses the context's prefill workspace and KV pages: any live sequences are dropped, and none
  * is live afterwards.  The first call allocates its workspace (one more stream copy, the
- * logits of up to 1024 positions).  Synchronises the stream before returning. */
+ * logits of up to 1024 positions, or of 128 where device
+ * memory is short).  Synchronises the stream before returning. */
 int first_soft_forward(first_ctx *ctx, int32_t B, const int32_t *ids, const int32_t *lens,
                        const int32_t *targets, float lambda, float alpha, float *rho_out,
                        float *terms_out, float *hidden_out);

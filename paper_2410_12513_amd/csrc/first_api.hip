@@ -86,14 +86,16 @@ struct first_ctx {
   float* pg_part = nullptr;               // k_pgemm: partial tiles of the slices of K, four for each of at most num_cu tiles of 64 x 128
   unsigned* pg_cnt = nullptr;             //          arrival counters per tile (zero between launches)
   int p_rows = 0;                         // rows of the prefill workspace: prompts of a batch go through it in groups of at most this many rows
-  int p_tp = 0;                           // padded rows of p_kc / p_vt (every prompt of a group starts at a multiple of PACK_PAD)
+  int p_tp = 0;                           // padded rows of p_kc / p_vt (every prompt of a group starts at a multiple of PACK_PAD): the groups' other limit
+  size_t p_least = 0;                     // bytes of the smallest workspace (first_create: set aside before copies of weights are made)
   int* d_off = nullptr;                   // [max_batch + 1] first row of every prompt of the call, behind the last one the total; then the
                                           // same in padded rows (uploaded together with the page tables, right behind them)
   std::vector<int> h_off;                 // their host copy
   int prefill_flash = 1;                  // FIRST_OPT_PREFILL_ATTN
   float2* p_cs = nullptr;
-  // soft-skip forward (first_soft_forward; allocated at its first call)
+  // soft-skip forward (first_soft_forward; allocated at its first call): rows of a group, positions whose logits are formed at a time
   float *p_Hs = nullptr, *p_lg = nullptr, *p_ce = nullptr;
+  int soft_group = 0, soft_rows = 0;
   // host state
   int B = 0;
   std::vector<int> hlen;
@@ -160,6 +162,13 @@ int dev_alloc(first_ctx* c, T** out, size_t count) {
   return FIRST_OK;
 }
 
+// Device memory that allocations which only serve speed leave to the rest of the program.
+constexpr size_t MEM_MARGIN = (size_t)4 << 30;
+bool memory_to_spare(size_t bytes) {
+  size_t free_b = 0, total_b = 0;
+  return hipMemGetInfo(&free_b, &total_b) == hipSuccess && free_b >= bytes + MEM_MARGIN;
+}
+
 int device_cus() {
   static int cus = 0;
   if (!cus) {
@@ -223,8 +232,7 @@ hipError_t make_permuted_down_copies(first_ctx* c) {
   const first_model_desc& d = c->d;
   if (!sk_zperm_fits(d.d_ffn, d.d_model, c->num_cu)) return hipSuccess;
   const size_t per_layer = (size_t)d.d_model * d.d_ffn * sizeof(bf16);
-  size_t free_b = 0, total_b = 0;
-  if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || free_b < per_layer * d.n_layers + ((size_t)4 << 30)) return hipSuccess;
+  if (!memory_to_spare(c->p_least + per_layer * d.n_layers)) return hipSuccess;
   for (int i = 0; i < d.n_layers; ++i) {
     LayerPtrs& l = c->layers[i];
     if (dev_alloc(c, &l.wd_perm, (size_t)d.d_model * d.d_ffn)) return hipErrorOutOfMemory;
@@ -422,8 +430,7 @@ hipError_t make_tiled_copies(first_ctx* c) {
   const size_t per_layer = tiled_elems(nqkv, d.d_model) + tiled_elems(d.d_model, c->nq) + 2 * tiled_elems(d.d_ffn, d.d_model) +
                            tiled_elems(d.d_model, d.d_ffn);
   const size_t total = (per_layer * d.n_layers + tiled_elems(d.vocab, d.d_model)) * sizeof(bf16);
-  size_t free_b = 0, total_b = 0;
-  if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || free_b < total + ((size_t)4 << 30)) return hipSuccess;
+  if (!memory_to_spare(c->p_least + total)) return hipSuccess;
   auto conv = [&](const void* src, bf16* dst, int N, int K) {
     const size_t items = tiled_elems(N, K) / 8;
     hipLaunchKernelGGL(k_tile_weights, dim3((unsigned)std::min<size_t>((items + WG - 1) / WG, 65535)), dim3(WG), 0, c->stream,
@@ -961,11 +968,61 @@ int enqueue_first_tokens(first_ctx* c, int B, float* logits_out, int* token_out)
   return FIRST_OK;
 }
 
-// Sequences that go through the layers together: as many as follow each other from b0 and fit the workspace.
-int group_size(const first_ctx* c, const int* lens, int B, int b0) {
-  int n = 1, rows = lens[b0];
-  while (b0 + n < B && rows + lens[b0 + n] <= c->p_rows) rows += lens[b0 + n++];
+// Sequences that go through the layers together: as many as follow each other from b0 and fit max_rows rows and the workspace.
+int group_size(const first_ctx* c, const int* lens, int B, int b0, int max_rows) {
+  auto padded = [](int n) { return (n + PACK_PAD - 1) / PACK_PAD * PACK_PAD; };
+  int n = 1, rows = lens[b0], pad = padded(lens[b0]);
+  while (b0 + n < B && rows + lens[b0 + n] <= max_rows && pad + padded(lens[b0 + n]) <= c->p_tp) {
+    rows += lens[b0 + n];
+    pad += padded(lens[b0 + n++]);
+  }
   return n;
+}
+
+// The buffers of the prompt pass: f(where the pointer goes, bytes) for each, for `rows` rows and tp padded ones.
+template <typename F>
+void each_prompt_buffer(first_ctx* c, int rows, int tp, F f) {
+  const first_model_desc& d = c->d;
+  const size_t T = rows, D = d.d_model, nq = c->nq, nkv = c->nkv, ff = d.d_ffn, B = d.max_batch;
+  auto fp32 = [&](auto** p, size_t n) { f(reinterpret_cast<void**>(p), n * sizeof(float)); };
+  auto half = [&](bf16** p, size_t n) { f(reinterpret_cast<void**>(p), n * sizeof(bf16)); };
+  fp32(&c->p_H, T * D); fp32(&c->p_q, T * nq); fp32(&c->p_k, T * nkv); fp32(&c->p_v, T * nkv);
+  fp32(&c->p_sig, T * d.n_layers); fp32(&c->p_cs, T * c->half * 2);
+  fp32(&c->p_a, T * nq);
+  if (d.dtype == FIRST_DTYPE_BF16) {     // activations leave their producers split: p_x holds the last positions' norm only
+    fp32(&c->p_x, B * D);
+    half(&c->p_xh, T * D); half(&c->p_xl, T * D); half(&c->p_ah, T * nq); half(&c->p_al, T * nq);
+    half(&c->p_zh, T * ff); half(&c->p_zl, T * ff); half(&c->p_qh, T * nq); half(&c->p_ql, T * nq);
+    half(&c->p_kc, tp * nkv); half(&c->p_vt, tp * nkv);
+  } else {                               // (a last position for each of up to max_batch prompts, which can be more than a group has rows)
+    fp32(&c->p_x, std::max(T, B) * D);
+    fp32(&c->p_g, T * ff); fp32(&c->p_u, T * ff); fp32(&c->p_z, T * ff);
+  }
+}
+size_t prompt_buffer_bytes(first_ctx* c, int rows, int tp) {
+  size_t sum = 0;
+  each_prompt_buffer(c, rows, tp, [&](void**, size_t bytes) { sum += bytes + 256; });
+  return sum;
+}
+
+// Rows for the longest prompt, and for batches up to 4096 rows together (at 2000 rows the projections have reached their rate:
+// 1160 TFLOP/s of 1180 at 4000 on the 8B shape's gate / up; 166 KB of workspace a row there) where memory is plentiful.
+int least_padded(const first_ctx* c) { return (c->d.max_seq_len + PACK_PAD - 1) / PACK_PAD * PACK_PAD; }
+int alloc_prompt_buffers(first_ctx* c) {
+  const int B = c->d.max_batch, T = c->d.max_seq_len;
+  c->p_rows = T; c->p_tp = least_padded(c);
+  if (B > 1) {
+    const int rows = (int)std::max<long long>(T, std::min<long long>((long long)B * T, 4096));
+    const int tp = (rows / PACK_PAD + 1 + std::min(B, rows)) * PACK_PAD;
+    if (memory_to_spare(prompt_buffer_bytes(c, rows, tp))) { c->p_rows = rows; c->p_tp = tp; }
+  }
+  int rc = FIRST_OK;
+  each_prompt_buffer(c, c->p_rows, c->p_tp, [&](void** p, size_t bytes) {
+    char* at = nullptr;
+    if (rc == FIRST_OK) rc = dev_alloc(c, &at, bytes);
+    *p = at;
+  });
+  return rc;
 }
 
 // Page tables and row offsets of the call's prompts, in one upload; the stream is idle when it returns.
@@ -1069,9 +1126,7 @@ int first_create(const first_model_desc* desc, const first_weights* w, void* hip
   c->n_pages = c->max_pages * d.max_batch;
   c->page_elems = (size_t)2 * d.n_kv_heads * d.kv_page_tokens * d.head_dim;
 
-  // Rows of the prefill workspace: the longest prompt, and for batches up to 4096 rows together (at 2000 rows the projections
-  // have reached their rate: 1160 TFLOP/s of 1180 at 4000 on the 8B shape's gate / up; 240 KB of workspace a row there).
-  const int B = d.max_batch, L = d.n_layers, T = c->p_rows = (int)std::max<long long>(d.max_seq_len, std::min<long long>((long long)B * d.max_seq_len, 4096));
+  const int B = d.max_batch, L = d.n_layers;
   int rc = FIRST_OK;
   auto A = [&](int r) { if (rc == FIRST_OK) rc = r; };
   c->kv_elide = d.kv_layer_slots > 0 && d.kv_layer_slots < L;
@@ -1095,27 +1150,6 @@ int first_create(const first_model_desc* desc, const first_weights* w, void* hip
   A(dev_alloc(c, &c->d_part_ml, (size_t)B * d.n_q_heads * S_MAX * 2));
   A(dev_alloc(c, &c->d_attn_cnt, (size_t)B * d.n_kv_heads)); A(dev_alloc(c, &c->d_head_cnt, B));
   A(dev_alloc(c, &c->d_rope_cs, (size_t)B * c->half)); A(dev_alloc(c, &c->d_arg_part, (size_t)B * ARG_MAX_WG));
-  A(dev_alloc(c, &c->p_H, (size_t)T * d.d_model)); A(dev_alloc(c, &c->p_q, (size_t)T * c->nq));
-  A(dev_alloc(c, &c->p_k, (size_t)T * c->nkv)); A(dev_alloc(c, &c->p_v, (size_t)T * c->nkv));
-  if (d.dtype != FIRST_DTYPE_BF16) {   // (bf16 models form SiLU(gate) * up in the GEMM's epilogue: no fp32 gate / up matrices)
-    A(dev_alloc(c, &c->p_g, (size_t)T * d.d_ffn)); A(dev_alloc(c, &c->p_u, (size_t)T * d.d_ffn));
-  }
-  A(dev_alloc(c, &c->p_sig, (size_t)T * L)); A(dev_alloc(c, &c->p_cs, (size_t)T * c->half));
-  // (bf16 models write the normed stream and the MLP activation split: fp32 copies hold the last positions' norm only / nothing.
-  // The last positions are a row for each of up to max_batch prompts, which can be more than a group has rows.)
-  A(dev_alloc(c, reinterpret_cast<char**>(&c->p_x), (size_t)(d.dtype == FIRST_DTYPE_BF16 ? B : std::max(T, B)) * d.d_model * 4));
-  A(dev_alloc(c, reinterpret_cast<char**>(&c->p_a), (size_t)T * c->nq * 4));
-  if (d.dtype == FIRST_DTYPE_BF16) {
-    A(dev_alloc(c, &c->p_xh, (size_t)T * d.d_model)); A(dev_alloc(c, &c->p_xl, (size_t)T * d.d_model));
-    A(dev_alloc(c, &c->p_ah, (size_t)T * c->nq)); A(dev_alloc(c, &c->p_al, (size_t)T * c->nq));
-    A(dev_alloc(c, &c->p_zh, (size_t)T * d.d_ffn)); A(dev_alloc(c, &c->p_zl, (size_t)T * d.d_ffn));
-  }
-  c->p_tp = (T / PACK_PAD + 1 + B) * PACK_PAD;
-  if (d.dtype == FIRST_DTYPE_BF16 && (d.head_dim == 64 || d.head_dim == 128)) {
-    A(dev_alloc(c, &c->p_qh, (size_t)T * c->nq)); A(dev_alloc(c, &c->p_ql, (size_t)T * c->nq));
-    A(dev_alloc(c, &c->p_kc, (size_t)c->p_tp * c->nkv)); A(dev_alloc(c, &c->p_vt, (size_t)c->p_tp * c->nkv));
-  }
-  if (d.dtype != FIRST_DTYPE_BF16) A(dev_alloc(c, reinterpret_cast<char**>(&c->p_z), (size_t)T * d.d_ffn * 4));
   c->xpitch = (std::max(std::max(d.d_model, c->nq), d.d_ffn) + 31) / 32 * 32;
   if (B > 1) {
     A(dev_alloc(c, &c->d_xh, (size_t)BATCH_SLOTS * c->xpitch)); A(dev_alloc(c, &c->d_xl, (size_t)BATCH_SLOTS * c->xpitch));
@@ -1152,7 +1186,10 @@ int first_create(const first_model_desc* desc, const first_weights* w, void* hip
   A(dev_alloc(c, &c->d_layers, L)); A(dev_alloc(c, &c->d_done, (size_t)c->num_cu)); A(dev_alloc(c, &c->d_err, 4));
   A(dev_alloc(c, &c->d_tdbg, (size_t)(4 * L + 1) * SK_TSLOTS));
   if (d.dtype == FIRST_DTYPE_BF16) {
-    A(dev_alloc(c, &c->pg_part, (size_t)4 * c->num_cu * 64 * 128)); A(dev_alloc(c, &c->pg_cnt, (size_t)2 * c->num_cu));
+    bool cut = false;                     // some product sums K in segments, which slices may share out
+    for (const auto& [N, K] : {std::pair<int, int>{c->nq + 2 * c->nkv, d.d_model}, {d.d_model, c->nq}, {d.d_model, d.d_ffn}, {d.vocab, d.d_model}})
+      cut = cut || pg_segments({N}, K, false) > 1;
+    if (cut) { A(dev_alloc(c, &c->pg_part, (size_t)4 * c->num_cu * 64 * 128)); A(dev_alloc(c, &c->pg_cnt, (size_t)2 * c->num_cu)); }
   }
   if (rc == FIRST_OK) {
     std::vector<double> theta(c->half);
@@ -1165,6 +1202,7 @@ int first_create(const first_model_desc* desc, const first_weights* w, void* hip
     if (e == hipSuccess) e = prefill_attributes();
     if (e == hipSuccess) e = hipMemset(c->d_err, 0, 4 * sizeof(int));
     if (e == hipSuccess) e = reset_tagged_exchange(c);
+    c->p_least = prompt_buffer_bytes(c, d.max_seq_len, least_padded(c));
     c->step_ok = step_kernel_fits(c);
     if (e == hipSuccess && c->step_ok) {
       e = make_permuted_down_copies(c);
@@ -1185,6 +1223,7 @@ int first_create(const first_model_desc* desc, const first_weights* w, void* hip
     if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_prefill<float, float>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
     if (e != hipSuccess) rc = fail(nullptr, FIRST_ERR_HIP, std::string("first_create: ") + hipGetErrorString(e));
+    else if ((rc = alloc_prompt_buffers(c)) != FIRST_OK) g_create_error = c->err;
   } else {
     g_create_error = c->err;
   }
@@ -1239,7 +1278,7 @@ int first_prefill_route(first_ctx* c, int32_t B, const int32_t* ids, const int32
   if (rc) return rc;
   const bool bf = c->d.dtype == FIRST_DTYPE_BF16;
   for (int b = 0; b < B;) {
-    const int n = group_size(c, lens, B, b);
+    const int n = group_size(c, lens, B, b, c->p_rows);
     const int32_t* at = ids + c->h_off[b];
     if ((rc = bf ? prefill_group<bf16>(c, b, n, at, hidden_out) : prefill_group<float>(c, b, n, at, hidden_out))) return rc;
     b += n;
@@ -1615,7 +1654,9 @@ int first_kv_usage(first_ctx* c, int64_t* pool_bytes, int32_t* layer_slots, int3
   return FIRST_OK;
 }
 
-constexpr int SOFT_ROWS = 1024;  // positions whose logits are formed at a time in first_soft_forward (128 left the LM head's GEMM a quarter of its rate)
+// Positions whose logits are formed at a time in first_soft_forward (128 leave the LM head's GEMM a quarter of its rate: for a card
+// that is nearly full, 525 MB against 66 at 128256 tokens of vocabulary).
+constexpr int SOFT_ROWS = 1024, SOFT_ROWS_LEAST = 128;
 
 int first_soft_forward(first_ctx* c, int32_t B, const int32_t* ids, const int32_t* lens, const int32_t* targets, float lambda,
                        float alpha, float* rho_out, float* terms_out, float* hidden_out) {
@@ -1630,9 +1671,15 @@ int first_soft_forward(first_ctx* c, int32_t B, const int32_t* ids, const int32_
   const int L = d.n_layers, P = d.kv_page_tokens, D = d.d_model, V = d.vocab;
   hipStream_t st = c->stream;
   if (!c->p_Hs) {
-    int rc = dev_alloc(c, &c->p_Hs, (size_t)c->p_rows * D);
-    if (rc == FIRST_OK) rc = dev_alloc(c, &c->p_lg, (size_t)std::min(SOFT_ROWS, c->p_rows) * V);
-    if (rc == FIRST_OK) rc = dev_alloc(c, &c->p_ce, (size_t)c->p_rows);
+    c->soft_group = c->p_rows;
+    c->soft_rows = std::min(SOFT_ROWS, c->p_rows);
+    if (!memory_to_spare(((size_t)c->soft_group * (D + 1) + (size_t)c->soft_rows * V) * sizeof(float))) {
+      c->soft_group = d.max_seq_len;
+      c->soft_rows = std::min(SOFT_ROWS_LEAST, d.max_seq_len);
+    }
+    int rc = dev_alloc(c, &c->p_Hs, (size_t)c->soft_group * D);
+    if (rc == FIRST_OK) rc = dev_alloc(c, &c->p_lg, (size_t)c->soft_rows * V);
+    if (rc == FIRST_OK) rc = dev_alloc(c, &c->p_ce, (size_t)c->soft_group);
     if (rc != FIRST_OK) { c->p_Hs = nullptr; return rc; }
   }
   release_sequences(c);
@@ -1645,17 +1692,17 @@ int first_soft_forward(first_ctx* c, int32_t B, const int32_t* ids, const int32_
   if (rc) return rc;
   const bool hl = d.dtype == FIRST_DTYPE_BF16;
   for (int b = 0; b < B;) {
-    const int n = group_size(c, lens, B, b);
+    const int n = group_size(c, lens, B, b, c->soft_group);
     const size_t off = c->h_off[b];
     const int R = c->h_off[b + n] - c->h_off[b];
     if ((rc = hl ? prefill_group<bf16>(c, b, n, ids + off, nullptr, true) : prefill_group<float>(c, b, n, ids + off, nullptr, true))) return rc;
     if (hidden_out)
       HIPCHK(c, hipMemcpyAsync(hidden_out + off * D, c->p_H, (size_t)R * D * sizeof(float), hipMemcpyDeviceToDevice, st));
-    // logits of every position = W_lm . RMSNorm(H_L; g_final), SOFT_ROWS positions at a time, then their cross entropy
+    // logits of every position = W_lm . RMSNorm(H_L; g_final), soft_rows positions at a time, then their cross entropy
     float* x = reinterpret_cast<float*>(c->p_x);
     launch_rmsnorm(c, st, c->g_final, nullptr, nullptr, R, hl);
-    for (int r0 = 0; r0 < R; r0 += SOFT_ROWS) {
-      const int rows = std::min(SOFT_ROWS, R - r0);
+    for (int r0 = 0; r0 < R; r0 += c->soft_rows) {
+      const int rows = std::min(c->soft_rows, R - r0);
       rc = hl ? launch_gemm_hl(c, st, c->p_xh + (size_t)r0 * D, c->p_xl + (size_t)r0 * D, c->lm_head, c->p_lg, rows, V, D, 0)
               : launch_gemm(c, st, d.dtype, x + (size_t)r0 * D, c->lm_head, c->p_lg, rows, V, D, 0, true);
       if (rc) return rc;

@@ -98,3 +98,52 @@ def test_more_prompts_than_workspace_rows(dtype):
     ctx.close()
     for k, v in out.items():
         assert torch.equal(v.cpu(), one[k][ids.long()]), k
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+def test_workspaces_stay_small_where_memory_is_short(dtype):
+    """Rows beyond the longest prompt, and logits of more than 128 positions at a time in the soft-skip forward, only serve speed: with
+    2 GiB of the card left they are not taken, and every prompt has the same bits as with them (other groups, other rounds)."""
+    import paper_2410_12513_amd as P
+    desc = ModelDesc(1, 512, 8, 2, 64, 8192, 50000, dtype=dtype)
+    B, n = 16, 200
+    w, r = to_device(make_weights(desc, 9), "cuda"), make_router(desc, 9).cuda()
+    lens = [n - 9 * b for b in range(B)]
+    ids = make_prompt(desc.vocab, sum(lens), 90).cuda()
+    targets = torch.roll(ids, -1)
+
+    def free():
+        torch.cuda.synchronize()
+        return torch.cuda.mem_get_info()[0]
+
+    def run():
+        out = dict(rho=torch.zeros(B, 1, device="cuda"), hidden=torch.zeros(B, desc.d_model, device="cuda"),
+                   logits=torch.zeros(B, desc.vocab, device="cuda"), token=torch.zeros(B, dtype=torch.int32, device="cuda"))
+        soft = dict(terms=torch.zeros(B, 4, device="cuda"), rho=torch.zeros(B, 1, device="cuda"),
+                    hidden=torch.zeros(sum(lens), desc.d_model, device="cuda"))
+        at = [free()]
+        ctx = P.FirstContext(desc, w, r, max_batch=B, max_seq_len=n + 1)
+        at.append(free())
+        ctx.prefill_route(ids, lens, **out)
+        ctx.soft_forward(ids, lens, targets, 0.01, 0.1, **soft)
+        at.append(free())
+        ctx.close()
+        return [a - b for a, b in zip(at, at[1:])], {**out, **{"soft " + k: v for k, v in soft.items()}}
+
+    run()                                      # (what the first use of the library takes for good)
+    usual, a = run()
+    hog = []
+    try:
+        while free() > 2 << 30:
+            hog.append(torch.empty(min(32 << 30, free() - (2 << 30) + 1), dtype=torch.uint8, device="cuda"))
+        short, b = run()
+    finally:
+        hog.clear()
+        torch.cuda.empty_cache()
+    # 3216 rows against 201, of the MLP's activations alone 12 bytes an element in fp32, 4 in two bf16 parts; 1024 positions' logits
+    # against 128
+    assert usual[0] - short[0] > 3000 * desc.d_ffn * (12 if dtype == "fp32" else 4), (usual, short)
+    assert usual[1] - short[1] > 890 * desc.vocab * 4, (usual, short)
+    for k in a:
+        assert torch.equal(a[k], b[k]), k
