@@ -108,7 +108,9 @@ __global__ void __launch_bounds__(WG) k_rope_split(const float* __restrict__ q, 
 //   O^T[dim][q] = V^T P^T   (A = rows of the transposed values, B = the probabilities straight from the accumulator
 //                            registers of S^T, split hi + lo)
 // The maximum of a query is per lane plus one exchange with lane ^ 32, the sum stays per lane until the end, and O^T
-// is only rescaled when some query's maximum has grown.  Accumulator layout of the 32x32 MFMA: lane l holds column
+// is only rescaled when some query's maximum has grown.  The maximum is kept as it enters the exponent, rounded once after
+// its product with log2 e: a weight is 2^(S log2 e - m) with one rounding of that difference, and a rescaling 2^(m - m').  (With
+// the product rounded anew for every maximum, weights of different tiles differ by 2^-24 of it: 6e-6 at scores of 100.)  Accumulator layout of the 32x32 MFMA: lane l holds column
 // l % 32, register r holds row 8 (r / 4) + 4 (l / 32) + r % 4.
 // Bound: matrix cores (64 MFMAs of 32 cycles per 64 keys and 32 queries) with the exponentials and splits of the other
 // wave of the SIMD beside them.  KH = 2 doubles the workgroups and halves each wave's walk where the prompts are too short
@@ -215,9 +217,9 @@ __global__ void __launch_bounds__(WG, 2) k_attn_prompt(const bf16* __restrict__ 
       for (int r = 0; r < 16; ++r) mt = fmaxf(mt, S[u][r]);
     float ma, mb;
     both_halves(mt, ma, mb);
-    const float mn = fmaxf(m, fmaxf(ma, mb));              // finite: the tile has a key that this query sees
+    const float mn = fmaxf(m, fmaxf(ma, mb) * LOG2E);      // finite: the tile has a key that this query sees
     if (__any(mn > m)) {
-      const float corr = __builtin_amdgcn_exp2f((m - mn) * LOG2E);
+      const float corr = __builtin_amdgcn_exp2f(m - mn);
       l *= corr;
 #pragma unroll
       for (int t = 0; t < DT; ++t)
@@ -225,12 +227,11 @@ __global__ void __launch_bounds__(WG, 2) k_attn_prompt(const bf16* __restrict__ 
         for (int r = 0; r < 16; ++r) O[t][r] *= corr;
       m = mn;
     }
-    const float m2e = m * LOG2E;
     float ls[4] = {0.f, 0.f, 0.f, 0.f};                    // the tile's sum first: a long prompt's l is thousands of terms
 #pragma unroll
     for (int u = 0; u < NS; ++u)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) { S[u][r] = __builtin_amdgcn_exp2f(fmaf(S[u][r], LOG2E, -m2e)); ls[r & 3] += S[u][r]; }
+      for (int r = 0; r < 16; ++r) { S[u][r] = __builtin_amdgcn_exp2f(fmaf(S[u][r], LOG2E, -m)); ls[r & 3] += S[u][r]; }
     l += (ls[0] + ls[1]) + (ls[2] + ls[3]);
     // O^T += V^T P^T: k-step s2 uses accumulator registers 8 s2 .. 8 s2 + 7 of P as they are
 #pragma unroll
@@ -267,7 +268,7 @@ __global__ void __launch_bounds__(WG, 2) k_attn_prompt(const bf16* __restrict__ 
     lds_barrier();
     if (kh == 1) return;
     const float m2 = ex[16 * DT * 64], l2 = ex[(16 * DT + 1) * 64], mm = fmaxf(m, m2);
-    const float c1 = __builtin_amdgcn_exp2f((m - mm) * LOG2E), c2 = __builtin_amdgcn_exp2f((m2 - mm) * LOG2E);    // (no tile for the second share: m2 = -inf, c2 = 0)
+    const float c1 = __builtin_amdgcn_exp2f(m - mm), c2 = __builtin_amdgcn_exp2f(m2 - mm);    // (no tile for the second share: m2 = -inf, c2 = 0)
     l = l * c1 + l2 * c2;
 #pragma unroll
     for (int t = 0; t < DT; ++t)

@@ -147,3 +147,41 @@ def test_workspaces_stay_small_where_memory_is_short(dtype):
     assert usual[1] - short[1] > 890 * desc.vocab * 4, (usual, short)
     for k in a:
         assert torch.equal(a[k], b[k]), k
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [1088, 2240])
+def test_weights_of_large_scores_do_not_depend_on_the_running_maximum(n):
+    """Scores around 8160 whose maximum grows from tile to tile, everything but the softmax exact by construction: embeddings of +-1
+    (their norm is 1), q = (96, 1) after scaling and k = (85, c) in two dims that the rotation leaves alone, c = odd / 16, v = +-1 the
+    same for a tile of 64 keys.  What is left are the 16 bits of a weight (2^-17) and of an output; a product with log2 e that is
+    rounded for every tile's maximum (11772 +- 2^-11) moves the tiles against each other by up to 3e-4."""
+    import paper_2410_12513_amd as P
+    D = 64
+    desc = ModelDesc(1, D, 1, 1, 64, 8, 256, rope_base=1e30, rms_eps=0.0)
+    bits = torch.arange(256)[:, None].bitwise_right_shift(torch.arange(8)[None, :]).bitwise_and(1) * 2 - 1      # +-1
+    emb = torch.ones(256, D)
+    emb[:, 1:9] = bits.float()
+    w = make_weights(desc, 1)
+    w["embed"] = emb.bfloat16()
+    lw = w["layers"][0]
+    for k in ("wq", "wk", "wv", "wo", "w_gate", "w_up", "w_down"):
+        lw[k].zero_()
+    lw["wq"][30, 0], lw["wq"][31, 0] = 768.0, 8.0
+    lw["wk"][30, 0] = 85.0
+    lw["wk"][31, 1:8] = 2.0 ** (torch.arange(7).float() - 4)
+    lw["wv"][0, 8] = 1.0
+    lw["wo"][20, 0] = 1.0
+    g = torch.Generator().manual_seed(4)
+    tile = torch.arange(n) // 64
+    level = 20 + tile - torch.randint(0, 20, (n,), generator=g)
+    level[torch.arange(n) % 32 == 7] = 20 + tile[torch.arange(n) % 32 == 7]        # every half tile has its maximum
+    sign = torch.randint(0, 2, (int(tile[-1]) + 1,), generator=g)[tile]
+    ids = (level + 128 * sign).int()
+    hidden = torch.zeros(1, D, device="cuda")
+    ctx = P.FirstContext(desc, to_device(w, "cuda"), torch.zeros(1, D, device="cuda"), max_batch=1, max_seq_len=n + 1)
+    ctx.prefill_route(ids.cuda(), [n], hidden=hidden)
+    ctx.close()
+    p = torch.softmax((2 * level.double() - 127) / 16, 0)
+    want = 1.0 + float((p * (2 * sign.double() - 1)).sum())
+    assert abs(float(hidden[0, 20]) - want) <= 2 * 2.0 ** -17, (float(hidden[0, 20]), want)
