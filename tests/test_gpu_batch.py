@@ -5,8 +5,10 @@ versions of the batch-16 / mixed-mask and the batch-4 / long-context workloads."
 import pytest
 import torch
 
+import paper_2410_12513_amd as P
 from oracle import first_oracle as O
-from synth import CONFIGS, make_prompt, make_skip_mask
+from synth import CONFIGS, make_prompt, make_router, make_skip_mask, make_weights
+from synth.generators import to_device
 from tests.gpu_util import build, logits_close, top2_gap
 from tests.test_gpu_path import _decode, _prefill
 
@@ -147,4 +149,33 @@ def test_shared_pass_is_refused_for_fp32_models():
     assert e.value.code == -2
     ctx.set_option(OPT_BATCH_PATH, -1)
     ctx.decode_step(tin, None, tin)
+    ctx.close()
+
+
+def test_lm_head_with_four_row_tiles_a_wave_and_a_ragged_last_group():
+    """From 98289 rows on a wave of the LM head takes four tiles of sixteen rows: here the last group has one tile, and that five rows.
+    Logits and tokens of three sequences against the oracle, with a head that puts the largest logits into the last rows."""
+    desc = CONFIGS["mini_bf16"].with_(n_layers=2, vocab=98309)
+    w = make_weights(desc, 35)
+    w["lm_head"][-5:] *= 2
+    router = make_router(desc, 35)
+    lens = [20, 33, 7]
+    prompts = [make_prompt(desc.vocab, n, 35 + b) for b, n in enumerate(lens)]
+    ctx = P.FirstContext(desc, to_device(w, "cuda"), router.cuda(), max_batch=3, max_seq_len=64)
+    ctx.set_option(OPT_BATCH_PATH, 1)
+    _prefill(ctx, desc, prompts)
+    states = [O.prefill_route(desc, w, router, p) for p in prompts]
+    for b, st in enumerate(states):
+        ctx.set_mask(b, [1, 1])
+        st.set_mask([1, 1])
+    steps = [[5, desc.vocab - 1, 17], [desc.vocab - 3, 2, 9]]
+    lg, tk = _decode(ctx, desc, steps, B=3)
+    for s, fed in enumerate(steps):
+        for b, st in enumerate(states):
+            ref, _ = O.decode_step(desc, w, st, fed[b])
+            ok, ma, rel = logits_close(lg[s, b], ref, desc.dtype)
+            assert ok, (s, b, ma, rel)
+            tail = ref[-21:].double()                              # the last two tiles on their own
+            assert float((lg[s, b][-21:].double() - tail).norm() / tail.norm()) <= 1e-2
+            assert int(tk[s, b]) == int(torch.argmax(lg[s, b]))
     ctx.close()

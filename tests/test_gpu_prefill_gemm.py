@@ -1,14 +1,20 @@
-"""The prompt pass's projections at the edges of their tiles, K steps and slices: prefill of a one-layer model against the
-oracle, three times over (the slices of K meet in memory in any order and must give the same bits each time)."""
+"""The prompt pass's projections at the edges of their tiles, K steps and slices: prefill and soft-skip forward (which gives every
+row) of a one-layer model against the oracle, three times over (the slices of K meet in memory in any order and must give
+the same bits each time)."""
 import pytest
 import torch
 
 from oracle import first_oracle as O
+from oracle import training_forward as TF
 from synth import make_prompt, make_router, make_weights
 from synth.generators import ModelDesc, to_device
 
-# widths that are not multiples of the K step (64), so every contraction ends in a partial step
+# widths that are not multiples of the K step (64): Q/K/V, gate / up and down end in a partial step (the output projection's K is
+# always a number of whole heads)
 RAGGED = ModelDesc(1, 520, 6, 2, 64, 1416, 500)
+# the same with K in four segments; at 256 compute units 100, 300, 500, 807 and 1500 rows take the four tiles, with four slices of K,
+# two or none (200 rows: 64 x 128 with four)
+RAGGED_WIDE = ModelDesc(1, 3080, 18, 3, 128, 2312, 500)
 # a K long enough for many slices, and an N for the widest tile
 WIDE = ModelDesc(1, 1024, 8, 4, 128, 4096, 700)
 
@@ -31,26 +37,31 @@ def _shift(w, names=MATRICES):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("desc,n,shifted", [(RAGGED, 1, False), (RAGGED, 31, False), (RAGGED, 33, False), (RAGGED, 65, True), (RAGGED, 129, False),
-                                            (RAGGED, 500, False), (WIDE, 32, False), (WIDE, 200, False), (WIDE, 200, True), (WIDE, 257, False), (WIDE, 1100, False)])
+                                            (RAGGED, 500, False), (WIDE, 32, False), (WIDE, 200, False), (WIDE, 200, True), (WIDE, 257, False), (WIDE, 1100, False), (RAGGED_WIDE, 100, False), (RAGGED_WIDE, 200, False),
+                                            (RAGGED_WIDE, 300, False), (RAGGED_WIDE, 500, False), (RAGGED_WIDE, 807, False), (RAGGED_WIDE, 1500, False)])
 def test_prefill_projections_at_tile_edges(desc, n, shifted):
     import paper_2410_12513_amd as P
     w, r, prompt = make_weights(desc, 11), make_router(desc, 11), make_prompt(desc.vocab, n, 11)
     wg = to_device(w, "cuda")
     ctx = P.FirstContext(desc, _shift(wg) if shifted else wg, r.cuda(), max_batch=1, max_seq_len=n + 1)
     ref = O.prefill_route(desc, w, r, prompt)
-    runs = []
+    soft = TF.soft_forward(desc, w, r, prompt)[0]
+    ids, runs = prompt.cuda(), []
     for _ in range(3):
         hidden, logits, rho = torch.zeros(1, desc.d_model, device="cuda"), torch.zeros(1, desc.vocab, device="cuda"), torch.zeros(1, 1, device="cuda")
-        ctx.prefill_route(prompt.cuda(), [n], rho=rho, hidden=hidden, logits=logits)
-        runs.append((hidden[0].cpu(), logits[0].cpu()))
+        rows, terms = torch.zeros(n, desc.d_model, device="cuda"), torch.zeros(1, 4, device="cuda")
+        ctx.prefill_route(ids, [n], rho=rho, hidden=hidden, logits=logits)
+        ctx.soft_forward(ids, [n], ids, 0.0, 0.0, terms, hidden=rows)
+        runs.append((hidden[0].cpu(), logits[0].cpu(), rows.cpu()))
     ctx.close()
-    for h, l in runs:
+    for h, l, rows in runs:
         # activations carry 16 bits into the products (2^-17 each); what is left is K, V values that round to the other
         # neighbouring bf16 (2^-9 of a value, few of them): well below 1.5e-3 of the stream, while one 32 x 32 block of a
         # projection that misses a slice of K is 1e-2 and more
         assert float((h.double() - ref.hidden).norm() / ref.hidden.norm()) <= 1.5e-3
         assert float((l.double() - ref.logits.double()).norm() / ref.logits.double().norm()) <= 1.5e-3
-        assert torch.equal(h, runs[0][0]) and torch.equal(l, runs[0][1])
+        assert float(((rows.double() - soft).norm(dim=1) / soft.norm(dim=1)).max()) <= 1.5e-3
+        assert all(torch.equal(x, y) for x, y in zip((h, l, rows), runs[0]))
 
 
 @pytest.mark.gpu

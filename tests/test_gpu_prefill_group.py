@@ -7,11 +7,15 @@ import torch
 from oracle import first_oracle as O
 from synth import make_prompt, make_router, make_weights
 from synth.generators import ModelDesc, to_device
-from tests.gpu_util import logits_close
+from tests.gpu_util import logits_close, routers_with_margin
 
 # a down projection in four segments of K (d_ffn >= 2048), both head dimensions
 HD64 = ModelDesc(2, 512, 8, 2, 64, 2048, 700)
 HD128 = ModelDesc(2, 512, 6, 2, 128, 2304, 701)
+# in fp32, where the rows of a launch choose among three kernels
+HD64_FP32 = HD64.with_(dtype="fp32")
+# all projections but gate / up in four segments of K, the last step of two of them partial
+WIDE = ModelDesc(1, 3080, 18, 3, 128, 2312, 500)
 
 
 def _run(desc, w, r, prompts, max_seq_len, slots=0, flash=1):
@@ -25,26 +29,30 @@ def _run(desc, w, r, prompts, max_seq_len, slots=0, flash=1):
     out = {k: v.cpu() for k, v in out.items()}
     out["kv"] = [[tuple(t.cpu() for t in ctx.kv_read(b, i, 0, p.numel())) for i in range(desc.n_layers)] for b, p in enumerate(prompts)] if not slots else None
     assert [ctx.seq_len(b) for b in range(B)] == [p.numel() for p in prompts]
+    # every position, through the soft-skip forward
+    ids, rows, terms = torch.cat(prompts).cuda(), torch.zeros(sum(p.numel() for p in prompts), desc.d_model, device="cuda"), torch.zeros(B, 4, device="cuda")
+    ctx.soft_forward(ids, [p.numel() for p in prompts], ids, 0.01, 0.1, terms, hidden=rows)
+    out["rows"], out["terms"] = rows.cpu().split([p.numel() for p in prompts]), terms.cpu()
     ctx.close()
     return out
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("desc", [HD64, HD128])
-def test_prompts_in_a_group_have_the_bits_they_have_alone(desc):
-    # 4096 rows of workspace: the prompts go through in two groups, the first with both attention kernels
-    lens = (2100, 5, 64, 129, 1100, 63, 2048, 300, 1)
+@pytest.mark.parametrize("desc,lens", [(HD64, (2100, 5, 64, 129, 1100, 63, 2048, 300, 1)), (HD128, (2100, 5, 64, 129, 1100, 63, 2048, 300, 1)),
+                                       (HD64_FP32, (2100, 5, 64, 129, 1100, 63, 600, 300, 1)), (WIDE, (807, 31, 100, 300, 1500))])
+def test_prompts_in_a_group_have_the_bits_they_have_alone(desc, lens):
+    # 4096 rows of workspace: the nine prompts go through in two groups, the first with both attention kernels
     w, r = make_weights(desc, 5), make_router(desc, 5)
     wg, rg = to_device(w, "cuda"), r.cuda()
     prompts = [make_prompt(desc.vocab, n, 50 + i) for i, n in enumerate(lens)]
     got = _run(desc, wg, rg, prompts, 2200)
     for b, p in enumerate(prompts):
         one = _run(desc, wg, rg, [p], 2200)
-        for k in ("rho", "hidden", "logits", "token"):
+        for k in ("rho", "hidden", "logits", "token", "rows", "terms"):
             assert torch.equal(one[k][0], got[k][b]), (k, lens[b])
         for i in range(desc.n_layers):
             assert torch.equal(one["kv"][0][i][0], got["kv"][b][i][0]) and torch.equal(one["kv"][0][i][1], got["kv"][b][i][1])
-    for b in (1, 3, 5, 7, 8):
+    for b in [b for b, n in enumerate(lens) if n <= 300]:
         st = O.prefill_route(desc, w, r, prompts[b])
         ok, ma, rel = logits_close(got["logits"][b], st.logits, desc.dtype)
         assert ok and float((got["rho"][b] - st.rho).abs().max()) <= 5e-4, (lens[b], ma, rel)
@@ -62,23 +70,50 @@ def test_prompt_attention_agrees_with_the_plain_kernel(desc, lens):
         assert float((a[k] - b[k]).norm() / b[k].norm()) <= 1.5e-3
 
 
+def _elided_setup():
+    """Four prompts in one group: the first layer is kept by the first and third, the second by nobody, the third from the second on."""
+    desc, want = HD64.with_(n_layers=3), [[1, 0, 0], [0, 0, 1], [1, 0, 1], [0, 0, 1]]
+    w = make_weights(desc, 7)
+    prompts = [make_prompt(desc.vocab, n, 70 + i) for i, n in enumerate((40, 130, 17, 64))]
+    r = routers_with_margin(desc, w, prompts, 7, want=want, max_tries=2000)
+    return desc, want, to_device(w, "cuda"), r.cuda(), prompts
+
+
 @pytest.mark.gpu
 def test_group_with_elided_layers_matches_one_without():
-    desc = HD64
-    w, r = to_device(make_weights(desc, 7), "cuda"), make_router(desc, 7)
-    r[0] = 1.0           # a router that adds up the embedding: some prompts keep the first layer, others do not
-    r = r.cuda()
-    prompts = [make_prompt(desc.vocab, n, 70 + i) for i, n in enumerate((40, 130, 17, 64))]
-    full = _run(desc, w, r, prompts, 160)
     import paper_2410_12513_amd as P
-    kept = (full["rho"] >= 0.5).any(0)
-    try:
-        part = _run(desc, w, r, prompts, 160, slots=1)
-        assert int(kept.sum()) <= 1
-        for k in ("rho", "hidden", "logits", "token"):
-            assert torch.equal(full[k], part[k])
-    except P.FirstError as e:
-        assert e.code == -3 and int(kept.sum()) > 1
+    desc, want, w, r, prompts = _elided_setup()
+    full = _run(desc, w, r, prompts, 160)
+    part = _run(desc, w, r, prompts, 160, slots=2)
+    assert (full["rho"] >= 0.5).int().tolist() == want
+    for k in ("rho", "hidden", "logits", "token", "terms"):
+        assert torch.equal(full[k], part[k]), k
+    ctx = P.FirstContext(desc, w, r, max_batch=4, max_seq_len=160, kv_layer_slots=2)
+    ctx.prefill_route(torch.cat(prompts).cuda(), [p.numel() for p in prompts])
+    assert ctx.kv_usage()[1:] == (2, 2)
+    for b, p in enumerate(prompts):
+        for i in range(3):
+            # a layer has its slice from the first sequence on that keeps it
+            if any(want[a][i] for a in range(b + 1)):
+                assert all(torch.equal(x, y.cpu()) for x, y in zip(full["kv"][b][i], ctx.kv_read(b, i, 0, p.numel()))), (b, i)
+            else:
+                with pytest.raises(P.FirstError) as e:
+                    ctx.kv_read(b, i, 0, p.numel())
+                assert e.value.code == -2
+    ctx.close()
+
+
+@pytest.mark.gpu
+def test_group_that_keeps_more_layers_than_slots_is_a_capacity_error():
+    import paper_2410_12513_amd as P
+    desc, _, w, r, prompts = _elided_setup()
+    ctx = P.FirstContext(desc, w, r, max_batch=4, max_seq_len=160, kv_layer_slots=1)
+    with pytest.raises(P.FirstError) as e:
+        ctx.prefill_route(torch.cat(prompts).cuda(), [p.numel() for p in prompts])
+    assert e.value.code == -3
+    ctx.prefill_route(prompts[1].cuda(), [prompts[1].numel()])        # one that keeps one layer has room
+    assert ctx.get_kept(0) == [2]
+    ctx.close()
 
 
 @pytest.mark.gpu

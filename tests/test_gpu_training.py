@@ -70,6 +70,31 @@ def test_soft_forward_and_loss_terms_match_oracle(model, lens):
     ctx.close()
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+def test_soft_forward_in_rounds_and_groups_matches_oracle(dtype):
+    """5100 positions in a workspace of 4096 rows: two groups of two prompts, logits of 1024 positions at a time, so that the first
+    prompt ends inside a round and the second group starts behind an offset in every array."""
+    desc = CONFIGS["mini_bf16"].with_(n_layers=2, d_model=256, n_q_heads=4, d_ffn=520, vocab=300, dtype=dtype)
+    lens = [1500, 1400, 1300, 900]
+    router = make_router(desc, 96, std=1.5)
+    desc, w, router, ctx = build(None, 96, max_batch=4, max_seq_len=1501, router=router, desc=desc)
+    prompts = [make_prompt(desc.vocab, n, 96 + b) for b, n in enumerate(lens)]
+    targets = [_targets(p, holes=(3, 1100) if p.numel() > 1100 else (3,)) for p in prompts]
+    got = _soft(ctx, desc, prompts, targets, 0.01, 0.05)
+    ctx.close()
+    for b, (p, t, h) in enumerate(zip(prompts, targets, got["hidden"].split(lens))):
+        ref = TF.loss_terms(desc, w, router, p, t, 0.01, 0.05)
+        assert float((got["rho"][b].double() - ref["rho"]).abs().max()) <= (2e-3 if dtype == "bf16" else 1e-5)
+        err = (h.double() - ref["hidden"]).norm(dim=1) / ref["hidden"].norm(dim=1)
+        assert float(err.max()) <= TOL[dtype]["rel"], (b, int(err.argmax()), float(err.max()))
+        ce, reg, pp, total = [float(x) for x in got["terms"][b]]
+        # the library's own head and loss on the hidden states it returned: a few fp32 roundings of logits of size 1
+        own = float(TF.cross_entropy(TF.all_position_logits(desc, w, h.double()), t))
+        assert abs(ce - own) <= 2e-4 and abs(ce - float(ref["ce"])) <= CE_TOL[dtype], (b, ce, own, float(ref["ce"]))
+        assert abs(reg - float(ref["reg"])) <= 1e-5 * float(ref["reg"]) and abs(pp - float(ref["pp"])) <= 2 * 2e-3
+        assert abs(total - (ce + 0.01 * reg + 0.05 * pp)) <= 1e-5 * max(1.0, abs(total))
+
+
 @pytest.mark.parametrize("model,n", [("mini_bf16", 131), ("mini_fp32", 40), ("step_hd128", 150)])
 def test_cross_entropy_sees_the_lm_head(model, n):
     """With N(0, 0.02) weights the cross entropy sits within 0.1 of ln V whatever the logits are, so the bar above barely
