@@ -6,8 +6,8 @@
 // workgroup fetches at a time is contiguous:
 //   kc [KV head][padded row][hd]             the keys as the cache stores them
 //   vt [KV head][tile of 64][hd][64 keys]    the values transposed; the 16 keys of a group stand in the order in which the
-//                                            score accumulators hold them (attn_key_slot), so that a B operand of the
-//                                            second product is one 16-byte read
+//                                            score accumulators hold them (0-3, 8-11, 4-7, 12-15), so that an A operand of
+//                                            the second product is one 16-byte read
 #pragma once
 #include "prefill_gemm.h"
 #include "prefill_kernels.h"

@@ -895,10 +895,6 @@ __global__ void __launch_bounds__(WG) k_split_bf16(const float* __restrict__ x, 
 
 __global__ void k_set_int(int* p, int v) { if (threadIdx.x == 0 && blockIdx.x == 0) *p = v; }
 
-__global__ void __launch_bounds__(WG) k_fill_u32(unsigned* p, unsigned v, size_t n) {
-  for (size_t i = (size_t)blockIdx.x * WG + threadIdx.x; i < n; i += (size_t)gridDim.x * WG) p[i] = v;
-}
-
 // KV taps: positions [pos0, pos0+n) of one layer <-> dense fp32 [n][Hkv][hd].
 template <typename KVT, bool WRITE>
 __global__ void __launch_bounds__(WG) k_kv_tap(KVT* __restrict__ pool, size_t page_elems, const int* __restrict__ pt,
