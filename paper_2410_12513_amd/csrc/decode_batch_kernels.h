@@ -130,8 +130,8 @@ __global__ void __launch_bounds__(WG) k_xsplit(BatchParams P, int src, int K, in
 
 // Start of a step for slot blockIdx.x.  blockIdx.y = 0: h = E[token] and, with a gain, the first norm op's input as k_xsplit
 // would leave it (same sums in the same order) - sixteen elements of the row requested at a time; blockIdx.y = 1: the
-// rotation table of the position (fp64 sines, beside the embedding instead of behind it).  10 + 8 us in two launches
-// before, 6.5 now (4096 wide).
+// rotation table of the position (fp64 sines, beside the embedding instead of behind it).  10.0 + 6.7 us in two launches
+// before, 6.4 now (sixteen slots, 4096 wide, kernel trace).
 __global__ void __launch_bounds__(WG) k_embed_b(BatchParams P, const float* gain) {
   __shared__ float red[WAVES];
   const DecParams& p = P.d;
@@ -1025,10 +1025,12 @@ __global__ void __launch_bounds__(GW * 64) k_bgemv_g(BatchParams P, int N, int K
 }
 
 // Greedy token: candidate of chunk blockIdx.y of slot blockIdx.x's logits row; the last chunk of a slot to finish takes the
-// lowest index among the best candidates and advances the sequence length.  (Eight logits of a thread in flight, one
-// launch: 9.4 us for 4 x 128256, 5.6 + 4 and a gap in two launches before.)
-constexpr int ARG_CHUNKS = 64;
-__global__ void __launch_bounds__(WG) k_argmax_b(BatchParams P, int advance) {
+// lowest index among the best candidates and advances the sequence length.  Eight logits of a thread in flight.  Bound:
+// latency, and the arrivals: with all sequences' counters in one cache line, 1024 additions queued there.  128256 logits
+// each of 4 / 16 sequences: 7.1 / 7.9 us (kernel trace), 9.6 / 18.7 with the counters side by side, 5.6 + 4.0 / 6.0 + 4.0 and a
+// gap in two launches.
+constexpr int ARG_CHUNKS = 64, ARG_CNT_PITCH = 32;         // (cnt: a cache line per sequence, zero between launches)
+__global__ void __launch_bounds__(WG) k_argmax_b(BatchParams P, unsigned* cnt, int advance) {
   __shared__ Best wbest[WAVES];
   __shared__ int last_flag;
   const DecParams& p = P.d;
@@ -1063,9 +1065,9 @@ __global__ void __launch_bounds__(WG) k_argmax_b(BatchParams P, int advance) {
     __hip_atomic_store(&mine->v, best.v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(&mine->i, best.i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     vm_wait_all();
-    const unsigned old = __hip_atomic_fetch_add(p.head_cnt + b, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned old = __hip_atomic_fetch_add(cnt + (size_t)b * ARG_CNT_PITCH, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const int last = old == (unsigned)(ARG_CHUNKS - 1);
-    if (last) __hip_atomic_store(p.head_cnt + b, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (last) __hip_atomic_store(cnt + (size_t)b * ARG_CNT_PITCH, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     last_flag = last;
   }
   __syncthreads();

@@ -69,7 +69,7 @@ struct first_ctx {
   float* d_rho = nullptr;
   double* d_theta = nullptr;
   float *d_h = nullptr, *d_qkv = nullptr, *d_attn = nullptr, *d_z = nullptr, *d_part_o = nullptr, *d_part_ml = nullptr;
-  unsigned *d_attn_cnt = nullptr, *d_head_cnt = nullptr;
+  unsigned *d_attn_cnt = nullptr, *d_head_cnt = nullptr, *d_arg_cnt = nullptr;
   float* d_bg_part = nullptr;             // k_bgemv_g: [workgroups][16 slots][128 rows] partial sums of the K-slices
   unsigned* d_bg_cnt = nullptr;           //            arrival counters per tile group (zero between launches)
   size_t bg_part_floats = 0, bg_cnt_n = 0;
@@ -583,7 +583,7 @@ void enqueue_decode_batched(first_ctx* c, const int* tokens, float* logits, int*
     P.ssq_groups = x_groups;
     launch_bgemv<BG_HEAD>(c, P, d.vocab, d.d_model);
     P.ssq_groups = 0;
-    hipLaunchKernelGGL(k_argmax_b, dim3(all.n, ARG_CHUNKS), dim3(WG), 0, c->stream, P, 1);
+    hipLaunchKernelGGL(k_argmax_b, dim3(all.n, ARG_CHUNKS), dim3(WG), 0, c->stream, P, c->d_arg_cnt, 1);
   }
 }
 
@@ -962,7 +962,7 @@ int enqueue_first_tokens(first_ctx* c, int B, float* logits_out, int* token_out)
       BatchParams P{};
       P.d = p; P.logits_all = p.logits;
       for (int j = b; j < std::min(B, b + BATCH_SLOTS); ++j) P.seqs.id[P.seqs.n++] = j;
-      hipLaunchKernelGGL(k_argmax_b, dim3(P.seqs.n, ARG_CHUNKS), dim3(WG), 0, c->stream, P, 0);
+      hipLaunchKernelGGL(k_argmax_b, dim3(P.seqs.n, ARG_CHUNKS), dim3(WG), 0, c->stream, P, c->d_arg_cnt, 0);
     }
   HIPCHK(c, hipGetLastError());
   return FIRST_OK;
@@ -1149,6 +1149,7 @@ int first_create(const first_model_desc* desc, const first_weights* w, void* hip
   A(dev_alloc(c, &c->d_part_o, (size_t)B * d.n_q_heads * S_MAX * d.head_dim));
   A(dev_alloc(c, &c->d_part_ml, (size_t)B * d.n_q_heads * S_MAX * 2));
   A(dev_alloc(c, &c->d_attn_cnt, (size_t)B * d.n_kv_heads)); A(dev_alloc(c, &c->d_head_cnt, B));
+  A(dev_alloc(c, &c->d_arg_cnt, (size_t)B * ARG_CNT_PITCH));
   A(dev_alloc(c, &c->d_rope_cs, (size_t)B * c->half)); A(dev_alloc(c, &c->d_arg_part, (size_t)B * ARG_MAX_WG));
   c->xpitch = (std::max(std::max(d.d_model, c->nq), d.d_ffn) + 31) / 32 * 32;
   if (B > 1) {
@@ -1197,6 +1198,7 @@ int first_create(const first_model_desc* desc, const first_weights* w, void* hip
     hipError_t e = hipMemcpy(c->d_theta, theta.data(), c->half * sizeof(double), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemset(c->d_attn_cnt, 0, (size_t)B * d.n_kv_heads * sizeof(unsigned));
     if (e == hipSuccess) e = hipMemset(c->d_head_cnt, 0, B * sizeof(unsigned));
+    if (e == hipSuccess) e = hipMemset(c->d_arg_cnt, 0, (size_t)B * ARG_CNT_PITCH * sizeof(unsigned));
     if (e == hipSuccess) e = hipMemset(c->d_len, 0, B * sizeof(int));
     if (e == hipSuccess && c->pg_cnt) e = hipMemset(c->pg_cnt, 0, (size_t)2 * c->num_cu * sizeof(unsigned));
     if (e == hipSuccess) e = prefill_attributes();
