@@ -411,7 +411,7 @@ int launch_bgemv(first_ctx* c, const BatchParams& P, int N, int K) {
     if (groups) return groups;
   }
   // four tiles per wave where that still gives three quarters of the waves a share: the split activations travel to every wave of
-  // the LM head, 256 KB each, and four tiles halve that next to two (128256 x 4096: 192 -> 163 us)
+  // the LM head, 256 KB each, and four tiles halve that next to two (128256 x 4096, sixteen slots: 188 -> 162 us)
   if constexpr (MODE == BG_HEAD)
     if ((N + 15) / 16 >= 4 * BG_WAVES * c->num_cu * 3 / 4) { launch_bgemv_rt<MODE, 4>(c, P, N, K); return 0; }
   // two tiles per wave once that still leaves every SIMD several waves
@@ -665,7 +665,7 @@ int launch_gemm(first_ctx* c, hipStream_t st, int dtype, const void* A, const vo
 // geometries with weights that no cache holds (within 1 % of the best of all choices on average, 15 % at worst).  What the
 // numbers say: 128 x 256 does most work per operand byte (1.76 us per step of 8.4 Mflop on a compute unit) and wins once
 // it fills the chip in whole rounds; 64 x 256 gives every compute unit a tile where 128 x 256 would leave half of them
-// idle (1024 x 4096 x 14336: 233 us against 323; 260 with 64 x 128); a prompt of a few dozen rows is a
+// idle (1024 x 4096 x 14336 in that sweep: 233 us against 323; 260 with 64 x 128); a prompt of a few dozen rows is a
 // stream of weights, which takes 32-row tiles and K cut into slices until every compute unit has work (16 x 4096 x 14336:
 // 28 us with four slices, 67 with one).  Slices cost a trip of the partial tiles through memory, so they are not used beyond
 // two workgroups a compute unit.

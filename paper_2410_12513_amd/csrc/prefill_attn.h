@@ -28,7 +28,7 @@ __device__ __forceinline__ void both_halves(float x, float& lower, float& upper)
 // Rotation, splits and cache writes of one head (blockIdx.y: query heads, then key heads, then value heads) for 32 padded rows
 // (blockIdx.x).  Queries leave rotated, scaled by qscale and split; keys and
 // values go to their pages and to kc / vt.  One pass over the fp32 projections, where a rotation in place, a split of the
-// queries and a gather of the pages were three (34 us a layer at 1024 tokens of the 8B shape, 11 now).
+// queries and a gather of the pages were three (36 us a layer at 1024 tokens of the 8B shape, 11 now).
 template <int HD>
 __global__ void __launch_bounds__(WG) k_rope_split(const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
                                                    const float2* __restrict__ cs, PromptPack pk, bf16* __restrict__ pool, size_t page_elems,
@@ -116,7 +116,7 @@ __global__ void __launch_bounds__(WG) k_rope_split(const float* __restrict__ q, 
 // wave of the SIMD beside them.  KH = 2 doubles the workgroups and halves each wave's walk where the prompts are too short
 // to fill the chip; KH = 1 moves half the operand bytes.  Workgroups with the longest walks start first, and workgroups that
 // follow each other belong to different KV heads, so that an XCD's L2 sees one head's keys where there are eight of them.
-// Measured, 8B heads: 16384 tokens 14.2 -> 3.65 ms a layer (1.2 PFLOP/s of matrix work), 1024 tokens 98 -> 36 us (against
+// Measured, 8B heads, kernel trace: 16384 tokens 13.9 -> 3.5 ms a layer (1.2 PFLOP/s of matrix work), 1024 tokens 103 -> 35 us (against
 // the earlier kernel: one wave per 32 queries, operands from global memory into registers).
 template <int HD, int QG, int KH>
 __global__ void __launch_bounds__(WG, 2) k_attn_prompt(const bf16* __restrict__ qh, const bf16* __restrict__ ql, const bf16* __restrict__ kc,

@@ -8,10 +8,10 @@
 // in LDS; its eight 16-byte chunks are permuted by (row / 2) % 8 - on the way in through the address each lane fetches - so
 // that the 32 rows a wave reads at one K offset spread over all banks.
 //
-// Measured, weights cold (matrix-core work, twice the useful flops): 1024 x 28672 x 4096 (gate + up of the 8B geometry) 425 us =
-// 1130 TFLOP/s with 128 x 256 tiles, 571 us with the earlier kernel (four waves of 64 x 64, operands through registers);
-// 1024 x 4096 x 14336 (down) 219 us = 1100 TFLOP/s with 64 x 256 tiles, 325 us before; the library's plain bf16 product of
-// the first shape runs at 1156 TFLOP/s, of 8192^3 at 1301.
+// Measured in the model (8B geometry, kernel trace; matrix-core work, twice the useful flops), the earlier kernel with four waves of
+// 64 x 64 and operands through registers in brackets: at 1024 rows gate + up 460 us = 1.05 PFLOP/s with 128 x 256 tiles (537),
+// down 241 us = 1.0 PFLOP/s with 64 x 256 tiles (301); at 16384 rows 6.5 and 3.4 ms = 1.18 and 1.14 PFLOP/s (9.4, 4.2).  The
+// library's plain bf16 product runs at 1.16 PFLOP/s on 1024 x 28672 x 4096, at 1.30 on 8192^3.
 #pragma once
 #include "step_kernel.h"
 
@@ -59,9 +59,9 @@ struct PgArgs {
 // the launch.  With SEG = 4 (a property of the matrix, see pg_segments) K is four segments of whole steps, each summed
 // from zero, added in order; slices of K take whole segments, and the upper half's two travel apart.
 //
-// BM x BN tile, WGM x WGN waves.  S: K steps in the LDS ring (three where they fit: with weights from HBM a third step in
-// flight took 1024 x 4096 x 14336 from 266 to 223 us; two 64 x 128 workgroups on a compute unit hide each other's waits
-// and have 64 KB each).
+// BM x BN tile, WGM x WGN waves.  S: K steps in the LDS ring (three where they fit: 64 x 256 tiles with a third step in flight
+// take 234 us for 1024 x 4096 x 14336 in the model, 267 with two; two 64 x 128 workgroups on a compute unit hide each other's
+// waits and have 64 KB each).
 // GU: the tile's BN weight rows are 32 (16 where a wave tile is 32 wide) gate rows and as many up rows in turn, so that
 // a gate value and its up value sit in the same lane (in lanes 16 apart).
 template <int BM, int BN, int WGM, int WGN, int S, bool GU, bool SPLIT, int SEG>

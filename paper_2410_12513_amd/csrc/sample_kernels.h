@@ -110,8 +110,8 @@ __device__ __forceinline__ int smp_pick(const Cand* top, const float* weight, in
 }
 
 // Stage 1.  grid (chunks, sequences).  part[(seq * chunks + chunk) * k + r] = r-th candidate of the chunk.
-// Latency, not bandwidth (16 x 128256 logits, k = 10: 24.6 us with a barrier pair and an LDS reduction per candidate,
-// 10.9 now; 8 MB).
+// Latency, not bandwidth (16 x 128256 logits, k = 10, kernel trace: 23.3 us with a barrier pair and an LDS reduction per
+// candidate, 10.5 now; 8 MB).
 __global__ void __launch_bounds__(SMP_THREADS) k_topk_part(const float* __restrict__ logits, int V, int k, Cand* __restrict__ part) {
   __shared__ unsigned long long lists[(SMP_THREADS / 64) * SMP_KMAX], top[SMP_KMAX];
   const int tid = threadIdx.x, chunk = blockIdx.x, seq = blockIdx.y;
@@ -130,7 +130,7 @@ __global__ void __launch_bounds__(SMP_THREADS) k_topk_part(const float* __restri
   if (tid < k) part[((size_t)seq * gridDim.x + chunk) * k + tid] = cand_of(top[tid]);
 }
 
-// Stage 2.  grid (sequences).  n = chunks * k candidates of the sequence, 2048 at a time (17.4 us before at n = 630, 9.9 now).
+// Stage 2.  grid (sequences).  n = chunks * k candidates of the sequence, 2048 at a time (17.2 us before at n = 630, 10.1 now).
 __global__ void __launch_bounds__(SMP_THREADS) k_topk_sample(const Cand* __restrict__ part, int n, int k, float temperature,
                                                             const float* __restrict__ uniforms, int* __restrict__ token_out,
                                                             int* __restrict__ cand_out) {
