@@ -160,7 +160,7 @@ __global__ void __launch_bounds__(WG, 2) k_attn_prompt(const bf16* __restrict__ 
   const size_t base = ((size_t)g * padded + pj) * HD;
   auto issue = [&](int st) __attribute__((always_inline)) {
     const i32x4_t rk = pg_rsrc(kc + base + (size_t)st * FA_TILE * HD, KB), rv = pg_rsrc(vt + base + (size_t)st * FA_TILE * HD, KB);
-    const uint32_t b = lds0 + (uint32_t)(st & 1) * STG;
+    const uint32_t b = (uint32_t)uni((int)(lds0 + (uint32_t)(st & 1) * STG));
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
       pg_load_lds(b + (wave * NI + i) * 1024, vk[i], rk, 0u);

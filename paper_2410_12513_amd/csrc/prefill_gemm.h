@@ -24,9 +24,6 @@ constexpr int PG_BK = 64;                       // K step: one row of a tile is 
 // compiler that writes the register, so it knows (m0 written in the asm text would be a write it knows nothing of).
 typedef int i32x4_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void pg_load_lds(uint32_t lds_off, uint32_t voff, i32x4_t rsrc, uint32_t soff) {
-  // (uniform by construction; said again for the compiler, which does not see it through every loop)
-  lds_off = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_off);
-  soff = (uint32_t)__builtin_amdgcn_readfirstlane((int)soff);
   asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"{m0}"(lds_off), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
 }
 __device__ __forceinline__ i32x4_t pg_rsrc(const void* p, uint32_t bytes) {
@@ -126,7 +123,10 @@ __global__ void __launch_bounds__(WGM * WGN * 64, 2) k_pgemm(PgArgs P) {
   const int s0 = nsteps * g0 / SEG, s1 = nsteps * g1 / SEG;
   const int tail_chunks = (K % BK) / 8;                                   // chunks of the last step that exist (0: all)
   auto issue = [&](int step) __attribute__((always_inline)) {
-    const uint32_t b = lds0 + (uint32_t)((step - s0) % S) * STG, so = (uint32_t)step * BK * 2;
+    // (uniform by construction; said again for the compiler, which does not see it through the loop: once a step, so that what a
+    // load adds is a constant)
+    const uint32_t b = (uint32_t)uni((int)(lds0 + (uint32_t)((step - s0) % S) * STG)), so = (uint32_t)uni(step * BK * 2);
+    const uint32_t ba = b + (uint32_t)wave * IA * 1024, bb = b + 2 * BM * BK * 2 + (uint32_t)wave * IB * 1024;
     const bool cut = tail_chunks != 0 && step == nsteps - 1;
     auto off = [&](uint32_t v, int r) __attribute__((always_inline)) {   // past the row's end: out of the descriptor's range, reads as zeros
       return cut && pg_chunk(r, lane & 7) >= tail_chunks ? 0x7ffffff0u : v;
@@ -134,15 +134,15 @@ __global__ void __launch_bounds__(WGM * WGN * 64, 2) k_pgemm(PgArgs P) {
 #pragma unroll
     for (int i = 0; i < IA; ++i) {
       const uint32_t v = off(va[i], (wave * IA + i) * 8 + lrow);
-      pg_load_lds(b + (wave * IA + i) * 1024, v, rh, so);
-      pg_load_lds(b + BM * BK * 2 + (wave * IA + i) * 1024, v, rl, so);
+      pg_load_lds(ba + i * 1024, v, rh, so);
+      pg_load_lds(ba + BM * BK * 2 + i * 1024, v, rl, so);
     }
 #pragma unroll
     for (int i = 0; i < IB; ++i) {
       const int r8 = (wave * IB + i) * 8;
       const bool up = GU && (r8 / GI) % 2 == 1;
       const i32x4_t rs = up ? ru : rb;
-      pg_load_lds(b + 2 * BM * BK * 2 + (wave * IB + i) * 1024, off(vb[i], r8 + lrow), rs, so);
+      pg_load_lds(bb + i * 1024, off(vb[i], r8 + lrow), rs, so);
     }
   };
   constexpr int NL = 2 * IA + IB;

@@ -688,7 +688,8 @@ __global__ void __launch_bounds__(WG) k_gemm_nt_f32(const float* __restrict__ A,
 // The same for shapes whose 64 x 64 tiles would leave most of the chip idle (short prompts of a small model): 16 TT x 16 TT
 // tiles, TT x TT outputs per thread, K in steps of 64 with the next step already on its way in registers.  Every output is
 // the same chain of multiply-adds over ascending k, so the bits are those of k_gemm_nt_f32.  Bound: latency (32 x 256 x 256:
-// 16 dependent steps and 4 workgroups there, 4 steps and 32 workgroups here; 17 -> 4.6 us, 32 x 256 x 688 50 -> 13.6 us).
+// 16 dependent steps and 4 workgroups there, 4 steps and 32 workgroups here; 17.6 -> 5.8 us, 32 x 256 x 688 49.4 -> 14.0 us,
+// kernel trace).
 template <int TT>
 __global__ void __launch_bounds__(WG) k_gemm_nt_f32_small(const float* __restrict__ A, const float* __restrict__ W, float* __restrict__ C,
                                                           int M, int N, int K, int accumulate) {
