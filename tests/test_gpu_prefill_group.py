@@ -8,6 +8,7 @@ from oracle import first_oracle as O
 from synth import make_prompt, make_router, make_weights
 from synth.generators import ModelDesc, to_device
 from tests.gpu_util import logits_close, routers_with_margin
+from tests.test_gpu_prefill_gemm import MATRICES, _shift as shifted
 
 # a down projection in four segments of K (d_ffn >= 2048), both head dimensions
 HD64 = ModelDesc(2, 512, 8, 2, 64, 2048, 700)
@@ -38,12 +39,14 @@ def _run(desc, w, r, prompts, max_seq_len, slots=0, flash=1):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("desc,lens", [(HD64, (2100, 5, 64, 129, 1100, 63, 2048, 300, 1)), (HD128, (2100, 5, 64, 129, 1100, 63, 2048, 300, 1)),
-                                       (HD64_FP32, (2100, 5, 64, 129, 1100, 63, 600, 300, 1)), (WIDE, (807, 31, 100, 300, 1500))])
-def test_prompts_in_a_group_have_the_bits_they_have_alone(desc, lens):
-    # 4096 rows of workspace: the nine prompts go through in two groups, the first with both attention kernels
+@pytest.mark.parametrize("desc,lens,off", [(HD64, (2100, 5, 64, 129, 1100, 63, 2048, 300, 1), ()), (HD128, (2100, 5, 64, 129, 1100, 63, 2048, 300, 1), ()),
+                                           (HD64_FP32, (2100, 5, 64, 129, 1100, 63, 600, 300, 1), ()), (WIDE, (807, 31, 100, 300, 1500), ()),
+                                           (HD64, (70, 2000, 200, 1), MATRICES), (HD128, (70, 2000, 200, 1), ("wk", "w_down"))])
+def test_prompts_in_a_group_have_the_bits_they_have_alone(desc, lens, off):
+    # 4096 rows of workspace: the nine prompts go through in two groups, the first with both attention kernels.  off: matrices off
+    # 16 bytes (128-row tiles together, 64-row ones for some alone)
     w, r = make_weights(desc, 5), make_router(desc, 5)
-    wg, rg = to_device(w, "cuda"), r.cuda()
+    wg, rg = shifted(to_device(w, "cuda"), off), r.cuda()
     prompts = [make_prompt(desc.vocab, n, 50 + i) for i, n in enumerate(lens)]
     got = _run(desc, wg, rg, prompts, 2200)
     for b, p in enumerate(prompts):
