@@ -83,7 +83,7 @@ struct first_ctx {
   void *p_x = nullptr, *p_a = nullptr, *p_z = nullptr;
   bf16 *p_qh = nullptr, *p_ql = nullptr, *p_kc = nullptr, *p_vt = nullptr;   // matrix-core prefill attention operands
   bf16 *p_xh = nullptr, *p_xl = nullptr, *p_ah = nullptr, *p_al = nullptr, *p_zh = nullptr, *p_zl = nullptr;   // split activations (bf16 models)
-  float* pg_part = nullptr;               // k_pgemm: partial tiles of the slices of K, four for each of at most num_cu tiles of 64 x 128
+  float* pg_part = nullptr;               // k_pgemm: partial tiles of the slices of K (pg_part_floats)
   unsigned* pg_cnt = nullptr;             //          arrival counters per tile (zero between launches)
   int p_rows = 0;                         // rows of the prefill workspace: prompts of a batch go through it in groups of at most this many rows
   int p_tp = 0;                           // padded rows of p_kc / p_vt (every prompt of a group starts at a multiple of PACK_PAD): the groups' other limit
@@ -660,20 +660,24 @@ int launch_gemm(first_ctx* c, hipStream_t st, int dtype, const void* A, const vo
   return FIRST_OK;
 }
 
-// Tile and number of K slices of a k_pgemm launch.  The estimate (in us) is fixed cost + K steps times the time of a step, summed
-// over the rounds the grid takes on the chip, fitted to a sweep over M = 16 .. 4000 and the projections of the 8B, 3B and 1B
-// geometries with weights that no cache holds (within 1 % of the best of all choices on average, 15 % at worst).  What the
-// numbers say: 128 x 256 does most work per operand byte (1.76 us per step of 8.4 Mflop on a compute unit) and wins once
-// it fills the chip in whole rounds; 64 x 256 gives every compute unit a tile where 128 x 256 would leave half of them
-// idle (1024 x 4096 x 14336 in that sweep: 233 us against 323; 260 with 64 x 128); a prompt of a few dozen rows is a
-// stream of weights, which takes 32-row tiles and K cut into slices until every compute unit has work (16 x 4096 x 14336:
-// 28 us with four slices, 67 with one).  Slices cost a trip of the partial tiles through memory, so they are not used beyond
-// two workgroups a compute unit.
-struct PgTile { int bm, bn, occ; double fix, full, one, red, red_ks, red_wg; };
-constexpr PgTile PG_TILES[4] = {{128, 256, 1, 9.3, 1.76, 1.29, 0, 0, 0},
-                                {64, 256, 1, 6.5, 1.07, 0.83, 0, 0, 0},
-                                {64, 128, 2, 3.3, 1.15, 0.78, 1.9, 0.3, 3.2},
-                                {32, 128, 2, 4.3, 0.75, 0.46, 0.8, 0.2, 0}};
+// Tile and number of K slices of a k_pgemm launch.  The estimate (in us) is a fixed cost + K steps of 64 times the time of a step, summed
+// over the rounds the grid takes on the chip; a step of the last round takes longer the more compute units share memory and power.
+// Fitted to a sweep over M = 16 .. 6000 and the projections of the 8B, 3B and 1B geometries with weights that no cache holds (within
+// 0.3 % of the best of all choices on average, 8 % at worst).  What the numbers say, us with the next best tile in brackets:
+//   256 x 256  gate / up wherever its rounds come out even: 16384 x 28672 x 4096 5.96 ms (6.19 with 128 x 256), 1024 rows 406 (429)
+//   128 x 256  most work per operand byte of those that hold K segments: 2000 x 4096 x 14336 379 (432 with 64 x 256); with two
+//              or four slices where that fills the chip once: 1024 x 4096 x 14336 213 (222 with 64 x 256 and one), 300 rows 90 (107)
+//   128 x 192  where 256 columns leave compute units without a tile: 826 x 5120 x 3072 58 (67 with 128 x 256)
+//   64 x 256   1024 x 4096 x 4096 67 (72 with 128 x 256 and two slices); 100 x 6144 x 4096 24 with four slices (27 with 64 x 128 tiles)
+//   32 x 128   a prompt of a few dozen rows is a stream of weights: 100 x 4096 x 14336 51 with four slices (58 with 64 x 256)
+// Slices cost a trip of the partial tiles through memory, so they are not used beyond one round of the chip.
+struct PgTile { int bm, bn, occ; double fix, full, one, slope, red, red_wg, fix_gu; };
+enum { PG_128x256, PG_64x256, PG_32x128, PG_128x192, PG_256x256, PG_NTILES };
+constexpr PgTile PG_TILES[PG_NTILES] = {{128, 256, 1, 8.5, 1.74, 1.15, 0.44, 5.5, 5.8, 0.7},
+                                        {64, 256, 1, 5.8, 1.02, 0.73, 0.21, 4.1, 3.3, 1.2},
+                                        {32, 128, 2, 3.0, 0.70, 0.43, 0.03, 2.8, 2.2, 4.0},
+                                        {128, 192, 1, 5.9, 1.41, 1.01, 0.31, 5.8, 5.4, 0},
+                                        {256, 256, 1, 7.3, 3.24, 2.09, 0.95, 0, 0, 7.2}};
 struct PgPlan { int tile = 0, ks = 1, gm = 0, gn = 0, seg = 1; };
 
 // Segments of K (see k_pgemm): four where a launch over few rows would leave compute units without a tile - fewer than 64
@@ -684,47 +688,62 @@ int pg_segments(std::initializer_list<int> Ns, int K, bool gu) {
   for (int N : Ns) cols += N;
   return !gu && cols <= 8192 && K >= 32 * PG_BK ? 4 : 1;
 }
+// Floats that the partial tiles of a sliced launch take: four a tile, for a round of the chip in two slices (of 128 x 256 tiles, or of two
+// 32 x 128 tiles a compute unit).
+size_t pg_part_floats(int num_cu) { return (size_t)4 * (num_cu / 2) * 128 * 256; }
 
 PgPlan pg_plan(int M, std::initializer_list<int> Ns, int K, bool gu, int num_cu) {
   PgPlan best;
   best.seg = pg_segments(Ns, K, gu);
   double best_t = 1e30;
   const int steps = (K + PG_BK - 1) / PG_BK;
-  for (int t = 0; t < 4; ++t) {
+  int widest = 0;
+  for (int N : Ns) widest = std::max(widest, N);
+  for (int t = 0; t < PG_NTILES; ++t) {
     const PgTile& T = PG_TILES[t];
+    if (t == PG_256x256 && (best.seg > 1 || widest > (1 << 20))) continue;   // no room for sums of segments; 256 rows within 31 bits of bytes
+    if (t == PG_128x192 && gu) continue;                                     // (three 32-column blocks a wave: no pairs of gate and up)
     const int cols = gu ? T.bn / 2 : T.bn, gm = (M + T.bm - 1) / T.bm;
     int gn = 0;
     for (int N : Ns) gn += (N + cols - 1) / cols;
     for (int ks : {1, 2, 4}) {
-      const long long wgs = (long long)gm * gn * ks;
-      if (ks > 1 && (T.occ == 1 || best.seg == 1 || wgs > 2 * num_cu)) break;
-      const long long rem = wgs % (num_cu * T.occ);
-      const bool pair = T.occ == 2 && rem > num_cu;               // the last round puts two workgroups on a compute unit
-      const double st = (steps + ks - 1) / ks;
-      double us = T.fix + st * (T.full * (wgs / (num_cu * T.occ) + (pair ? 1 : 0)) + T.one * (rem > 0 && !pair ? 1 : 0));
-      if (ks > 1) us += T.red + T.red_ks * ks + (wgs > num_cu ? T.red_wg * wgs / (2 * num_cu) : 0);
+      const long long wgs = (long long)gm * gn * ks, round = (long long)num_cu * T.occ;
+      if (ks > 1 && (best.seg == 1 || wgs > round)) break;
+      const long long rem = wgs % round, rounds = wgs / round + (rem > 0);
+      const double last = rem == 0 ? 0 : rem > num_cu ? T.full : T.one + T.slope * rem / num_cu;   // (two on some compute units: as on all)
+      double us = T.fix + (steps + ks - 1) / ks * (T.full * (wgs / round) + last) + (gu ? T.fix_gu * rounds : 0);
+      if (ks > 1) us += T.red + T.red_wg * wgs / num_cu;
       if (us < best_t) { best_t = us; best.tile = t; best.ks = ks; best.gm = gm; best.gn = gn; }
     }
   }
   return best;
 }
 
-template <int BM, int BN, int S> constexpr int pg_lds() { return S * (2 * BM + BN) * PG_BK * 2; }
+// f(kernel, threads, bytes of LDS) for the tile; SEG = 4 with slices, gate / up where the tile has pairs of gate and up.
+template <bool GU, int SEG, typename F>
+void pg_with_tile(int tile, F f) {
+  auto lds = [](int bm, int bn, int bk, int s) { return s * (2 * bm + bn) * bk * 2; };
+  if (tile == PG_128x256) f(&k_pgemm<128, 256, 2, 4, 64, 2, GU, SEG == 4, SEG>, 512, lds(128, 256, 64, 2));
+  if (tile == PG_64x256) f(&k_pgemm<64, 256, 2, 4, 64, 3, GU, SEG == 4, SEG>, 512, lds(64, 256, 64, 3));
+  if (tile == PG_32x128) f(&k_pgemm<32, 128, 1, 4, 64, 3, GU, SEG == 4, SEG>, 256, lds(32, 128, 64, 3));
+  if constexpr (!GU)
+    if (tile == PG_128x192) f(&k_pgemm<128, 192, 4, 2, 64, 2, GU, SEG == 4, SEG>, 512, lds(128, 192, 64, 2));
+  if constexpr (SEG == 1)
+    if (tile == PG_256x256) f(&k_pgemm<256, 256, 4, 2, 32, 3, GU, false, SEG>, 512, lds(256, 256, 32, 3));
+}
 template <bool GU, int SEG>
 void launch_pgemm_seg(hipStream_t st, const PgPlan& plan, const PgArgs& P) {
-  const dim3 grid((unsigned)(plan.gm * plan.gn * plan.ks));
-  if (plan.tile == 0) hipLaunchKernelGGL((k_pgemm<128, 256, 2, 4, 2, GU, false, SEG>), grid, dim3(512), (pg_lds<128, 256, 2>()), st, P);
-  else if (plan.tile == 2) hipLaunchKernelGGL((k_pgemm<64, 128, 1, 4, 2, GU, true, SEG>), grid, dim3(256), (pg_lds<64, 128, 2>()), st, P);
-  else if (plan.tile == 3) hipLaunchKernelGGL((k_pgemm<32, 128, 1, 4, 3, GU, true, SEG>), grid, dim3(256), (pg_lds<32, 128, 3>()), st, P);
-  else hipLaunchKernelGGL((k_pgemm<64, 256, 2, 4, 3, GU, false, SEG>), grid, dim3(512), (pg_lds<64, 256, 3>()), st, P);
+  pg_with_tile<GU, SEG>(plan.tile, [&](void (*kernel)(PgArgs), int threads, int lds) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(plan.gm * plan.gn * plan.ks)), dim3(threads), lds, st, P);
+  });
 }
 template <bool GU, int SEG>
 hipError_t pg_set_lds() {
-  auto set = [](const void* fn, int lds) { return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds); };
-  hipError_t e = set(reinterpret_cast<const void*>(&k_pgemm<128, 256, 2, 4, 2, GU, false, SEG>), pg_lds<128, 256, 2>());
-  if (e == hipSuccess) e = set(reinterpret_cast<const void*>(&k_pgemm<64, 128, 1, 4, 2, GU, true, SEG>), pg_lds<64, 128, 2>());
-  if (e == hipSuccess) e = set(reinterpret_cast<const void*>(&k_pgemm<32, 128, 1, 4, 3, GU, true, SEG>), pg_lds<32, 128, 3>());
-  if (e == hipSuccess) e = set(reinterpret_cast<const void*>(&k_pgemm<64, 256, 2, 4, 3, GU, false, SEG>), pg_lds<64, 256, 3>());
+  hipError_t e = hipSuccess;
+  for (int t = 0; t < PG_NTILES && e == hipSuccess; ++t)
+    pg_with_tile<GU, SEG>(t, [&](void (*kernel)(PgArgs), int, int lds) {
+      e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    });
   return e;
 }
 // k_pgemm's loads start on 16 bytes (K is a multiple of 8, so the first row decides), and it addresses the rows of a tile with
@@ -1190,7 +1209,7 @@ int first_create(const first_model_desc* desc, const first_weights* w, void* hip
     bool cut = false;                     // some product sums K in segments, which slices may share out
     for (const auto& [N, K] : {std::pair<int, int>{c->nq + 2 * c->nkv, d.d_model}, {d.d_model, c->nq}, {d.d_model, d.d_ffn}, {d.vocab, d.d_model}})
       cut = cut || pg_segments({N}, K, false) > 1;
-    if (cut) { A(dev_alloc(c, &c->pg_part, (size_t)4 * c->num_cu * 64 * 128)); A(dev_alloc(c, &c->pg_cnt, (size_t)2 * c->num_cu)); }
+    if (cut) { A(dev_alloc(c, &c->pg_part, pg_part_floats(c->num_cu))); A(dev_alloc(c, &c->pg_cnt, (size_t)2 * c->num_cu)); }
   }
   if (rc == FIRST_OK) {
     std::vector<double> theta(c->half);

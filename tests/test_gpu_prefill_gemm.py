@@ -64,6 +64,19 @@ def test_prefill_projections_at_tile_edges(desc, n, shifted):
         assert all(torch.equal(x, y) for x, y in zip((h, l, rows), runs[0]))
 
 
+# widths that are no multiples of the large tiles nor of their K steps; at 256 compute units: 256 x 256 tiles in gate / up (700 rows) and
+# in Q/K/V (1300); then the down projection's 128 x 192 and 128 x 256 tiles with four slices of K (330, 390 rows) and two (700, 900)
+MANY_HEADS = ModelDesc(1, 1032, 64, 8, 128, 9000, 500)
+LONG_DOWN = ModelDesc(1, 3080, 4, 2, 64, 8200, 500)
+DOWN = ModelDesc(1, 3080, 4, 2, 64, 4104, 500)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("desc,n", [(MANY_HEADS, 700), (MANY_HEADS, 1300), (LONG_DOWN, 330), (LONG_DOWN, 390), (DOWN, 700), (LONG_DOWN, 900)])
+def test_prefill_projections_in_large_tiles(desc, n):
+    test_prefill_projections_at_tile_edges(desc, n, False)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("names", [("embed", "lm_head"), ("wo",), ("w_up",)])
 def test_a_matrix_off_16_bytes_leaves_the_other_products_alone(names):
