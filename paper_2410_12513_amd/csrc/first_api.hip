@@ -663,21 +663,23 @@ int launch_gemm(first_ctx* c, hipStream_t st, int dtype, const void* A, const vo
 // Tile and number of K slices of a k_pgemm launch.  The estimate (in us) is a fixed cost + K steps of 64 times the time of a step, summed
 // over the rounds the grid takes on the chip; a step of the last round takes longer the more compute units share memory and power.
 // Fitted to a sweep over M = 16 .. 6000 and the projections of the 8B, 3B and 1B geometries with weights that no cache holds (within
-// 0.3 % of the best of all choices on average, 8 % at worst).  What the numbers say, us with the next best tile in brackets:
+// 0.4 % of the best of all choices on average, 12 % at worst).  What the numbers say, us with the next best tile in brackets:
 //   256 x 256  gate / up wherever its rounds come out even: 16384 x 28672 x 4096 5.96 ms (6.19 with 128 x 256), 1024 rows 406 (429)
 //   128 x 256  most work per operand byte of those that hold K segments: 2000 x 4096 x 14336 379 (432 with 64 x 256); with two
 //              or four slices where that fills the chip once: 1024 x 4096 x 14336 213 (222 with 64 x 256 and one), 300 rows 90 (107)
 //   128 x 192  where 256 columns leave compute units without a tile: 826 x 5120 x 3072 58 (67 with 128 x 256)
-//   64 x 256   1024 x 4096 x 4096 67 (72 with 128 x 256 and two slices); 100 x 6144 x 4096 24 with four slices (27 with 64 x 128 tiles)
-//   32 x 128   a prompt of a few dozen rows is a stream of weights: 100 x 4096 x 14336 51 with four slices (58 with 64 x 256)
+//   64 x 256   1024 x 4096 x 4096 67 (72 with 128 x 256 and two slices); 100 x 8192 x 2048 (gate / up) 33 (52)
+//   32 x 128   a prompt of a few dozen rows is a stream of weights: 16 x 4096 x 14336 32 with four slices (54 with 64 x 256).  Two
+//              workgroups a compute unit have room for three steps of K; where there is at most one, four steps (16 x 6144 x 4096
+//              in two slices 19.5 against 20.8, 100 x 3072 x 8192 30.5 against 33.9; six steps are no better)
 // Slices cost a trip of the partial tiles through memory, so they are not used beyond one round of the chip.
 struct PgTile { int bm, bn, occ; double fix, full, one, slope, red, red_wg, fix_gu; };
 enum { PG_128x256, PG_64x256, PG_32x128, PG_128x192, PG_256x256, PG_NTILES };
-constexpr PgTile PG_TILES[PG_NTILES] = {{128, 256, 1, 8.5, 1.74, 1.15, 0.44, 5.5, 5.8, 0.7},
-                                        {64, 256, 1, 5.8, 1.02, 0.73, 0.21, 4.1, 3.3, 1.2},
-                                        {32, 128, 2, 3.0, 0.70, 0.43, 0.03, 2.8, 2.2, 4.0},
-                                        {128, 192, 1, 5.9, 1.41, 1.01, 0.31, 5.8, 5.4, 0},
-                                        {256, 256, 1, 7.3, 3.24, 2.09, 0.95, 0, 0, 7.2}};
+constexpr PgTile PG_TILES[PG_NTILES] = {{128, 256, 1, 7.4, 1.70, 1.19, 0.36, 5.3, 4.3, 1.7},
+                                        {64, 256, 1, 5.4, 0.99, 0.75, 0.17, 3.8, 2.5, 1.7},
+                                        {32, 128, 2, 3.5, 0.72, 0.375, 0.05, 1.8, 1.6, 4.3},
+                                        {128, 192, 1, 4.9, 1.36, 1.04, 0.25, 5.5, 3.9, 0},
+                                        {256, 256, 1, 9.6, 3.25, 2.14, 0.80, 0, 0, 4.7}};
 struct PgPlan { int tile = 0, ks = 1, gm = 0, gn = 0, seg = 1; };
 
 // Segments of K (see k_pgemm): four where a launch over few rows would leave compute units without a tile - fewer than 64
@@ -719,30 +721,32 @@ PgPlan pg_plan(int M, std::initializer_list<int> Ns, int K, bool gu, int num_cu)
   return best;
 }
 
-// f(kernel, threads, bytes of LDS) for the tile; SEG = 4 with slices, gate / up where the tile has pairs of gate and up.
+// f(kernel, threads, bytes of LDS) for the tile; SEG = 4 with slices, gate / up where the tile has pairs of gate and up.  alone: at most
+// one workgroup a compute unit.
 template <bool GU, int SEG, typename F>
-void pg_with_tile(int tile, F f) {
+void pg_with_tile(int tile, bool alone, F f) {
   auto lds = [](int bm, int bn, int bk, int s) { return s * (2 * bm + bn) * bk * 2; };
   if (tile == PG_128x256) f(&k_pgemm<128, 256, 2, 4, 64, 2, GU, SEG == 4, SEG>, 512, lds(128, 256, 64, 2));
   if (tile == PG_64x256) f(&k_pgemm<64, 256, 2, 4, 64, 3, GU, SEG == 4, SEG>, 512, lds(64, 256, 64, 3));
-  if (tile == PG_32x128) f(&k_pgemm<32, 128, 1, 4, 64, 3, GU, SEG == 4, SEG>, 256, lds(32, 128, 64, 3));
+  if (tile == PG_32x128 && alone) f(&k_pgemm<32, 128, 1, 4, 64, 4, GU, SEG == 4, SEG>, 256, lds(32, 128, 64, 4));
+  if (tile == PG_32x128 && !alone) f(&k_pgemm<32, 128, 1, 4, 64, 3, GU, SEG == 4, SEG>, 256, lds(32, 128, 64, 3));
   if constexpr (!GU)
     if (tile == PG_128x192) f(&k_pgemm<128, 192, 4, 2, 64, 2, GU, SEG == 4, SEG>, 512, lds(128, 192, 64, 2));
   if constexpr (SEG == 1)
     if (tile == PG_256x256) f(&k_pgemm<256, 256, 4, 2, 32, 3, GU, false, SEG>, 512, lds(256, 256, 32, 3));
 }
 template <bool GU, int SEG>
-void launch_pgemm_seg(hipStream_t st, const PgPlan& plan, const PgArgs& P) {
-  pg_with_tile<GU, SEG>(plan.tile, [&](void (*kernel)(PgArgs), int threads, int lds) {
+void launch_pgemm_seg(hipStream_t st, const PgPlan& plan, const PgArgs& P, int num_cu) {
+  pg_with_tile<GU, SEG>(plan.tile, plan.gm * plan.gn * plan.ks <= num_cu, [&](void (*kernel)(PgArgs), int threads, int lds) {
     hipLaunchKernelGGL(kernel, dim3((unsigned)(plan.gm * plan.gn * plan.ks)), dim3(threads), lds, st, P);
   });
 }
 template <bool GU, int SEG>
 hipError_t pg_set_lds() {
   hipError_t e = hipSuccess;
-  for (int t = 0; t < PG_NTILES && e == hipSuccess; ++t)
-    pg_with_tile<GU, SEG>(t, [&](void (*kernel)(PgArgs), int, int lds) {
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  for (int t = 0; t < 2 * PG_NTILES; ++t)
+    pg_with_tile<GU, SEG>(t / 2, t % 2 == 0, [&](void (*kernel)(PgArgs), int, int lds) {
+      if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     });
   return e;
 }
@@ -766,7 +770,7 @@ int launch_gemm_hl_seg(first_ctx* c, hipStream_t st, const bf16* Ah, const bf16*
     const PgPlan plan = list.size() == 3 ? pg_plan(M, {g[0].N, g[1].N, g[2].N}, K, false, c->num_cu) : pg_plan(M, {g[0].N}, K, false, c->num_cu);
     PgArgs P = pg_args(c, plan, Ah, Al, M, K, acc);
     for (const GemmSeg& s : list) P.seg[P.nseg++] = PgSeg{s.W, s.C, s.N, (s.N + PG_TILES[plan.tile].bn - 1) / PG_TILES[plan.tile].bn};
-    if (plan.seg == 4) launch_pgemm_seg<false, 4>(st, plan, P); else launch_pgemm_seg<false, 1>(st, plan, P);
+    if (plan.seg == 4) launch_pgemm_seg<false, 4>(st, plan, P, c->num_cu); else launch_pgemm_seg<false, 1>(st, plan, P, c->num_cu);
   } else {
     // (matrices off 16 bytes)  at most one 128-row tile per compute unit: 64-row tiles, as long as the rows need more than one
     GemmSegs segs{};
@@ -800,7 +804,7 @@ int launch_gemm_hl_gu(first_ctx* c, hipStream_t st, const bf16* Ah, const bf16* 
     PgArgs P = pg_args(c, plan, Ah, Al, M, K, 0);
     P.nseg = 1; P.seg[0] = PgSeg{reinterpret_cast<const bf16*>(Wg), nullptr, F, plan.gn}; P.Wu = reinterpret_cast<const bf16*>(Wu);
     P.zh = zh; P.zl = zl;
-    launch_pgemm_seg<true, 1>(st, plan, P);
+    launch_pgemm_seg<true, 1>(st, plan, P, c->num_cu);
   } else {
     hipLaunchKernelGGL(k_gemm_nt_bf16_hl_gu, dim3((F + GB_N / 2 - 1) / (GB_N / 2), (M + GB_M - 1) / GB_M), dim3(WG), 0, st, Ah, Al,
                        reinterpret_cast<const bf16*>(Wg), reinterpret_cast<const bf16*>(Wu), zh, zl, M, F, K);

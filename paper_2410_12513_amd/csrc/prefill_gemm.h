@@ -254,9 +254,17 @@ __global__ void __launch_bounds__(WGM * WGN * 64, 2) k_pgemm(PgArgs P) {
   // read as zeros and are not written, without a branch per element.
   // D layout of the 32x32 MFMA: lane -> column (lane & 31); register r -> row 8 (r / 4) + 4 (lane / 32) + r % 4
   const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(uni(C + (size_t)m0 * N), (short)0, rowsA * N * 4, 0x00020000);
+  // (a select per column, none per element: the compiler makes branches of those, with a wait for all loads in each)
+  uint32_t colb[JN];
+#pragma unroll
+  for (int j = 0; j < JN; ++j) {
+    const int col = n0 + wn + j * 32 + lr;
+    colb[j] = (uint32_t)(wm + 4 * lg) * N * 4 + (col < N ? col * 4u : 0x40000000u);   // (a tile's rows are at most 2^30 bytes)
+  }
   auto at = [&](int i, int j, int r) __attribute__((always_inline)) {
-    const int col = n0 + wn + j * 32 + lr, row = wm + i * 32 + 8 * (r >> 2) + 4 * lg + (r & 3);
-    return col < N ? (row * N + col) * 4 : 0x7ffffffc;
+    uint32_t b = colb[j];
+    asm volatile("" : "+v"(b));                // (formed where it is used: kept from a load to its store, the offsets take 64 registers)
+    return (int)(b + (uint32_t)(i * 32 + 8 * (r >> 2) + (r & 3)) * N * 4);
   };
   if constexpr (SPLIT && SEG > 1) {
     // Slices of K (two or four): every workgroup stores its partial tile (accumulator order, 16 bytes a lane, write-through),
