@@ -27,7 +27,9 @@ using namespace first;
 // the process ends.  Host code never uses the array's name as an address: g_scratch_ptr[device] is what
 // hipGetSymbolAddress returned with that device current.
 constexpr long long STATIC_SCRATCH_CANDS = 131072;           // 1 MiB of {logit, index} pairs
+constexpr int STATIC_SCRATCH_CHUNK = 2048;
 constexpr int STATIC_SCRATCH_MAX_DEV = 64;
+static_assert(SMP_PART >= STATIC_SCRATCH_CHUNK, "the lists of a call that is not refused fit");
 static __device__ __align__(256) unsigned char scratch[STATIC_SCRATCH_CANDS * 8];
 static void* g_scratch_ptr[STATIC_SCRATCH_MAX_DEV] = {};
 static std::mutex g_scratch_mutex;
@@ -73,7 +75,7 @@ struct first_ctx {
   float* d_bg_part = nullptr;             // k_bgemv_g: [workgroups][16 slots][128 rows] partial sums of the K-slices
   unsigned* d_bg_cnt = nullptr;           //            arrival counters per tile group (zero between launches)
   size_t bg_part_floats = 0, bg_cnt_n = 0;
-  Cand* d_topk_part = nullptr;            // [max_batch][chunks][SMP_KMAX] per-chunk candidates of first_sample_top_k
+  Cand* d_topk_part = nullptr;            // [max_batch][parts][SMP_KMAX] candidates of parts of long rows (first_sample_top_k)
   float* d_logits_own = nullptr;          // [max_batch][V] logits of a sampled step whose caller wants none
   Cand* d_step_cands = nullptr;           // [workgroups][SMP_KMAX] per-workgroup candidates of a sampled step of the persistent kernel
   float2* d_rope_cs = nullptr;
@@ -660,6 +662,21 @@ int launch_gemm(first_ctx* c, hipStream_t st, int dtype, const void* A, const vo
   return FIRST_OK;
 }
 
+// The top-k draw on n_seq rows of logits: one workgroup a row, or lists of parts of the row and a second launch that merges them
+// (part: room for n_seq * ceil(vocab / SMP_PART) * k candidates).  Parts are twice as long where there would be more of them than
+// run at a time (two on each of 256 compute units).
+void launch_sample(hipStream_t st, const float* logits, int n_seq, int vocab, const float* uniforms, float temperature, int k, Cand* part,
+                   int* token_out, int* candidates_out) {
+  if (vocab <= SMP_ROW_MAX) {
+    hipLaunchKernelGGL(k_topk<true>, dim3(1, n_seq), dim3(SMP_THREADS), 0, st, logits, vocab, vocab, k, temperature, uniforms, part, token_out, candidates_out);
+    return;
+  }
+  auto parts = [&](int len) { return (vocab - 1) / len + 1; };
+  const int len = (long long)n_seq * parts(SMP_PART) > 512 ? 2 * SMP_PART : SMP_PART;
+  hipLaunchKernelGGL(k_topk<false>, dim3(parts(len), n_seq), dim3(SMP_THREADS), 0, st, logits, vocab, len, k, temperature, uniforms, part, token_out, candidates_out);
+  hipLaunchKernelGGL(k_topk_draw, dim3(n_seq), dim3(SMP_THREADS), 0, st, part, parts(len) * k, k, temperature, uniforms, token_out, candidates_out);
+}
+
 // Tile and number of K slices of a k_pgemm launch.  The estimate (in us) is a fixed cost + K steps of 64 times the time of a step, summed
 // over the rounds the grid takes on the chip; a step of the last round takes longer the more compute units share memory and power.
 // Fitted to a sweep over M = 16 .. 6000 and the projections of the 8B, 3B and 1B geometries with weights that no cache holds (within
@@ -1200,7 +1217,7 @@ int first_create(const first_model_desc* desc, const first_weights* w, void* hip
     FIRST_BGG_ATTR(BG_QKV) FIRST_BGG_ATTR(BG_O) FIRST_BGG_ATTR(BG_DN) FIRST_BGG_ATTR(BG_GU)
 #undef FIRST_BGG_ATTR
   }
-  A(dev_alloc(c, &c->d_topk_part, (size_t)B * ((d.vocab + SMP_CHUNK - 1) / SMP_CHUNK) * SMP_KMAX));
+  A(dev_alloc(c, &c->d_topk_part, (size_t)B * ((d.vocab - 1) / SMP_PART + 1) * SMP_KMAX));
   A(dev_alloc(c, &c->d_step_cands, (size_t)c->num_cu * SMP_KMAX));
   A(dev_alloc(c, &c->d_logits_own, (size_t)B * d.vocab));
   A(dev_alloc(c, &c->x_h, (size_t)B * d.d_model)); A(dev_alloc(c, &c->x_qkv, (size_t)B * (c->nq + 2 * c->nkv)));
@@ -1403,12 +1420,9 @@ int decode_step_impl(first_ctx* c, const int32_t* last_tokens, float* logits_out
     else if (batched) enqueue_decode_batched(c, last_tokens, logits_out, token_out, S);
     else if (bf) enqueue_decode_ops<bf16>(c, last_tokens, logits_out, token_out, S);
     else enqueue_decode_ops<float>(c, last_tokens, logits_out, token_out, S);
-    if (smp && !fused) {
-      const int chunks = (c->d.vocab + SMP_CHUNK - 1) / SMP_CHUNK;
-      hipLaunchKernelGGL(k_topk_part, dim3(chunks, c->B), dim3(SMP_THREADS), 0, c->stream, logits_out, c->d.vocab, smp->top_k, c->d_topk_part);
-      hipLaunchKernelGGL(k_topk_sample, dim3(c->B), dim3(SMP_THREADS), 0, c->stream, c->d_topk_part, chunks * smp->top_k, smp->top_k,
-                         smp->temperature, smp->uniforms, token_out, smp->candidates_out);
-    }
+    if (smp && !fused)
+      launch_sample(c->stream, logits_out, c->B, c->d.vocab, smp->uniforms, smp->temperature, smp->top_k, c->d_topk_part, token_out,
+                    smp->candidates_out);
   };
   if (!c->use_graph) {
     enqueue();
@@ -1483,10 +1497,7 @@ int first_sample_top_k(first_ctx* c, const float* logits, const float* uniforms,
   if (!(temperature > 0.f) || !std::isfinite(temperature)) return fail(c, FIRST_ERR_ARG, "first_sample_top_k: temperature must be positive");
   if (top_k < 1 || top_k > SMP_KMAX) return fail(c, FIRST_ERR_ARG, "first_sample_top_k: top_k must be in 1..64");
   if (c->B < 1) return fail(c, FIRST_ERR_STATE, "first_sample_top_k: no live sequence");
-  const int chunks = (c->d.vocab + SMP_CHUNK - 1) / SMP_CHUNK;
-  hipLaunchKernelGGL(k_topk_part, dim3(chunks, c->B), dim3(SMP_THREADS), 0, c->stream, logits, c->d.vocab, top_k, c->d_topk_part);
-  hipLaunchKernelGGL(k_topk_sample, dim3(c->B), dim3(SMP_THREADS), 0, c->stream, c->d_topk_part, chunks * top_k, top_k,
-                     temperature, uniforms, token_out, candidates_out);
+  launch_sample(c->stream, logits, c->B, c->d.vocab, uniforms, temperature, top_k, c->d_topk_part, token_out, candidates_out);
   HIPCHK(c, hipGetLastError());
   return FIRST_OK;
 }
@@ -1498,7 +1509,7 @@ int first_sample_top_k_static(void* hip_stream, const float* logits, int32_t n_s
   if (!(temperature > 0.f) || !std::isfinite(temperature)) return bad(FIRST_ERR_ARG, "first_sample_top_k_static: temperature must be positive");
   if (top_k < 1 || top_k > SMP_KMAX) return bad(FIRST_ERR_ARG, "first_sample_top_k_static: top_k must be in 1..64");
   if (n_seq < 1 || vocab < 1) return bad(FIRST_ERR_ARG, "first_sample_top_k_static: n_seq and vocab must be positive");
-  const long long chunks = ((long long)vocab + SMP_CHUNK - 1) / SMP_CHUNK;
+  const long long chunks = ((long long)vocab + STATIC_SCRATCH_CHUNK - 1) / STATIC_SCRATCH_CHUNK;   // (the limit that the header states; parts are longer)
   if ((long long)n_seq * chunks * top_k > STATIC_SCRATCH_CANDS || chunks > 65535 || n_seq > 65535)
     return bad(FIRST_ERR_CAPACITY, "first_sample_top_k_static: n_seq * ceil(vocab / 2048) * top_k exceeds the 131072 candidates "
                                    "of the static scratch array");
@@ -1521,9 +1532,7 @@ int first_sample_top_k_static(void* hip_stream, const float* logits, int32_t n_s
   }
   hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
   // every candidate slot stage 2 reads is written by stage 1 of the same call: nothing to clear
-  hipLaunchKernelGGL(k_topk_part, dim3((unsigned)chunks, n_seq), dim3(SMP_THREADS), 0, st, logits, vocab, top_k, part);
-  hipLaunchKernelGGL(k_topk_sample, dim3(n_seq), dim3(SMP_THREADS), 0, st, part, (int)chunks * top_k, top_k, temperature, uniforms,
-                     token_out, candidates_out);
+  launch_sample(st, logits, n_seq, vocab, uniforms, temperature, top_k, part, token_out, candidates_out);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) {
     g_create_error = std::string("first_sample_top_k_static: ") + hipGetErrorString(e);

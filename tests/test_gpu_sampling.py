@@ -184,3 +184,36 @@ def test_sampled_step_on_the_other_paths_and_its_refusals():
         assert e.value.code == -1
     assert ca.seq_len(0) == before
     ca.close(); cb.close()
+
+
+@pytest.mark.parametrize("V,k", [(1, 1), (3, 5), (6, 4), (1023, 64), (4097, 10), (16387, 64), (65536, 1), (65537, 10), (128256, 10), (128256, 1)])
+def test_candidates_of_awkward_rows(V, k):
+    """Ties, infinities, NaN (no candidates) and orders that put the largest logits into few or all of the groups that a row is
+    looked through by; rows that start off 16 bytes; the longest row of the one-workgroup kernel and the shortest in parts."""
+    import paper_2410_12513_amd as P
+    rng, at = np.random.default_rng(V + k), np.arange(V)
+    plain = rng.normal(size=V).astype(np.float32)
+    few = np.full(V, -np.inf, np.float32)
+    few[rng.integers(0, V, 3)] = 1.5
+    lone = np.full(V, np.nan, np.float32)
+    lone[rng.integers(0, V, 5)] = -2.0
+    odd = plain.copy()
+    odd[::3], odd[1::5], odd[V // 2] = 0.0, -0.0, np.inf
+    rows = [plain, np.full(V, 7.0, np.float32), few, lone, np.where(at % 4096 < 256, plain, np.float32(np.nan)),
+            at.astype(np.float32), -at.astype(np.float32), np.where(at % 4096 < 64, np.float32(9.0), plain), odd]
+    lg = np.stack(rows)
+    n = len(rows)
+    tok = torch.full((n,), -7, dtype=torch.int32, device="cuda")
+    cand = torch.full((n, k), -7, dtype=torch.int32, device="cuda")
+    P.sample_top_k_static(torch.from_numpy(lg).cuda(), torch.zeros(n, device="cuda"), 0.8, k, tok, cand)
+    torch.cuda.synchronize()
+    for row, t, got in zip(rows, tok.tolist(), cand.cpu().numpy()):
+        live = at[~np.isnan(row)]
+        want = live[np.lexsort((live, -(row[live].astype(np.float64))))][:k]
+        assert got.tolist() == want.tolist() + [-1] * (k - len(want))
+        if len(want) == 0:
+            assert t == 0
+        elif np.isfinite(row[want[0]]):
+            assert t == want[0]              # u = 0: the first candidate with a weight
+        else:
+            assert t in want
