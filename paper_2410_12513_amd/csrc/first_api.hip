@@ -969,21 +969,23 @@ int prefill_group(first_ctx* c, int b0, int n, const int* ids, float* hidden_out
   return FIRST_OK;
 }
 
-// First-token logits and tokens of sequences 0 .. B - 1 from their residual slots.  One sequence: the decode head.  More: one
-// pass over the LM head for up to eight of them (as many as have room in LDS), argmax over the logits.
-constexpr size_t HEAD_ROWS_LDS = 128 * 1024;
+// First-token logits and tokens of sequences 0 .. B - 1 from their residual slots.  One pass over the LM head for up to eight of
+// them (as many as have room in LDS), argmax over the logits: three launches.  One sequence with a small LM head: the decode head, a
+// single launch at 4.1 TB/s; 128256 x 4096 (1.05 GB) takes it 258 us, the three 178 + 16 + 7, 24000 x 4096 (197 MB) some 50 us against 45.
+constexpr size_t HEAD_ROWS_LDS = 128 * 1024, HEAD_ROWS_FROM = (size_t)160 << 20;
 template <typename WT, int NS>
 void launch_head_rows(first_ctx* c, DecParams p, int b0, int n) {
   const size_t lds = (size_t)NS * c->d.d_model * sizeof(float);
   const int need = (c->d.vocab + 4 * HR_WAVES - 1) / (4 * HR_WAVES);
-  hipLaunchKernelGGL((k_head_rows<WT, NS>), dim3(std::min(need, c->num_cu)), dim3(HR_THREADS), lds, c->stream, p,
+  hipLaunchKernelGGL((k_head_rows<WT, NS>), dim3(std::min(need, NS == 1 ? 2 * c->num_cu : c->num_cu)), dim3(HR_THREADS), lds, c->stream, p,
                      reinterpret_cast<const float*>(c->p_x), b0, n);
 }
 template <typename WT>
 int enqueue_first_tokens(first_ctx* c, int B, float* logits_out, int* token_out) {
   DecParams p = base_params(c, 0, 1);
   const int fit = (int)(HEAD_ROWS_LDS / sizeof(float) / c->d.d_model);
-  if (B == 1 || fit < 2) {
+  const bool one = B == 1 && (size_t)c->d.vocab * c->d.d_model * sizeof(WT) < HEAD_ROWS_FROM;
+  if (one || fit < 2) {
     for (int b = 0; b < B; ++b) { p.b = b; enqueue_head<WT>(c, p, logits_out, token_out, 0); }
     HIPCHK(c, hipGetLastError());
     return FIRST_OK;
@@ -992,7 +994,8 @@ int enqueue_first_tokens(first_ctx* c, int B, float* logits_out, int* token_out)
   hipLaunchKernelGGL(k_head_norm<WT>, dim3(B), dim3(WG), ((size_t)c->d.d_model + WAVES) * sizeof(float), c->stream, p, reinterpret_cast<float*>(c->p_x));
   for (int b = 0; b < B;) {
     const int n = std::min(B - b, fit >= 8 ? 8 : fit >= 4 ? 4 : 2);
-    if (n > 4) launch_head_rows<WT, 8>(c, p, b, n);
+    if (B == 1) launch_head_rows<WT, 1>(c, p, b, n);
+    else if (n > 4) launch_head_rows<WT, 8>(c, p, b, n);
     else if (n > 2) launch_head_rows<WT, 4>(c, p, b, n);
     else launch_head_rows<WT, 2>(c, p, b, n);
     b += n;
@@ -1095,7 +1098,7 @@ hipError_t prefill_attributes() {
   if (e == hipSuccess) e = pg_set_lds<true, 1>();
   for (const void* fn : {reinterpret_cast<const void*>(&k_attn_prompt<128, 4, 1>), reinterpret_cast<const void*>(&k_attn_prompt<128, 2, 2>)})
     if (e == hipSuccess) e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * FA_TILE * 128 * 2);
-  for (const void* fn : {reinterpret_cast<const void*>(&k_head_rows<bf16, 2>), reinterpret_cast<const void*>(&k_head_rows<bf16, 4>),
+  for (const void* fn : {reinterpret_cast<const void*>(&k_head_rows<bf16, 1>), reinterpret_cast<const void*>(&k_head_rows<float, 1>), reinterpret_cast<const void*>(&k_head_rows<bf16, 2>), reinterpret_cast<const void*>(&k_head_rows<bf16, 4>),
                          reinterpret_cast<const void*>(&k_head_rows<bf16, 8>), reinterpret_cast<const void*>(&k_head_rows<float, 2>),
                          reinterpret_cast<const void*>(&k_head_rows<float, 4>), reinterpret_cast<const void*>(&k_head_rows<float, 8>)})
     if (e == hipSuccess) e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)HEAD_ROWS_LDS);
