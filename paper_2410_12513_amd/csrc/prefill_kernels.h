@@ -686,54 +686,70 @@ __global__ void __launch_bounds__(WG) k_gemm_nt_f32(const float* __restrict__ A,
 }
 
 // The same for shapes whose 64 x 64 tiles would leave most of the chip idle (short prompts of a small model): 16 TT x 16 TT
-// tiles, TT x TT outputs per thread, K in steps of 64 with the next step already on its way in registers.  Every output is
-// the same chain of multiply-adds over ascending k, so the bits are those of k_gemm_nt_f32.  Bound: latency (32 x 256 x 256:
-// 16 dependent steps and 4 workgroups there, 4 steps and 32 workgroups here; 17.6 -> 5.8 us, 32 x 256 x 688 49.4 -> 14.0 us,
-// kernel trace).
-template <int TT>
-__global__ void __launch_bounds__(WG) k_gemm_nt_f32_small(const float* __restrict__ A, const float* __restrict__ W, float* __restrict__ C,
-                                                          int M, int N, int K, int accumulate) {
-  constexpr int T = 16 * TT, BK = 64, PITCH = BK + 4;      // (rows 16 bytes apart modulo the banks)
-  __shared__ __align__(16) float sA[T * PITCH], sB[T * PITCH];
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4, m0 = blockIdx.y * T, n0 = blockIdx.x * T;
-  float4 ra[TT], rb[TT];
+// tiles, TT x TT outputs per thread, K in steps of 256 / TT with the next step already on its way in registers.  Up to three matrices
+// applied to the same rows, their column tiles one after the other; GU: matrix 0 is the gate, 1 up, and C[0] = SiLU(gate) * up.  Every
+// output is the same chain of multiply-adds over ascending k, so the bits are those of k_gemm_nt_f32 (and k_silu_mul).  Bound: latency, a
+// memory round trip per step (32 x 256 x 256: 17.6 us in 64 x 64 tiles, 5.8 in steps of 64, 5.2 now - Q, K and V together 5.2 -;
+// 32 x 256 x 688: 49.4, 14.0, 10.1; gate and up of 32 x 688 x 256 with SiLU 6.0 + 6.0 + 2.1 in three launches, 7.0 here; kernel trace).
+struct SmallSegs { const float* W[3]; float* C[3]; int N[3], blocks[3]; };
+template <int TT, bool GU>
+__global__ void __launch_bounds__(WG) k_gemm_nt_f32_small(const float* __restrict__ A, SmallSegs S, int M, int K, int accumulate) {
+  constexpr int T = 16 * TT, BK = 256 / TT, PITCH = BK + 4, NB = GU ? 2 : 1;      // (rows 16 bytes apart modulo the banks)
+  constexpr int PR = BK / 4, NP = T * PR / WG;             // pieces of 16 bytes in a row of a step; pieces of a thread
+  __shared__ __align__(16) float sA[T * PITCH], sB[NB][T * PITCH];
+  int bx = blockIdx.x, si = 0;
+  if (!GU)
+    while (si < 2 && bx >= S.blocks[si]) bx -= S.blocks[si++];
+  const float* const W = S.W[si];
+  float* const C = S.C[si];
+  const int N = S.N[si];
+  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4, m0 = blockIdx.y * T, n0 = bx * T;
+  float4 ra[NP], rb[NB][NP];
   auto fetch = [&](int k0) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < TT; ++u) {                         // 16 rows of 16 pieces per round
-      const int row = u * 16 + ty, k = k0 + tx * 4;
+    for (int u = 0; u < NP; ++u) {
+      const int row = (u * WG + tid) / PR, k = k0 + (u * WG + tid) % PR * 4;
       // (a piece that exists is loaded whatever happens and zeroed afterwards: choosing between a load and a constant makes
       // the compiler choose between two addresses, one of them in scratch memory)
       ra[u] = keep4(*reinterpret_cast<const float4*>(A + (size_t)min(m0 + row, M - 1) * K + min(k, K - 4)), k < K && m0 + row < M);
-      rb[u] = keep4(*reinterpret_cast<const float4*>(W + (size_t)min(n0 + row, N - 1) * K + min(k, K - 4)), k < K && n0 + row < N);
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+        rb[b][u] = keep4(*reinterpret_cast<const float4*>((b ? S.W[1] : W) + (size_t)min(n0 + row, N - 1) * K + min(k, K - 4)), k < K && n0 + row < N);
     }
   };
-  float acc[TT][TT] = {};
+  float acc[NB][TT][TT] = {};
   fetch(0);
   for (int k0 = 0; k0 < K; k0 += BK) {
     __syncthreads();
 #pragma unroll
-    for (int u = 0; u < TT; ++u) {
-      *reinterpret_cast<float4*>(sA + (u * 16 + ty) * PITCH + tx * 4) = ra[u];
-      *reinterpret_cast<float4*>(sB + (u * 16 + ty) * PITCH + tx * 4) = rb[u];
+    for (int u = 0; u < NP; ++u) {
+      const int at = (u * WG + tid) / PR * PITCH + (u * WG + tid) % PR * 4;
+      *reinterpret_cast<float4*>(sA + at) = ra[u];
+#pragma unroll
+      for (int b = 0; b < NB; ++b) *reinterpret_cast<float4*>(sB[b] + at) = rb[b][u];
     }
     __syncthreads();
     if (k0 + BK < K) fetch(k0 + BK);
     const int kn = min(BK, K - k0);                        // a multiple of 4: K is one of 8
 #pragma unroll 8
     for (int k = 0; k < kn; k += 4) {
-      float4 a[TT], b[TT];
+      float4 a[TT], w[NB][TT];
 #pragma unroll
       for (int u = 0; u < TT; ++u) {
         a[u] = *reinterpret_cast<const float4*>(sA + (u * 16 + ty) * PITCH + k);
-        b[u] = *reinterpret_cast<const float4*>(sB + (u * 16 + tx) * PITCH + k);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) w[b][u] = *reinterpret_cast<const float4*>(sB[b] + (u * 16 + tx) * PITCH + k);
       }
 #pragma unroll
-      for (int i = 0; i < TT; ++i)
+      for (int b = 0; b < NB; ++b)
 #pragma unroll
-        for (int j = 0; j < TT; ++j) {
-          acc[i][j] = fmaf(a[i].x, b[j].x, acc[i][j]); acc[i][j] = fmaf(a[i].y, b[j].y, acc[i][j]);
-          acc[i][j] = fmaf(a[i].z, b[j].z, acc[i][j]); acc[i][j] = fmaf(a[i].w, b[j].w, acc[i][j]);
-        }
+        for (int i = 0; i < TT; ++i)
+#pragma unroll
+          for (int j = 0; j < TT; ++j) {
+            float& t = acc[b][i][j];
+            t = fmaf(a[i].x, w[b][j].x, t); t = fmaf(a[i].y, w[b][j].y, t);
+            t = fmaf(a[i].z, w[b][j].z, t); t = fmaf(a[i].w, w[b][j].w, t);
+          }
     }
   }
 #pragma unroll
@@ -743,7 +759,8 @@ __global__ void __launch_bounds__(WG) k_gemm_nt_f32_small(const float* __restric
       const int row = m0 + i * 16 + ty, col = n0 + j * 16 + tx;
       if (row < M && col < N) {
         float* c = C + (size_t)row * N + col;
-        *c = accumulate ? *c + acc[i][j] : acc[i][j];
+        if (GU) *c = siluf(acc[0][i][j]) * acc[NB - 1][i][j];
+        else *c = accumulate ? *c + acc[0][i][j] : acc[0][i][j];
       }
     }
 }
