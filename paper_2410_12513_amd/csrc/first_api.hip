@@ -14,6 +14,7 @@
 #include "decode_kernels.h"
 #include "prefill_kernels.h"
 #include "step_kernel.h"
+#include "small_step.h"
 #include "prefill_gemm.h"
 #include "prefill_attn.h"
 #include "decode_batch_kernels.h"
@@ -132,6 +133,10 @@ struct first_ctx {
   unsigned long long* d_tdbg = nullptr;   // step-kernel timestamps (FIRST_OPT_STEP_TIMING)
   int step_timing = 0;
   bool step_ok = false;        // geometry fits the persistent kernel
+  // whole step of a small fp32 model as one kernel a sequence: workgroups (0: does not fit), its exchange and its last epoch
+  int small_wgs = 0;
+  ss_word* d_small = nullptr;
+  unsigned* d_small_epoch = nullptr;
   bool zperm = false;          // ... and every layer has its column-permuted copy of the down-projection matrix
   size_t step_lds = 0;
   // options and graph cache
@@ -200,6 +205,17 @@ hipError_t reset_tagged_exchange(first_ctx* c) {
   if (e == hipSuccess) e = hipMemset(c->d_tagstate, 0, Bm * 8 * sizeof(int));
   if (e == hipSuccess) e = hipMemset(c->d_done, 0, (size_t)c->num_cu * sizeof(unsigned));
   return e;
+}
+
+// Words of the small-model kernel's exchange: residual, projections, attention, MLP activation, candidates.
+size_t small_exchange_words(const first_ctx* c) {
+  return (size_t)c->d.d_model + (c->nq + 2 * c->nkv) + c->nq + c->d.d_ffn + 2 * c->small_wgs;
+}
+// (no word carries an epoch that a launch after epoch 0 waits for)
+hipError_t reset_small_exchange(first_ctx* c) {
+  if (!c->small_wgs) return hipSuccess;
+  const hipError_t e = hipMemset(c->d_small, 0, small_exchange_words(c) * sizeof(ss_word));
+  return e == hipSuccess ? hipMemset(c->d_small_epoch, 0, sizeof(unsigned)) : e;
 }
 
 size_t kv_slice_bytes(const first_ctx* c) { return (size_t)c->n_pages * c->page_elems * c->elem; }
@@ -276,6 +292,7 @@ int check_step_error(first_ctx* c, const char* who) {
   if (err & 1) {                                   // (the bits above bit 0: a poll limit set by FIRST_OPT_STEP_POLL_LIMIT, gone with the error)
     (void)hipMemset(c->d_err, 0, 4 * sizeof(int));
     (void)reset_tagged_exchange(c);
+    (void)reset_small_exchange(c);
     return fail(c, FIRST_ERR_HIP, std::string(who) + ": a wait between workgroups of the persistent decode kernel gave up; "
                                   "the tokens and logits of the steps since are not valid");
   }
@@ -614,6 +631,34 @@ void enqueue_decode_step_kernel(first_ctx* c, const int* tokens, float* logits, 
   }
   hipLaunchKernelGGL(reinterpret_cast<void (*)(StepParams)>(const_cast<void*>(step_kernel_fn(c))), dim3(c->num_cu), dim3(SK_THREADS),
                      c->step_lds, c->stream, P);
+}
+
+// Workgroups of the small-model kernel, 0 where it does not fit: full precision, vectors and rows that its waves hold, contexts short
+// enough for one workgroup a head, and a row of every mat-vec for every workgroup (its exchange counts on that).
+constexpr int SS_WGS = 64;
+int small_step_wgs(const first_ctx* c) {
+  const first_model_desc& d = c->d;
+  const int n = std::min(SS_WGS, c->num_cu), k = std::max({d.d_model, c->nq, d.d_ffn});
+  const bool fits = d.dtype == FIRST_DTYPE_FP32 && (d.head_dim == 64 || d.head_dim == 128) && d.d_model % 4 == 0 && d.d_ffn % 4 == 0 &&
+                    d.d_model <= SS_MAX_D && c->nq <= SS_MAX_F && d.d_ffn <= SS_MAX_F && d.vocab <= SS_MAX_V && d.max_seq_len <= SS_MAX_SEQ &&
+                    d.n_q_heads <= n &&
+                    std::min({d.d_model, c->nq + 2 * c->nkv, d.d_ffn}) >= n && k >= 2 * n &&
+                    (size_t)c->n_pages * c->page_elems < (size_t)1 << 31 &&
+                    ss_lds_floats(d.d_model, c->nq, d.d_ffn, d.head_dim) * sizeof(float) <= SS_MAX_LDS;
+  return fits ? n : 0;
+}
+size_t small_step_lds(const first_ctx* c) { return ss_lds_floats(c->d.d_model, c->nq, c->d.d_ffn, c->d.head_dim) * sizeof(float); }
+void enqueue_small_steps(first_ctx* c, const int* tokens, float* logits, int* token_out) {
+  for (int b = 0; b < c->B; ++b) {
+    SmallStep P{};
+    P.d = base_params(c, b, 1);
+    P.d.tokens = tokens; P.d.logits = logits; P.d.token_out = token_out; P.d.advance_len = 1;
+    P.layers = c->d_layers; P.kept = c->d_kept; P.n_kept = c->d_nkept; P.L = c->d.n_layers;
+    P.xh = c->d_small; P.xqkv = P.xh + c->d.d_model; P.xattn = P.xqkv + c->nq + 2 * c->nkv; P.xz = P.xattn + c->nq; P.xcand = P.xz + c->d.d_ffn;
+    P.epoch = c->d_small_epoch; P.err = c->d_err;
+    auto kernel = c->d.head_dim == 128 ? &k_small_step<128> : &k_small_step<64>;
+    hipLaunchKernelGGL(kernel, dim3(c->small_wgs), dim3(SS_THREADS), small_step_lds(c), c->stream, P);
+  }
 }
 
 // Does the geometry fit the persistent kernel's static work split?
@@ -1239,6 +1284,8 @@ int first_create(const first_model_desc* desc, const first_weights* w, void* hip
   A(dev_alloc(c, &c->x_attn, (size_t)B * c->nq)); A(dev_alloc(c, &c->x_z, (size_t)B * d.d_ffn));
   A(dev_alloc(c, &c->x_part, sk_part_index(d.n_q_heads, d.head_dim, B, 0, 0)));
   A(dev_alloc(c, &c->d_tagstate, (size_t)B * 8));
+  c->small_wgs = small_step_wgs(c);
+  if (c->small_wgs) { A(dev_alloc(c, &c->d_small, small_exchange_words(c))); A(dev_alloc(c, &c->d_small_epoch, 1)); }
   A(dev_alloc(c, &c->d_layers, L)); A(dev_alloc(c, &c->d_done, (size_t)c->num_cu)); A(dev_alloc(c, &c->d_err, 4));
   A(dev_alloc(c, &c->d_tdbg, (size_t)(4 * L + 1) * SK_TSLOTS));
   if (d.dtype == FIRST_DTYPE_BF16) {
@@ -1270,6 +1317,10 @@ int first_create(const first_model_desc* desc, const first_weights* w, void* hip
       int per_cu = 0;
       if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, SK_THREADS, c->step_lds);
       if (e == hipSuccess && per_cu < 1) c->step_ok = false;   // grid would not be co-resident
+    }
+    if (e == hipSuccess && c->small_wgs) {
+      e = reset_small_exchange(c);
+      if (e == hipSuccess) e = upload_layer_table(c);
     }
     if (e == hipSuccess && B > 1 && d.dtype == FIRST_DTYPE_BF16 && d_batch_fits(c)) e = make_tiled_copies(c);
     if (e == hipSuccess) e = hipMemset(c->d_mask, 0, (size_t)B * L);
@@ -1351,7 +1402,7 @@ int first_prefill_route(first_ctx* c, int32_t B, const int32_t* ids, const int32
   if (mask_out) HIPCHK(c, hipMemcpyAsync(mask_out, c->d_mask, (size_t)B * L, hipMemcpyDeviceToDevice, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
   for (int b = 0; b < B; ++b) c->hmask[b].assign(hm.begin() + (size_t)b * L, hm.begin() + (size_t)(b + 1) * L);
-  if (c->kv_elide && c->step_ok) HIPCHK(c, upload_layer_table(c));   // the layers' slices are new
+  if (c->kv_elide && (c->step_ok || c->small_wgs)) HIPCHK(c, upload_layer_table(c));   // the layers' slices are new
   return FIRST_OK;
 }
 
@@ -1401,6 +1452,7 @@ int decode_step_impl(first_ctx* c, const int32_t* last_tokens, float* logits_out
   S = std::max(1, std::min(S, 32));
   const bool bf = c->d.dtype == FIRST_DTYPE_BF16;
   const bool persistent = c->step_ok && c->B == 1 && c->decode_path != 0;
+  const bool small = c->small_wgs > 0 && c->decode_path != 0;
   if (c->decode_path == 1 && !persistent)
     return fail(c, FIRST_ERR_STATE, "first_decode_step: the persistent kernel needs a bf16 model whose widths are "
                                     "multiples of 256, 16-token pages and exactly one live sequence");
@@ -1433,6 +1485,7 @@ int decode_step_impl(first_ctx* c, const int32_t* last_tokens, float* logits_out
   auto enqueue = [&]() {
     if (persistent) enqueue_decode_step_kernel(c, last_tokens, logits_out, token_out, fused ? smp : nullptr);
     else if (batched) enqueue_decode_batched(c, last_tokens, logits_out, token_out, S);
+    else if (small) enqueue_small_steps(c, last_tokens, logits_out, token_out);
     else if (bf) enqueue_decode_ops<bf16>(c, last_tokens, logits_out, token_out, S);
     else enqueue_decode_ops<float>(c, last_tokens, logits_out, token_out, S);
     if (smp && !fused)
@@ -1443,14 +1496,14 @@ int decode_step_impl(first_ctx* c, const int32_t* last_tokens, float* logits_out
     enqueue();
     HIPCHK(c, hipGetLastError());
   } else {
-    // the persistent kernel reads the kept list from the device: one graph whatever the mask
-    const int kind = persistent ? -1 : batched ? S + 1000 : S;
+    // the whole-step kernels read the kept list from the device: one graph whatever the mask
+    const int kind = persistent ? -1 : small ? -1 - c->B : batched ? S + 1000 : S;
     std::string key(reinterpret_cast<const char*>(&kind), sizeof(kind));
     key.append(reinterpret_cast<const char*>(&last_tokens), sizeof(void*));
     key.append(reinterpret_cast<const char*>(&logits_out), sizeof(void*));
     key.append(reinterpret_cast<const char*>(&token_out), sizeof(void*));
     if (smp) key.append(reinterpret_cast<const char*>(smp), sizeof(*smp));      // (pointers and values are part of the captured arguments)
-    if (!persistent)
+    if (!persistent && !small)
       for (int b = 0; b < c->B; ++b) key.append(reinterpret_cast<const char*>(c->hmask[b].data()), c->hmask[b].size());
     auto it = c->graphs.find(key);
     if (it == c->graphs.end()) {

@@ -1,0 +1,116 @@
+"""The whole-step kernel of small full-precision models against the oracle and against the per-op kernels: row lengths of one, two, four
+and more pieces, rows that do not divide among the waves, head dimensions and groups, contexts at the edges of the key tiles and of the
+waves' rounds, pages of other sizes, masks, batches, and a wait that gives up."""
+import pytest
+import torch
+
+from oracle import first_oracle as O
+from synth import make_prompt
+from synth.generators import ModelDesc
+from tests.gpu_util import build, logits_close, top2_gap
+
+pytestmark = pytest.mark.gpu
+torch.set_grad_enabled(False)
+
+HD64 = ModelDesc(3, 256, 4, 2, 64, 696, 1001, dtype="fp32")
+HD128 = ModelDesc(3, 512, 4, 1, 128, 1032, 500, dtype="fp32")
+WIDE = ModelDesc(3, 512, 8, 8, 64, 2048, 77, dtype="fp32")
+NARROW = ModelDesc(3, 72, 2, 1, 64, 96, 67, dtype="fp32")
+OPT_DECODE_PATH = 3
+
+
+def _prefilled(desc, prompts, seed, page=16, room=16, path=-1, max_seq_len=None):
+    n = [p.numel() for p in prompts]
+    _, w, r, ctx = build(None, seed, desc=desc, max_batch=len(prompts), max_seq_len=max_seq_len or max(n) + room, page=page)
+    ctx.set_option(OPT_DECODE_PATH, path)
+    tok = torch.zeros(len(prompts), dtype=torch.int32, device="cuda")
+    ctx.prefill_route(torch.cat(prompts).cuda(), n, token=tok)
+    return w, r, ctx, tok
+
+
+@pytest.mark.parametrize("desc,n,mask,page,max_seq_len", [
+    (HD64, 1, [1, 1, 1], 16, None), (HD64, 30, [1, 0, 1], 16, None), (HD64, 127, [1, 1, 1], 16, None), (HD64, 290, [0, 1, 1], 24, None),
+    (HD128, 14, [1, 1, 1], 16, None), (HD128, 63, [1, 0, 1], 8, None), (HD128, 140, [1, 1, 0], 16, None), (WIDE, 40, [1, 1, 1], 16, None),
+    (NARROW, 33, [1, 1, 1], 16, None), (HD64, 20, [0, 0, 0], 16, None), (HD64, 20, [1, 1, 1], 16, 2056)])
+def test_steps_match_the_oracle_and_the_per_op_kernels(desc, n, mask, page, max_seq_len):
+    prompt = make_prompt(desc.vocab, n, 91)
+    w, r, ctx, tok = _prefilled(desc, [prompt], 91, page, max_seq_len=max_seq_len)
+    _, _, ops, _ = _prefilled(desc, [prompt], 91, page, path=0)
+    st = O.prefill_route(desc, w, r, prompt)
+    assert int(tok[0]) == st.token or top2_gap(st.logits) < 4e-4
+    for c in (ctx, ops):
+        c.set_mask(0, mask)
+    st.set_mask(mask)
+    fed = torch.tensor([st.token], dtype=torch.int32, device="cuda")
+    lg, lo, out = torch.zeros(1, desc.vocab, device="cuda"), torch.zeros(1, desc.vocab, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+    for step in range(6):
+        ctx.decode_step(fed, lg if step != 2 else None, out)
+        ops.decode_step(fed, lo, out.clone())
+        ctx.sync(), ops.sync()
+        ref, ref_tok = O.decode_step(desc, w, st, int(fed[0]))
+        if step != 2:
+            ok, worst, rel = logits_close(lg[0], ref, "fp32")
+            assert ok, (step, worst, rel)
+            # the same products, other orders of fp32 sums: a few units in the last place of each of some thousand terms
+            assert float((lg - lo).norm() / lo.norm()) <= 1e-5
+        if top2_gap(ref) > 4e-4:
+            assert int(out[0]) == ref_tok
+        fed[0] = ref_tok
+    assert ctx.seq_len(0) == n + 6
+    h, ho = ctx.get_hidden(), ops.get_hidden()
+    assert torch.equal(h, ho) if not any(mask) else float((h - ho).norm() / ho.norm()) <= 1e-5
+    for i, keep in enumerate(mask):
+        for a, b in zip(ctx.kv_read(0, i, 0, n + 6 if keep else n), ops.kv_read(0, i, 0, n + 6 if keep else n)):
+            assert float((a - b).norm()) <= 1e-5 * float(b.norm())
+    ctx.close(), ops.close()
+
+
+def test_a_batch_has_the_bits_of_each_sequence_alone():
+    prompts = [make_prompt(HD64.vocab, n, 92 + n) for n in (9, 150, 40)]
+    masks = [[1, 0, 1], [1, 1, 1], [0, 1, 0]]
+    _, _, ctx, tok = _prefilled(HD64, prompts, 92)
+    lg = torch.zeros(3, HD64.vocab, device="cuda")
+    for b, m in enumerate(masks):
+        ctx.set_mask(b, m)
+    first, hist = tok.clone(), []
+    for _ in range(5):
+        ctx.decode_step(tok, lg, tok)
+        ctx.sync()
+        hist.append((tok.clone(), lg.clone()))
+    for b, (p, m) in enumerate(zip(prompts, masks)):
+        _, _, one, t = _prefilled(HD64, [p], 92, max_seq_len=166)
+        assert int(t[0]) == int(first[b])
+        one.set_mask(0, m)
+        l1 = torch.zeros(1, HD64.vocab, device="cuda")
+        for tokens, logits in hist:
+            one.decode_step(t, l1, t)
+            one.sync()
+            assert int(t[0]) == int(tokens[b]) and torch.equal(l1[0], logits[b])
+        one.close()
+    ctx.close()
+
+
+def test_a_wait_that_gives_up_ends_the_launch_and_is_reported_once():
+    """A poll limit of 0, set from the host: every first unsuccessful poll gives up and every workgroup leaves."""
+    import paper_2410_12513_amd as P
+    prompt = make_prompt(HD64.vocab, 50, 94)
+    outs = []
+    for provoke in (False, True):
+        _, _, ctx, tok = _prefilled(HD64, [prompt], 94)
+        if provoke:
+            ctx.set_option(10, 0)
+            ctx.decode_step(tok, None, tok.clone())
+            with pytest.raises(P.FirstError) as e:
+                ctx.sync()
+            assert e.value.code == -4 and "gave up" in str(e.value)
+            ctx.sync()
+            ctx.prefill_route(prompt.cuda(), [50], token=tok)
+        lg, hist = torch.zeros(1, HD64.vocab, device="cuda"), []
+        for _ in range(6):
+            ctx.decode_step(tok, lg, tok)
+            ctx.sync()
+            hist.append((int(tok[0]), lg.clone()))
+        outs.append(hist)
+        ctx.close()
+    for (ta, la), (tb, lb) in zip(*outs):
+        assert ta == tb and torch.equal(la, lb)
