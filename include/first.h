@@ -45,13 +45,15 @@ extern "C" {
 #define FIRST_DTYPE_BF16 1
 
 /* options for first_set_option */
-#define FIRST_OPT_USE_GRAPH     1  /* 1 (default): a decode step is a cached hipGraph (one per set of masks on the per-op and batched
-                                      paths; a single one on the persistent path, whose kernel reads the kept layers from
-                                      the device); 0: eager launches */
+#define FIRST_OPT_USE_GRAPH     1  /* 1 (default): a decode step of several launches is a cached hipGraph (one per set of masks on the
+                                      per-op and batched paths; one for all masks where a whole step is one kernel a sequence,
+                                      which reads the kept layers from the device), a step of one launch goes out directly;
+                                      0: eager launches */
 #define FIRST_OPT_ATTN_SPLITS   2  /* KV splits per (sequence, KV head) in decode attention; 0 = auto   */
 #define FIRST_OPT_DECODE_PATH   3  /* -1 (default): persistent whole-step kernel when the model fits it
-                                      (bf16, widths multiples of 256, one live sequence), else per-op
-                                      kernels; 0: always per-op kernels; 1: persistent kernel or error.
+                                      (bf16, widths multiples of 256, one live sequence), a whole-step kernel a sequence for
+                                      small fp32 models (widths up to 512 / 2048, contexts up to 2048), else per-op
+                                      kernels; 0: always per-op kernels; 1: persistent kernel (bf16) or error.
                                       When device memory allows, first_create gives the persistent kernel a copy of every
                                       layer's down-projection matrix with permuted columns (as much memory again as those
                                       matrices); the caller's matrices must then not change after first_create. */

@@ -678,6 +678,25 @@ bool step_kernel_fits(const first_ctx* c) {
   return sk_lds_floats(d.d_model, c->nq, d.d_ffn, c->G, d.head_dim) * sizeof(float) <= 150 * 1024;
 }
 
+// n fp32 matrices applied to the same rows in one launch of small tiles, where there are fewer 64 x 64 tiles than compute units: 32 x 32
+// tiles, or 16 x 16 ones while those do not fill the chip either.  GU: gate and up, SiLU(gate) * up to C[0].  False: more tiles than that.
+template <bool GU>
+bool launch_f32_small(hipStream_t st, const float* A, SmallSegs S, int n, int M, int K, int acc) {
+  auto tiles = [&](int t) {
+    long long sum = 0;
+    for (int i = 0; i < (GU ? 1 : n); ++i) sum += S.blocks[i] = (S.N[i] + t - 1) / t;
+    return sum;
+  };
+  const int cus = device_cus();
+  if (tiles(64) * (GU ? 2 : 1) * ((M + 63) / 64) >= cus) return false;
+  const bool wide = tiles(32) * ((M + 31) / 32) >= cus;
+  const int t = wide ? 32 : 16;
+  const dim3 grid((unsigned)tiles(t), (M + t - 1) / t);
+  if (wide) hipLaunchKernelGGL((k_gemm_nt_f32_small<2, GU>), grid, dim3(WG), 0, st, A, S, M, K, acc);
+  else hipLaunchKernelGGL((k_gemm_nt_f32_small<1, GU>), grid, dim3(WG), 0, st, A, S, M, K, acc);
+  return true;
+}
+
 // a_fp32: the activations are fp32 (prefill path); bf16 weights then use the split-precision
 // matrix-core kernel.
 int launch_gemm(first_ctx* c, hipStream_t st, int dtype, const void* A, const void* W, float* C, int M, int N,
@@ -716,25 +735,6 @@ void launch_sample(hipStream_t st, const float* logits, int n_seq, int vocab, co
 }
 
 // Tile and number of K slices of a k_pgemm launch.  The estimate (in us) is a fixed cost + K steps of 64 times the time of a step, summed
-// n fp32 matrices applied to the same rows in one launch of small tiles, where there are fewer 64 x 64 tiles than compute units: 32 x 32
-// tiles, or 16 x 16 ones while those do not fill the chip either.  GU: gate and up, SiLU(gate) * up to C[0].  False: more tiles than that.
-template <bool GU>
-bool launch_f32_small(hipStream_t st, const float* A, SmallSegs S, int n, int M, int K, int acc) {
-  auto tiles = [&](int t) {
-    long long sum = 0;
-    for (int i = 0; i < (GU ? 1 : n); ++i) sum += S.blocks[i] = (S.N[i] + t - 1) / t;
-    return sum;
-  };
-  const int cus = device_cus();
-  if (tiles(64) * (GU ? 2 : 1) * ((M + 63) / 64) >= cus) return false;
-  const bool wide = tiles(32) * ((M + 31) / 32) >= cus;
-  const int t = wide ? 32 : 16;
-  const dim3 grid((unsigned)tiles(t), (M + t - 1) / t);
-  if (wide) hipLaunchKernelGGL((k_gemm_nt_f32_small<2, GU>), grid, dim3(WG), 0, st, A, S, M, K, acc);
-  else hipLaunchKernelGGL((k_gemm_nt_f32_small<1, GU>), grid, dim3(WG), 0, st, A, S, M, K, acc);
-  return true;
-}
-
 // over the rounds the grid takes on the chip; a step of the last round takes longer the more compute units share memory and power.
 // Fitted to a sweep over M = 16 .. 6000 and the projections of the 8B, 3B and 1B geometries with weights that no cache holds (within
 // 0.4 % of the best of all choices on average, 12 % at worst).  What the numbers say, us with the next best tile in brackets:
@@ -964,7 +964,7 @@ int prefill_group(first_ctx* c, int b0, int n, const int* ids, float* hidden_out
                                    {GemmSeg{(const bf16*)l.wq, c->p_q, c->nq, 0}, GemmSeg{(const bf16*)l.wk, c->p_k, c->nkv, 0},
                                     GemmSeg{(const bf16*)l.wv, c->p_v, c->nkv, 0}})))
         return rc;
-    } else if (!launch_f32_small<true>(st, x, {{(const float*)l.wg, (const float*)l.wu}, {z}, {F}, {}}, 2, R, D, 0)) {
+    } else if (!launch_f32_small<false>(st, x, {{(const float*)l.wq, (const float*)l.wk, (const float*)l.wv}, {c->p_q, c->p_k, c->p_v}, {c->nq, c->nkv, c->nkv}, {}}, 3, R, D, 0)) {
       if ((rc = gemm(x, c->p_xh, c->p_xl, l.wq, c->p_q, c->nq, D, 0))) return rc;
       if ((rc = gemm(x, c->p_xh, c->p_xl, l.wk, c->p_k, c->nkv, D, 0))) return rc;
       if ((rc = gemm(x, c->p_xh, c->p_xl, l.wv, c->p_v, c->nkv, D, 0))) return rc;
@@ -1008,7 +1008,7 @@ int prefill_group(first_ctx* c, int b0, int n, const int* ids, float* hidden_out
     launch_rmsnorm(c, st, l.g_mlp, nullptr, nullptr, R, hl);
     if (hl) {        // SiLU(gate) * up in the GEMM's epilogue, written split for the down projection
       if ((rc = launch_gemm_hl_gu(c, st, c->p_xh, c->p_xl, l.wg, l.wu, c->p_zh, c->p_zl, R, F, D))) return rc;
-    } else if (!launch_f32_small<false>(st, x, {{(const float*)l.wq, (const float*)l.wk, (const float*)l.wv}, {c->p_q, c->p_k, c->p_v}, {c->nq, c->nkv, c->nkv}, {}}, 3, R, D, 0)) {
+    } else if (!launch_f32_small<true>(st, x, {{(const float*)l.wg, (const float*)l.wu}, {z}, {F}, {}}, 2, R, D, 0)) {
       if ((rc = gemm(x, c->p_xh, c->p_xl, l.wg, c->p_g, F, D, 0))) return rc;
       if ((rc = gemm(x, c->p_xh, c->p_xl, l.wu, c->p_u, F, D, 0))) return rc;
       const unsigned sm_grid = (unsigned)std::min<size_t>(((size_t)R * F + WG - 1) / WG, 65536);
@@ -1492,7 +1492,9 @@ int decode_step_impl(first_ctx* c, const int32_t* last_tokens, float* logits_out
       launch_sample(c->stream, logits_out, c->B, c->d.vocab, smp->uniforms, smp->temperature, smp->top_k, c->d_topk_part, token_out,
                     smp->candidates_out);
   };
-  if (!c->use_graph) {
+  // a step that is one launch goes out as one: 6.7 us between two of them, against 13 between replays of a graph with one node
+  const bool one_launch = (persistent && !(smp && !fused)) || (small && c->B == 1 && !smp);
+  if (!c->use_graph || one_launch) {
     enqueue();
     HIPCHK(c, hipGetLastError());
   } else {
