@@ -24,6 +24,14 @@ __device__ __forceinline__ uint16_t f2bf(float f) {
   return (uint16_t)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);
 }
 
+typedef __attribute__((__vector_size__(2 * sizeof(float)))) float float2v_t;
+typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2_t;
+// two fp32 -> two bf16 (nearest even) in one register, low half first
+__device__ __forceinline__ uint32_t pk_bf16(float a, float b) {
+  const float2v_t v = {a, b};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
+}
+
 __device__ __forceinline__ float to_f32(float x) { return x; }
 __device__ __forceinline__ float to_f32(bf16 x) { return bf2f(x.v); }
 template <typename T> __device__ __forceinline__ T from_f32(float x);

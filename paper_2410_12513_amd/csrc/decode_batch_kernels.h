@@ -213,18 +213,19 @@ __global__ void __launch_bounds__(AT_THREADS, 4) k_attn_tiles_b(BatchParams P) {
   sk_attention<HD, SK_WAVES, true>(SP, reinterpret_cast<bf16*>(p.kv_layer), S, blockIdx.y, blockIdx.x, nsplit, nullptr);
 }
 
-// Decode attention of (split, KV head, slot) for models with G = Hq / Hkv query heads per KV
-// head (G = 4 instantiated): k_attn_tiles_b lets every head wave fetch its own copy of each
+// Decode attention of (split, KV head, slot) for models with G = 2 .. 4 query heads per KV
+// head: k_attn_tiles_b lets every head wave fetch its own copy of each
 // 64-key tile and form scores and weighted values with scalar FMAs, which at long context is
 // bound by the vector ALUs and by G-fold traffic through the compute unit's memory pipeline.
 // Here a wave takes 16 keys (one cache page) at a time for ALL G heads and fetches them once,
 // straight into the registers that use them (three pages per wave in flight; see Stage): scores
-// = Q K^T on the matrix cores (16x16x32 bf16, Q split into high + low halves so that the product
-// with the stored bf16 keys is exact to 2^-16), the G heads' online softmax side by side in the
+// = Q K^T on the matrix cores (16x16x32 bf16, Q split into bf16 parts, see QP), the G heads' online softmax side by side in the
 // four 16-lane groups, weighted values with the value rows shared across the heads.  Between
 // the prologue and the merge no wave waits for another.  The 8 waves' partial results meet in
 // LDS; partial / count / merge across splits and the output format are those of
-// sk_attention<.., SPLIT_OUT>.  The host sizes the grid to about one workgroup per compute unit.
+// sk_attention<.., SPLIT_OUT>; a sequence that is not split writes its output at once (with the queries' conversion in
+// hardware and their request ahead of the page ids 6.5 us less a launch at 40 keys).  The host sizes the grid to about one workgroup per
+// compute unit.  Sixteen sequences of 4000 keys, us a layer less than k_attn_tiles_b: 3B heads 64, 1B heads 51.
 // (An earlier version relayed 64-key tiles through 128 KB of LDS with a workgroup barrier per
 // pair of tiles: 0.4 % slower steps at 16 k keys.)
 constexpr int AS_THREADS = SK_WAVES * 64;
@@ -253,7 +254,7 @@ __device__ __forceinline__ float row16_sum(float v) {
 
 template <int HD, int G>
 __global__ void __launch_bounds__(AS_THREADS) k_attn_mfma_b(BatchParams P) {
-  static_assert(HD == 128 && G == 4, "lane layouts below: 8 value dims per lane, one head per group of four score rows");
+  static_assert((HD == 128 || HD == 64) && G >= 2 && G <= 4, "lane layouts below: a head per group of four score rows");
   extern __shared__ __align__(16) float smem_f[];
   DecParams p = P.d;
   const bool listed = P.attn_nwork > 0;
@@ -263,7 +264,11 @@ __global__ void __launch_bounds__(AS_THREADS) k_attn_mfma_b(BatchParams P) {
   p.b = P.seqs.id[slot];
   constexpr int HALF = HD / 2;
   constexpr int KS = HD / 32;                           // MFMA k-steps over the head dimension
-  constexpr int DL = HD / 16;                           // value dims per lane: lane (sub, dc), dc = lane % 16
+  constexpr int DL = 8, LPR = HD / DL;                  // value dims per lane, lanes of a value row: lane (sub, dc), dc = lane % LPR
+  constexpr int SUBS = 64 / LPR, NV = 16 / SUBS;        // value rows per request, requests of a slice
+  // bf16 parts of the queries: two where scores always had 16 bits of them, three - all of an fp32 - for the geometries that
+  // k_attn_tiles_b used to serve with fp32 multiply-adds (the matrix cores have nothing else to do here)
+  constexpr int QP = HD == 128 && G == 4 ? 2 : 3;
   const int b = p.b, Pg = p.P, g = listed ? blockIdx.x : blockIdx.y;
   const int tid = threadIdx.x, wave = uni((int)(threadIdx.x >> 6)), lane = tid & 63;
   const int pos = uni(p.len[b]), nkeys = pos + 1, tiles = (nkeys + 63) >> 6;
@@ -293,14 +298,21 @@ __global__ void __launch_bounds__(AS_THREADS) k_attn_mfma_b(BatchParams P) {
   const bool owns_new = (pos >> 6) >= t_first && (pos >> 6) < t_last;
   const int last_page = pos / Pg;
   const int T1 = max(T, 1);                             // (a split without tiles still issues its requests, on a valid page)
+  // this step's q (G heads), k and v of the KV head, requested before the page ids that the first slices wait for
+  const int iq = min(tid, G * HALF - 1), hh = iq / HALF, dq = iq - hh * HALF;
+  const int dk = min(tid, HALF - 1), dv = min(tid, HD - 1);
+  const float q1 = qkv[(g * G + hh) * HD + dq], q2 = qkv[(g * G + hh) * HD + dq + HALF];
+  const float k1 = qkv[nq + g * HD + dk], k2 = qkv[nq + g * HD + dk + HALF];
+  const float vv = qkv[nq + nkv + g * HD + dv];
+  const float2 c_own = p.rope_cs[(size_t)b * HALF + min(tid, HALF - 1)];                 // made by k_embed_b
   for (int i = tid; i < min(T1 * 4, AS_PT); i += AS_THREADS) pt_lds[i] = pt[min(t_first * 4 + i, last_page)];
   lds_barrier();
 
   // A slice's keys and values straight into the registers that use them: for the scores lane (key = lane % 16, kq = lane / 16)
-  // holds dims 32 ks + 8 kq .. + 8 of its key (the B operand of MFMA k-step ks), for the weighted values lane (sub = lane / 16,
-  // dc = lane % 16) holds dims 8 dc .. + 8 of keys 4 i + sub - sixteen 64-byte pieces per key request, four whole rows per
-  // value request.  No wave needs another wave's keys, so nothing goes through LDS and the waves never wait for each other.
-  struct Stage { u32x4_t k[KS], v[4]; };
+  // holds dims 32 ks + 8 kq .. + 8 of its key (the B operand of MFMA k-step ks), for the weighted values lane (sub = lane / LPR,
+  // dc = lane % LPR) holds dims 8 dc .. + 8 of keys SUBS i + sub - sixteen 64-byte pieces per key request, four (HD = 64: eight) whole
+  // rows per value request.  No wave needs another wave's keys, so nothing goes through LDS and the waves never wait for each other.
+  struct Stage { u32x4_t k[KS], v[NV]; };
   Stage st0, st1, st2;                                  // three slices of this wave in flight
   auto issue = [&](Stage& st, int j) __attribute__((always_inline)) {
     const int jj = max(0, min(j, n_sl - 1));             // (past the split: a harmless reload of a valid page)
@@ -310,18 +322,11 @@ __global__ void __launch_bounds__(AS_THREADS) k_attn_mfma_b(BatchParams P) {
     for (int ks = 0; ks < KS; ++ks)
       st.k[ks] = *reinterpret_cast<const u32x4_t*>(base + (lane & 15) * HD + ks * 32 + ((lane >> 4) << 3));
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      st.v[i] = *reinterpret_cast<const u32x4_t*>(base + v_off + (4 * i + (lane >> 4)) * HD + (lane & 15) * DL);
+    for (int i = 0; i < NV; ++i)
+      st.v[i] = *reinterpret_cast<const u32x4_t*>(base + v_off + (SUBS * i + lane / LPR) * HD + (lane % LPR) * DL);
   };
 
-  // this step's q (G heads), k and v of the KV head (requested before the pages: loads return in order)
   {
-    const int iq = min(tid, G * HALF - 1), hh = iq / HALF, dq = iq - hh * HALF;
-    const int dk = min(tid, HALF - 1), dv = min(tid, HD - 1);
-    const float q1 = qkv[(g * G + hh) * HD + dq], q2 = qkv[(g * G + hh) * HD + dq + HALF];
-    const float k1 = qkv[nq + g * HD + dk], k2 = qkv[nq + g * HD + dk + HALF];
-    const float vv = qkv[nq + nkv + g * HD + dv];
-    const float2 c_own = p.rope_cs[(size_t)b * HALF + min(tid, HALF - 1)];               // made by k_embed_b
     issue(st0, wave);                                   // (a wave without slices reloads a valid page and ignores it)
     issue(st1, wave + SK_WAVES);
     issue(st2, wave + 2 * SK_WAVES);
@@ -352,24 +357,29 @@ __global__ void __launch_bounds__(AS_THREADS) k_attn_mfma_b(BatchParams P) {
   // A operand of the score MFMA: row m = lane % 16 holds query head m / 4, k = dims.  A lane's four result registers
   // are rows 4 (lane / 16) .. + 3, so the 16 lanes of group g = lane / 16 all hold the scores of head g (one key each):
   // the four heads' softmax steps run side by side in the four lane groups instead of one after the other in every lane.
-  bf16x8_t qh[KS], ql[KS];
+  bf16x8_t qp[QP][KS];
   {
     const int hm = (lane & 15) >> 2;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-      union { unsigned short u[8]; bf16x8_t v; } H, L;
+      union { uint32_t u[4]; bf16x8_t v; } part[QP];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float x = hm < G ? qs[hm * HD + ks * 32 + ((lane >> 4) << 3) + e] : 0.f;
-        const bf16 h = from_f32<bf16>(x);
-        H.u[e] = h.v; L.u[e] = from_f32<bf16>(x - to_f32(h)).v;
+      for (int e = 0; e < 4; ++e) {
+        const float* x = qs + min(hm, G - 1) * HD + ks * 32 + ((lane >> 4) << 3) + 2 * e;
+        float x0 = hm < G ? x[0] : 0.f, x1 = hm < G ? x[1] : 0.f;
+#pragma unroll
+        for (int q = 0; q < QP; ++q) {
+          part[q].u[e] = pk_bf16(x0, x1);
+          x0 -= __uint_as_float(part[q].u[e] << 16); x1 -= __uint_as_float(part[q].u[e] & 0xffff0000u);
+        }
       }
-      qh[ks] = H.v; ql[ks] = L.v;
+#pragma unroll
+      for (int q = 0; q < QP; ++q) qp[q][ks] = part[q].v;
     }
   }
 
   // per wave: running maximum, sum and weighted values of its 16-key slices, for all G heads;
-  // lane (sub = lane / 16, dc = lane % 16) accumulates dims dc*DL .. +DL over keys 4 i + sub
+  // lane (sub, dc) accumulates dims dc*DL .. +DL over keys SUBS i + sub
   float m1 = -INFINITY, l1 = 0.f;                        // head lane / 16: running maximum and sum
   float o[G][DL];
 #pragma unroll
@@ -377,7 +387,7 @@ __global__ void __launch_bounds__(AS_THREADS) k_attn_mfma_b(BatchParams P) {
 #pragma unroll
     for (int e = 0; e < DL; ++e) o[h][e] = 0.f;
   }
-  const int sub = lane >> 4, dc = lane & 15;
+  const int sub = lane / LPR, dc = lane % LPR;
   const int new_sl = (pos >> 4) - 4 * t_first;          // the slice that holds the new position (if this split owns it)
 
   auto slice = [&](Stage& st, int j) __attribute__((always_inline)) {
@@ -398,8 +408,8 @@ __global__ void __launch_bounds__(AS_THREADS) k_attn_mfma_b(BatchParams P) {
           }
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-          if (4 * i + sub == r) {
+        for (int i = 0; i < NV; ++i)
+          if (SUBS * i + sub == r) {
             unsigned w[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e)
@@ -412,8 +422,8 @@ __global__ void __launch_bounds__(AS_THREADS) k_attn_mfma_b(BatchParams P) {
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
         const bf16x8_t kb = as_bf16x8(st.k[ks]);
-        sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qh[ks], kb, sc, 0, 0, 0);
-        sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ql[ks], kb, sc, 0, 0, 0);
+#pragma unroll
+        for (int q = 0; q < QP; ++q) sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qp[q][ks], kb, sc, 0, 0, 0);
       }
       // lane (key = lane % 16, head = lane / 16): every register of sc is S[head][key]
       {
@@ -426,7 +436,7 @@ __global__ void __launch_bounds__(AS_THREADS) k_attn_mfma_b(BatchParams P) {
         const float ls = row16_sum(pv);
         l1 = l1 * corr + ls;
         m1 = mn;
-        // the weights go through LDS: lane (sub, dc) needs those of keys 4 i + sub, for all heads
+        // the weights go through LDS: lane (sub, dc) needs those of keys SUBS i + sub, for all heads
         wbuf[(lane & 15) * 4 + (lane >> 4)] = pv;
         if (__any(corr != 1.f)) {                          // (after the first slices the maxima rarely move: 1.0 would change nothing)
           if ((lane & 15) == 0) wbuf[64 + (lane >> 4)] = corr;
@@ -437,10 +447,10 @@ __global__ void __launch_bounds__(AS_THREADS) k_attn_mfma_b(BatchParams P) {
             for (int e = 0; e < DL; ++e) o[h][e] *= c4[h];
         }
       }
-      // weighted values: 4 rows per lane group, each value row shared by the G heads
+      // weighted values: each value row shared by the G heads
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int kr = 4 * i + sub;                      // key of this lane within the slice
+      for (int i = 0; i < NV; ++i) {
+        const int kr = SUBS * i + sub;                   // key of this lane within the slice
         const int key = k0 + kr;
         const u32x4_t w = st.v[i];
         float vf[DL];
@@ -463,30 +473,29 @@ __global__ void __launch_bounds__(AS_THREADS) k_attn_mfma_b(BatchParams P) {
     }
     issue(st, j + 3 * SK_WAVES);
   };
-  static_assert(DL == 8, "one 16-byte value load per lane and key");
   for (int j = wave; j < n_sl; j += 3 * SK_WAVES) {
     slice(st0, j);
     slice(st1, j + SK_WAVES);
     slice(st2, j + 2 * SK_WAVES);
   }
 
-  // fold the key subgroups (lanes sub = 0..3), then every wave leaves its partial per head in LDS
+  // fold the key subgroups, then every wave leaves its partial per head in LDS
 #pragma unroll
   for (int h = 0; h < G; ++h)
 #pragma unroll
     for (int e = 0; e < DL; ++e) {
-      o[h][e] += __shfl_xor(o[h][e], 16, 64);
-      o[h][e] += __shfl_xor(o[h][e], 32, 64);
+#pragma unroll
+      for (int off = LPR; off < 64; off <<= 1) o[h][e] += __shfl_xor(o[h][e], off, 64);
     }
 #pragma unroll
   for (int h = 0; h < G; ++h) {
     float* mb = mbuf + (size_t)(wave * G + h) * (HD + 2);
-    if (lane < 16) {
+    if (lane < LPR) {
 #pragma unroll
       for (int e = 0; e < DL; ++e) mb[dc * DL + e] = o[h][e];
     }
   }
-  if ((lane & 15) == 0) {
+  if ((lane & 15) == 0 && (lane >> 4) < G) {
     float* mb = mbuf + (size_t)(wave * G + (lane >> 4)) * (HD + 2);
     mb[HD] = m1; mb[HD + 1] = l1;
   }
@@ -508,6 +517,17 @@ __global__ void __launch_bounds__(AS_THREADS) k_attn_mfma_b(BatchParams P) {
       }
     }
     const int H = g * G + hq;
+    if (nsplit == 1) {                                     // nothing to meet: three memory round trips less
+#pragma unroll
+      for (int d = 0; d < HD; d += 64) {
+        const float v = (d ? a1 : a0) / den;
+        const bf16 h = from_f32<bf16>(v);
+        const size_t at = bg_aidx(slot, H * HD + d + lane);
+        P.x2h[at] = h;
+        P.x2l[at] = from_f32<bf16>(v - to_f32(h));
+      }
+      return;
+    }
     float* po = p.part_o + (((size_t)b * p.Hq + H) * S_MAX + s) * HD;
     st_coh(po + lane, a0);
     if (HD > 64) st_coh(po + lane + 64, a1);
@@ -516,6 +536,7 @@ __global__ void __launch_bounds__(AS_THREADS) k_attn_mfma_b(BatchParams P) {
       st_coh(pml, M); st_coh(pml + 1, den);
     }
   }
+  if (nsplit == 1) return;
   // the last split of this KV head to finish merges all splits (fixed order) and writes the output
   vm_wait_all();
   __syncthreads();

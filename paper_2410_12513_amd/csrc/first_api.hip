@@ -490,8 +490,21 @@ void enqueue_decode_batched(first_ctx* c, const int* tokens, float* logits, int*
   const int nkg = std::max(1, SK_WAVES / c->G);
   const int nsplit = std::max(1, std::min(S_MAX, (2 * S + nkg - 1) / nkg));
   const size_t attn_tiles_lds = sk_lds_floats(0, 0, 0, c->G, d.head_dim) * sizeof(float);
-  // models with 4 query heads per KV head and head dimension 128: tiles fetched once per workgroup, scores on the matrix cores
-  const bool shared_attn = c->G == 4 && d.head_dim == 128;
+  // two to four query heads per KV head: tiles fetched once per workgroup, scores on the matrix cores.  Where that is the better of the two
+  // kernels was measured on five geometries, us a step of four layers, k_attn_tiles_b / k_attn_mfma_b: four heads of 128: everywhere;
+  // the others where no sequence is split (3B heads, two of 200 keys 452 / 449, of 500 453 / 461; 64 dims: two of 500 310 / 311) or there are
+  // some 3000 keys in all (1B heads: 3 x 900 318 / 322, 10 of 200..800 349 / 341, 16 x 4000 646 / 442; 3B heads: 16 x 4000 913 / 656)
+  auto shared = [&](const SeqList& keep) {
+    if (c->G < 2 || c->G > 4) return false;
+    if (c->G == 4 && d.head_dim == 128) return true;
+    int sum = 0, most = 0;
+    for (int j = 0; j < keep.n; ++j) { const int t = c->hlen[keep.id[j]] / 64 + 1; sum += t; most = std::max(most, t); }
+    return c->attn_splits <= 0 && (sum >= 50 || most <= (d.head_dim == 64 ? 10 : 6));
+  };
+  auto mfma_attn = [&]() -> void (*)(BatchParams) {
+    if (d.head_dim == 128) return c->G == 4 ? &k_attn_mfma_b<128, 4> : c->G == 3 ? &k_attn_mfma_b<128, 3> : &k_attn_mfma_b<128, 2>;
+    return c->G == 4 ? &k_attn_mfma_b<64, 4> : c->G == 3 ? &k_attn_mfma_b<64, 3> : &k_attn_mfma_b<64, 2>;
+  };
   for (int b0 = 0; b0 < c->B; b0 += BATCH_SLOTS) {
     BatchParams P{};
     P.d = base_params(c, 0, S);
@@ -547,16 +560,19 @@ void enqueue_decode_batched(first_ctx* c, const int* tokens, float* logits, int*
       // does not move with the lengths, so a captured graph stays valid)
       ns_shared = std::max(ns_shared, ((d.max_seq_len + 64) / 64 * 4 + AS_PT - 1) / AS_PT);
       P.attn_nwork = 0;
+      const bool shared_attn = shared(keep);
       if (tiles_attn && shared_attn && c->attn_splits <= 0) {
         // work list: splits in proportion to each sequence's length - the fewest tiles per workgroup for which the batch
         // still fits one round of the compute units at today's lengths (a cached graph keeps the list while the
-        // sequences grow: their splits just get longer)
+        // sequences grow: their splits just get longer).  Up to ten tiles are not split: walking them takes no longer than the
+        // splits' meeting (8B, two sequences of 200 keys 634 -> 614 us a step of four layers, six of 100..600 658 -> 640)
         const int min_sp = ((d.max_seq_len + 64) / 64 * 4 + AS_PT - 1) / AS_PT;    // a split's page ids fit the LDS table
         int sp[BATCH_SLOTS];
         for (int tpw = AS_NT; tpw <= AS_PT / 4; ++tpw) {
           int wgs = 0;
           for (int j = 0; j < keep.n; ++j) {
-            sp[j] = std::min(S_MAX, std::max(min_sp, (c->hlen[keep.id[j]] / 64 + 1 + tpw - 1) / tpw));
+            const int t = c->hlen[keep.id[j]] / 64 + 1;
+            sp[j] = std::min(S_MAX, std::max(min_sp, t <= 10 ? 1 : (t + tpw - 1) / tpw));
             wgs += sp[j];
           }
           if (wgs * d.n_kv_heads <= c->num_cu || tpw == AS_PT / 4) {
@@ -569,9 +585,9 @@ void enqueue_decode_batched(first_ctx* c, const int* tokens, float* logits, int*
         }
       }
       if (tiles_attn && shared_attn && P.attn_nwork > 0)
-        hipLaunchKernelGGL((k_attn_mfma_b<128, 4>), dim3(d.n_kv_heads, P.attn_nwork), dim3(AS_THREADS), as_lds_bytes(4, 128), c->stream, P);
+        hipLaunchKernelGGL(mfma_attn(), dim3(d.n_kv_heads, P.attn_nwork), dim3(AS_THREADS), as_lds_bytes(c->G, d.head_dim), c->stream, P);
       else if (tiles_attn && shared_attn)
-        hipLaunchKernelGGL((k_attn_mfma_b<128, 4>), dim3(ns_shared, d.n_kv_heads, keep.n), dim3(AS_THREADS), as_lds_bytes(4, 128), c->stream, P);
+        hipLaunchKernelGGL(mfma_attn(), dim3(ns_shared, d.n_kv_heads, keep.n), dim3(AS_THREADS), as_lds_bytes(c->G, d.head_dim), c->stream, P);
       else if (tiles_attn && d.head_dim == 128)
         hipLaunchKernelGGL(k_attn_tiles_b<128>, dim3(nsplit, d.n_kv_heads, keep.n), dim3(AT_THREADS), attn_tiles_lds, c->stream, P);
       else if (tiles_attn)

@@ -8,13 +8,6 @@ namespace first {
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16_t;
 
-typedef __attribute__((__vector_size__(2 * sizeof(float)))) float float2v_t;
-typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2_t;
-// two fp32 -> two bf16 (nearest even) in one register, low half first
-__device__ __forceinline__ uint32_t pk_bf16(float a, float b) {
-  const float2v_t v = {a, b};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
-}
 // hi = bf16(x), lo = bf16(x - hi) for a pair
 __device__ __forceinline__ void split_pair(float a, float b, uint32_t& hi, uint32_t& lo) {
   hi = pk_bf16(a, b);

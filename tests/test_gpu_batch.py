@@ -7,7 +7,7 @@ import torch
 
 import paper_2410_12513_amd as P
 from oracle import first_oracle as O
-from synth import CONFIGS, make_prompt, make_router, make_skip_mask, make_weights
+from synth import CONFIGS, ModelDesc, make_prompt, make_router, make_skip_mask, make_weights
 from synth.generators import to_device
 from tests.gpu_util import build, logits_close, top2_gap
 from tests.test_gpu_path import _decode, _prefill
@@ -179,3 +179,12 @@ def test_lm_head_with_four_row_tiles_a_wave_and_a_ragged_last_group():
             assert float((lg[s, b][-21:].double() - tail).norm() / tail.norm()) <= 1e-2
             assert int(tk[s, b]) == int(torch.argmax(lg[s, b]))
     ctx.close()
+
+
+@pytest.mark.parametrize("hq,hkv,hd", [(4, 2, 128), (6, 2, 128), (8, 4, 64), (6, 2, 64), (8, 2, 64)])
+@pytest.mark.parametrize("lens", [[1, 16, 63, 64, 200], [900, 1300, 31, 640, 900]])
+def test_shared_key_tiles_of_every_head_geometry(hq, hkv, hd, lens, monkeypatch):
+    """Two, three and four query heads a KV head in both head dimensions: sequences that one workgroup a KV head walks (up to the edges
+    of pages and tiles), and a batch that is split."""
+    monkeypatch.setitem(CONFIGS, "geometry", ModelDesc(2, 512, hq, hkv, hd, 1032, 600))
+    _run("geometry", lens, 4, 97, masks=[[1, 1]] * 4 + [[0, 1]])
