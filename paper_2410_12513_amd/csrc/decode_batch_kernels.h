@@ -811,7 +811,7 @@ __global__ void __launch_bounds__(BG_THREADS) k_bgemv(BatchParams P, int N, int 
 // pipeline as the weights (for the small matrices it is twice the weight bytes).  The K-slices of a
 // tile group then live in different workgroups: each stores its partial sums, and the last one to
 // finish (a counter per tile group) adds them in slice order - the result does not depend on which
-// workgroup that is - and applies the epilogue.  GW (5..8 waves) and the number of slices are chosen
+// workgroup that is - and applies the epilogue.  GW (4..8 waves) and the number of slices are chosen
 // on the host so that the workgroups come to a whole number of rounds over the compute units.
 // Tile-order weights only.  Dynamic LDS: 2 * per * 1024 bytes (per = K-steps per slice).
 __host__ __device__ inline int bgg_per(int K, int ks) { return (((K + 31) >> 5) + ks - 1) / ks; }
@@ -848,6 +848,26 @@ __global__ void __launch_bounds__(GW * 64) k_bgemv_g(BatchParams P, int N, int K
   };
   Chunk A, B;
   load(A, 0);                                          // the weight stream starts before the activations are staged
+  // What the epilogue of the last arriver needs beside the partial sums - its elements' sequences, residual values and gains - is
+  // requested before the activations: it is there long before
+  // the partial sums are counted.  A thread's elements are rows r of slots
+  // tid / ROWS + 4 u.
+  constexpr bool RES = MODE == BG_O || MODE == BG_DN;
+  constexpr int EPT = 16 * ROWS / THREADS;
+  static_assert(EPT * THREADS == 16 * ROWS && EPT == 4 && THREADS == 4 * ROWS, "whole rounds, four slots each");
+  const bool fuse = RES && P.fuse_gain != nullptr;
+  const int er = tid % ROWS, row = tg * ROWS + er, eslot = tid / ROWS, rowc = min(row, N - 1);
+  int eb[EPT];
+  float hv[RES ? EPT : 1], gain = 0.f;
+  if (RES || MODE == BG_QKV) {
+#pragma unroll
+    for (int u = 0; u < EPT; ++u) eb[u] = P.seqs.id[min(eslot + 4 * u, P.seqs.n - 1)];
+  }
+  if constexpr (RES) {
+    if (fuse) gain = P.fuse_gain[rowc];
+#pragma unroll
+    for (int u = 0; u < EPT; ++u) hv[u] = p.h[(size_t)eb[u] * p.D + rowc];
+  }
   {
     const uint4* xh = reinterpret_cast<const uint4*>((MODE == BG_DN ? P.zh : MODE == BG_O ? P.x2h : P.xh) + (size_t)s0 * 512);
     const uint4* xl = reinterpret_cast<const uint4*>((MODE == BG_DN ? P.zl : MODE == BG_O ? P.x2l : P.xl) + (size_t)s0 * 512);
@@ -934,18 +954,16 @@ __global__ void __launch_bounds__(GW * 64) k_bgemv_g(BatchParams P, int N, int K
   if (!last_flag) return;
   // the last slice of this tile group to finish adds the slices in order and applies the epilogue
   const float* grp = part + (size_t)tg * ks * (NS * 16 * ROWS);
-  __shared__ float ssq_lds[(MODE == BG_O || MODE == BG_DN) ? BATCH_SLOTS * ROWS : 1];   // squares of the updated h, [slot][row]
-  const bool fuse = (MODE == BG_O || MODE == BG_DN) && P.fuse_gain != nullptr;
+  __shared__ float ssq_lds[RES ? BATCH_SLOTS * ROWS : 1];   // squares of the updated h, [slot][row]
   const bool remap = fuse && P.next.n > 0;
-  auto finish = [&](int e, const float (&sum)[NS]) __attribute__((always_inline)) {
-    const int slot = e / ROWS, r = e % ROWS, row = tg * ROWS + r;
+  auto finish = [&](int u, const float (&sum)[NS]) __attribute__((always_inline)) {
+    const int slot = eslot + 4 * u;
     if (slot >= P.seqs.n || row >= N) {
-      if (MODE == BG_O || MODE == BG_DN) ssq_lds[e] = 0.f;
+      if constexpr (RES) ssq_lds[slot * ROWS + er] = 0.f;
       return;
     }
-    const int b = P.seqs.id[slot];
     if (MODE == BG_QKV) {
-      p.qkv[(size_t)b * N + row] = sum[0] * rinv_lds[slot];
+      p.qkv[(size_t)eb[u] * N + row] = sum[0] * rinv_lds[slot];
     } else if (MODE == BG_GU) {
       const float rr = rinv_lds[slot];
       const float z = siluf(sum[0] * rr) * (sum[NS - 1] * rr);
@@ -953,25 +971,27 @@ __global__ void __launch_bounds__(GW * 64) k_bgemv_g(BatchParams P, int N, int K
       P.zh[bg_aidx(slot, row)] = hi;                           // input of the down projection, already split
       P.zl[bg_aidx(slot, row)] = from_f32<bf16>(z - to_f32(hi));
     } else {
-      const float hn = p.h[(size_t)b * p.D + row] + sum[0];
-      p.h[(size_t)b * p.D + row] = hn;
-      ssq_lds[e] = hn * hn;
+      const float hn = hv[RES ? u : 0] + sum[0];
+      p.h[(size_t)eb[u] * p.D + row] = hn;
+      ssq_lds[slot * ROWS + er] = hn * hn;
       if (fuse && !remap) {                                    // the next norm op's input, split as k_xsplit would
-        const float v = hn * P.fuse_gain[row];
+        const float v = hn * gain;
         const bf16 hi = from_f32<bf16>(v);
         P.xh[bg_aidx(slot, row)] = hi;
         P.xl[bg_aidx(slot, row)] = from_f32<bf16>(v - to_f32(hi));
       }
     }
   };
-  if constexpr (MODE == BG_QKV || MODE == BG_GU) {
-    // every partial sum this thread needs - its 4 elements x streams x up to 8 slices - is requested before the first
-    // is used: one memory round trip for the whole epilogue instead of one per element and stream
-    constexpr int EPT = 16 * ROWS / THREADS;
-    static_assert(EPT * THREADS == 16 * ROWS, "whole rounds");
-    float pv[EPT][NS][8];
+  // Every partial sum this thread needs - R elements x streams x up to 8 slices; R = 1 serves four sequences - is requested
+  // before the first is used: one memory round trip for the whole epilogue.  (O and down took an element per round, each with
+  // its sequence, residual and gain one behind the other.  Four layers and the head for 16 short sequences: D 3072, F 8192 507 us a
+  // step -> 479, D 2048, F 8192 354 -> 321 with four-wave groups; D 4096, F 14336 within 0.4 %.  Requesting the residuals behind the
+  // K loop instead of before it costs every workgroup their latency: 0.9 % of that step.)
+  auto epilogue = [&](auto rc) __attribute__((always_inline)) {
+    constexpr int R = decltype(rc)::value;
+    float pv[R][NS][8];
 #pragma unroll
-    for (int u = 0; u < EPT; ++u)
+    for (int u = 0; u < R; ++u)
 #pragma unroll
       for (int i = 0; i < NS; ++i)
 #pragma unroll
@@ -979,7 +999,7 @@ __global__ void __launch_bounds__(GW * 64) k_bgemv_g(BatchParams P, int N, int K
           coh_issue4(pv[u][i][q], grp + (size_t)min(q, ks - 1) * (NS * 16 * ROWS) + i * (16 * ROWS) + tid + u * THREADS);
     coh_wait();
 #pragma unroll
-    for (int u = 0; u < EPT; ++u) {
+    for (int u = 0; u < R; ++u) {
       float sum[NS];
 #pragma unroll
       for (int i = 0; i < NS; ++i) {
@@ -987,26 +1007,16 @@ __global__ void __launch_bounds__(GW * 64) k_bgemv_g(BatchParams P, int N, int K
 #pragma unroll
         for (int q = 0; q < 8; ++q) { coh_use(pv[u][i][q]); if (q < ks) sum[i] += pv[u][i][q]; }
       }
-      finish(tid + u * THREADS, sum);
+      finish(u, sum);
     }
-  } else {
-    // (the projections that add to the residual stream take one element per round: measured, the batch of loads
-    //  above makes them slower)
-    for (int e = tid; e < 16 * ROWS; e += THREADS) {
-      float sum[NS];
+    if constexpr (RES) {
 #pragma unroll
-      for (int i = 0; i < NS; ++i) {
-        float v[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) coh_issue4(v[q], grp + (size_t)min(q, ks - 1) * (NS * 16 * ROWS) + i * (16 * ROWS) + e);
-        coh_wait();
-        sum[i] = 0.f;
-#pragma unroll
-        for (int q = 0; q < 8; ++q) { coh_use(v[q]); if (q < ks) sum[i] += v[q]; }
-      }
-      finish(e, sum);
+      for (int u = R; u < EPT; ++u) ssq_lds[(eslot + 4 * u) * ROWS + er] = 0.f;
     }
-  }
+  };
+  if (P.seqs.n <= 4) epilogue(std::integral_constant<int, 1>{});
+  else if (P.seqs.n <= 8) epilogue(std::integral_constant<int, 2>{});
+  else epilogue(std::integral_constant<int, 4>{});
   if ((MODE == BG_O || MODE == BG_DN) && remap) {
     // the consumer's slots: this group's rows of every sequence it will read, straight from the residual stream
     __syncthreads();                                           // (waits for the stores above as well)

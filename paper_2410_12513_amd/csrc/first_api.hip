@@ -385,8 +385,10 @@ bool d_batch_fits(const first_ctx* c) {
 }
 
 // Mat-vecs with tile-order weights as (GW row tiles) x (one slice of K) per workgroup (k_bgemv_g): GW in
-// 5..8 and at most 8 slices, chosen so that the workgroups fill whole rounds over the compute units
-// (ties: more waves per workgroup, fewer slices).
+// 4..8 and at most 8 slices, chosen so that the workgroups fill whole rounds over the compute units
+// (ties: more waves per workgroup, fewer slices).  Four waves serve the widths of at most 2048 rows, where
+// eight slices of five leave a fifth of the chip idle: a layer step of 16 short sequences at D 2048, F 8192
+// takes 77.7 us with O 5 x 8 and down 5 x 8, 77.0 with O 4 x 8 and 75.7 with down 4 x 8.
 template <int MODE, int GW>
 void launch_bgemv_gw(first_ctx* c, const BatchParams& P, int N, int K, int groups, int ks) {
   hipLaunchKernelGGL((k_bgemv_g<MODE, GW>), dim3(groups * ks), dim3(GW * 64), (size_t)2 * bgg_per(K, ks) * 1024, c->stream, P, N, K, ks,
@@ -401,7 +403,7 @@ int launch_bgemv_g(first_ctx* c, const BatchParams& P, int N, int K) {
   const int tiles = (N + 15) / 16, ksteps = (K + 31) / 32;
   int best_gw = 0, best_ks = 0;
   double best = 0.0;
-  for (int gw = 8; gw >= 5; --gw)
+  for (int gw = 8; gw >= 4; --gw)
     for (int ks = 1; ks <= std::min(8, ksteps); ++ks) {
       const int groups = (tiles + gw - 1) / gw, wgs = groups * ks;
       if ((size_t)2 * bgg_per(K, ks) * 1024 > 150 * 1024) continue;
@@ -417,7 +419,8 @@ int launch_bgemv_g(first_ctx* c, const BatchParams& P, int N, int K) {
     case 8: launch_bgemv_gw<MODE, 8>(c, P, N, K, groups, best_ks); break;
     case 7: launch_bgemv_gw<MODE, 7>(c, P, N, K, groups, best_ks); break;
     case 6: launch_bgemv_gw<MODE, 6>(c, P, N, K, groups, best_ks); break;
-    default: launch_bgemv_gw<MODE, 5>(c, P, N, K, groups, best_ks); break;
+    case 5: launch_bgemv_gw<MODE, 5>(c, P, N, K, groups, best_ks); break;
+    default: launch_bgemv_gw<MODE, 4>(c, P, N, K, groups, best_ks); break;
   }
   return groups;
 }
@@ -1274,7 +1277,7 @@ int first_create(const first_model_desc* desc, const first_weights* w, void* hip
     A(dev_alloc(c, &c->d_rinv, BATCH_SLOTS)); A(dev_alloc(c, &c->d_logits_all, (size_t)B * d.vocab));
     {                                                   // partial sums: up to 8 slices x 16 slots x (rows padded to a tile group), gate + up
       const size_t nmax = (size_t)std::max(std::max(c->nq + 2 * c->nkv, d.d_model), 2 * d.d_ffn);
-      c->bg_cnt_n = nmax / (5 * 16) + 2;
+      c->bg_cnt_n = nmax / (4 * 16) + 2;
       c->bg_part_floats = (size_t)8 * 16 * (nmax + 8 * 16 * 2);
     }
     A(dev_alloc(c, &c->d_bg_part, c->bg_part_floats)); A(dev_alloc(c, &c->d_bg_cnt, c->bg_cnt_n));

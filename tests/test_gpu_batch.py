@@ -188,3 +188,12 @@ def test_shared_key_tiles_of_every_head_geometry(hq, hkv, hd, lens, monkeypatch)
     of pages and tiles), and a batch that is split."""
     monkeypatch.setitem(CONFIGS, "geometry", ModelDesc(2, 512, hq, hkv, hd, 1032, 600))
     _run("geometry", lens, 4, 97, masks=[[1, 1]] * 4 + [[0, 1]])
+
+
+@pytest.mark.parametrize("d_model", [200, 2056])
+def test_mat_vec_epilogue_of_four_eight_and_sixteen_slots(d_model, monkeypatch):
+    """O and down request the partial sums of four, eight or all sixteen slots: layers kept by 4, 5, 8 and 9 of nine sequences, widths
+    whose last row tile is half a tile, and consumers with other slots than the producer's."""
+    monkeypatch.setitem(CONFIGS, "slots", ModelDesc(5, d_model, 4, 2, 64, 520, 600))
+    masks = [[1, int(b < 4), int(b > 3), int(b != 4), 1] for b in range(9)]
+    _run("slots", [3 + 7 * b for b in range(9)], 3, 61, masks=masks)
