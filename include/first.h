@@ -47,7 +47,7 @@ extern "C" {
 /* options for first_set_option */
 #define FIRST_OPT_USE_GRAPH     1  /* 1 (default): a decode step of several launches is a cached hipGraph (one per set of masks on the
                                       per-op and batched paths; one for all masks where a whole step is one kernel a sequence,
-                                      which reads the kept layers from the device), a step of one launch goes out directly;
+                                      which reads the kept layers from the device), a small fp32 model's single launch goes out directly;
                                       0: eager launches */
 #define FIRST_OPT_ATTN_SPLITS   2  /* KV splits per (sequence, KV head) in decode attention; 0 = auto   */
 #define FIRST_OPT_DECODE_PATH   3  /* -1 (default): persistent whole-step kernel when the model fits it
@@ -206,10 +206,10 @@ int first_decode_step_sampled(first_ctx *ctx, const int32_t *last_tokens, const 
 
 /* first_sample_top_k for callers that cannot allocate device memory or hold a context: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same rule, same kernels and the same
- * results as first_sample_top_k, on any logits: the per-chunk candidate lists of the first stage live in a
+ * results as first_sample_top_k, on any logits: the candidate lists of the parts of its rows live in a
  * 1 MiB device array that is part of the library image (one copy per GPU, held until the process ends), and
  * the call makes no hipMalloc / hipFree or other allocating call.
- *   hip_stream     hipStream_t the two kernels are enqueued on (NULL: the null stream)
+ *   hip_stream     hipStream_t the kernels (one or two) are enqueued on (NULL: the null stream)
  *   logits         DEV fp32  [n_seq, vocab]
  *   uniforms       DEV fp32  [n_seq]          one number in [0, 1) per sequence
  *   token_out      DEV int32 [n_seq]

@@ -23,8 +23,8 @@
 
 using namespace first;
 
-// Scratch of first_sample_top_k_static, the entry point that allocates nothing: the per-chunk candidate lists of
-// its first stage.  Every device the library runs on holds its own copy of the array (at its own address) until
+// Scratch of first_sample_top_k_static, the entry point that allocates nothing: the candidate lists of the parts of its
+// rows.  Every device the library runs on holds its own copy of the array (at its own address) until
 // the process ends.  Host code never uses the array's name as an address: g_scratch_ptr[device] is what
 // hipGetSymbolAddress returned with that device current.
 constexpr long long STATIC_SCRATCH_CANDS = 131072;           // 1 MiB of {logit, index} pairs
@@ -1291,7 +1291,8 @@ int first_create(const first_model_desc* desc, const first_weights* w, void* hip
     (void)hipMemset(c->d_x2h, 0, (size_t)BATCH_SLOTS * c->xpitch * 2); (void)hipMemset(c->d_x2l, 0, (size_t)BATCH_SLOTS * c->xpitch * 2);
 #define FIRST_BGG_ATTR(MODE)                                                                                          \
   for (const void* fn : {reinterpret_cast<const void*>(&k_bgemv_g<MODE, 8>), reinterpret_cast<const void*>(&k_bgemv_g<MODE, 7>),      \
-                         reinterpret_cast<const void*>(&k_bgemv_g<MODE, 6>), reinterpret_cast<const void*>(&k_bgemv_g<MODE, 5>)})      \
+                         reinterpret_cast<const void*>(&k_bgemv_g<MODE, 6>), reinterpret_cast<const void*>(&k_bgemv_g<MODE, 5>),       \
+                         reinterpret_cast<const void*>(&k_bgemv_g<MODE, 4>)})                                                          \
     (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024);
     FIRST_BGG_ATTR(BG_QKV) FIRST_BGG_ATTR(BG_O) FIRST_BGG_ATTR(BG_DN) FIRST_BGG_ATTR(BG_GU)
 #undef FIRST_BGG_ATTR
@@ -1511,8 +1512,10 @@ int decode_step_impl(first_ctx* c, const int32_t* last_tokens, float* logits_out
       launch_sample(c->stream, logits_out, c->B, c->d.vocab, smp->uniforms, smp->temperature, smp->top_k, c->d_topk_part, token_out,
                     smp->candidates_out);
   };
-  // a step that is one launch goes out as one: 6.7 us between two of them, against 13 between replays of a graph with one node
-  const bool one_launch = (persistent && !(smp && !fused)) || (small && c->B == 1 && !smp);
+  // A small model's step of one launch goes out as one: 6.7 us between two of them, against 13 between replays of a graph with one node.
+  // The persistent kernel stays a graph: it needs every compute unit, so two of them (contexts on streams of their own) must not be
+  // dispatched together, and two launches that follow each other within a few us, behind the same event, are: a wait in one gave up.
+  const bool one_launch = small && c->B == 1 && !smp;
   if (!c->use_graph || one_launch) {
     enqueue();
     HIPCHK(c, hipGetLastError());
