@@ -70,6 +70,9 @@ extern "C" {
                                       gives up at its first exchange: every wave leaves at its next wait, nothing hangs, and the next
                                       call that synchronises (first_sync, first_seq_len, ...) returns FIRST_ERR_HIP, clears the limit
                                       and resets the exchange state; the live sequences must be prefilled again.  Synchronises. */
+#define FIRST_OPT_SMALL_EPOCH 11  /* test tap: the small fp32 models' whole-step kernel goes on as if its exchange counter stood at this value
+                                      (the 32 bits as an unsigned number), the exchange itself cleared.  Synchronises.  FIRST_ERR_STATE
+                                      where the context has no such kernel. */
 #define FIRST_OPT_BATCH_PATH    6  /* decode with several live sequences.  -1 (default): per layer, the sequences that
                                       keep it share one pass over its weights (bf16 models, widths multiples of 8),
                                       else one pass per sequence; 0: always one pass per sequence; 1: shared pass or error */

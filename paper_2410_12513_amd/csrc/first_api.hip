@@ -211,7 +211,7 @@ hipError_t reset_tagged_exchange(first_ctx* c) {
 size_t small_exchange_words(const first_ctx* c) {
   return (size_t)c->d.d_model + (c->nq + 2 * c->nkv) + c->nq + c->d.d_ffn + 2 * c->small_wgs;
 }
-// (no word carries an epoch that a launch after epoch 0 waits for)
+// (a word of zeros carries epoch 0, which no launch waits for)
 hipError_t reset_small_exchange(first_ctx* c) {
   if (!c->small_wgs) return hipSuccess;
   const hipError_t e = hipMemset(c->d_small, 0, small_exchange_words(c) * sizeof(ss_word));
@@ -1663,6 +1663,12 @@ int first_set_option(first_ctx* c, int32_t option, int32_t value) {
       HIPCHK(c, hipMemcpy(c->d_err, &word, sizeof(int), hipMemcpyHostToDevice));
       return FIRST_OK;
     }
+    case FIRST_OPT_SMALL_EPOCH:
+      if (!c->small_wgs) return fail(c, FIRST_ERR_STATE, "first_set_option: no whole-step kernel for small fp32 models in this context");
+      HIPCHK(c, hipStreamSynchronize(c->stream));
+      HIPCHK(c, reset_small_exchange(c));
+      HIPCHK(c, hipMemcpy(c->d_small_epoch, &value, sizeof(int), hipMemcpyHostToDevice));
+      return FIRST_OK;
     default: return fail(c, FIRST_ERR_ARG, "first_set_option: unknown option");
   }
 }

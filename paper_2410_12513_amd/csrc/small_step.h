@@ -4,8 +4,9 @@
 // compute units read in a microsecond, so that a launch per op spends its time starting and draining (two layers of 256 x 688, 30
 // tokens: 61 us a step in 12 launches, 37.6 here, 36.5 of them in the kernel: some 2.5 us an exchange).  The workgroups stay and hand vectors to each other through memory:
 // every element travels as a 64-bit word {value, epoch}, stored at once; whoever needs the vector loads it until all its words carry the
-// epoch it waits for.  Epochs only grow: within a launch every vector has the next one, and the last one of a launch is
-// kept in device memory for the launch that follows.
+// epoch it waits for.  Within a launch every vector has the next epoch, and the last one of a launch is kept in device memory for the
+// launch that follows.  No vector ever has epoch 0: a launch whose epochs would not all lie below 2^32 begins again at 1 (after hours of
+// steps; by then every word carries an epoch of the launches just before, far from 1).
 //
 // A word is never overwritten before everyone has read it: each vector is written again one layer later, by workgroups that have
 // seen complete vectors since to which EVERY workgroup contributed after reading this one (each owns at least one row
@@ -162,8 +163,9 @@ __global__ void __launch_bounds__(SS_THREADS, 4) k_small_step(SmallStep P) {
   Best* wbest = reinterpret_cast<Best*>(parts + SS_WAVES * (HD + 2));
   int* bad = reinterpret_cast<int*>(wbest + SS_WAVES);
   if (__hip_atomic_load(P.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 1) return;
-  unsigned ep = *P.epoch;
   const int pos = uni(p.len[b]), n_kept = uni(P.n_kept[b]), tok = min(max(p.tokens[b], 0), p.V - 1);
+  unsigned ep = *P.epoch;
+  if (ep > ~0u - (5u * n_kept + 1u)) ep = 0u;        // (five epochs a layer, one for the candidates)
   const int head = wg, g = head / p.G;               // workgroups 0 .. Hq - 1: a query head each
   const bool attends = wg < p.Hq;
   for (int i = tid; i < D; i += SS_THREADS) hbuf[i] = reinterpret_cast<const float*>(p.embed)[(size_t)tok * D + i];
@@ -173,7 +175,7 @@ __global__ void __launch_bounds__(SS_THREADS, 4) k_small_step(SmallStep P) {
   int turn = 0;
   float* xs = xbuf[0];
   float rms = 0.f;
-  // xs = x * gain of the residual of this epoch (0: the one in hbuf), and what 1/rms multiplies the results with
+  // xs = x * gain of the residual of this epoch (0, nobody's: the embedding, which is in hbuf), and what 1/rms multiplies the results with
   auto stage_norm = [&](const float* gain, unsigned epoch) __attribute__((always_inline)) {
     float ss = 0.f;
     auto take = [&](int i, float v) __attribute__((always_inline)) { hbuf[i] = v; xs[i] = v * gain[i]; ss = fmaf(v, v, ss); };

@@ -16,7 +16,7 @@ HD64 = ModelDesc(3, 256, 4, 2, 64, 696, 1001, dtype="fp32")
 HD128 = ModelDesc(3, 512, 4, 1, 128, 1032, 500, dtype="fp32")
 WIDE = ModelDesc(3, 512, 8, 8, 64, 2048, 77, dtype="fp32")
 NARROW = ModelDesc(3, 72, 2, 1, 64, 96, 67, dtype="fp32")
-OPT_DECODE_PATH = 3
+OPT_DECODE_PATH, OPT_SMALL_EPOCH = 3, 11
 
 
 def _prefilled(desc, prompts, seed, page=16, room=16, path=-1, max_seq_len=None):
@@ -87,6 +87,28 @@ def test_a_batch_has_the_bits_of_each_sequence_alone():
             one.sync()
             assert int(t[0]) == int(tokens[b]) and torch.equal(l1[0], logits[b])
         one.close()
+    ctx.close()
+
+
+@pytest.mark.parametrize("mask", [[1, 1, 1], [0, 1, 0]])
+def test_the_exchange_counter_passes_its_largest_value(mask):
+    """Three steps from every place before the end of the counter's 32 bits from which one of their first two exchanges passes it: the same
+    logits, hidden states and keys as from the counter's start."""
+    n, per_step = 40, 5 * sum(mask) + 1
+    prompt = make_prompt(HD64.vocab, n, 93)
+    _, _, ctx, tok = _prefilled(HD64, [prompt], 93)
+    ctx.set_mask(0, mask)
+    fed = torch.tensor([[3], [700], [41]], dtype=torch.int32, device="cuda")
+    lg, outs = torch.zeros(3, 1, HD64.vocab, device="cuda"), {}
+    for back in [0] + list(range(1, 2 * per_step + 2)):
+        ctx.set_option(OPT_SMALL_EPOCH, -back)                  # 2^32 - back
+        ctx.set_seq_len(0, n)
+        lg.zero_()
+        for t, out in zip(fed, lg):
+            ctx.decode_step(t, out, tok)
+        ctx.sync()
+        outs[back] = (lg.clone(), ctx.get_hidden().clone(), torch.stack(ctx.kv_read(0, 1, n, 3)))
+        assert all(torch.equal(a, b) for a, b in zip(outs[back], outs[0])), back
     ctx.close()
 
 
