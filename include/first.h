@@ -56,7 +56,12 @@ extern "C" {
                                       kernels; 0: always per-op kernels; 1: persistent kernel (bf16) or error.
                                       When device memory allows, first_create gives the persistent kernel a copy of every
                                       layer's down-projection matrix with permuted columns (as much memory again as those
-                                      matrices); the caller's matrices must then not change after first_create. */
+                                      matrices); the caller's matrices must then not change after first_create.
+                                      The persistent kernel needs every compute unit: the library runs the persistent steps of
+                                      a process's contexts on one device one after the other, whatever their streams and host
+                                      threads (events between the streams; none while all contexts share one).  Steps that a
+                                      caller captures into a graph of their own, and those of other processes on the same
+                                      device, are the caller's to keep apart. */
 
 #define FIRST_OPT_STEP_TIMING   4  /* 1: the persistent kernel records per-phase timestamps (first_step_timing) */
 #define FIRST_OPT_BATCH_TILED   9  /* batched decode: 1 (default when max_batch > 1 and device memory allows) = the mat-vecs

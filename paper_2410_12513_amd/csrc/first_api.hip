@@ -14,6 +14,7 @@
 #include "decode_kernels.h"
 #include "prefill_kernels.h"
 #include "step_kernel.h"
+#include "step_order.h"
 #include "small_step.h"
 #include "prefill_gemm.h"
 #include "prefill_attn.h"
@@ -39,6 +40,28 @@ namespace {
 
 thread_local std::string g_create_error;
 
+struct HipOrderApi {
+  using Stream = hipStream_t;
+  using Event = hipEvent_t;
+  using Error = hipError_t;
+  static Error make(Event* e) { return hipEventCreateWithFlags(e, hipEventDisableTiming); }
+  static Error record(Event e, Stream s) { return hipEventRecord(e, s); }
+  static Error wait(Stream s, Event e) { return hipStreamWaitEvent(s, e, 0); }
+  static bool capturing(Stream s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone;
+  }
+};
+using HipOrder = StepOrder<HipOrderApi>;
+// The current device's order of persistent steps.  (Never destroyed: contexts may go after the statics of this library.)
+HipOrder* step_order() {
+  static std::mutex* mutex = new std::mutex;
+  static auto* orders = new std::map<int, HipOrder>;
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return nullptr;
+  std::lock_guard<std::mutex> lock(*mutex);
+  return &(*orders)[dev];
+}
 
 struct LayerPtrs {
   const void *wq, *wk, *wv, *wo, *wg, *wu, *wd;
@@ -133,6 +156,7 @@ struct first_ctx {
   unsigned long long* d_tdbg = nullptr;   // step-kernel timestamps (FIRST_OPT_STEP_TIMING)
   int step_timing = 0;
   bool step_ok = false;        // geometry fits the persistent kernel
+  HipOrder* order = nullptr;   // the device's order of such steps, where this context is part of it
   // whole step of a small fp32 model as one kernel a sequence: workgroups (0: does not fit), its exchange and its last epoch
   int small_wgs = 0;
   ss_word* d_small = nullptr;
@@ -1363,6 +1387,15 @@ int first_create(const first_model_desc* desc, const first_weights* w, void* hip
     delete c;
     return rc;
   }
+  if (c->step_ok) {
+    HipOrder* order = step_order();
+    const hipError_t e = order ? order->join(c->stream) : hipErrorInvalidDevice;
+    if (e != hipSuccess) {
+      first_destroy(c);
+      return fail(nullptr, FIRST_ERR_HIP, std::string("first_create: order of the persistent steps: ") + hipGetErrorString(e));
+    }
+    c->order = order;
+  }
   c->hlen.assign(B, 0); c->decoded.assign(B, 0); c->seq_npages.assign(B, 0);
   c->hmask.assign(B, std::vector<uint8_t>(L, 0));
   c->h_page_table.assign((size_t)B * c->max_pages, 0);
@@ -1376,6 +1409,7 @@ int first_create(const first_model_desc* desc, const first_weights* w, void* hip
 int first_destroy(first_ctx* c) {
   if (!c) return FIRST_ERR_ARG;
   (void)hipStreamSynchronize(c->stream);
+  if (c->order) c->order->leave(c->stream);
   drop_graphs(c);
   for (void* p : c->allocs) (void)hipFree(p);
   if (c->h_keep) (void)hipHostFree(c->h_keep);
@@ -1513,13 +1547,13 @@ int decode_step_impl(first_ctx* c, const int32_t* last_tokens, float* logits_out
                     smp->candidates_out);
   };
   // A small model's step of one launch goes out as one: 6.7 us between two of them, against 13 between replays of a graph with one node.
-  // The persistent kernel stays a graph: it needs every compute unit, so two of them (contexts on streams of their own) must not be
-  // dispatched together, and two launches that follow each other within a few us, behind the same event, are: a wait in one gave up.
   const bool one_launch = small && c->B == 1 && !smp;
-  if (!c->use_graph || one_launch) {
-    enqueue();
-    HIPCHK(c, hipGetLastError());
-  } else {
+  auto launch = [&]() -> int {
+    if (!c->use_graph || one_launch) {
+      enqueue();
+      HIPCHK(c, hipGetLastError());
+      return FIRST_OK;
+    }
     // the whole-step kernels read the kept list from the device: one graph whatever the mask
     const int kind = persistent ? -1 : small ? -1 - c->B : batched ? S + 1000 : S;
     std::string key(reinterpret_cast<const char*>(&kind), sizeof(kind));
@@ -1559,7 +1593,14 @@ int decode_step_impl(first_ctx* c, const int32_t* last_tokens, float* logits_out
     }
     it->second.used = ++c->graph_clock;
     HIPCHK(c, hipGraphLaunch(it->second.exec, c->stream));
-  }
+    return FIRST_OK;
+  };
+  // persistent steps of a device one after the other; a capture only while no other context places an event on this stream
+  int rc = FIRST_OK;
+  if (!c->order) rc = launch();
+  else if (!persistent) rc = c->order->hold(launch);
+  else HIPCHK(c, c->order->run(c->stream, [&]() { rc = launch(); return hipSuccess; }));
+  if (rc) return rc;
   for (int b = 0; b < c->B; ++b) { c->hlen[b] += 1; c->decoded[b] = 1; }
   return FIRST_OK;
 }
