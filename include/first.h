@@ -59,7 +59,8 @@ extern "C" {
                                       matrices); the caller's matrices must then not change after first_create.
                                       The persistent kernel needs every compute unit: the library runs the persistent steps of
                                       a process's contexts on one device one after the other, whatever their streams and host
-                                      threads (events between the streams; none while all contexts share one).  Steps that a
+                                      threads (events between the streams; none while all contexts share one).  Whole-step
+                                      kernels of small fp32 models run beside them, four at a time.  Steps that a
                                       caller captures into a graph of their own, and those of other processes on the same
                                       device, are the caller's to keep apart. */
 

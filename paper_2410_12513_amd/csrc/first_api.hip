@@ -52,11 +52,12 @@ struct HipOrderApi {
     return hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone;
   }
 };
-using HipOrder = StepOrder<HipOrderApi>;
-// The current device's order of persistent steps.  (Never destroyed: contexts may go after the statics of this library.)
-HipOrder* step_order() {
+using HipOrders = StepOrders<HipOrderApi>;
+// The current device's orders of steps whose workgroups wait for each other.  (Never destroyed: contexts may go after the statics of
+// this library.)
+HipOrders* step_orders() {
   static std::mutex* mutex = new std::mutex;
-  static auto* orders = new std::map<int, HipOrder>;
+  static auto* orders = new std::map<int, HipOrders>;
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return nullptr;
   std::lock_guard<std::mutex> lock(*mutex);
@@ -156,9 +157,9 @@ struct first_ctx {
   unsigned long long* d_tdbg = nullptr;   // step-kernel timestamps (FIRST_OPT_STEP_TIMING)
   int step_timing = 0;
   bool step_ok = false;        // geometry fits the persistent kernel
-  HipOrder* order = nullptr;   // the device's order of such steps, where this context is part of it
   // whole step of a small fp32 model as one kernel a sequence: workgroups (0: does not fit), its exchange and its last epoch
   int small_wgs = 0;
+  HipOrders::Set orders;       // the device's orders that the persistent or small steps go through
   ss_word* d_small = nullptr;
   unsigned* d_small_epoch = nullptr;
   bool zperm = false;          // ... and every layer has its column-permuted copy of the down-projection matrix
@@ -679,6 +680,8 @@ void enqueue_decode_step_kernel(first_ctx* c, const int* tokens, float* logits, 
 // Workgroups of the small-model kernel, 0 where it does not fit: full precision, vectors and rows that its waves hold, contexts short
 // enough for one workgroup a head, and a row of every mat-vec for every workgroup (its exchange counts on that).
 constexpr int SS_WGS = 64;
+constexpr size_t SS_BESIDE_LDS = (160 - 4) * 1024 - SS_MAX_LDS;     // LDS of a persistent kernel that leaves a compute unit room for a workgroup (4 KB: granularity)
+static_assert(ss_lds_floats(SS_MAX_D, SS_MAX_F, SS_MAX_F, 128) * sizeof(float) <= SS_MAX_LDS, "what the limits admit");
 int small_step_wgs(const first_ctx* c) {
   const first_model_desc& d = c->d;
   const int n = std::min(SS_WGS, c->num_cu), k = std::max({d.d_model, c->nq, d.d_ffn});
@@ -686,8 +689,7 @@ int small_step_wgs(const first_ctx* c) {
                     d.d_model <= SS_MAX_D && c->nq <= SS_MAX_F && d.d_ffn <= SS_MAX_F && d.vocab <= SS_MAX_V && d.max_seq_len <= SS_MAX_SEQ &&
                     d.n_q_heads <= n &&
                     std::min({d.d_model, c->nq + 2 * c->nkv, d.d_ffn}) >= n && k >= 2 * n &&
-                    (size_t)c->n_pages * c->page_elems < (size_t)1 << 31 &&
-                    ss_lds_floats(d.d_model, c->nq, d.d_ffn, d.head_dim) * sizeof(float) <= SS_MAX_LDS;
+                    (size_t)c->n_pages * c->page_elems < (size_t)1 << 31;
   return fits ? n : 0;
 }
 size_t small_step_lds(const first_ctx* c) { return ss_lds_floats(c->d.d_model, c->nq, c->d.d_ffn, c->d.head_dim) * sizeof(float); }
@@ -1387,14 +1389,14 @@ int first_create(const first_model_desc* desc, const first_weights* w, void* hip
     delete c;
     return rc;
   }
-  if (c->step_ok) {
-    HipOrder* order = step_order();
-    const hipError_t e = order ? order->join(c->stream) : hipErrorInvalidDevice;
+  if (c->step_ok || c->small_wgs) {
+    const StepKind kind = !c->step_ok ? StepKind::SMALL : c->step_lds <= SS_BESIDE_LDS ? StepKind::PERSISTENT : StepKind::PERSISTENT_NO_ROOM;
+    HipOrders* orders = step_orders();
+    const hipError_t e = orders ? orders->join(kind, c->stream, &c->orders) : hipErrorInvalidDevice;
     if (e != hipSuccess) {
       first_destroy(c);
-      return fail(nullptr, FIRST_ERR_HIP, std::string("first_create: order of the persistent steps: ") + hipGetErrorString(e));
+      return fail(nullptr, FIRST_ERR_HIP, std::string("first_create: order of the decode steps: ") + hipGetErrorString(e));
     }
-    c->order = order;
   }
   c->hlen.assign(B, 0); c->decoded.assign(B, 0); c->seq_npages.assign(B, 0);
   c->hmask.assign(B, std::vector<uint8_t>(L, 0));
@@ -1409,7 +1411,7 @@ int first_create(const first_model_desc* desc, const first_weights* w, void* hip
 int first_destroy(first_ctx* c) {
   if (!c) return FIRST_ERR_ARG;
   (void)hipStreamSynchronize(c->stream);
-  if (c->order) c->order->leave(c->stream);
+  HipOrders::leave(c->orders, c->stream);
   drop_graphs(c);
   for (void* p : c->allocs) (void)hipFree(p);
   if (c->h_keep) (void)hipHostFree(c->h_keep);
@@ -1595,11 +1597,11 @@ int decode_step_impl(first_ctx* c, const int32_t* last_tokens, float* logits_out
     HIPCHK(c, hipGraphLaunch(it->second.exec, c->stream));
     return FIRST_OK;
   };
-  // persistent steps of a device one after the other; a capture only while no other context places an event on this stream
+  // steps whose workgroups wait for each other as the device's orders say; a capture only while no other context places an event on this stream
   int rc = FIRST_OK;
-  if (!c->order) rc = launch();
-  else if (!persistent) rc = c->order->hold(launch);
-  else HIPCHK(c, c->order->run(c->stream, [&]() { rc = launch(); return hipSuccess; }));
+  auto step = [&]() { rc = launch(); return hipSuccess; };
+  if (persistent || small) HIPCHK(c, HipOrders::run(c->orders, c->stream, step));
+  else (void)HipOrders::hold(c->orders, step);
   if (rc) return rc;
   for (int b = 0; b < c->B; ++b) { c->hlen[b] += 1; c->decoded[b] = 1; }
   return FIRST_OK;

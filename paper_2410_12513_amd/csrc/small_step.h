@@ -10,7 +10,7 @@
 //
 // A word is never overwritten before everyone has read it: each vector is written again one layer later, by workgroups that have
 // seen complete vectors since to which EVERY workgroup contributed after reading this one (each owns at least one row
-// of each mat-vec, see small_step_fits).  The residual h is written twice a layer; the MLP's activation lies between, and attention's
+// of each mat-vec, see small_step_wgs).  The residual h is written twice a layer; the MLP's activation lies between, and attention's
 // output before.
 //
 // Weights of a wave's first rows are requested before it waits for the vector they are multiplied with; the keys and values of a wave's
@@ -26,9 +26,13 @@ constexpr int SS_CH = 4;                 // 1 KB pieces of a row (256 elements) 
 // 107.8 / 92.4, 4000 142 / 156 (one workgroup a head walks the keys); 512 / 1536 at 30 tokens 89.9 / 67.5, 2000 141 / 126; 1024 / 2816 120.5 / 120.5
 // and 1024 / 4096 183 / 248 (64 compute units read 4.2 TB/s, the others' share is missed).
 constexpr int SS_MAX_D = 512, SS_MAX_F = 2048, SS_MAX_SEQ = 2048, SS_MAX_V = 16384;
-// Four waves, 128 registers and at most 44 KB of LDS: 64 such workgroups find room beside a persistent kernel that holds every compute unit,
-// and beside the same of three other queues, so that kernels whose workgroups wait for each other never wait for each other's places.
-constexpr size_t SS_MAX_LDS = 44 * 1024;
+// Four waves, 128 registers and at most 23 KB of LDS: one such workgroup fits on a compute unit beside one of the persistent kernel (eight waves
+// of at most 192 registers, up to 133 KB), so 256 of them, four steps, find room beside a persistent kernel that holds every compute
+// unit.  Kernels whose workgroups wait for each other then never wait for each other's places; step_order.h sees to the four, and to persistent
+// kernels that take more LDS; the build refuses more registers of either kernel.  The compiler keeps to 128 registers by spilling (236 bytes of scratch
+// a lane at 64 dims a head, 228 at 128; its own loads, none of them in flight); 512 threads and 254 registers spill nothing and took 33 us
+// a step instead of 36.5, but left no room.
+constexpr size_t SS_MAX_LDS = 23 * 1024;
 typedef unsigned long long ss_word;
 
 struct SmallStep {
@@ -40,7 +44,7 @@ struct SmallStep {
   unsigned* epoch;                       // the last epoch of the launches before
   int* err;
 };
-__host__ __device__ inline size_t ss_lds_floats(int D, int nq, int F, int hd) {
+__host__ __device__ constexpr size_t ss_lds_floats(int D, int nq, int F, int hd) {
   const int k = D > nq ? (D > F ? D : F) : (nq > F ? nq : F);
   return (size_t)D + 2 * k + 2 * SS_WAVES + 4 * hd + SS_WAVES * (hd + 2) + 2 * SS_WAVES + 4;
 }

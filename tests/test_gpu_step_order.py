@@ -1,12 +1,13 @@
-"""Contexts on streams of their own whose decode steps hold the whole chip: steps enqueued a few microseconds behind each other, without a
-synchronisation between them, give each context the bits that it has alone."""
+"""Contexts on streams of their own whose decode steps wait between workgroups: steps enqueued a few microseconds behind each other, without a
+synchronisation between them, give each context the bits that it has alone.  Persistent steps need the whole chip, those of small fp32 models
+64 places beside them, or, where a persistent kernel's LDS leaves none, the chip without it."""
 import threading
 
 import pytest
 import torch
 
 import paper_2410_12513_amd as P
-from synth import CONFIGS, make_prompt, make_router, make_weights
+from synth import CONFIGS, ModelDesc, make_prompt, make_router, make_weights
 from synth.generators import to_device
 
 pytestmark = pytest.mark.gpu
@@ -15,11 +16,16 @@ torch.set_grad_enabled(False)
 STEPS, PROMPT = 60, 90
 
 
+SMALL = ModelDesc(3, 256, 4, 2, 64, 696, 1001, dtype="fp32")
+NO_ROOM = ModelDesc(1, 2048, 128, 32, 128, 14336, 1000, dtype="bf16")        # 146 KB of LDS a workgroup
+
+
 def _context(model, seed, stream=None):
-    desc = CONFIGS[model]
+    desc = model if isinstance(model, ModelDesc) else CONFIGS[model]
     ctx = P.FirstContext(desc, to_device(make_weights(desc, seed), "cuda"), make_router(desc, seed).cuda(), max_batch=1,
                          max_seq_len=PROMPT + STEPS + 1, stream=stream)
-    ctx.set_option(3, 1)                                # the persistent kernel or an error
+    if desc.dtype == "bf16":
+        ctx.set_option(3, 1)                            # the persistent kernel or an error
     tok = torch.zeros(1, dtype=torch.int32, device="cuda")
     prompt = make_prompt(desc.vocab, PROMPT, seed).cuda()
     torch.cuda.synchronize()
@@ -38,8 +44,10 @@ def _steps(ctx, tok, hist, use_graph):
 
 @pytest.mark.parametrize("use_graph", [1, 0])
 @pytest.mark.parametrize("streams", ["private", "caller's", "threads"])
-def test_steps_of_contexts_on_different_streams(use_graph, streams):
-    models = [("step_hd128", 21), ("step_hd64", 22), ("step_hd128", 23)]
+@pytest.mark.parametrize("models", [[("step_hd128", 21), ("step_hd64", 22), ("step_hd128", 23)],
+                                    [("step_hd128", 21)] + [(SMALL, 30 + i) for i in range(6)],
+                                    [(NO_ROOM, 26), (SMALL, 30), (SMALL, 31), ("step_hd64", 22)]], ids=["persistent", "beside", "no room"])
+def test_steps_of_contexts_on_different_streams(use_graph, streams, models):
     alone = []
     for model, seed in models:
         ctx, tok, hist = _context(model, seed)

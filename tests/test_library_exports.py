@@ -61,3 +61,19 @@ b.h:20:1: remark:     VGPRs Spill: 89 [-Rpass-analysis=kernel-resource-usage]
     assert r["_ZN5first6k_stepILi128ELb1EEEvNS_10StepParamsE"] == {"vgprs": 233, "scratch": 0, "spills": 0}
     assert r["_ZN5first8k_gateupINS_4bf16EEEvNS_9DecParamsE"] == {"vgprs": 64, "scratch": 288, "spills": 89}
     assert B.SCRATCH_LIMITS["k_step"] == 0 and B.SCRATCH_LIMITS["k_attn_mfma_b"] == 0
+
+
+@pytest.mark.parametrize("kernel,use,said", [
+    ("_ZN5first6k_stepILi128EEEvNS_10StepParamsE", {"vgprs": 192, "agprs": 0, "scratch": 0}, None),
+    ("_ZN5first6k_stepILi128EEEvNS_10StepParamsE", {"vgprs": 193, "agprs": 0, "scratch": 0}, "193 registers"),
+    ("_ZN5first6k_stepILi128EEEvNS_10StepParamsE", {"vgprs": 128, "agprs": 72, "scratch": 0}, "200 registers"),
+    ("_ZN5first6k_stepILi128EEEvNS_10StepParamsE", {"vgprs": 128, "agprs": 0, "scratch": 4}, "scratch"),
+    ("_ZN5first12k_small_stepILi64EEEvNS_9SmallStepE", {"vgprs": 128, "agprs": 0, "scratch": 236}, None),
+    ("_ZN5first12k_small_stepILi64EEEvNS_9SmallStepE", {"vgprs": 136, "agprs": 0, "scratch": 0}, "136 registers"),
+    ("_ZN5first12k_small_stepILi64EEEvNS_9SmallStepE", {"vgprs": 128, "agprs": 0, "scratch": 244}, "scratch"),
+    ("_ZN5first9k_gateupINS_4bf16EEEvNS_9DecParamsE", {"vgprs": 250, "agprs": 6, "scratch": 288}, None)])
+def test_build_limits_registers_of_the_kernels_that_must_fit_beside_each_other(kernel, use, said):
+    from paper_2410_12513_amd import build as B
+    over = B.over_limits({kernel: use})
+    assert not over if said is None else len(over) == 1 and said in over[0]
+    assert 2 * B.REGISTER_LIMITS["k_step"] + B.REGISTER_LIMITS["k_small_step"] <= 512
