@@ -592,7 +592,7 @@ void enqueue_decode_batched(first_ctx* c, const int* tokens, float* logits, int*
       if (tiles_attn && shared_attn && c->attn_splits <= 0) {
         // work list: splits in proportion to each sequence's length - the fewest tiles per workgroup for which the batch
         // still fits one round of the compute units at today's lengths (a cached graph keeps the list while the
-        // sequences grow: their splits just get longer).  Up to ten tiles are not split: walking them takes no longer than the
+        // sequences grow, within the bounds that decode_step_impl puts into its key: their splits just get longer).  Up to ten tiles are not split: walking them takes no longer than the
         // splits' meeting (8B, two sequences of 200 keys 634 -> 614 us a step of four layers, six of 100..600 658 -> 640)
         const int min_sp = ((d.max_seq_len + 64) / 64 * 4 + AS_PT - 1) / AS_PT;    // a split's page ids fit the LDS table
         int sp[BATCH_SLOTS];
@@ -1503,9 +1503,10 @@ int decode_step_impl(first_ctx* c, const int32_t* last_tokens, float* logits_out
     if (c->hlen[b] + 1 > c->d.max_seq_len) return fail(c, FIRST_ERR_CAPACITY, "first_decode_step: sequence is full");
     max_len = std::max(max_len, c->hlen[b]);
   }
+  constexpr int S_GRAPH_MAX = 32;
   int S = c->attn_splits;
   if (S <= 0) S = (max_len + 128 + 127) / 128;
-  S = std::max(1, std::min(S, 32));
+  S = std::max(1, std::min(S, S_GRAPH_MAX));
   const bool bf = c->d.dtype == FIRST_DTYPE_BF16;
   const bool persistent = c->step_ok && c->B == 1 && c->decode_path != 0;
   const bool small = c->small_wgs > 0 && c->decode_path != 0;
@@ -1565,6 +1566,16 @@ int decode_step_impl(first_ctx* c, const int32_t* last_tokens, float* logits_out
     if (smp) key.append(reinterpret_cast<const char*>(smp), sizeof(*smp));      // (pointers and values are part of the captured arguments)
     if (!persistent && !small)
       for (int b = 0; b < c->B; ++b) key.append(reinterpret_cast<const char*>(c->hmask[b].data()), c->hmask[b].size());
+    // The attention's split list and kernel are chosen from the lengths when a graph is made.  S renews it every 128 tokens of the longest
+    // sequence; once S stands at its limit, each sequence does when it passes the lengths up to which it is not split (6 or 10 tiles of 64 keys,
+    // see enqueue_decode_batched) and twice, four times ... the latter: a capture per doubling.
+    if (batched && c->attn_splits <= 0 && S == S_GRAPH_MAX)
+      for (int b = 0; b < c->B; ++b) {
+        const long long tiles = c->hlen[b] / 64 + 1;
+        char grown = tiles > 6;
+        for (long long edge = 10; tiles > edge; edge *= 2) ++grown;
+        key.push_back(grown);
+      }
     auto it = c->graphs.find(key);
     if (it == c->graphs.end()) {
       if (c->graphs.size() >= 32) {

@@ -197,3 +197,31 @@ def test_mat_vec_epilogue_of_four_eight_and_sixteen_slots(d_model, monkeypatch):
     monkeypatch.setitem(CONFIGS, "slots", ModelDesc(5, d_model, 4, 2, 64, 520, 600))
     masks = [[1, int(b < 4), int(b > 3), int(b != 4), 1] for b in range(9)]
     _run("slots", [3 + 7 * b for b in range(9)], 3, 61, masks=masks)
+
+
+@pytest.mark.parametrize("model,edge", [("step_hd128", 640), ("step_hd64", 640), ("step_g2", 384)])
+def test_a_short_sequence_that_outgrows_its_one_workgroup_beside_a_long_one(model, edge):
+    """Beside 3910 keys the cached graph of a step serves all further ones.  A sequence that one workgroup a KV head walks when the graph is made
+    is split (its layers alone: walked by the other kernel) from `edge` keys on, as where the graphs are dropped there."""
+    desc, n, steps = CONFIGS[model], [3910, edge - 10], 20
+    prompts = [make_prompt(desc.vocab, k, 98 + k) for k in n]
+    fed = [torch.tensor([7 + s, 400 + s], dtype=torch.int32, device="cuda") for s in range(steps)]
+    hist = []
+    for drop in (False, True):
+        _, _, _, ctx = build(model, 98, max_batch=2, max_seq_len=4000)
+        ctx.set_option(OPT_BATCH_PATH, 1)
+        _prefill(ctx, desc, prompts)
+        ctx.set_mask(0, [1] + [0] * (desc.n_layers - 1))          # the other layers are the short sequence's alone
+        ctx.set_mask(1, [1] * desc.n_layers)
+        lg, tk, tin = torch.zeros(2, desc.vocab, device="cuda"), torch.zeros(2, dtype=torch.int32, device="cuda"), fed[0].clone()
+        hist.append([])
+        for s, t in enumerate(fed):
+            if drop and s == 10:
+                ctx.set_option(9, 1)
+            tin.copy_(t)
+            ctx.decode_step(tin, lg, tk)                           # (the same buffers: one graph as long as its key stays)
+            ctx.sync()
+            hist[-1].append(lg.clone())
+        ctx.close()
+    for s, (a, b) in enumerate(zip(*hist)):
+        assert torch.equal(a, b), s
