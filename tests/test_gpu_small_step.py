@@ -4,6 +4,7 @@ waves' rounds, pages of other sizes, masks, batches, and a wait that gives up.""
 import pytest
 import torch
 
+import paper_2410_12513_amd as P
 from oracle import first_oracle as O
 from synth import make_prompt
 from synth.generators import ModelDesc
@@ -16,7 +17,8 @@ HD64 = ModelDesc(3, 256, 4, 2, 64, 696, 1001, dtype="fp32")
 HD128 = ModelDesc(3, 512, 4, 1, 128, 1032, 500, dtype="fp32")
 WIDE = ModelDesc(3, 512, 8, 8, 64, 2048, 77, dtype="fp32")
 NARROW = ModelDesc(3, 72, 2, 1, 64, 96, 67, dtype="fp32")
-OPT_DECODE_PATH, OPT_SMALL_EPOCH = 3, 11
+VOCAB = ModelDesc(2, 256, 4, 2, 64, 696, 16384, dtype="fp32")
+OPT_DECODE_PATH, OPT_STEP_POLL_LIMIT, OPT_SMALL_EPOCH = 3, 10, 11
 
 
 def _prefilled(desc, prompts, seed, page=16, room=16, path=-1, max_seq_len=None):
@@ -28,10 +30,25 @@ def _prefilled(desc, prompts, seed, page=16, room=16, path=-1, max_seq_len=None)
     return w, r, ctx, tok
 
 
+def _waits_between_workgroups(ctx, tok):
+    """Does a step of this context take the whole-step kernel?  Only that one has waits that a poll limit of 0 makes give up."""
+    ctx.set_option(OPT_STEP_POLL_LIMIT, 0)
+    ctx.decode_step(tok, None, tok.clone())
+    try:
+        ctx.sync()
+    except P.FirstError as e:
+        assert e.code == -4 and "gave up" in str(e)
+        return True
+    ctx.set_option(OPT_STEP_POLL_LIMIT, -1)
+    return False
+
+
 @pytest.mark.parametrize("desc,n,mask,page,max_seq_len", [
     (HD64, 1, [1, 1, 1], 16, None), (HD64, 30, [1, 0, 1], 16, None), (HD64, 127, [1, 1, 1], 16, None), (HD64, 290, [0, 1, 1], 24, None),
     (HD128, 14, [1, 1, 1], 16, None), (HD128, 63, [1, 0, 1], 8, None), (HD128, 140, [1, 1, 0], 16, None), (WIDE, 40, [1, 1, 1], 16, None),
-    (NARROW, 33, [1, 1, 1], 16, None), (HD64, 20, [0, 0, 0], 16, None), (HD64, 20, [1, 1, 1], 16, 2056)])
+    (NARROW, 33, [1, 1, 1], 16, None), (HD64, 20, [0, 0, 0], 16, None), (HD64, 20, [1, 1, 1], 16, 2056),
+    (HD64, 2040, [1, 1, 1], 16, 2048), (HD128, 2040, [0, 1, 1], 16, 2048), (VOCAB, 25, [1, 1], 16, None),
+    (VOCAB.with_(vocab=16385), 25, [1, 1], 16, None)])
 def test_steps_match_the_oracle_and_the_per_op_kernels(desc, n, mask, page, max_seq_len):
     prompt = make_prompt(desc.vocab, n, 91)
     w, r, ctx, tok = _prefilled(desc, [prompt], 91, page, max_seq_len=max_seq_len)
@@ -62,6 +79,9 @@ def test_steps_match_the_oracle_and_the_per_op_kernels(desc, n, mask, page, max_
     for i, keep in enumerate(mask):
         for a, b in zip(ctx.kv_read(0, i, 0, n + 6 if keep else n), ops.kv_read(0, i, 0, n + 6 if keep else n)):
             assert float((a - b).norm()) <= 1e-5 * float(b.norm())
+    if any(mask):                                       # (without a layer only one workgroup waits, for the others' candidates)
+        assert _waits_between_workgroups(ctx, fed) == ((max_seq_len or 0) <= 2048 and desc.vocab <= 16384)
+    assert not _waits_between_workgroups(ops, fed)
     ctx.close(), ops.close()
 
 
@@ -114,13 +134,12 @@ def test_the_exchange_counter_passes_its_largest_value(mask):
 
 def test_a_wait_that_gives_up_ends_the_launch_and_is_reported_once():
     """A poll limit of 0, set from the host: every first unsuccessful poll gives up and every workgroup leaves."""
-    import paper_2410_12513_amd as P
     prompt = make_prompt(HD64.vocab, 50, 94)
     outs = []
     for provoke in (False, True):
         _, _, ctx, tok = _prefilled(HD64, [prompt], 94)
         if provoke:
-            ctx.set_option(10, 0)
+            ctx.set_option(OPT_STEP_POLL_LIMIT, 0)
             ctx.decode_step(tok, None, tok.clone())
             with pytest.raises(P.FirstError) as e:
                 ctx.sync()
