@@ -72,7 +72,7 @@ extern "C" {
 #define FIRST_OPT_PREFILL_ATTN  7  /* prompt attention.  1 (default): tiled kernel on the matrix cores when the cache is bf16
                                       and head_dim is 64 or 128, else the plain kernel; 0: always the plain fp32 kernel */
 #define FIRST_OPT_STEP_POLL_LIMIT 10 /* test tap: value >= 0 = the number of unsuccessful polls after which a wait between workgroups of
-                                      the persistent kernel gives up (default, or -1: 2^21, seconds).  With 0 the next decode step
+                                      the persistent kernel, or of the small fp32 models', gives up (default, or -1: 2^21, seconds).  With 0 the next decode step
                                       gives up at its first exchange: every wave leaves at its next wait, nothing hangs, and the next
                                       call that synchronises (first_sync, first_seq_len, ...) returns FIRST_ERR_HIP, clears the limit
                                       and resets the exchange state; the live sequences must be prefilled again.  Synchronises. */

@@ -1568,7 +1568,8 @@ int decode_step_impl(first_ctx* c, const int32_t* last_tokens, float* logits_out
       for (int b = 0; b < c->B; ++b) key.append(reinterpret_cast<const char*>(c->hmask[b].data()), c->hmask[b].size());
     // The attention's split list and kernel are chosen from the lengths when a graph is made.  S renews it every 128 tokens of the longest
     // sequence; once S stands at its limit, each sequence does when it passes the lengths up to which it is not split (6 or 10 tiles of 64 keys,
-    // see enqueue_decode_batched) and twice, four times ... the latter: a capture per doubling.
+    // see enqueue_decode_batched) and twice, four times ... the latter: a capture per doubling.  (8B heads, four layers, 8000 and 500 keys after 2600
+    // steps: 694 us a step with the lists of the start, 633 so; 3B heads 510 / 452.)
     if (batched && c->attn_splits <= 0 && S == S_GRAPH_MAX)
       for (int b = 0; b < c->B; ++b) {
         const long long tiles = c->hlen[b] / 64 + 1;

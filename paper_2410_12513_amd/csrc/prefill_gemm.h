@@ -185,8 +185,8 @@ __global__ void __launch_bounds__(WGM * WGN * 64, 2) k_pgemm(PgArgs P) {
     for (int i = 0; i < IM; ++i) fa[buf][0][i] = *reinterpret_cast<const bf16x8_t*>(base + oa[k] + i * 32 * RB);
   };
   auto mfma = [&](int buf) __attribute__((always_inline)) {
-    // low halves before high halves, two products into the same accumulator never back to back; with two row blocks a weight
-    // fragment's products follow each other (up to 4 % over products by row block: each fragment is needed later)
+    // low halves before high halves; two products into the same accumulator are not back to back except where a wave has only one (32 x 128
+    // tiles); with two row blocks a weight fragment's products follow each other (up to 4 % over products by row block: each fragment is needed later)
     if constexpr (IM > 1) {
 #pragma unroll
       for (int j = 0; j < JN; ++j)

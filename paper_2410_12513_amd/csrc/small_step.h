@@ -2,7 +2,7 @@
 //
 // What bounds such a step is latency: five dependent mat-vecs and an attention per layer over weights that a few dozen
 // compute units read in a microsecond, so that a launch per op spends its time starting and draining (two layers of 256 x 688, 30
-// tokens: 61 us a step in 12 launches, 37.6 here, 36.5 of them in the kernel: some 2.5 us an exchange).  The workgroups stay and hand vectors to each other through memory:
+// tokens: 61 us a step in 12 launches, 37.6 here, 36.5 of them in the kernel: 11 exchanges of 3.3 us with the work between them).  The workgroups stay and hand vectors to each other through memory:
 // every element travels as a 64-bit word {value, epoch}, stored at once; whoever needs the vector loads it until all its words carry the
 // epoch it waits for.  Within a launch every vector has the next epoch, and the last one of a launch is kept in device memory for the
 // launch that follows.  No vector ever has epoch 0: a launch whose epochs would not all lie below 2^32 begins again at 1 (after hours of

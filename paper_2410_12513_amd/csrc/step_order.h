@@ -3,7 +3,8 @@
 // The persistent step kernel (step_kernel.h) needs every compute unit.  Two of them at once - contexts on streams of their own - would each
 // hold compute units that the other needs until a wait gives up, so a device's steps of that kind run one after the other: a step waits
 // for an event behind the latest one on another stream, and leaves an event behind itself.  As long as all such contexts of a device share one
-// stream (one context: always) the stream does that, and no event is recorded or waited for.
+// stream (one context: always) the stream does that, and no event is recorded or waited for.  (A step of the 1B shape, 520 us, takes 5 us longer
+// with the event, 11 where two contexts take turns.)
 //
 // The whole-step kernel of small fp32 models (small_step.h) waits between its 64 workgroups too, but needs little: a persistent kernel on
 // every compute unit leaves each of them room for one such workgroup, so four of these steps always find their places, whatever else
