@@ -58,8 +58,8 @@ using HipOrders = StepOrders<HipOrderApi>;
 HipOrders* step_orders() {
   static std::mutex* mutex = new std::mutex;
   static auto* orders = new std::map<int, HipOrders>;
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return nullptr;
+  int dev = -1;                                       // (no device: nothing will be launched either)
+  (void)hipGetDevice(&dev);
   std::lock_guard<std::mutex> lock(*mutex);
   return &(*orders)[dev];
 }
@@ -159,7 +159,8 @@ struct first_ctx {
   bool step_ok = false;        // geometry fits the persistent kernel
   // whole step of a small fp32 model as one kernel a sequence: workgroups (0: does not fit), its exchange and its last epoch
   int small_wgs = 0;
-  HipOrders::Set orders;       // the device's orders that the persistent or small steps go through
+  HipOrders* device_orders = nullptr;     // of steps whose workgroups wait for each other ...
+  HipOrders::Set orders;                  // ... those that this context's go through (from its first one on)
   ss_word* d_small = nullptr;
   unsigned* d_small_epoch = nullptr;
   bool zperm = false;          // ... and every layer has its column-permuted copy of the down-projection matrix
@@ -1251,6 +1252,7 @@ int first_create(const first_model_desc* desc, const first_weights* w, void* hip
     c->own_stream = true;
   }
   c->num_cu = device_cus();
+  c->device_orders = step_orders();
   c->embed = w->embed; c->lm_head = w->lm_head; c->g_final = w->final_norm; c->router = w->router;
   c->layers.resize(d.n_layers);
   for (int i = 0; i < d.n_layers; ++i) {
@@ -1389,15 +1391,6 @@ int first_create(const first_model_desc* desc, const first_weights* w, void* hip
     delete c;
     return rc;
   }
-  if (c->step_ok || c->small_wgs) {
-    const StepKind kind = !c->step_ok ? StepKind::SMALL : c->step_lds <= SS_BESIDE_LDS ? StepKind::PERSISTENT : StepKind::PERSISTENT_NO_ROOM;
-    HipOrders* orders = step_orders();
-    const hipError_t e = orders ? orders->join(kind, c->stream, &c->orders) : hipErrorInvalidDevice;
-    if (e != hipSuccess) {
-      first_destroy(c);
-      return fail(nullptr, FIRST_ERR_HIP, std::string("first_create: order of the decode steps: ") + hipGetErrorString(e));
-    }
-  }
   c->hlen.assign(B, 0); c->decoded.assign(B, 0); c->seq_npages.assign(B, 0);
   c->hmask.assign(B, std::vector<uint8_t>(L, 0));
   c->h_page_table.assign((size_t)B * c->max_pages, 0);
@@ -1411,7 +1404,7 @@ int first_create(const first_model_desc* desc, const first_weights* w, void* hip
 int first_destroy(first_ctx* c) {
   if (!c) return FIRST_ERR_ARG;
   (void)hipStreamSynchronize(c->stream);
-  HipOrders::leave(c->orders, c->stream);
+  c->device_orders->leave(c->orders, c->stream);
   drop_graphs(c);
   for (void* p : c->allocs) (void)hipFree(p);
   if (c->h_keep) (void)hipHostFree(c->h_keep);
@@ -1551,12 +1544,8 @@ int decode_step_impl(first_ctx* c, const int32_t* last_tokens, float* logits_out
   };
   // A small model's step of one launch goes out as one: 6.7 us between two of them, against 13 between replays of a graph with one node.
   const bool one_launch = small && c->B == 1 && !smp;
-  auto launch = [&]() -> int {
-    if (!c->use_graph || one_launch) {
-      enqueue();
-      HIPCHK(c, hipGetLastError());
-      return FIRST_OK;
-    }
+  hipGraphExec_t replay = nullptr;
+  if (c->use_graph && !one_launch) {
     // the whole-step kernels read the kept list from the device: one graph whatever the mask
     const int kind = persistent ? -1 : small ? -1 - c->B : batched ? S + 1000 : S;
     std::string key(reinterpret_cast<const char*>(&kind), sizeof(kind));
@@ -1590,14 +1579,17 @@ int decode_step_impl(first_ctx* c, const int32_t* last_tokens, float* logits_out
       }
       hipGraph_t graph = nullptr;
       hipGraphExec_t exec = nullptr;
-      HIPCHK(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
-      enqueue();
-      const hipError_t e_launch = hipGetLastError();
-      const hipError_t e_end = hipStreamEndCapture(c->stream, &graph);      // (also what abandons a capture that went wrong)
-      if (e_launch != hipSuccess || e_end != hipSuccess) {
+      const hipError_t e_capture = c->device_orders->hold([&]() {
+        hipError_t e = hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal);
+        if (e != hipSuccess) return e;
+        enqueue();
+        e = hipGetLastError();
+        const hipError_t e_end = hipStreamEndCapture(c->stream, &graph);      // (also what abandons a capture that went wrong)
+        return e != hipSuccess ? e : e_end;
+      });
+      if (e_capture != hipSuccess) {
         if (graph) (void)hipGraphDestroy(graph);
-        return fail(c, FIRST_ERR_HIP, std::string("first_decode_step: graph capture: ") +
-                                          hipGetErrorString(e_launch != hipSuccess ? e_launch : e_end));
+        return fail(c, FIRST_ERR_HIP, std::string("first_decode_step: graph capture: ") + hipGetErrorString(e_capture));
       }
       const hipError_t e_inst = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
       (void)hipGraphDestroy(graph);
@@ -1606,15 +1598,22 @@ int decode_step_impl(first_ctx* c, const int32_t* last_tokens, float* logits_out
       it = c->graphs.emplace(key, first_ctx::CachedGraph{exec, 0}).first;
     }
     it->second.used = ++c->graph_clock;
-    HIPCHK(c, hipGraphLaunch(it->second.exec, c->stream));
-    return FIRST_OK;
+    replay = it->second.exec;
+  }
+  auto launch = [&]() {
+    if (replay) return hipGraphLaunch(replay, c->stream);
+    enqueue();
+    return hipGetLastError();
   };
-  // steps whose workgroups wait for each other as the device's orders say; a capture only while no other context places an event on this stream
-  int rc = FIRST_OK;
-  auto step = [&]() { rc = launch(); return hipSuccess; };
-  if (persistent || small) HIPCHK(c, HipOrders::run(c->orders, c->stream, step));
-  else (void)HipOrders::hold(c->orders, step);
-  if (rc) return rc;
+  if (persistent || small) {
+    if (c->orders.empty()) {
+      const StepKind kind = small ? StepKind::SMALL : c->step_lds <= SS_BESIDE_LDS ? StepKind::PERSISTENT : StepKind::PERSISTENT_NO_ROOM;
+      HIPCHK(c, c->device_orders->join(kind, c->stream, std::max(1, std::min(SMALL_STEP_LANES, c->num_cu / SS_WGS)), &c->orders));
+    }
+    HIPCHK(c, c->device_orders->run(c->orders, c->stream, launch));
+  } else {
+    HIPCHK(c, launch());
+  }
   for (int b = 0; b < c->B; ++b) { c->hlen[b] += 1; c->decoded[b] = 1; }
   return FIRST_OK;
 }

@@ -7,10 +7,12 @@
 // with the event, 11 where two contexts take turns.)
 //
 // The whole-step kernel of small fp32 models (small_step.h) waits between its 64 workgroups too, but needs little: a persistent kernel on
-// every compute unit leaves each of them room for one such workgroup, so four of these steps always find their places, whatever else
-// runs.  They go through four lanes, in each of which steps are ordered as above; contexts are spread over the lanes by their streams, so that
+// every compute unit leaves each of them room for one such workgroup, so four of these steps always find their places on 256 compute units,
+// whatever else runs.  They go through four lanes, in each of which steps are ordered as above; contexts are spread over the lanes by their streams, so that
 // up to four streams see no event.  A persistent kernel of a geometry that takes so much LDS that no workgroup fits beside it is
 // ordered against all lanes.
+//
+// A context belongs to an order from its first such step on: one that decodes batches, or not at all, costs the others nothing.
 //
 // The runtime's calls come in through Api, so that the rule can be run against a model of streams and events without a GPU.
 #pragma once
@@ -21,6 +23,7 @@
 namespace first {
 
 // Api: types Stream, Event, Error; Error{} is success.  make(Event*), record(Event, Stream), wait(Stream, Event): Error; capturing(Stream): bool.
+// One order.  Not safe for several threads by itself: StepOrders holds its lock around every call.
 template <typename Api>
 class StepOrder {
  public:
@@ -30,7 +33,6 @@ class StepOrder {
 
   // A context that launches such steps works on st from now on / no longer (its steps are done).
   Error join(Stream st) {
-    std::lock_guard<std::mutex> lock(mutex);
     Error e{};
     if (!made) { e = Api::make(&event); made = e == Error{}; }
     if (made && streams.size() == 1 && !streams.count(st)) e = mark_latest();      // (its steps so far left no events)
@@ -38,7 +40,6 @@ class StepOrder {
     return e;
   }
   void leave(Stream st) {
-    std::lock_guard<std::mutex> lock(mutex);
     const auto it = streams.find(st);
     if (it == streams.end() || --it->second > 0) return;
     streams.erase(it);
@@ -48,7 +49,6 @@ class StepOrder {
   // other streams cannot be waited for there: the launch goes into the graph as it is, and ordering its replays is up to the caller.
   template <typename F>
   Error run(Stream st, F launch) {
-    std::lock_guard<std::mutex> lock(mutex);
     Error e{};
     const bool alone = streams.size() < 2;
     if (!alone && Api::capturing(st)) return launch();
@@ -61,20 +61,8 @@ class StepOrder {
     has_latest = true; latest = st; marked = false;
     return alone ? e : mark_latest();
   }
-  bool has(Stream st) {
-    std::lock_guard<std::mutex> lock(mutex);
-    return streams.count(st) > 0;
-  }
-  size_t size() {
-    std::lock_guard<std::mutex> lock(mutex);
-    return streams.size();
-  }
-  // f() while no step is being enqueued and no event recorded: the context's own captures, whose stream must not see an event.
-  template <typename F>
-  auto hold(F f) {
-    std::lock_guard<std::mutex> lock(mutex);
-    return f();
-  }
+  bool has(Stream st) const { return streams.count(st) > 0; }
+  size_t size() const { return streams.size(); }
 
  private:
   // The event stands behind the latest step.
@@ -84,8 +72,7 @@ class StepOrder {
     marked = e == Error{};
     return e;
   }
-  std::mutex mutex;
-  std::map<Stream, int> streams;       // of the live contexts, with their number
+  std::map<Stream, int> streams;       // of the contexts, with their number
   Event event{};
   bool made = false, has_latest = false, marked = false;
   Stream latest{};                     // stream of the latest step
@@ -100,16 +87,17 @@ class StepOrders {
  public:
   using Stream = typename Api::Stream;
   using Error = typename Api::Error;
-  using Set = std::vector<StepOrder<Api>*>;           // what a context's steps go through (locks are taken in the order of the members below)
+  using Set = std::vector<StepOrder<Api>*>;           // what a context's steps go through
 
-  // in: the orders of a context of this kind on st; on an error none.
-  Error join(StepKind kind, Stream st, Set* in) {
+  // in: the orders of a context of this kind on st; on an error none.  n_lanes: small steps that find room beside a persistent one (of this
+  // device: the same in every call).
+  Error join(StepKind kind, Stream st, int n_lanes, Set* in) {
     std::lock_guard<std::mutex> lock(mutex);
     Set want;
     if (kind == StepKind::SMALL) {
       StepOrder<Api>* lane = &lanes[0];
-      for (auto& l : lanes)
-        if (!lane->has(st) && (l.has(st) || l.size() < lane->size())) lane = &l;
+      for (int i = 1; i < n_lanes; ++i)
+        if (!lane->has(st) && (lanes[i].has(st) || lanes[i].size() < lane->size())) lane = &lanes[i];
       want = {lane};
     } else {
       if (kind == StepKind::PERSISTENT_NO_ROOM)
@@ -118,26 +106,37 @@ class StepOrders {
     }
     for (StepOrder<Api>* o : want) {
       const Error e = o->join(st);
-      if (e != Error{}) { leave(*in, st); in->clear(); return e; }
+      if (e != Error{}) {
+        for (StepOrder<Api>* joined : *in) joined->leave(st);
+        in->clear();
+        return e;
+      }
       in->push_back(o);
     }
     return Error{};
   }
-  static void leave(const Set& in, Stream st) {
+  void leave(const Set& in, Stream st) {
+    std::lock_guard<std::mutex> lock(mutex);
     for (StepOrder<Api>* o : in) o->leave(st);
   }
   template <typename F>
-  static Error run(const Set& in, Stream st, F& launch, size_t i = 0) {
-    if (i == in.size()) return launch();
-    return in[i]->run(st, [&]() { return run(in, st, launch, i + 1); });
+  Error run(const Set& in, Stream st, F launch) {
+    std::lock_guard<std::mutex> lock(mutex);
+    return run_through(in, st, launch, 0);
   }
+  // f() while no event is recorded: what captures a stream that contexts share, so that none gets into the graph.
   template <typename F>
-  static auto hold(const Set& in, F& f, size_t i = 0) -> decltype(f()) {
-    if (i == in.size()) return f();
-    return in[i]->hold([&]() { return hold(in, f, i + 1); });
+  auto hold(F f) {
+    std::lock_guard<std::mutex> lock(mutex);
+    return f();
   }
 
  private:
+  template <typename F>
+  static Error run_through(const Set& in, Stream st, F& launch, size_t i) {
+    if (i == in.size()) return launch();
+    return in[i]->run(st, [&]() { return run_through(in, st, launch, i + 1); });
+  }
   std::mutex mutex;
   StepOrder<Api> lanes[SMALL_STEP_LANES], persistent;
 };

@@ -35,9 +35,9 @@ int Model::calls, Model::bad;
 using first::StepKind;
 struct Unordered {                               // steps just go out
   using Set = int;
-  int join(StepKind, int, Set*) { return 0; }
-  static void leave(Set, int) {}
-  template <typename F> static int run(Set, int, F& f) { return f(); }
+  int join(StepKind, int, int, Set*) { return 0; }
+  void leave(Set, int) {}
+  template <typename F> int run(Set, int, F f) { return f(); }
 };
 
 struct Step { StepKind kind; int stream; };
@@ -74,7 +74,7 @@ int violations(unsigned seed, int mode) {
     if (contexts.empty() || (what <= 1 && contexts.size() < 9 && !any_captured)) {
       const int s = mode == 1 ? 1 : rng() % (mode == 2 ? 4 : STREAMS), k = rng() % 8;
       Context c{mode == 2 || k < 5 ? StepKind::SMALL : k < 7 ? StepKind::PERSISTENT : StepKind::PERSISTENT_NO_ROOM, s, {}};
-      if (orders.join(c.kind, s, &c.in)) return -1;
+      if (orders.join(c.kind, s, 4, &c.in)) return -1;
       contexts.push_back(c);
       ++Model::contexts[s];
     } else if (what == 2 && contexts.size() > 1) {
@@ -82,7 +82,7 @@ int violations(unsigned seed, int mode) {
       const int s = contexts[i].stream;
       if (Model::captured[s]) continue;
       for (auto& b : Model::before) b.insert(Model::before[s].begin(), Model::before[s].end());    // destroying waits for the stream
-      Orders::leave(contexts[i].in, s);
+      orders.leave(contexts[i].in, s);
       contexts.erase(contexts.begin() + i);
       --Model::contexts[s];
     } else if (what == 3 && rng() % 4 == 0) {
@@ -105,7 +105,7 @@ int violations(unsigned seed, int mode) {
         steps.push_back(Step{c.kind, s});
         return 0;
       };
-      if (Orders::run(c.in, s, launch)) return -1;
+      if (orders.run(c.in, s, launch)) return -1;
     }
   }
   std::vector<int> small, pick;
