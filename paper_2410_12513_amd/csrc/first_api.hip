@@ -525,6 +525,7 @@ void enqueue_decode_batched(first_ctx* c, const int* tokens, float* logits, int*
   // some 3000 keys in all (1B heads: 3 x 900 318 / 322, 10 of 200..800 349 / 341, 16 x 4000 646 / 442; 3B heads: 16 x 4000 913 / 656)
   auto shared = [&](const SeqList& keep) {
     if (c->G < 2 || c->G > 4) return false;
+    if (((long long)d.max_seq_len + 64) / 64 * 4 > (long long)S_MAX * AS_PT) return false;   // (the page ids of the most splits there are, 2^20 keys)
     if (c->G == 4 && d.head_dim == 128) return true;
     int sum = 0, most = 0;
     for (int j = 0; j < keep.n; ++j) { const int t = c->hlen[keep.id[j]] / 64 + 1; sum += t; most = std::max(most, t); }

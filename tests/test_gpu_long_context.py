@@ -103,3 +103,38 @@ def test_batched_decode_with_the_8b_head_geometry_at_16k_keys():
     kr = sts[0].K[1][n_ctx:].double()
     assert float((k.cpu().double() - kr).norm() / kr.norm()) <= 1.5e-2
     ctx.close()
+
+
+@pytest.mark.parametrize("hq,hkv,hd", [(2, 1, 64), (4, 1, 128)])
+def test_batched_decode_past_a_million_positions(hq, hkv, hd):
+    """Two and four query heads a KV head, longer than the shared-tile attention kernel has room for page ids: one pass over a batch against
+    one pass per sequence.  Values grow along the sequence, so keys taken from other pages would show."""
+    from synth import ModelDesc
+    n = (1 << 20) + 133
+    desc = ModelDesc(1, 256, hq, hkv, hd, 264, 300, dtype="bf16")
+    prompts = [make_prompt(desc.vocab, k, 99) for k in (40, 25)]
+    g = torch.Generator(device="cuda")
+    out = []
+    for path in (0, 1):
+        _, _, _, ctx = build(None, 99, desc=desc, max_batch=2, max_seq_len=n + 8)
+        ctx.set_option(6, path)
+        ctx.prefill_route(torch.cat(prompts).cuda(), [40, 25])
+        for b in range(2):
+            ctx.set_mask(b, [1])
+        ctx.set_seq_len(0, n)
+        g.manual_seed(99)
+        for at in range(0, n, 1 << 18):
+            m = min(1 << 18, n - at)
+            k = torch.randn((m, hkv, hd), device="cuda", generator=g)
+            v = torch.randn((m, hkv, hd), device="cuda", generator=g) + torch.arange(at, at + m, device="cuda").view(-1, 1, 1) * (4.0 / n)
+            ctx.kv_write(0, 0, at, k, v)
+        lg, tk = torch.zeros(2, desc.vocab, device="cuda"), torch.zeros(2, dtype=torch.int32, device="cuda")
+        for t in (5, 6, 7):
+            tin = torch.tensor([t, t + 20], dtype=torch.int32, device="cuda")
+            ctx.decode_step(tin, lg, tk)
+            ctx.sync()
+        assert ctx.seq_len(0) == n + 3
+        out.append((lg.clone(), ctx.get_hidden().clone()))
+        ctx.close()
+    for a, b in zip(*out):
+        assert float((a - b).abs().max()) <= 3e-3 * float(a.abs().max())
