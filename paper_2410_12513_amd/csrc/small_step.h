@@ -6,7 +6,7 @@
 // every element travels as a 64-bit word {value, epoch}, stored at once; whoever needs the vector loads it until all its words carry the
 // epoch it waits for.  Within a launch every vector has the next epoch, and the last one of a launch is kept in device memory for the
 // launch that follows.  No vector ever has epoch 0: a launch whose epochs would not all lie below 2^32 begins again at 1 (after hours of
-// steps; by then every word carries an epoch of the launches just before, far from 1).
+// steps; every word then carries an epoch of the launches just before, far from 1, or a layer's has not been written in that whole cycle).
 //
 // A word is never overwritten before everyone has read it: each vector is written again one layer later, by workgroups that have
 // seen complete vectors since to which EVERY workgroup contributed after reading this one (each owns at least one row
