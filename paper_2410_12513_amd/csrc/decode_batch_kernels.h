@@ -18,6 +18,8 @@ constexpr int BATCH_SLOTS = 16;      // sequences per pass = rows of one MFMA ti
 constexpr int BG_THREADS = 512;      // 8 waves: (row tiles per workgroup) x (slices of K) = 8
 constexpr int BG_WAVES = BG_THREADS / 64;
 
+enum { BG_QKV = 0, BG_O = 1, BG_GU = 2, BG_DN = 3, BG_HEAD = 4 };
+
 struct SeqList {
   int n;
   int id[BATCH_SLOTS];
@@ -67,6 +69,7 @@ struct BatchParams {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4v_t;
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ bf16x8_t as_bf16x8(uint4 v) {
   union { uint4 u; bf16x8_t b; } c;
@@ -226,6 +229,10 @@ __global__ void __launch_bounds__(AT_THREADS, 4) k_attn_tiles_b(BatchParams P) {
 // sk_attention<.., SPLIT_OUT>; a sequence that is not split writes its output at once (with the queries' conversion in
 // hardware and their request ahead of the page ids 6.5 us less a launch at 40 keys).  The host sizes the grid to about one workgroup per
 // compute unit.  Sixteen sequences of 4000 keys, us a layer less than k_attn_tiles_b: 3B heads 64, 1B heads 51.
+// Short contexts are bound by the serial chain in front of and behind the walk (16 sequences of 1000 keys with the 8B heads: some 15 us a launch
+// for 65 MB).  What belongs to it is kept short: pages that do not exist are not requested, and the subgroups' sums meet in 24 or 28 exchanges (us a
+// step before and after, eight launches: 8B heads, 16 sequences of 256 .. 2048 keys 9335 / 9225; 1B heads, four of 300 4020 / 3920; four of 16384 keys
+// 6275 / 6280: there HBM is the bound).
 // (An earlier version relayed 64-key tiles through 128 KB of LDS with a workgroup barrier per
 // pair of tiles: 0.4 % slower steps at 16 k keys.)
 constexpr int AS_THREADS = SK_WAVES * 64;
@@ -252,16 +259,15 @@ __device__ __forceinline__ float row16_sum(float v) {
   return v;
 }
 
-template <int HD, int G>
-__global__ void __launch_bounds__(AS_THREADS) k_attn_mfma_b(BatchParams P) {
+// Positions of the first splits' LDS: see as_lds_bytes.
+constexpr int as_flag_at(int G, int hd) { return G * hd + 2 * hd + hd + SK_WAVES * G * (hd + 2); }
+
+// The walk of k_attn_mfma_b over one split of one sequence's keys, shared with the kernel that runs a whole batched step.  src brings this step's
+// projections of KV head g: request() before the page ids are asked for, arrive() behind the first slices' requests, a workgroup
+// barrier later get().  Afterwards the eight waves' partial results are in LDS: out(head, maximum, sum, dims lane, lane + 64) in waves 0 .. G - 1.
+template <int HD, int G, typename Src, typename Out>
+__device__ __forceinline__ void attn_mfma_split(const DecParams& p, int b, int g, int s, int nsplit, int pos, float* smem_f, Src& src, Out out) {
   static_assert((HD == 128 || HD == 64) && G >= 2 && G <= 4, "lane layouts below: a head per group of four score rows");
-  extern __shared__ __align__(16) float smem_f[];
-  DecParams p = P.d;
-  const bool listed = P.attn_nwork > 0;
-  const AttnWork work = P.attn_work[listed ? blockIdx.y : 0];
-  const int work_slot = work & 0xff, work_split = (work >> 8) & 0xff, work_nsplit = (work >> 16) & 0xff;
-  const int slot = listed ? work_slot : (int)blockIdx.z;
-  p.b = P.seqs.id[slot];
   constexpr int HALF = HD / 2;
   constexpr int KS = HD / 32;                           // MFMA k-steps over the head dimension
   constexpr int DL = 8, LPR = HD / DL;                  // value dims per lane, lanes of a value row: lane (sub, dc), dc = lane % LPR
@@ -269,12 +275,9 @@ __global__ void __launch_bounds__(AS_THREADS) k_attn_mfma_b(BatchParams P) {
   // bf16 parts of the queries: two where scores always had 16 bits of them, three - all of an fp32 - for the geometries that
   // k_attn_tiles_b used to serve with fp32 multiply-adds (the matrix cores have nothing else to do here)
   constexpr int QP = HD == 128 && G == 4 ? 2 : 3;
-  const int b = p.b, Pg = p.P, g = listed ? blockIdx.x : blockIdx.y;
-  const int tid = threadIdx.x, wave = uni((int)(threadIdx.x >> 6)), lane = tid & 63;
-  const int pos = uni(p.len[b]), nkeys = pos + 1, tiles = (nkeys + 63) >> 6;
-  const int nsplit = max(1, min(listed ? work_nsplit : (int)gridDim.x, (tiles + AS_NT - 1) / AS_NT));
-  const int s = listed ? work_split : (int)blockIdx.x;
-  if (s >= nsplit) return;
+  const int Pg = p.P;
+  const int wave = uni((int)(threadIdx.x >> 6)), lane = sk_lane_opaque(), tid = wave * 64 + lane;     // (nothing here is worth keeping from one call to the next)
+  const int nkeys = pos + 1, tiles = (nkeys + 63) >> 6;
   // LDS carve-up
   float* fb = smem_f;
   float* qs = fb; fb += G * HD;
@@ -282,7 +285,7 @@ __global__ void __launch_bounds__(AS_THREADS) k_attn_mfma_b(BatchParams P) {
   float* vnew = fb; fb += HD;
   float2* cs = reinterpret_cast<float2*>(fb); fb += HD;
   float* mbuf = fb; fb += SK_WAVES * G * (HD + 2);      // [wave][head][HD dims, max, sum]
-  int* flag = reinterpret_cast<int*>(fb); fb += 8;
+  fb += 8;
   int* pt_lds = reinterpret_cast<int*>(fb); fb += AS_PT;   // page ids of this split's slices: a lookup in global memory before every
                                                         // page request would put a second, dependent round trip in front of each
   float* wbuf = fb + (size_t)wave * (16 * 4 + 4);       // [16 keys][4 heads] softmax weights of this wave's slice, then the 4 heads' rescale factors
@@ -290,9 +293,7 @@ __global__ void __launch_bounds__(AS_THREADS) k_attn_mfma_b(BatchParams P) {
   const int t_first = s * tps, t_last = min(tiles, t_first + tps), T = max(0, t_last - t_first);
   // slices of 16 keys (one cache page each): wave w takes the split's slices w, w + 8, ...
   const int n_sl = max(0, min(4 * t_last, (nkeys + 15) >> 4) - 4 * t_first);
-  const int nq = p.Hq * HD, nkv = p.Hkv * HD;
-  const float* qkv = p.qkv + (size_t)b * (nq + 2 * nkv);
-  const int* pt = p.page_table + (size_t)b * p.max_pages;
+  const SK_GLOBAL int* pt = as_global(p.page_table + (size_t)b * p.max_pages);
   bf16* pool = reinterpret_cast<bf16*>(p.kv_layer);
   const size_t head_off = (size_t)g * Pg * HD, v_off = (size_t)p.Hkv * Pg * HD;
   const bool owns_new = (pos >> 6) >= t_first && (pos >> 6) < t_last;
@@ -301,12 +302,15 @@ __global__ void __launch_bounds__(AS_THREADS) k_attn_mfma_b(BatchParams P) {
   // this step's q (G heads), k and v of the KV head, requested before the page ids that the first slices wait for
   const int iq = min(tid, G * HALF - 1), hh = iq / HALF, dq = iq - hh * HALF;
   const int dk = min(tid, HALF - 1), dv = min(tid, HD - 1);
-  const float q1 = qkv[(g * G + hh) * HD + dq], q2 = qkv[(g * G + hh) * HD + dq + HALF];
-  const float k1 = qkv[nq + g * HD + dk], k2 = qkv[nq + g * HD + dk + HALF];
-  const float vv = qkv[nq + nkv + g * HD + dv];
-  const float2 c_own = p.rope_cs[(size_t)b * HALF + min(tid, HALF - 1)];                 // made by k_embed_b
-  for (int i = tid; i < min(T1 * 4, AS_PT); i += AS_THREADS) pt_lds[i] = pt[min(t_first * 4 + i, last_page)];
-  lds_barrier();
+  src.request(hh * HD + dq, dk, dv, HALF);
+  const f32x2_t c_own = *as_global(reinterpret_cast<const f32x2_t*>(p.rope_cs + (size_t)b * HALF + min(tid, HALF - 1)));                 // made by k_embed_b
+  int* const ahead = src.ahead(T1 * 4);                 // (already there)
+  if (ahead != nullptr) {
+    pt_lds = ahead;
+  } else {
+    for (int i = tid; i < min(T1 * 4, AS_PT); i += AS_THREADS) pt_lds[i] = pt[min(t_first * 4 + i, last_page)];
+    lds_barrier();
+  }
 
   // A slice's keys and values straight into the registers that use them: for the scores lane (key = lane % 16, kq = lane / 16)
   // holds dims 32 ks + 8 kq .. + 8 of its key (the B operand of MFMA k-step ks), for the weighted values lane (sub = lane / LPR,
@@ -314,24 +318,28 @@ __global__ void __launch_bounds__(AS_THREADS) k_attn_mfma_b(BatchParams P) {
   // rows per value request.  No wave needs another wave's keys, so nothing goes through LDS and the waves never wait for each other.
   struct Stage { u32x4_t k[KS], v[NV]; };
   Stage st0, st1, st2;                                  // three slices of this wave in flight
+  // (a page through a descriptor of its own: one for a slice that does not exist is empty and costs no memory access.  With a reload of the last page in
+  // its place, up to 24 of them a wave were waited for at the end of the walk.)
+  const int page_bytes = (int)(p.page_elems * sizeof(bf16));
+  const int k_at = (int)(head_off + (lane & 15) * HD + ((lane >> 4) << 3)) * 2, v_at = (int)(head_off + (lane / LPR) * HD + (lane % LPR) * DL) * 2;
   auto issue = [&](Stage& st, int j) __attribute__((always_inline)) {
-    const int jj = max(0, min(j, n_sl - 1));             // (past the split: a harmless reload of a valid page)
-    const int pg = pt_lds[min(jj, AS_PT - 1)];
-    const bf16* base = pool + (size_t)pg * p.page_elems + head_off;
+    const int pg = uni(pt_lds[min(max(0, min(j, n_sl - 1)), AS_PT - 1)]);
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(uni(pool + (size_t)pg * p.page_elems), (short)0, uni(j < n_sl ? page_bytes : 0), 0x00020000);
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-      st.k[ks] = *reinterpret_cast<const u32x4_t*>(base + (lane & 15) * HD + ks * 32 + ((lane >> 4) << 3));
+    for (int ks = 0; ks < KS; ++ks) st.k[ks] = __builtin_amdgcn_raw_buffer_load_b128(rs, k_at + ks * 64, 0, 0);
 #pragma unroll
-    for (int i = 0; i < NV; ++i)
-      st.v[i] = *reinterpret_cast<const u32x4_t*>(base + v_off + (SUBS * i + lane / LPR) * HD + (lane % LPR) * DL);
+    for (int i = 0; i < NV; ++i) st.v[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, v_at + SUBS * i * HD * 2, (int)(v_off * 2), 0);
   };
 
   {
-    issue(st0, wave);                                   // (a wave without slices reloads a valid page and ignores it)
+    issue(st0, wave);
     issue(st1, wave + SK_WAVES);
     issue(st2, wave + 2 * SK_WAVES);
-    if (tid < HALF) cs[tid] = c_own;
+    if (tid < HALF) cs[tid] = make_float2(c_own.x, c_own.y);
+    src.arrive();
     lds_barrier();
+    float q1, q2, k1, k2, vv;
+    src.get(q1, q2, k1, k2, vv, hh * HD + dq, dk, dv, HALF);
     if (tid < G * HALF) {                              // rotate and pre-scale the queries
       const float2 c = cs[dq];
       qs[hh * HD + dq] = (q1 * c.x - q2 * c.y) * p.qscale;
@@ -342,12 +350,12 @@ __global__ void __launch_bounds__(AS_THREADS) k_attn_mfma_b(BatchParams P) {
       if (tid < HALF) {
         const float2 c = cs[dk];
         const bf16 r1 = from_f32<bf16>(k1 * c.x - k2 * c.y), r2 = from_f32<bf16>(k2 * c.x + k1 * c.y);
-        pool[base + dk] = r1; pool[base + dk + HALF] = r2;
+        stg_bf16(pool + base + dk, r1); stg_bf16(pool + base + dk + HALF, r2);
         knew[dk] = __uint_as_float((unsigned)r1.v); knew[dk + HALF] = __uint_as_float((unsigned)r2.v);   // raw bf16 bits
       }
       if (tid < HD) {
         const bf16 r = from_f32<bf16>(vv);
-        pool[base + v_off + dv] = r;
+        stg_bf16(pool + base + v_off + dv, r);
         vnew[dv] = __uint_as_float((unsigned)r.v);
       }
     }
@@ -479,21 +487,43 @@ __global__ void __launch_bounds__(AS_THREADS) k_attn_mfma_b(BatchParams P) {
     slice(st2, j + 2 * SK_WAVES);
   }
 
-  // fold the key subgroups, then every wave leaves its partial per head in LDS
+  // Fold the key subgroups (lanes LPR, 2 LPR, .. apart), then every wave leaves its partial per head in LDS.  At each step a lane gives away the half of
+  // its sums that its partner keeps: in the end the sixteen lanes of group h have head h, as many dims a lane as that leaves (24 or 28 exchanges;
+  // all sums in all lanes took 64 or 96).
+  float f[4][DL];
 #pragma unroll
-  for (int h = 0; h < G; ++h)
+  for (int h = 0; h < 4; ++h)
 #pragma unroll
-    for (int e = 0; e < DL; ++e) {
+    for (int e = 0; e < DL; ++e) f[h][e] = h < G ? o[h < G ? h : 0][e] : 0.f;
+  constexpr int DE = HD == 64 ? DL / 2 : DL;             // dims a lane ends up with
+  int d_first = dc * DL;
+  if constexpr (HD == 64) {                              // lanes 8 apart: halves of the dims
+    const bool up = lane & 8;
+    d_first += up ? DE : 0;
 #pragma unroll
-      for (int off = LPR; off < 64; off <<= 1) o[h][e] += __shfl_xor(o[h][e], off, 64);
+    for (int h = 0; h < G; ++h)
+#pragma unroll
+      for (int e = 0; e < DE; ++e) f[h][e] = (up ? f[h][DE + e] : f[h][e]) + __shfl_xor(up ? f[h][e] : f[h][DE + e], 8, 64);
+  }
+  {                                                      // 16 apart: even and odd heads
+    const bool up = lane & 16;
+#pragma unroll
+    for (int h = 0; h < G; h += 2)
+#pragma unroll
+      for (int e = 0; e < DE; ++e) f[h][e] = (up ? f[h + 1][e] : f[h][e]) + __shfl_xor(up ? f[h][e] : f[h + 1][e], 16, 64);
+  }
+  {                                                      // 32 apart: heads 0, 1 and 2, 3
+    const bool up = lane & 32;
+#pragma unroll
+    for (int e = 0; e < DE; ++e) {
+      if constexpr (G > 2) f[0][e] = (up ? f[2][e] : f[0][e]) + __shfl_xor(up ? f[0][e] : f[2][e], 32, 64);
+      else f[0][e] += __shfl_xor(f[0][e], 32, 64);
     }
+  }
+  if ((lane >> 4) < G) {
+    float* mb = mbuf + (size_t)(wave * G + (lane >> 4)) * (HD + 2) + d_first;
 #pragma unroll
-  for (int h = 0; h < G; ++h) {
-    float* mb = mbuf + (size_t)(wave * G + h) * (HD + 2);
-    if (lane < LPR) {
-#pragma unroll
-      for (int e = 0; e < DL; ++e) mb[dc * DL + e] = o[h][e];
-    }
+    for (int e = 0; e < DE; ++e) mb[e] = f[0][e];
   }
   if ((lane & 15) == 0 && (lane >> 4) < G) {
     float* mb = mbuf + (size_t)(wave * G + (lane >> 4)) * (HD + 2);
@@ -516,6 +546,39 @@ __global__ void __launch_bounds__(AS_THREADS) k_attn_mfma_b(BatchParams P) {
         if (HD > 64) a1 = fmaf(src[lane + 64 < HD ? lane + 64 : lane], w, a1);
       }
     }
+    out(hq, M, den, a0, a1);
+  }
+}
+
+template <int HD, int G>
+__global__ void __launch_bounds__(AS_THREADS) k_attn_mfma_b(BatchParams P) {
+  extern __shared__ __align__(16) float smem_f[];
+  DecParams p = P.d;
+  const bool listed = P.attn_nwork > 0;
+  const AttnWork work = P.attn_work[listed ? blockIdx.y : 0];
+  const int work_slot = work & 0xff, work_split = (work >> 8) & 0xff, work_nsplit = (work >> 16) & 0xff;
+  const int slot = listed ? work_slot : (int)blockIdx.z;
+  p.b = P.seqs.id[slot];
+  const int b = p.b, g = listed ? blockIdx.x : blockIdx.y;
+  const int tid = threadIdx.x, wave = uni((int)(threadIdx.x >> 6)), lane = tid & 63;
+  const int pos = uni(p.len[b]), tiles = (pos + 64) >> 6;
+  const int nsplit = max(1, min(listed ? work_nsplit : (int)gridDim.x, (tiles + AS_NT - 1) / AS_NT));
+  const int s = listed ? work_split : (int)blockIdx.x;
+  if (s >= nsplit) return;
+  struct Src {                                          // the projections of an earlier launch
+    const float *q, *k, *v;
+    float q1, q2, k1, k2, vv;
+    __device__ __forceinline__ void request(int iq, int dk, int dv, int half) { q1 = q[iq]; q2 = q[iq + half]; k1 = k[dk]; k2 = k[dk + half]; vv = v[dv]; }
+    __device__ __forceinline__ void arrive() {}
+    __device__ __forceinline__ int* ahead(int) const { return nullptr; }
+    __device__ __forceinline__ void get(float& a, float& b, float& c, float& d, float& e, int, int, int, int) { a = q1; b = q2; c = k1; d = k2; e = vv; }
+  } src;
+  {
+    const int nq = p.Hq * HD, nkv = p.Hkv * HD;
+    const float* qkv = p.qkv + (size_t)b * (nq + 2 * nkv);
+    src.q = qkv + g * G * HD; src.k = qkv + nq + g * HD; src.v = qkv + nq + nkv + g * HD;
+  }
+  attn_mfma_split<HD, G>(p, b, g, s, nsplit, pos, smem_f, src, [&](int hq, float M, float den, float a0, float a1) __attribute__((always_inline)) {
     const int H = g * G + hq;
     if (nsplit == 1) {                                     // nothing to meet: three memory round trips less
 #pragma unroll
@@ -535,7 +598,8 @@ __global__ void __launch_bounds__(AS_THREADS) k_attn_mfma_b(BatchParams P) {
       float* pml = p.part_ml + (((size_t)b * p.Hq + H) * S_MAX + s) * 2;
       st_coh(pml, M); st_coh(pml + 1, den);
     }
-  }
+  });
+  int* flag = reinterpret_cast<int*>(smem_f + as_flag_at(G, HD));
   if (nsplit == 1) return;
   // the last split of this KV head to finish merges all splits (fixed order) and writes the output
   vm_wait_all();
@@ -626,8 +690,6 @@ __global__ void __launch_bounds__(WG) k_tile_weights(const bf16* __restrict__ sr
     *reinterpret_cast<uint4*>(dst + idx * 8) = v;
   }
 }
-
-enum { BG_QKV = 0, BG_O = 1, BG_GU = 2, BG_DN = 3, BG_HEAD = 4 };
 
 // Y[slot][row] for RT tiles of 16 rows per wave group.  Workgroup = 8 waves = (8 / kslices) tile
 // groups x kslices slices of the contraction; the slices of a group are added in slice order
