@@ -81,7 +81,12 @@ extern "C" {
                                       where the context has no such kernel. */
 #define FIRST_OPT_BATCH_PATH    6  /* decode with several live sequences.  -1 (default): per layer, the sequences that
                                       keep it share one pass over its weights (bf16 models, widths multiples of 8),
-                                      else one pass per sequence; 0: always one pass per sequence; 1: shared pass or error */
+                                      else one pass per sequence; 0: always one pass per sequence; 1: shared pass or error.
+                                      Up to 16 sequences of a bf16 model whose widths are multiples of 256, with 2 to 4 query
+                                      heads a KV head, 16-token pages and memory for the exchange, take all layers in one
+                                      persistent kernel; it needs every compute unit and is ordered like the persistent step
+                                      above.  FIRST_OPT_DECODE_PATH 0, a fixed number of splits or a stream under capture get
+                                      launches per op. */
 
 typedef struct first_ctx first_ctx;
 

@@ -8,6 +8,9 @@
 // as x = hi + lo with hi = bf16(x), lo = bf16(x - hi) (16 significant bits), and every weight
 // tile is multiplied with both halves, accumulating in fp32.  RMSNorm's gain is applied before
 // the split and its 1/rms after the product (it is one scalar per sequence).
+//
+// batch_step.h runs all of a step's layers in one kernel where it can; the launches below serve the rest: other geometries, more than sixteen sequences, fixed
+// numbers of splits, steps under capture.
 #pragma once
 #include "decode_kernels.h"
 #include "step_kernel.h"

@@ -19,6 +19,7 @@
 #include "prefill_gemm.h"
 #include "prefill_attn.h"
 #include "decode_batch_kernels.h"
+#include "batch_step.h"
 #include "sample_kernels.h"
 #include "train_kernels.h"
 
@@ -144,12 +145,21 @@ struct first_ctx {
   unsigned* d_done = nullptr;             // [num_cu] per-workgroup epochs of the final reduction
   // batched decode (several live sequences): split activations, 1/rms per slot, logits when the caller wants none
   bf16 *d_xh = nullptr, *d_xl = nullptr, *d_zh = nullptr, *d_zl = nullptr, *d_x2h = nullptr, *d_x2l = nullptr;
-  float* d_ssq = nullptr;                 // [SSQ_GROUPS][16] per-tile-group sums of squares (fused split of the O / down epilogues)
+  float* d_ssq = nullptr;                 // [tile group, or tile][16] sums of squares (fused split of the O / down epilogues)
   float *d_rinv = nullptr, *d_logits_all = nullptr;
   int xpitch = 0;
   int batch_path = -1;                    // FIRST_OPT_BATCH_PATH
   bf16* t_head = nullptr;                 // tile-order copy of the LM head
   bool tiled = false;                     // tile-order copies of all matrices exist
+  // all layers of a batched step as one kernel (batch_step.h): its layer table, two sets of exchange words, and attention's partial results
+  bool bs_ok = false;
+  BsLayer* d_bs_layers = nullptr;
+  BsPhase bs_phase[4] = {};
+  int bs_acc_tiles = 0;
+  unsigned *bs_ex = nullptr, *bs_att = nullptr;
+  size_t bs_ex_words = 0, bs_att_words = 0;
+  int bs_set = 0, bs_layers = -1, bs_slots = 0;        // set of the next launch; kept layers and sequences of the last one (-1: all words are to be emptied)
+  HipOrders::Set batch_orders;
   float *x_h = nullptr, *x_qkv = nullptr, *x_attn = nullptr, *x_z = nullptr;   // tagged exchange vectors (written by k_step only)
   float* x_part = nullptr;                // tagged partial attention results of key splits 1.. (sk_part_index)
   int* d_tagstate = nullptr;              // [B][8] tags of their latest writes, epoch of the latest final reduction
@@ -319,6 +329,7 @@ int check_step_error(first_ctx* c, const char* who) {
     (void)hipMemset(c->d_err, 0, 4 * sizeof(int));
     (void)reset_tagged_exchange(c);
     (void)reset_small_exchange(c);
+    c->bs_layers = -1;
     return fail(c, FIRST_ERR_HIP, std::string(who) + ": a wait between workgroups of the persistent decode kernel gave up; "
                                   "the tokens and logits of the steps since are not valid");
   }
@@ -487,9 +498,10 @@ hipError_t make_tiled_copies(first_ctx* c) {
   for (int i = 0; i < d.n_layers; ++i) {
     LayerPtrs& l = c->layers[i];
     if (dev_alloc(c, &l.t_qkv, tiled_elems(nqkv, d.d_model)) || dev_alloc(c, &l.t_o, tiled_elems(d.d_model, c->nq)) ||
-        dev_alloc(c, &l.t_g, tiled_elems(d.d_ffn, d.d_model)) || dev_alloc(c, &l.t_u, tiled_elems(d.d_ffn, d.d_model)) ||
+        dev_alloc(c, &l.t_g, 2 * tiled_elems(d.d_ffn, d.d_model)) ||
         dev_alloc(c, &l.t_d, tiled_elems(d.d_model, d.d_ffn)))
       return hipErrorOutOfMemory;
+    l.t_u = l.t_g + tiled_elems(d.d_ffn, d.d_model);           // (up behind gate: batch_step.h reads both through one descriptor)
     // q, k and v stacked: nq and nkv are multiples of 64, so no tile straddles two matrices
     conv(l.wq, l.t_qkv, c->nq, d.d_model);
     conv(l.wk, l.t_qkv + tiled_elems(c->nq, d.d_model), c->nkv, d.d_model);
@@ -650,6 +662,96 @@ void enqueue_decode_batched(first_ctx* c, const int* tokens, float* logits, int*
     P.ssq_groups = 0;
     hipLaunchKernelGGL(k_argmax_b, dim3(all.n, ARG_CHUNKS), dim3(WG), 0, c->stream, P, c->d_arg_cnt, 1);
   }
+}
+
+const void* batch_step_fn(const first_ctx* c) {
+  const void* fn[2][3] = {{reinterpret_cast<const void*>(&k_batch_step<64, 2>), reinterpret_cast<const void*>(&k_batch_step<64, 3>), reinterpret_cast<const void*>(&k_batch_step<64, 4>)},
+                          {reinterpret_cast<const void*>(&k_batch_step<128, 2>), reinterpret_cast<const void*>(&k_batch_step<128, 3>), reinterpret_cast<const void*>(&k_batch_step<128, 4>)}};
+  return fn[c->d.head_dim == 128][c->G - 2];
+}
+
+int bs_x_bytes(const first_ctx* c) { return (int)std::max((size_t)BS_X_LDS, (bs_attn_lds(c->G, c->d.head_dim) + 15) / 16 * 16); }
+int bs_own(const first_ctx* c) { return (c->d.d_model / 8 + c->num_cu - 1) / c->num_cu * 8; }
+
+// Everything the one-kernel batched step needs, where the geometry admits it and memory is plentiful.  Which geometries: those of the attention walk it
+// shares (G, page size), whole MFMA chunks of K (widths in 256s), and what its tables and LDS hold.  Of those it is the faster one from the smallest
+// (1B heads and widths, four sequences: 502 us a step as launches per op, 439 so) to the largest (8B, sixteen: 1167 / 1120 with eight layers).
+hipError_t make_batch_step(first_ctx* c) {
+  const first_model_desc& d = c->d;
+  if (!c->tiled || c->G < 2 || c->G > 4 || d.kv_page_tokens != 16 || d.d_model % 256 || c->nq % 256 || d.d_ffn % 256 || d.n_layers > BS_MAX_L) return hipSuccess;
+  const int ncu = c->num_cu, slots = bs_slots(std::min(d.max_batch, BATCH_SLOTS));
+  if (bs_own(c) > BS_OWN || ncu < d.n_kv_heads || ncu > BS_MAX_WGS) return hipSuccess;
+  const int tiles = (d.max_seq_len + 63) / 64, splits = (4 * tiles + AS_PT - 1) / AS_PT;       // (a split's page ids fit its LDS table)
+  if (splits > 1 && splits * std::min(d.max_batch, BATCH_SLOTS) > std::min(BS_WORKS, ncu / d.n_kv_heads)) return hipSuccess;
+  const size_t up = (const char*)c->layers[0].t_u - (const char*)c->layers[0].t_g;
+  if (up > ((size_t)1 << 30)) return hipSuccess;
+  c->bs_phase[BG_QKV] = BsPhase{(c->nq + 2 * c->nkv) / 8, d.d_model / 32};
+  c->bs_phase[BG_O] = BsPhase{d.d_model / 8, c->nq / 32};
+  c->bs_phase[BG_GU] = BsPhase{d.d_ffn / 8, d.d_model / 32};
+  c->bs_phase[BG_DN] = BsPhase{d.d_model / 8, d.d_ffn / 32};
+  c->bs_acc_tiles = 0;
+  for (int k = 0; k < 4; ++k) c->bs_acc_tiles = std::max(c->bs_acc_tiles, bs_tiles(c->bs_phase[k], ncu, k == BG_GU));
+  const size_t lds = bs_lds(bs_x_bytes(c), c->bs_acc_tiles, bs_own(c));
+  if (lds > 160 * 1024) return hipSuccess;
+  c->bs_ex_words = (size_t)2 * d.n_layers * bs_words(d.d_model, c->nq, c->nkv, d.d_ffn, slots, ncu).all;
+  c->bs_att_words = (size_t)bs_items(d.n_kv_heads, ncu) * c->G * (d.head_dim + 4);
+  if (!memory_to_spare(c->p_least + (c->bs_ex_words + c->bs_att_words) * sizeof(unsigned))) return hipSuccess;
+  const void* fn = batch_step_fn(c);
+  int per_cu = 0;
+  hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, BS_THREADS, lds);
+  if (e != hipSuccess || per_cu < 1) return e;         // (not co-resident: the launches per op do it)
+  if (dev_alloc(c, &c->bs_ex, c->bs_ex_words) || dev_alloc(c, &c->bs_att, c->bs_att_words) || dev_alloc(c, &c->d_bs_layers, d.n_layers)) return hipErrorOutOfMemory;
+  std::vector<BsLayer> table(d.n_layers);
+  for (int i = 0; i < d.n_layers; ++i) {
+    const LayerPtrs& l = c->layers[i];
+    table[i] = BsLayer{l.t_qkv, l.t_o, l.t_g, l.t_d, l.g_attn, l.g_mlp};
+  }
+  e = hipMemcpy(c->d_bs_layers, table.data(), table.size() * sizeof(BsLayer), hipMemcpyHostToDevice);
+  if (e == hipSuccess) e = upload_layer_table(c);
+  c->bs_ok = e == hipSuccess;
+  return e;
+}
+
+// Layers that a live sequence keeps.
+int kept_by_somebody(const first_ctx* c) {
+  int kept = 0;
+  for (int i = 0; i < c->d.n_layers; ++i) {
+    bool any = false;
+    for (int b = 0; b < c->B; ++b) any = any || c->hmask[b][i];
+    kept += any;
+  }
+  return kept;
+}
+
+// One decode token for up to BATCH_SLOTS live sequences: the embedding, one kernel for all layers, the LM head and the argmax.
+void enqueue_batch_step(first_ctx* c, const int* tokens, float* logits, int* token_out) {
+  const first_model_desc& d = c->d;
+  BatchParams P{};
+  P.d = base_params(c, 0, 1);
+  P.d.tokens = tokens; P.d.token_out = token_out;
+  P.xh = c->d_xh; P.xl = c->d_xl; P.rinv = c->d_rinv; P.xpitch = c->xpitch; P.ssq_part = c->d_ssq;
+  P.logits_all = logits ? logits : c->d_logits_all;
+  P.t_head = c->t_head;
+  for (int b = 0; b < c->B; ++b) P.seqs.id[P.seqs.n++] = b;
+  hipLaunchKernelGGL(k_embed_b, dim3(c->B, 2), dim3(WG), 0, c->stream, P, (const float*)nullptr);
+  BatchStep S{};
+  S.d = P.d; S.layers = c->d_bs_layers; S.pools = c->d_layers; S.mask = c->d_mask; S.L = d.n_layers; S.n = c->B;
+  const int slots = bs_slots(c->B);
+  S.slots = slots;
+  for (int k = 0; k < 4; ++k) S.phase[k] = c->bs_phase[k];
+  S.up_offset = (unsigned)((const char*)c->layers[0].t_u - (const char*)c->layers[0].t_g);
+  S.w = bs_words(d.d_model, c->nq, c->nkv, d.d_ffn, slots, c->num_cu);
+  const size_t set = (size_t)d.n_layers * S.w.all;
+  S.ex = c->bs_ex + c->bs_set * set; S.ex_next = c->bs_ex + (c->bs_set ^ 1) * set; S.att = c->bs_att;
+  S.x_bytes = bs_x_bytes(c); S.own = bs_own(c); S.acc_tiles = c->bs_acc_tiles; S.g_final = c->g_final;
+  S.xh = c->d_xh; S.xl = c->d_xl; S.ssq_part = c->d_ssq; S.err = c->d_err;
+  hipLaunchKernelGGL(reinterpret_cast<void (*)(BatchStep)>(const_cast<void*>(batch_step_fn(c))), dim3(c->num_cu), dim3(BS_THREADS),
+                     bs_lds(S.x_bytes, S.acc_tiles, S.own), c->stream, S);
+  P.ssq_groups = std::min(c->num_cu, d.d_model / 8);
+  launch_bgemv<BG_HEAD>(c, P, d.vocab, d.d_model);
+  P.ssq_groups = 0;
+  hipLaunchKernelGGL(k_argmax_b, dim3(c->B, ARG_CHUNKS), dim3(WG), 0, c->stream, P, c->d_arg_cnt, 1);
 }
 
 // The instantiation of the persistent kernel for this context's head dimension.
@@ -1311,7 +1413,7 @@ int first_create(const first_model_desc* desc, const first_weights* w, void* hip
     }
     A(dev_alloc(c, &c->d_bg_part, c->bg_part_floats)); A(dev_alloc(c, &c->d_bg_cnt, c->bg_cnt_n));
     A(dev_alloc(c, &c->d_x2h, (size_t)BATCH_SLOTS * c->xpitch)); A(dev_alloc(c, &c->d_x2l, (size_t)BATCH_SLOTS * c->xpitch));
-    A(dev_alloc(c, &c->d_ssq, c->bg_cnt_n * BATCH_SLOTS));
+    A(dev_alloc(c, &c->d_ssq, std::max(c->bg_cnt_n, (size_t)d.d_model / 8 + 1) * BATCH_SLOTS));
   }
   if (B > 1 && rc == FIRST_OK) {
     (void)hipMemset(c->d_xh, 0, (size_t)BATCH_SLOTS * c->xpitch * 2); (void)hipMemset(c->d_xl, 0, (size_t)BATCH_SLOTS * c->xpitch * 2);
@@ -1371,7 +1473,10 @@ int first_create(const first_model_desc* desc, const first_weights* w, void* hip
       e = reset_small_exchange(c);
       if (e == hipSuccess) e = upload_layer_table(c);
     }
-    if (e == hipSuccess && B > 1 && d.dtype == FIRST_DTYPE_BF16 && d_batch_fits(c)) e = make_tiled_copies(c);
+    if (e == hipSuccess && B > 1 && d.dtype == FIRST_DTYPE_BF16 && d_batch_fits(c)) {
+      e = make_tiled_copies(c);
+      if (e == hipSuccess) e = make_batch_step(c);
+    }
     if (e == hipSuccess) e = hipMemset(c->d_mask, 0, (size_t)B * L);
     if (e == hipSuccess) e = hipMemset(c->d_page_table, 0, (size_t)B * c->max_pages * sizeof(int));
     // the prefill attention kernels stage more than 64 KB of LDS for head_dim 128
@@ -1406,6 +1511,7 @@ int first_destroy(first_ctx* c) {
   if (!c) return FIRST_ERR_ARG;
   (void)hipStreamSynchronize(c->stream);
   c->device_orders->leave(c->orders, c->stream);
+  c->device_orders->leave(c->batch_orders, c->stream);
   drop_graphs(c);
   for (void* p : c->allocs) (void)hipFree(p);
   if (c->h_keep) (void)hipHostFree(c->h_keep);
@@ -1452,7 +1558,7 @@ int first_prefill_route(first_ctx* c, int32_t B, const int32_t* ids, const int32
   if (mask_out) HIPCHK(c, hipMemcpyAsync(mask_out, c->d_mask, (size_t)B * L, hipMemcpyDeviceToDevice, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
   for (int b = 0; b < B; ++b) c->hmask[b].assign(hm.begin() + (size_t)b * L, hm.begin() + (size_t)(b + 1) * L);
-  if (c->kv_elide && (c->step_ok || c->small_wgs)) HIPCHK(c, upload_layer_table(c));   // the layers' slices are new
+  if (c->kv_elide && (c->step_ok || c->small_wgs || c->bs_ok)) HIPCHK(c, upload_layer_table(c));   // the layers' slices are new
   return FIRST_OK;
 }
 
@@ -1509,6 +1615,10 @@ int decode_step_impl(first_ctx* c, const int32_t* last_tokens, float* logits_out
                                     "multiples of 256, 16-token pages and exactly one live sequence");
   const bool batch_ok = bf && c->B > 1 && c->d_xh && d_batch_fits(c);
   const bool batched = !persistent && batch_ok && c->batch_path != 0;
+  // all layers in one kernel, unless the caller asked for launches per op or a number of splits, or is capturing (its replays would neither be ordered
+  // against other steps nor take the two sets of words in turn), or has more sequences than a tile has rows
+  const int layers_kept = batched && c->bs_ok ? kept_by_somebody(c) : 0;
+  const bool whole = layers_kept > 0 && c->tiled && c->B <= BATCH_SLOTS && c->decode_path != 0 && c->attn_splits <= 0 && !HipOrderApi::capturing(c->stream);
   // (the persistent kernel merges the workgroups' candidate lists in LDS: a large top_k may not fit there)
   const bool fused = smp && persistent && smp->top_k <= sk_sample_kmax(c->d.d_model, c->nq, c->d.d_ffn, c->num_cu);
   if (smp && !fused && !logits_out) logits_out = c->d_logits_own;
@@ -1535,6 +1645,7 @@ int decode_step_impl(first_ctx* c, const int32_t* last_tokens, float* logits_out
   }
   auto enqueue = [&]() {
     if (persistent) enqueue_decode_step_kernel(c, last_tokens, logits_out, token_out, fused ? smp : nullptr);
+    else if (whole) enqueue_batch_step(c, last_tokens, logits_out, token_out);
     else if (batched) enqueue_decode_batched(c, last_tokens, logits_out, token_out, S);
     else if (small) enqueue_small_steps(c, last_tokens, logits_out, token_out);
     else if (bf) enqueue_decode_ops<bf16>(c, last_tokens, logits_out, token_out, S);
@@ -1548,19 +1659,19 @@ int decode_step_impl(first_ctx* c, const int32_t* last_tokens, float* logits_out
   hipGraphExec_t replay = nullptr;
   if (c->use_graph && !one_launch) {
     // the whole-step kernels read the kept list from the device: one graph whatever the mask
-    const int kind = persistent ? -1 : small ? -1 - c->B : batched ? S + 1000 : S;
+    const int kind = persistent ? -1 : whole ? 2000 + c->bs_set : small ? -1 - c->B : batched ? S + 1000 : S;
     std::string key(reinterpret_cast<const char*>(&kind), sizeof(kind));
     key.append(reinterpret_cast<const char*>(&last_tokens), sizeof(void*));
     key.append(reinterpret_cast<const char*>(&logits_out), sizeof(void*));
     key.append(reinterpret_cast<const char*>(&token_out), sizeof(void*));
     if (smp) key.append(reinterpret_cast<const char*>(smp), sizeof(*smp));      // (pointers and values are part of the captured arguments)
-    if (!persistent && !small)
+    if (!persistent && !small && !whole)
       for (int b = 0; b < c->B; ++b) key.append(reinterpret_cast<const char*>(c->hmask[b].data()), c->hmask[b].size());
     // The attention's split list and kernel are chosen from the lengths when a graph is made.  S renews it every 128 tokens of the longest
     // sequence; once S stands at its limit, each sequence does when it passes the lengths up to which it is not split (6 or 10 tiles of 64 keys,
     // see enqueue_decode_batched) and twice, four times ... the latter: a capture per doubling.  (8B heads, four layers, 8000 and 500 keys after 2600
     // steps: 694 us a step with the lists of the start, 633 so; 3B heads 510 / 452.)
-    if (batched && c->attn_splits <= 0 && S == S_GRAPH_MAX)
+    if (batched && !whole && c->attn_splits <= 0 && S == S_GRAPH_MAX)
       for (int b = 0; b < c->B; ++b) {
         const long long tiles = c->hlen[b] / 64 + 1;
         char grown = tiles > 6;
@@ -1606,7 +1717,22 @@ int decode_step_impl(first_ctx* c, const int32_t* last_tokens, float* logits_out
     enqueue();
     return hipGetLastError();
   };
-  if (persistent || small) {
+  if (whole) {
+    // (a launch empties what the next one will fill, for the layers and sequences it has itself)
+    if (c->bs_layers != layers_kept || c->bs_slots != c->B) {
+      hipLaunchKernelGGL(k_fill_words, dim3(2048), dim3(WG), 0, c->stream, c->bs_ex, c->bs_ex_words, BS_EMPTY);
+      hipLaunchKernelGGL(k_fill_words, dim3(256), dim3(WG), 0, c->stream, c->bs_att, c->bs_att_words, BS_EMPTY);
+      HIPCHK(c, hipGetLastError());
+      c->bs_layers = layers_kept; c->bs_slots = c->B;
+    }
+    // (its workgroups fill the compute units: no small step's workgroups fit beside them)
+    if (c->batch_orders.empty())
+      HIPCHK(c, c->device_orders->join(StepKind::PERSISTENT_NO_ROOM, c->stream, std::max(1, std::min(SMALL_STEP_LANES, c->num_cu / SS_WGS)), &c->batch_orders));
+    const hipError_t e_run = c->device_orders->run(c->batch_orders, c->stream, launch);
+    if (e_run != hipSuccess) c->bs_layers = -1;        // (what it has left of the words is not known)
+    HIPCHK(c, e_run);
+    c->bs_set ^= 1;
+  } else if (persistent || small) {
     if (c->orders.empty()) {
       const StepKind kind = small ? StepKind::SMALL : c->step_lds <= SS_BESIDE_LDS ? StepKind::PERSISTENT : StepKind::PERSISTENT_NO_ROOM;
       HIPCHK(c, c->device_orders->join(kind, c->stream, std::max(1, std::min(SMALL_STEP_LANES, c->num_cu / SS_WGS)), &c->orders));

@@ -195,6 +195,29 @@ __device__ __forceinline__ T* uni(T* p) {
   const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)v), hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
   return reinterpret_cast<T*>(((unsigned long long)hi << 32) | lo);
 }
+__device__ __forceinline__ unsigned long long sk_uniform(unsigned long long v) {
+  return ((unsigned long long)(unsigned)uni((int)(v >> 32)) << 32) | (unsigned)uni((int)v);
+}
+// Arguments and tables of a kernel of many phases, read where they are needed (scalar loads): kept in registers through all of them they are far too many.
+// `at` is the same in the whole wave, and what it points to does not change while the kernel runs.
+template <typename T>
+__device__ __forceinline__ T sk_const(unsigned long long at) {
+  static_assert(sizeof(T) % 4 == 0, "whole words");
+  typedef const __attribute__((address_space(4))) unsigned word;
+  at = sk_uniform(at);
+  asm volatile("" : "+s"(at));
+  word* p = reinterpret_cast<word*>(at);
+  unsigned d[sizeof(T) / 4];
+#pragma unroll
+  for (int i = 0; i < (int)(sizeof(T) / 4); ++i) d[i] = p[i];
+  T r;
+  __builtin_memcpy(&r, d, sizeof(r));
+  return r;
+}
+__device__ __forceinline__ unsigned long long sk_args() {
+  typedef const __attribute__((address_space(4))) char arg_byte;
+  return reinterpret_cast<unsigned long long>((arg_byte*)__builtin_amdgcn_kernarg_segment_ptr());
+}
 __device__ __forceinline__ LayerDev load_layer(const LayerDev* arr, int i) {
   LayerDev l = arr[i];
   l.wq = uni(l.wq); l.wk = uni(l.wk); l.wv = uni(l.wv); l.wo = uni(l.wo); l.wg = uni(l.wg); l.wu = uni(l.wu);

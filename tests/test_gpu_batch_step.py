@@ -1,0 +1,134 @@
+"""All layers of a batched decode step in one kernel against the launches per op (option 3 = 0), which the oracle tests of the batched path pin."""
+import pytest
+import torch
+
+import paper_2410_12513_amd as P
+from synth import CONFIGS, ModelDesc, make_prompt, make_router, make_weights
+from synth.generators import to_device
+from tests.gpu_util import build
+
+pytestmark = pytest.mark.gpu
+torch.set_grad_enabled(False)
+
+# Both form the same products of bf16 weights with 16-bit-split activations and add them in fp32, in another order.  That is 1e-6 of a sum, but now and
+# then a key or value falls on the other side of its bf16 rounding: 2^-8 of one element, which reaches a logit as one of hundreds of terms of
+# its size (logits of size 4: 2^-8 * 4 / sqrt(256) = 1e-3 a flip at most; a few of them at a time).
+TOLERANCE = 3e-3
+
+
+def _steps(ctx, desc, masks, n, first):
+    B = len(masks[0])
+    lg, tk = torch.zeros(B, desc.vocab, device="cuda"), torch.zeros(B, dtype=torch.int32, device="cuda")
+    tin, out = torch.zeros(B, dtype=torch.int32, device="cuda"), []
+    for s in range(n):
+        for b, m in enumerate(masks[s * len(masks) // n]):
+            ctx.set_mask(b, m)
+        tin.copy_(torch.tensor([(first + 7 * s + 13 * b) % desc.vocab for b in range(B)], dtype=torch.int32))
+        ctx.decode_step(tin, lg, tk)
+        ctx.sync()                                               # raises if a wait between workgroups gave up
+        assert tk.tolist() == lg.argmax(dim=1).tolist()
+        out.append(lg.clone())
+    return torch.stack(out)
+
+
+# (layers, width, heads, KV heads, head dimension, FFN width), contexts.  Workgroups without a row (32 units for 256 of them), with one or two units and with half
+# tiles (288, 544), pairs of waves without a share of K, a last pass that is not whole (2304, 4352); 4, 8 and 16 slots, all used or not; one and several splits;
+# contexts at the edges of pages and tiles.
+@pytest.mark.parametrize("shape,lens", [
+    ((3, 256, 4, 2, 64, 256), [1, 16, 63, 64]),
+    ((3, 256, 4, 1, 64, 512), [5, 900]),
+    ((2, 768, 6, 2, 128, 1280), [15, 700, 33, 64, 1400]),
+    ((3, 2304, 8, 4, 64, 4352), [20 + 170 * b for b in range(9)]),
+    ((2, 512, 8, 2, 128, 2304), [3 + 11 * b for b in range(16)]),
+    ((2, 1536, 12, 4, 64, 2560), [2047, 40, 9]),
+    ((2, 2048, 8, 4, 128, 2048), [30] * 8),
+], ids=str)
+@pytest.mark.parametrize("graph", [1, 0])
+def test_one_kernel_agrees_with_launches_per_op(shape, lens, graph):
+    desc, B, L, n = ModelDesc(*shape, 1003, dtype="bf16"), len(lens), shape[0], 8
+    w, r = to_device(make_weights(desc, 5), "cuda"), make_router(desc, 5).cuda()
+    ids = torch.cat([make_prompt(desc.vocab, k, 5 + b) for b, k in enumerate(lens)]).cuda()
+    # every layer; a layer for some of the sequences; fewer layers (the exchange begins anew), most sequences without any
+    some = [[int(i == 0 or (i + b) % 2) for i in range(L)] for b in range(B)]
+    few = [[m if i == L - 1 else 0 for i, m in enumerate(row)] for row in some]
+    masks = [[[1] * L] * B, some, few]
+    out, kv = [], []
+    for path in (0, -1):
+        ctx = P.FirstContext(desc, w, r, max_batch=B, max_seq_len=max(lens) + n + 1)
+        ctx.set_option(1, graph)
+        ctx.set_option(3, path)
+        for first in (3, 400):                                   # (a new prompt: every layer again)
+            ctx.prefill_route(ids, lens)
+            out.append(_steps(ctx, desc, masks, n, first))
+            kv.append([ctx.kv_read(b, i, lens[b], 3) for b in range(B) for i in range(L)])
+        ctx.close()
+    for i in (0, 1):
+        assert float((out[i] - out[2 + i]).abs().max()) <= TOLERANCE
+        assert not torch.equal(out[i], out[2 + i])               # (the same bits would come of the same kernels)
+        for x, y in zip(kv[i], kv[2 + i]):
+            for p, q in zip(x, y):                               # (bf16 roundings that fall on the other side)
+                assert float((p.double() - q.double()).norm() / p.double().norm()) <= 2 ** -8
+
+
+def test_batched_and_single_steps_on_streams_of_their_own():
+    """Two kernels that each need the whole chip, a few microseconds behind each other: each context has the bits that it has alone."""
+    def contexts():
+        out = []
+        for model, lens in (("step_hd128", [40, 21, 300]), ("step_hd64", [70]), ("step_g2", [90] * 5)):
+            desc, _, _, ctx = build(model, 11, max_batch=len(lens), max_seq_len=400)
+            ctx.prefill_route(torch.cat([make_prompt(desc.vocab, k, 5 + b) for b, k in enumerate(lens)]).cuda(), lens)
+            for b in range(len(lens)):
+                ctx.set_mask(b, [1] * desc.n_layers)
+            out.append((ctx, torch.full((len(lens),), 9, dtype=torch.int32, device="cuda"), torch.zeros(40, len(lens), desc.vocab, device="cuda")))
+        torch.cuda.synchronize()
+        return out
+    alone = contexts()
+    for ctx, tok, hist in alone:
+        for lg in hist:
+            ctx.decode_step(tok, lg, tok)
+        ctx.sync()
+    together = contexts()
+    for i in range(40):
+        for ctx, tok, hist in together:
+            ctx.decode_step(tok, hist[i], tok)
+    for (ctx, tok, hist), (c, t, ref) in zip(together, alone):
+        ctx.sync()
+        assert torch.equal(hist, ref) and torch.equal(tok, t)
+        ctx.close()
+        c.close()
+
+
+def test_a_captured_step_takes_the_launches_per_op():
+    desc = CONFIGS["step_hd64"]
+    lens, stream = [50, 20, 33], torch.cuda.Stream()
+    w, r = to_device(make_weights(desc, 5), "cuda"), make_router(desc, 5).cuda()
+    ids, out = torch.cat([make_prompt(desc.vocab, k, b) for b, k in enumerate(lens)]).cuda(), []
+    for captured in (False, True):
+        ctx = P.FirstContext(desc, w, r, max_batch=3, max_seq_len=100, stream=stream)
+        ctx.set_option(1, 0)
+        torch.cuda.synchronize()
+        ctx.prefill_route(ids, lens)
+        for b in range(3):
+            ctx.set_mask(b, [1] * desc.n_layers)
+        tok, lg, hist = torch.full((3,), 9, dtype=torch.int32, device="cuda"), torch.zeros(3, desc.vocab, device="cuda"), []
+        torch.cuda.synchronize()
+        if captured:
+            g = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(g, stream=stream):
+                ctx.decode_step(tok, lg, tok)
+        else:
+            ctx.set_option(3, 0)
+        for _ in range(4):
+            if captured:
+                with torch.cuda.stream(stream):
+                    g.replay()
+            else:
+                ctx.decode_step(tok, lg, tok)
+            stream.synchronize()
+            hist.append(lg.clone())
+            torch.cuda.synchronize()
+        if not captured:
+            ctx.sync()
+        out.append(torch.stack(hist))
+        ctx.close()
+    assert torch.equal(*out)
