@@ -243,9 +243,13 @@ hipError_t reset_tagged_exchange(first_ctx* c) {
   return e;
 }
 
-// Words of the small-model kernel's exchange: residual, projections, attention, MLP activation, candidates.
+// Words of the small-model kernel's exchange: residual, projections, attention (its output, or each head's share of the output projection),
+// MLP activation, candidates.
+size_t small_attn_words(const first_ctx* c) {
+  return std::max((size_t)c->nq, ss_by_head(c->d.n_q_heads, c->d.d_model) ? (size_t)c->d.n_q_heads * c->d.d_model : 0);
+}
 size_t small_exchange_words(const first_ctx* c) {
-  return (size_t)c->d.d_model + (c->nq + 2 * c->nkv) + c->nq + c->d.d_ffn + 2 * c->small_wgs;
+  return (size_t)c->d.d_model + (c->nq + 2 * c->nkv) + small_attn_words(c) + c->d.d_ffn + 2 * c->small_wgs;
 }
 // (a word of zeros carries epoch 0, which no launch waits for)
 hipError_t reset_small_exchange(first_ctx* c) {
@@ -803,9 +807,10 @@ void enqueue_small_steps(first_ctx* c, const int* tokens, float* logits, int* to
     P.d = base_params(c, b, 1);
     P.d.tokens = tokens; P.d.logits = logits; P.d.token_out = token_out; P.d.advance_len = 1;
     P.layers = c->d_layers; P.kept = c->d_kept; P.n_kept = c->d_nkept; P.L = c->d.n_layers;
-    P.xh = c->d_small; P.xqkv = P.xh + c->d.d_model; P.xattn = P.xqkv + c->nq + 2 * c->nkv; P.xz = P.xattn + c->nq; P.xcand = P.xz + c->d.d_ffn;
+    P.xh = c->d_small; P.xqkv = P.xh + c->d.d_model; P.xattn = P.xqkv + c->nq + 2 * c->nkv; P.xz = P.xattn + small_attn_words(c); P.xcand = P.xz + c->d.d_ffn;
     P.epoch = c->d_small_epoch; P.err = c->d_err;
-    auto kernel = c->d.head_dim == 128 ? &k_small_step<128> : &k_small_step<64>;
+    const bool by_head = ss_by_head(c->d.n_q_heads, c->d.d_model);
+    auto kernel = c->d.head_dim == 128 ? by_head ? &k_small_step<128, true> : &k_small_step<128, false> : by_head ? &k_small_step<64, true> : &k_small_step<64, false>;
     hipLaunchKernelGGL(kernel, dim3(c->small_wgs), dim3(SS_THREADS), small_step_lds(c), c->stream, P);
   }
 }

@@ -155,3 +155,26 @@ def test_a_wait_that_gives_up_ends_the_launch_and_is_reported_once():
         ctx.close()
     for (ta, la), (tb, lb) in zip(*outs):
         assert ta == tb and torch.equal(la, lb)
+
+
+@pytest.mark.parametrize("heads,kv_heads,hd,width", [(1, 1, 64, 256), (3, 1, 64, 200), (4, 4, 64, 256), (2, 1, 128, 256), (3, 3, 128, 72), (4, 2, 64, 264), (5, 5, 64, 256)])
+@pytest.mark.parametrize("n", [1, 63, 300])
+def test_output_projection_by_head_and_by_row(heads, kv_heads, hd, width, n):
+    """One to four heads and a thread an element: every group of workgroups has a head's columns of the output projection (1, 3 heads: groups that do not
+    divide the 64 workgroups or the rows); 264 wide or five heads: the heads' outputs go round.  Against the launches per op: the same fp32 products, other orders of
+    sums (a few units in the last place of some thousand terms)."""
+    desc = ModelDesc(2, width, heads, kv_heads, hd, 264, 300, dtype="fp32")
+    prompt = make_prompt(desc.vocab, n, 95)
+    ctxs = [_prefilled(desc, [prompt], 95, path=p)[2] for p in (-1, 0)]
+    tok, lg = torch.zeros(1, dtype=torch.int32, device="cuda"), [torch.zeros(1, desc.vocab, device="cuda") for _ in ctxs]
+    for c in ctxs:
+        c.set_mask(0, [1, 1])
+    for step in range(4):
+        tok.fill_(7 + 50 * step)
+        for c, out in zip(ctxs, lg):
+            c.decode_step(tok, out, tok.clone())
+            c.sync()
+        assert float((lg[0] - lg[1]).norm() / lg[1].norm()) <= 1e-5
+    assert _waits_between_workgroups(ctxs[0], tok) and not _waits_between_workgroups(ctxs[1], tok)
+    for c in ctxs:
+        c.close()
