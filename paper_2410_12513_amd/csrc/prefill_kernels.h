@@ -796,6 +796,8 @@ __global__ void __launch_bounds__(WG) k_rope_kvwrite(float* __restrict__ q, cons
 // Causal GQA attention over the prompt, reading K and V back from the cache pages.
 // grid = (ceil(T/QB), Hkv); the workgroup owns QB query positions x G heads (<= 64 rows),
 // one wave per row in turn; 64-key tiles of K (padded rows) and V are shared through LDS.
+// Bound: the chain of one row - 64 multiply-adds of a score, a value a key -, so what it reads from LDS is requested eight at a time (prompts of an fp32 model of
+// four layers, 256 x 688, us a pass before / after: 200 tokens 384 / 348, 1000 1387 / 1094, 2000 4088 / 2920; the same sums in the same order).
 constexpr int PA_RPW = 16;      // rows per wave
 template <typename XT, typename KVT>
 __global__ void __launch_bounds__(WG) k_attn_prefill(const float* __restrict__ q, XT* __restrict__ out,
@@ -857,8 +859,15 @@ __global__ void __launch_bounds__(WG) k_attn_prefill(const float* __restrict__ q
             sc = fmaf(qv[d + 1], __uint_as_float(w2 & 0xffff0000u), sc);
           }
         } else {
-#pragma unroll 32
-          for (int d = 0; d < hd; ++d) sc = fmaf(qv[d], *reinterpret_cast<const float*>(krow + d * 4), sc);
+#pragma unroll 4
+          for (int d = 0; d < hd; d += 8) {                // (hd: a multiple of 8)
+            float k8[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) k8[e] = *reinterpret_cast<const float*>(krow + (d + e) * 4);
+            const float4 qa = *reinterpret_cast<const float4*>(qv + d), qb = *reinterpret_cast<const float4*>(qv + d + 4);
+            sc = fmaf(qa.x, k8[0], sc); sc = fmaf(qa.y, k8[1], sc); sc = fmaf(qa.z, k8[2], sc); sc = fmaf(qa.w, k8[3], sc);
+            sc = fmaf(qb.x, k8[4], sc); sc = fmaf(qb.y, k8[5], sc); sc = fmaf(qb.z, k8[6], sc); sc = fmaf(qb.w, k8[7], sc);
+          }
         }
         if (lane >= jn) sc = -INFINITY;
         const float mn = fmaxf(m[ri], wave_max(sc));
@@ -867,10 +876,22 @@ __global__ void __launch_bounds__(WG) k_attn_prefill(const float* __restrict__ q
         l[ri] = l[ri] * corr + wave_sum(pj);
         o0[ri] *= corr; o1[ri] *= corr;
         m[ri] = mn;
-        for (int j = 0; j < jn; ++j) {
-          const float pb = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(pj), j));
-          if (lane < hd) o0[ri] = fmaf(pb, to_f32(vt[j * hd + lane]), o0[ri]);
-          if (lane + 64 < hd) o1[ri] = fmaf(pb, to_f32(vt[j * hd + lane + 64]), o1[ri]);
+        // eight values requested together (one at a time each waited for LDS: 32 keys of a row 1.8 us); behind the row's own position weight and value are zero
+        const int c0 = min(lane, hd - 1), c1 = min(lane + 64, hd - 1);
+        for (int j0 = 0; j0 < jn; j0 += 8) {
+          KVT v0[8], v1[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) {
+            v0[u] = vt[(j0 + u) * hd + c0];
+            if (hd > 64) v1[u] = vt[(j0 + u) * hd + c1];
+          }
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int u = 0; u < 8; ++u) {
+            const float pb = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(pj), j0 + u));
+            o0[ri] = fmaf(pb, j0 + u < jn ? to_f32(v0[u]) : 0.f, o0[ri]);
+            if (hd > 64) o1[ri] = fmaf(pb, j0 + u < jn ? to_f32(v1[u]) : 0.f, o1[ri]);
+          }
         }
       }
     }
