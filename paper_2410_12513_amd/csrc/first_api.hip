@@ -2050,15 +2050,16 @@ int first_lora_merge(void* hip_stream, int32_t dtype, void* W, const float* A, c
   const int rows_per_wg = std::min(64, std::max(2 * LM_RG, ((n + want_y - 1) / want_y + 2 * LM_RG - 1) / (2 * LM_RG) * (2 * LM_RG)));
   const dim3 grid(chunks, (n + rows_per_wg - 1) / rows_per_wg);
   const size_t lds = ((size_t)r * LM_COLS + (size_t)rows_per_wg * r) * sizeof(float);
+  const bool past = lora_past_caches((size_t)n * k * (dtype == FIRST_DTYPE_BF16 ? 2 : 4), dtype == FIRST_DTYPE_BF16, r);
   if (r <= 8) {            // A in registers; about eight workgroups per CU, at least 16 rows each
     const int want = std::max(1, (8 * device_cus() + chunks - 1) / chunks);
     const int rows = std::min(64, std::max(4 * LM_RG, ((n + want - 1) / want + 2 * LM_RG - 1) / (2 * LM_RG) * (2 * LM_RG)));
     const dim3 g(chunks, (n + rows - 1) / rows);
     if (g.y <= 65535) {
       if (dtype == FIRST_DTYPE_BF16)
-        hipLaunchKernelGGL(k_lora_merge_small<bf16>, g, dim3(WG), 0, st, reinterpret_cast<bf16*>(W), A, Bm, n, k, r, scale, rows);
+        hipLaunchKernelGGL((past ? k_lora_merge_small<bf16, true> : k_lora_merge_small<bf16, false>), g, dim3(WG), 0, st, reinterpret_cast<bf16*>(W), A, Bm, n, k, r, scale, rows);
       else
-        hipLaunchKernelGGL(k_lora_merge_small<float>, g, dim3(WG), 0, st, reinterpret_cast<float*>(W), A, Bm, n, k, r, scale, rows);
+        hipLaunchKernelGGL((k_lora_merge_small<float, false>), g, dim3(WG), 0, st, reinterpret_cast<float*>(W), A, Bm, n, k, r, scale, rows);
       const hipError_t es = hipGetLastError();
       if (es == hipSuccess) return FIRST_OK;
       g_create_error = std::string("first_lora_merge: ") + hipGetErrorString(es);
@@ -2067,13 +2068,15 @@ int first_lora_merge(void* hip_stream, int32_t dtype, void* W, const float* A, c
   }
   hipError_t e;
   if (dtype == FIRST_DTYPE_BF16) {
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_lora_merge<bf16>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    auto kernel = past ? &k_lora_merge<bf16, true> : &k_lora_merge<bf16, false>;
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e == hipSuccess)
-      hipLaunchKernelGGL(k_lora_merge<bf16>, grid, dim3(WG), lds, st, reinterpret_cast<bf16*>(W), A, Bm, n, k, r, scale, rows_per_wg);
+      hipLaunchKernelGGL(kernel, grid, dim3(WG), lds, st, reinterpret_cast<bf16*>(W), A, Bm, n, k, r, scale, rows_per_wg);
   } else {
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_lora_merge<float>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    auto kernel = past ? &k_lora_merge<float, true> : &k_lora_merge<float, false>;
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e == hipSuccess)
-      hipLaunchKernelGGL(k_lora_merge<float>, grid, dim3(WG), lds, st, reinterpret_cast<float*>(W), A, Bm, n, k, r, scale, rows_per_wg);
+      hipLaunchKernelGGL(kernel, grid, dim3(WG), lds, st, reinterpret_cast<float*>(W), A, Bm, n, k, r, scale, rows_per_wg);
   }
   if (e == hipSuccess) e = hipGetLastError();
   if (e != hipSuccess) {

@@ -94,29 +94,42 @@ constexpr int LM_COLS = 1024;      // columns per workgroup: 128 threads x 8 col
 constexpr int LM_RMAX = 32;        // largest rank (LDS: r * LM_COLS floats + the Bm rows)
 constexpr int LM_RG = 4;           // rows per thread and iteration
 
+// A matrix that the caches would not hold until it is next used goes past them (NT): what it would push out is written back meanwhile.  us of all matrices of an
+// 8B layer, bf16 (436 MB, rank 8): 205 / 190 with and without its small ones; matrices of a layer that the 256 MB memory-side cache holds are up to 15 %
+// slower that way (two of 117 MB in turn 41 / 48), fp32 ones of any size 5 to 12 %.  Ranks above 8, where W waits for the sums, gain from
+// 32 MB on: 4096 x 4096 rank 16 bf16 44.6 / 32.0, fp32 65.0 / 45.6; 14336 x 4096 rank 32 242 / 169 and 288 / 185; 1024 x 4096 fp32 17.3 / 18.2.
+__host__ inline bool lora_past_caches(size_t bytes, bool is_bf16, int r) { return r > 8 ? bytes >= (32u << 20) : is_bf16 && bytes >= (64u << 20); }
+template <bool NT> __device__ __forceinline__ u32x4_t lora_ld(const void* p) {
+  return NT ? __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(p)) : *reinterpret_cast<const u32x4_t*>(p);
+}
+template <bool NT> __device__ __forceinline__ void lora_st(void* p, const u32x4_t& v) {
+  if (NT) __builtin_nontemporal_store(v, reinterpret_cast<u32x4_t*>(p));
+  else *reinterpret_cast<u32x4_t*>(p) = v;
+}
+
 // One row's eight columns: W + scale * sum, rounded once.
-template <typename WT> struct LoraRow;
-template <> struct LoraRow<bf16> {
+template <typename WT, bool NT> struct LoraRow;
+template <bool NT> struct LoraRow<bf16, NT> {
   u32x4_t v[1];
-  __device__ __forceinline__ void load(const bf16* w) { v[0] = *reinterpret_cast<const u32x4_t*>(w); }
+  __device__ __forceinline__ void load(const bf16* w) { v[0] = lora_ld<NT>(w); }
   __device__ __forceinline__ void store(bf16* w, const float (&acc)[8], float scale) const {
     u32x4_t o;
 #pragma unroll
     for (int e = 0; e < 4; ++e)
       o[e] = pk_bf16(fmaf(scale, acc[2 * e], __uint_as_float(v[0][e] << 16)), fmaf(scale, acc[2 * e + 1], __uint_as_float(v[0][e] & 0xffff0000u)));
-    *reinterpret_cast<u32x4_t*>(w) = o;
+    lora_st<NT>(w, o);
   }
 };
-template <> struct LoraRow<float> {
+template <bool NT> struct LoraRow<float, NT> {
   u32x4_t v[2];
-  __device__ __forceinline__ void load(const float* w) { v[0] = reinterpret_cast<const u32x4_t*>(w)[0]; v[1] = reinterpret_cast<const u32x4_t*>(w)[1]; }
+  __device__ __forceinline__ void load(const float* w) { v[0] = lora_ld<NT>(w); v[1] = lora_ld<NT>(w + 4); }
   __device__ __forceinline__ void store(float* w, const float (&acc)[8], float scale) const {
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
       u32x4_t o;
 #pragma unroll
       for (int e = 0; e < 4; ++e) o[e] = __float_as_uint(fmaf(scale, acc[4 * q + e], __uint_as_float(v[q][e])));
-      reinterpret_cast<u32x4_t*>(w)[q] = o;
+      lora_st<NT>(w + 4 * q, o);
     }
   }
 };
@@ -126,7 +139,7 @@ template <> struct LoraRow<float> {
 // wave and come through the scalar cache.  Ranks below 8 are padded with zeros.  Bound: HBM, W read and written once
 // (14336 x 4096 / 4096 x 14336 bf16, rank 8: 59.2 / 66.9 us before, 53.5 / 51.3 now by the kernel trace = 4.4 / 4.6 TB/s; a plain
 // copy runs at 4.66).
-template <typename WT>
+template <typename WT, bool NT>
 __global__ void __launch_bounds__(WG) k_lora_merge_small(WT* __restrict__ W, const float* __restrict__ A, const float* __restrict__ Bm,
                                                          int n, int k, int r, float scale, int rows_per_wg) {
   const int col = blockIdx.x * LM_COLS + (threadIdx.x & 127) * 8, half = uni((int)(threadIdx.x >> 7));
@@ -134,7 +147,7 @@ __global__ void __launch_bounds__(WG) k_lora_merge_small(WT* __restrict__ W, con
   const int half_rows = rows_per_wg / 2;                 // a multiple of LM_RG
   const int row0 = blockIdx.y * rows_per_wg + half * half_rows, row1 = min(n, row0 + half_rows);
   if (row0 >= row1) return;
-  LoraRow<WT> cur[LM_RG], nxt[LM_RG];
+  LoraRow<WT, NT> cur[LM_RG], nxt[LM_RG];
 #pragma unroll
   for (int q = 0; q < LM_RG; ++q) cur[q].load(W + (size_t)min(row0 + q, row1 - 1) * k + col);
   float a[8][8];
@@ -165,7 +178,7 @@ __global__ void __launch_bounds__(WG) k_lora_merge_small(WT* __restrict__ W, con
   }
 }
 
-template <typename WT>
+template <typename WT, bool NT>
 __global__ void __launch_bounds__(WG) k_lora_merge(WT* __restrict__ W, const float* __restrict__ A, const float* __restrict__ Bm,
                                                    int n, int k, int r, float scale, int rows_per_wg) {
   extern __shared__ float lm_lds[];                      // A tile [r][LM_COLS], then Bm rows [rows_per_wg][r] (zero beyond n)
@@ -184,7 +197,7 @@ __global__ void __launch_bounds__(WG) k_lora_merge(WT* __restrict__ W, const flo
   const int col = c0 + tc;
   if (col >= k) return;                                  // k is a multiple of 8: a thread's 8 columns are in or out together
   for (int rb = half * LM_RG; row0 + rb < row1; rb += 2 * LM_RG) {
-    LoraRow<WT> raw[LM_RG];
+    LoraRow<WT, NT> raw[LM_RG];
 #pragma unroll
     for (int q = 0; q < LM_RG; ++q) raw[q].load(W + (size_t)min(row0 + rb + q, row1 - 1) * k + col);   // rows past the end re-read the last one and are not stored
     float acc[LM_RG][8];

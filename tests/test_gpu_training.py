@@ -245,3 +245,17 @@ def test_merged_adapters_enter_the_path():
     ok, ma, rel = logits_close(lg[0, 0], ref, desc.dtype)
     assert ok, (ma, rel)
     ctx.close()
+
+
+@pytest.mark.parametrize("dtype,n,k,r", [("bf16", 8195, 4096, 8), ("bf16", 4097, 4096, 16), ("fp32", 2051, 4096, 9), ("bf16", 16385, 2056, 3)])
+def test_a_merge_past_the_caches_has_the_bits_of_its_rows_alone(dtype, n, k, r):
+    """Large matrices take other loads and stores than their parts do (a quarter of the rows each): every row's sums are its own."""
+    g = torch.Generator(device="cuda").manual_seed(7)
+    W = torch.randn(n, k, device="cuda", generator=g).to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    A, Bm = torch.randn(r, k, device="cuda", generator=g), torch.randn(n, r, device="cuda", generator=g)
+    parts = [w.clone() for w in W.split((n + 3) // 4)]
+    P.lora_merge(W, A, Bm, 0.25)
+    for w, b in zip(parts, Bm.split((n + 3) // 4)):
+        P.lora_merge(w, A, b.contiguous(), 0.25)
+    torch.cuda.synchronize()
+    assert torch.equal(W, torch.cat(parts))
