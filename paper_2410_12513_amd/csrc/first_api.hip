@@ -833,7 +833,7 @@ bool step_kernel_fits(const first_ctx* c) {
 }
 
 // n fp32 matrices applied to the same rows in one launch of small tiles, where there are fewer 64 x 64 tiles than compute units: 32 x 32
-// tiles, or 16 x 16 ones while those do not fill the chip either.  GU: gate and up, SiLU(gate) * up to C[0].  False: more tiles than that.
+// tiles, 16 x 16 ones while those do not fill the chip either, 8 x 8 ones where 16 x 16 leave half of it idle.  GU: gate and up, SiLU(gate) * up to C[0].  False: more tiles than that.
 template <bool GU>
 bool launch_f32_small(hipStream_t st, const float* A, SmallSegs S, int n, int M, int K, int acc) {
   auto tiles = [&](int t) {
@@ -844,10 +844,12 @@ bool launch_f32_small(hipStream_t st, const float* A, SmallSegs S, int n, int M,
   const int cus = device_cus();
   if (tiles(64) * (GU ? 2 : 1) * ((M + 63) / 64) >= cus) return false;
   const bool wide = tiles(32) * ((M + 31) / 32) >= cus;
-  const int t = wide ? 32 : 16;
+  const bool tight = 2 * tiles(16) * ((M + 15) / 16) <= cus;
+  const int t = wide ? 32 : tight ? 8 : 16;
   const dim3 grid((unsigned)tiles(t), (M + t - 1) / t);
-  if (wide) hipLaunchKernelGGL((k_gemm_nt_f32_small<2, GU>), grid, dim3(WG), 0, st, A, S, M, K, acc);
-  else hipLaunchKernelGGL((k_gemm_nt_f32_small<1, GU>), grid, dim3(WG), 0, st, A, S, M, K, acc);
+  if (wide) hipLaunchKernelGGL((k_gemm_nt_f32_small<16, 2, GU>), grid, dim3(256), 0, st, A, S, M, K, acc);
+  else if (tight) hipLaunchKernelGGL((k_gemm_nt_f32_small<8, 1, GU>), grid, dim3(64), 0, st, A, S, M, K, acc);
+  else hipLaunchKernelGGL((k_gemm_nt_f32_small<16, 1, GU>), grid, dim3(256), 0, st, A, S, M, K, acc);
   return true;
 }
 

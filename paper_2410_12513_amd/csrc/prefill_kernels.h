@@ -678,36 +678,38 @@ __global__ void __launch_bounds__(WG) k_gemm_nt_f32(const float* __restrict__ A,
     }
 }
 
-// The same for shapes whose 64 x 64 tiles would leave most of the chip idle (short prompts of a small model): 16 TT x 16 TT
-// tiles, TT x TT outputs per thread, K in steps of 256 / TT with the next step already on its way in registers.  Up to three matrices
+// The same for shapes whose 64 x 64 tiles would leave most of the chip idle (short prompts of a small model): S TT x S TT
+// tiles, S x S threads, TT x TT outputs per thread, K in steps of 256 / TT with the next step already on its way in registers.  Up to three matrices
 // applied to the same rows, their column tiles one after the other; GU: matrix 0 is the gate, 1 up, and C[0] = SiLU(gate) * up.  Every
 // output is the same chain of multiply-adds over ascending k, so the bits are those of k_gemm_nt_f32 (and k_silu_mul).  Bound: latency, a
 // memory round trip per step (32 x 256 x 256: 17.6 us in 64 x 64 tiles, 5.8 in steps of 64, 5.2 now - Q, K and V together 5.2 -;
-// 32 x 256 x 688: 49.4, 14.0, 10.1; gate and up of 32 x 688 x 256 with SiLU 6.0 + 6.0 + 2.1 in three launches, 7.0 here; kernel trace).
+// 32 x 256 x 688: 49.4, 14.0, 10.1; gate and up of 32 x 688 x 256 with SiLU 6.0 + 6.0 + 2.1 in three launches, 7.0 here; kernel trace).  With one
+// output a thread a multiply-add waits for 8 bytes from LDS: 16 x 16 tiles that leave half the chip without one are cut into four
+// (32 tokens, four layers of 256 x 688: 267 us a prompt pass, 245 so).
 struct SmallSegs { const float* W[3]; float* C[3]; int N[3], blocks[3]; };
-template <int TT, bool GU>
-__global__ void __launch_bounds__(WG) k_gemm_nt_f32_small(const float* __restrict__ A, SmallSegs S, int M, int K, int accumulate) {
-  constexpr int T = 16 * TT, BK = 256 / TT, PITCH = BK + 4, NB = GU ? 2 : 1;      // (rows 16 bytes apart modulo the banks)
-  constexpr int PR = BK / 4, NP = T * PR / WG;             // pieces of 16 bytes in a row of a step; pieces of a thread
+template <int S, int TT, bool GU>
+__global__ void __launch_bounds__(S * S) k_gemm_nt_f32_small(const float* __restrict__ A, SmallSegs segs, int M, int K, int accumulate) {
+  constexpr int N_THR = S * S, T = S * TT, BK = 256 / TT, PITCH = BK + 4, NB = GU ? 2 : 1;      // (rows 16 bytes apart modulo the banks)
+  constexpr int PR = BK / 4, NP = T * PR / N_THR;             // pieces of 16 bytes in a row of a step; pieces of a thread
   __shared__ __align__(16) float sA[T * PITCH], sB[NB][T * PITCH];
   int bx = blockIdx.x, si = 0;
   if (!GU)
-    while (si < 2 && bx >= S.blocks[si]) bx -= S.blocks[si++];
-  const float* const W = S.W[si];
-  float* const C = S.C[si];
-  const int N = S.N[si];
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4, m0 = blockIdx.y * T, n0 = bx * T;
+    while (si < 2 && bx >= segs.blocks[si]) bx -= segs.blocks[si++];
+  const float* const W = segs.W[si];
+  float* const C = segs.C[si];
+  const int N = segs.N[si];
+  const int tid = threadIdx.x, tx = tid & (S - 1), ty = tid / S, m0 = blockIdx.y * T, n0 = bx * T;
   float4 ra[NP], rb[NB][NP];
   auto fetch = [&](int k0) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < NP; ++u) {
-      const int row = (u * WG + tid) / PR, k = k0 + (u * WG + tid) % PR * 4;
+      const int row = (u * N_THR + tid) / PR, k = k0 + (u * N_THR + tid) % PR * 4;
       // (a piece that exists is loaded whatever happens and zeroed afterwards: choosing between a load and a constant makes
       // the compiler choose between two addresses, one of them in scratch memory)
       ra[u] = keep4(*reinterpret_cast<const float4*>(A + (size_t)min(m0 + row, M - 1) * K + min(k, K - 4)), k < K && m0 + row < M);
 #pragma unroll
       for (int b = 0; b < NB; ++b)
-        rb[b][u] = keep4(*reinterpret_cast<const float4*>((b ? S.W[1] : W) + (size_t)min(n0 + row, N - 1) * K + min(k, K - 4)), k < K && n0 + row < N);
+        rb[b][u] = keep4(*reinterpret_cast<const float4*>((b ? segs.W[1] : W) + (size_t)min(n0 + row, N - 1) * K + min(k, K - 4)), k < K && n0 + row < N);
     }
   };
   float acc[NB][TT][TT] = {};
@@ -716,7 +718,7 @@ __global__ void __launch_bounds__(WG) k_gemm_nt_f32_small(const float* __restric
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < NP; ++u) {
-      const int at = (u * WG + tid) / PR * PITCH + (u * WG + tid) % PR * 4;
+      const int at = (u * N_THR + tid) / PR * PITCH + (u * N_THR + tid) % PR * 4;
       *reinterpret_cast<float4*>(sA + at) = ra[u];
 #pragma unroll
       for (int b = 0; b < NB; ++b) *reinterpret_cast<float4*>(sB[b] + at) = rb[b][u];
@@ -729,9 +731,9 @@ __global__ void __launch_bounds__(WG) k_gemm_nt_f32_small(const float* __restric
       float4 a[TT], w[NB][TT];
 #pragma unroll
       for (int u = 0; u < TT; ++u) {
-        a[u] = *reinterpret_cast<const float4*>(sA + (u * 16 + ty) * PITCH + k);
+        a[u] = *reinterpret_cast<const float4*>(sA + (u * S + ty) * PITCH + k);
 #pragma unroll
-        for (int b = 0; b < NB; ++b) w[b][u] = *reinterpret_cast<const float4*>(sB[b] + (u * 16 + tx) * PITCH + k);
+        for (int b = 0; b < NB; ++b) w[b][u] = *reinterpret_cast<const float4*>(sB[b] + (u * S + tx) * PITCH + k);
       }
 #pragma unroll
       for (int b = 0; b < NB; ++b)
@@ -749,7 +751,7 @@ __global__ void __launch_bounds__(WG) k_gemm_nt_f32_small(const float* __restric
   for (int i = 0; i < TT; ++i)
 #pragma unroll
     for (int j = 0; j < TT; ++j) {
-      const int row = m0 + i * 16 + ty, col = n0 + j * 16 + tx;
+      const int row = m0 + i * S + ty, col = n0 + j * S + tx;
       if (row < M && col < N) {
         float* c = C + (size_t)row * N + col;
         if (GU) *c = siluf(acc[0][i][j]) * acc[NB - 1][i][j];

@@ -223,3 +223,16 @@ def test_weights_of_large_scores_do_not_depend_on_the_running_maximum(n):
     p = torch.softmax((2 * level.double() - 127) / 16, 0)
     want = 1.0 + float((p * (2 * sign.double() - 1)).sum())
     assert abs(float(hidden[0, 20]) - want) <= 2 * 2.0 ** -17, (float(hidden[0, 20]), want)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("desc", [ModelDesc(2, 72, 2, 1, 64, 104, 67, dtype="fp32"), ModelDesc(2, 256, 4, 4, 64, 688, 301, dtype="fp32")])
+def test_short_fp32_prompts_have_the_bits_of_a_long_group(desc):
+    """Products of a few rows go in tiles of 8 x 8, those of a group with a long prompt in 16, 32 or 64: the same chain of multiply-adds an output."""
+    w, r = to_device(make_weights(desc, 6), "cuda"), make_router(desc, 6).cuda()
+    prompts = [make_prompt(desc.vocab, n, 60 + n) for n in (1, 7, 8, 9, 17, 31, 33, 600)]
+    got = _run(desc, w, r, prompts, 700)
+    for b, p in enumerate(prompts[:-1]):
+        one = _run(desc, w, r, [p], 700)
+        for k in ("rho", "hidden", "logits", "rows"):
+            assert torch.equal(one[k][0], got[k][b]), (k, p.numel())
