@@ -9,10 +9,10 @@
 // The whole-step kernel of small fp32 models (small_step.h) waits between its 64 workgroups too, but needs little: a persistent kernel on
 // every compute unit leaves each of them room for one such workgroup, so four of these steps always find their places on 256 compute units,
 // whatever else runs.  They go through four lanes, in each of which steps are ordered as above; contexts are spread over the lanes by their streams, so that
-// up to four streams see no event.  A persistent kernel of a geometry that takes so much LDS that no workgroup fits beside it is
-// ordered against all lanes.
+// up to four streams see no event.  A persistent kernel of a geometry that takes so much LDS that no workgroup fits beside it, and the
+// one that runs a batched step (batch_step.h), is ordered against all lanes.
 //
-// A context belongs to an order from its first such step on: one that decodes batches, or not at all, costs the others nothing.
+// A context belongs to an order from its first such step on: one that does not decode costs the others nothing.
 //
 // The runtime's calls come in through Api, so that the rule can be run against a model of streams and events without a GPU.
 #pragma once
