@@ -26,7 +26,9 @@
 // Sequences keep their slot through all layers.  A slot whose sequence skips a layer goes through its products like the others (the tile has
 // sixteen rows anyway) and is left out of attention and of the residual stream.
 //
-// The workgroups wait for each other, so all of them have to be on the chip: step_order.h.  The waits are bounded (sk_poll_give_up).
+// The workgroups wait for each other, so all of them have to be on the chip: step_order.h.  The waits are bounded: polls of memory by sk_poll_give_up, those for
+// the other wave of a pair by bs_inside.  One that does not get what it waits for says so in *err and to its workgroup, and nothing is made of what did
+// not come: a streaming wave without its activations does not count itself done, a serving wave without all sums stores none.
 //
 // us a step, launches per op / this kernel, bf16, embedding and head included: 8B shape, eight layers, 16 sequences of 256 to 2048 keys 1165 / 1120 (436 MB of
 // weights a layer: 61 us at the 7.1 TB/s of a large read, 112 here); four of 16384 keys, four layers 782 / 746; 3B shape, six layers, three
@@ -169,6 +171,17 @@ __device__ __forceinline__ void bs_wait_loads(int n) {
 // A counter in LDS that waves of this workgroup advance.
 __device__ __forceinline__ int bs_count(const int* c) { return uni(__hip_atomic_load(c, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP)); }
 
+// Until there() holds, which another wave of this workgroup sees to; false: it never will.
+template <typename F>
+__device__ __forceinline__ bool bs_inside(int* bad, int* err, F there) {
+  const WaitEnd end = wait_inside(there, [=]() __attribute__((always_inline)) { return bs_count(bad) != 0; }, []() __attribute__((always_inline)) { __builtin_amdgcn_s_sleep(1); });
+  if (end == WaitEnd::RAN_OUT) {
+    *bad = 1;
+    __hip_atomic_fetch_or(as_global(err), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  return end == WaitEnd::THERE;
+}
+
 __global__ void __launch_bounds__(WG) k_fill_words(unsigned* p, size_t n, unsigned v) {
   for (size_t i = (size_t)blockIdx.x * WG + threadIdx.x; i < n; i += (size_t)gridDim.x * WG) p[i] = v;
 }
@@ -220,7 +233,7 @@ __device__ __forceinline__ void bs_issue(const BsSeg& s, int p, int t, int wave,
 
 // Streams phase `cur`, whose first BS_RING chunks are in the ring, and requests the first ones of `nxt` behind it.  x: this pair's activations, two
 // passes in turn; acc: this wave's sums, [tile][lane].  One code for all phases.
-struct BsLink { int* staged; int* consumed; int* done; const int* bad; int base, n; const unsigned* words; int* err; };     // counters in LDS: passes staged / taken so far, base at the phase's start
+struct BsLink { int* staged; int* consumed; int* done; int* bad; int base, n; const unsigned* words; int* err; };     // counters in LDS: passes staged / taken so far, base at the phase's start
 __device__ __forceinline__ void bs_stream(const BsSeg& cur, const BsSeg& nxt, u32x4_t (&ring)[BS_RING][BS_CHUNK], const char* x, int slots, f32x4_t* acc, unsigned up_offset, int wave,
                                           const BsLink& link) {
   const int lane = sk_lane_opaque();
@@ -241,8 +254,9 @@ __device__ __forceinline__ void bs_stream(const BsSeg& cur, const BsSeg& nxt, u3
   for (int j = 0; j < BS_RING; ++j) step(rp, rt, cur.tiles);
   auto consume = [&](const u32x4_t (&b)[BS_CHUNK]) __attribute__((always_inline)) {
     if (ct == 0) {
-      unsigned spins = 0;
-      while (bs_count(link.staged) <= link.base + cp && *(volatile const int*)link.bad == 0 && ++spins < SK_SPIN_LIMIT) __builtin_amdgcn_s_sleep(1);
+      // (without its activations the wave walks through the rest on what is in LDS, waits for nothing - whoever has set *bad has set *err - and does not
+      // count itself done: a branch here would make two kernels of this one, with 34 registers more)
+      bs_inside(link.bad, link.err, [&]() __attribute__((always_inline)) { return bs_count(link.staged) > link.base + cp; });
       const char* xc = x + (cp & ring_mask) * slots * 1024 + place;
       unsigned most = 0;
 #pragma unroll
@@ -261,7 +275,7 @@ __device__ __forceinline__ void bs_stream(const BsSeg& cur, const BsSeg& nxt, u3
       if (lane == 0) __hip_atomic_store(link.consumed, link.base + cp + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
       if (!__all(most != BS_EMPTY || !live)) {        // a word was not there yet although its producer's first one was: read the pass itself, coherently
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned*>(uni(link.words)), (short)0, cur.ksteps * slots * 128, 0x00020000);
-        bs_poll(link.err, [&]() __attribute__((always_inline)) {
+        if (!bs_poll(link.err, [&]() __attribute__((always_inline)) {
           unsigned m = 0;
 #pragma unroll
           for (int u = 0; u < BS_CHUNK; ++u) {
@@ -271,7 +285,7 @@ __device__ __forceinline__ void bs_stream(const BsSeg& cur, const BsSeg& nxt, u3
             split(u, a, b);
           }
           return m != BS_EMPTY || !live;
-        });                                           // (a wait that gives up has said so: the next phase's ends the workgroup)
+        })) *link.bad = 1;
       }
     }
     f32x4v_t hi = {0.f, 0.f, 0.f, 0.f}, lo = {0.f, 0.f, 0.f, 0.f};
@@ -290,7 +304,7 @@ __device__ __forceinline__ void bs_stream(const BsSeg& cur, const BsSeg& nxt, u3
 #pragma unroll
     for (int j = 0; j < BS_RING; ++j) {
       if (c0 + j < total) consume(ring[j]);
-      if (c0 + j == max(total, 1) - 1 && lane == 0) __hip_atomic_fetch_add(link.done, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+      if (c0 + j == max(total, 1) - 1 && bs_count(link.bad) == 0 && lane == 0) __hip_atomic_fetch_add(link.done, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
       bs_issue(g, rp, rt, wave, lane, up_offset, ring[j]);
       step(rp, rt, g.tiles);
     }
@@ -409,7 +423,6 @@ __global__ void __launch_bounds__(BS_THREADS) k_batch_step(BatchStep) {
     const unsigned x_off = (unsigned)uni((int)(unsigned)(size_t)(__attribute__((address_space(3))) void*)x);
     int issued = 0, out = 0;
     bool ahead = false;
-    unsigned spins = 0;
     while (out < passes || !ahead) {
       if (!ahead && out == min(passes, when)) {
         meanwhile();
@@ -425,9 +438,8 @@ __global__ void __launch_bounds__(BS_THREADS) k_batch_step(BatchStep) {
         bs_wait_loads((issued - 1 - out) * slots);
         ++out;
         if (lane == 0) __hip_atomic_store(staged + pair, base + out, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-      } else {
-        if (++spins > SK_SPIN_LIMIT) { *bad = 1; return; }
-        __builtin_amdgcn_s_sleep(1);
+      } else if (!bs_inside(bad, P.err, [&]() __attribute__((always_inline)) { return bs_count(consumed + pair) >= base + issued - room + 1; })) {
+        return;
       }
     }
   };
@@ -634,11 +646,12 @@ __global__ void __launch_bounds__(BS_THREADS) k_batch_step(BatchStep) {
       const int passes = bs_share(ph, kind == BG_GU).tiles > 0 ? (ph.ksteps / BS_CHUNK - pair + BS_PAIRS - 1) / BS_PAIRS : 0;
       stage(P, bs_input(P, kind, kl), ph.ksteps, passes, kind == BG_GU ? 1 : passes, meanwhile);
       base += passes;
-      unsigned spins = 0;
-      while (bs_count(done) < BS_PAIRS * (s + 1) && ++spins < SK_SPIN_LIMIT) __builtin_amdgcn_s_sleep(1);
-      if (kind == BG_QKV) projections(P, to);
-      else if (kind == BG_GU) glu(P, to);
-      else residual(P, false, ph.ksteps, gains, bits, last ? nullptr : to, sq);
+      // (a wait of this wave that gave up, for activations or squares, has set *bad)
+      if (bs_inside(bad, P.err, [&]() __attribute__((always_inline)) { return bs_count(done) >= BS_PAIRS * (s + 1); }) && bs_count(bad) == 0) {
+        if (kind == BG_QKV) projections(P, to);
+        else if (kind == BG_GU) glu(P, to);
+        else residual(P, false, ph.ksteps, gains, bits, last ? nullptr : to, sq);
+      }
     }
     lds_barrier();                                                // phase over: its sums have been read
     if (uni(*bad)) return;

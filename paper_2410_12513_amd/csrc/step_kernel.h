@@ -6,6 +6,7 @@
 #pragma once
 #include <type_traits>
 
+#include "wait_inside.h"
 #include "decode_kernels.h"
 #include "sample_kernels.h"
 
@@ -23,7 +24,6 @@ constexpr int SK_PD = 2;
 constexpr int SK_PSUM = 2048;         // partial sums a workgroup can hold (row segments per phase)
 constexpr int SK_SMP_LISTS = 8;       // sampling in the kernel: candidate lists per lane of the merging wave (grids up to 512 workgroups)
 constexpr int SK_QSPLIT_MAX = 8;      // attention of the persistent kernel: at most this many key splits per query head
-constexpr unsigned SK_SPIN_LIMIT = 1u << 21;
 constexpr int SK_TSLOTS = 12;         // timestamps per segment: arrive, -, attention, stage, stream, results, then six marks inside attention
 
 
