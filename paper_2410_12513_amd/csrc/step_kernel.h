@@ -804,7 +804,7 @@ __device__ __forceinline__ void sk_consume(const SegDesc& d, int round, int wave
     do {
       seen = uni(__hip_atomic_load(staged, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP));
       if (seen <= sg) __builtin_amdgcn_s_sleep(4);
-    } while (seen <= sg && ++spins < SK_SPIN_LIMIT);      // bounded; the service wave always gets there
+    } while (seen <= sg && ++spins < INSIDE_LIMIT);       // bounded; the service wave, whose polls are shorter than that, always gets there
   }
   const float* x0p = xs + ((sg * SK_SEG + lane * 8) >> 1);
   const float* x1p = x0p + uni(d.xplane);
@@ -1731,7 +1731,7 @@ __global__ void __launch_bounds__(SK_THREADS) __attribute__((aligned(4096))) k_s
           unsigned spins = 0;
           for (;;) {
             const int done = __hip_atomic_load(S.flag + 4 + min(lane, SK_SWAVES - 1), __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP);
-            if (__all(done * SK_SWAVES + min(lane, SK_SWAVES - 1) >= need) || ++spins > SK_SPIN_LIMIT) break;
+            if (__all(done * SK_SWAVES + min(lane, SK_SWAVES - 1) >= need) || ++spins > INSIDE_LIMIT) break;
             __builtin_amdgcn_s_sleep(8);
           }
           for (int r = lane; r < cs; r += 64) {

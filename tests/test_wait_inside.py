@@ -26,3 +26,12 @@ def test_no_wait_of_the_batched_step_goes_on_without_what_it_waits_for():
     assert len(calls) >= 8
     unlooked = [body[at:at + 24] for at in calls if not re.search(r"if \(!?$", body[body.rindex("\n", 0, at) + 1:at])]
     assert unlooked == ["bs_inside(link.bad, link"] and re.search(r"bs_count\(link\.bad\) == 0 && lane == 0\) __hip_atomic_fetch_add\(link\.done", body)
+
+
+def test_only_polls_of_memory_have_the_shorter_limit():
+    for name in sorted(os.listdir(CSRC)):
+        with open(os.path.join(CSRC, name)) as fh:
+            code = re.sub(r"//.*", "", fh.read())
+        uses = [line for line in code.splitlines() if "SK_SPIN_LIMIT" in line]
+        want = {"wait_inside.h": "constexpr unsigned SK_SPIN_LIMIT", "step_kernel.h": "((unsigned)e >> 1) - 1u : SK_SPIN_LIMIT"}.get(name)
+        assert len(uses) == (want is not None) and all(want in line for line in uses), (name, uses)
