@@ -72,7 +72,7 @@ extern "C" {
 #define FIRST_OPT_PREFILL_ATTN  7  /* prompt attention.  1 (default): tiled kernel on the matrix cores when the cache is bf16
                                       and head_dim is 64 or 128, else the plain kernel; 0: always the plain fp32 kernel */
 #define FIRST_OPT_STEP_POLL_LIMIT 10 /* test tap: value >= 0 = the number of unsuccessful polls after which a wait between workgroups of
-                                      the persistent kernel, or of the small fp32 models', gives up (default, or -1: 2^21, seconds).  With 0 the next decode step
+                                      the persistent kernel, of a batched step's, or of the small fp32 models', gives up (default, or -1: 2^21, seconds).  With 0 the next decode step
                                       gives up at its first exchange: every wave leaves at its next wait, nothing hangs, and the next
                                       call that synchronises (first_sync, first_seq_len, ...) returns FIRST_ERR_HIP, clears the limit
                                       and resets the exchange state; the live sequences must be prefilled again.  Synchronises. */
@@ -240,7 +240,7 @@ int first_sample_top_k_static(void *hip_stream, const float *logits, int32_t n_s
 int first_set_option(first_ctx *ctx, int32_t option, int32_t value);
 /* hipStreamSynchronize of the stream.  The workgroups of the persistent decode kernel wait for each other with bounded
  * waits; one that gives up (it should never happen: it means part of the grid was not running) makes every later
- * launch leave at its first wait, so tokens and logits stop changing.  first_sync - and every other entry point that
+ * launch leave at once or at its first wait, so tokens (drawn ones too), logits and lengths stop changing.  first_sync - and every other entry point that
  * synchronises the stream: first_get_kept, first_seq_len, first_get_hidden, first_kv_read / first_kv_write - reports
  * this once as FIRST_ERR_HIP and resets the exchange state; the steps since the failed wait must be repeated. */
 int first_sync(first_ctx *ctx);

@@ -369,6 +369,7 @@ __global__ void __launch_bounds__(BS_THREADS) k_batch_step(BatchStep) {
   int *bad = ctl, *done = ctl + 1, *n_works = ctl + 2, *n_kept = ctl + 3, *staged = ctl + 4, *consumed = ctl + 8;
   if (wave == 0) {                                              // layers that somebody keeps
     const BatchStep P = bs_params();
+    const int gave_up = (int)bs_ld(reinterpret_cast<const unsigned*>(P.err)) & 1;      // in an earlier launch: its words are in nobody's order
     const int L = P.L, lane = tid & 63;
     const uint8_t* mask = P.mask;
     int nk = 0;
@@ -381,7 +382,7 @@ __global__ void __launch_bounds__(BS_THREADS) k_batch_step(BatchStep) {
       if (bits) kept[nk + __popcll(m & ((1ull << lane) - 1))] = i | (int)(bits << 16);
       nk += __popcll(m);
     }
-    if (lane < 12) ctl[lane] = lane == 3 ? nk : 0;
+    if (lane < 12) ctl[lane] = lane == 3 ? nk : lane == 0 ? gave_up : 0;
   } else if (wave == 2) {                                       // the tables into the scalar cache, which nothing else of this kernel fills: a first look at an entry costs 2 us
     const BatchStep P = bs_params();
     unsigned seen = 0;
@@ -390,6 +391,7 @@ __global__ void __launch_bounds__(BS_THREADS) k_batch_step(BatchStep) {
   }
   if (wave == 1 && (tid & 63) < 16) pos[tid & 63] = *as_global(bs_params().d.len + min(tid & 63, n - 1));
   lds_barrier();
+  if (uni(*bad)) return;
   const int nk = uni(*n_kept);
   auto layer_of = [&](int kl) __attribute__((always_inline)) { return uni(kept[min(kl, nk - 1)] & 0xffff); };
   auto table = [&](const BatchStep& P, int layer) __attribute__((always_inline)) { return sk_const<BsLayer>(reinterpret_cast<unsigned long long>(P.layers) + layer * sizeof(BsLayer)); };

@@ -65,6 +65,7 @@ struct BatchParams {
   int attn_nwork;
   AttnWork attn_work[ATTN_WORK_MAX];
   int xpitch;
+  const int* err;       // the head's and the argmax's, behind the kernel of batch_step.h: where *err & 1, a wait gave up and they leave everything as it is
   float* logits_all;    // [B][V] logits of the step (caller's buffer or the library's)
   // optional copies of the layer's matrices (and of the LM head) in MFMA tile order, see k_tile_weights
   const bf16 *t_qkv, *t_o, *t_g, *t_u, *t_d, *t_head;
@@ -757,6 +758,7 @@ __global__ void __launch_bounds__(BG_THREADS) k_bgemv(BatchParams P, int N, int 
 
   // norm ops: 1/rms of slot lane / 4 (requested here so that the loads overlap the weight stream)
   const float rv = (MODE == BG_QKV || MODE == BG_GU || MODE == BG_HEAD) ? bg_rinv_wave(P, K, lane) : 0.f;
+  const int gave_up = MODE == BG_HEAD && P.err != nullptr ? *P.err & 1 : 0;
 
   f32x4v_t acc[NS];
 #pragma unroll
@@ -840,6 +842,7 @@ __global__ void __launch_bounds__(BG_THREADS) k_bgemv(BatchParams P, int N, int 
         acc[i][j] = a;
       }
   }
+  if (MODE == BG_HEAD && gave_up) return;
   float rinv4[4];                                    // 1/rms of this lane's four slots (4 g + j)
 #pragma unroll
   for (int j = 0; j < 4; ++j) rinv4[j] = __shfl(rv, (4 * g + j) * 4, 64);
@@ -1133,6 +1136,7 @@ __global__ void __launch_bounds__(WG) k_argmax_b(BatchParams P, unsigned* cnt, i
   const DecParams& p = P.d;
   const int b = P.seqs.id[blockIdx.x], tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const float* lg = P.logits_all + (size_t)b * p.V;
+  const int gave_up = P.err != nullptr ? *P.err & 1 : 0;
   const int per = (p.V + ARG_CHUNKS - 1) / ARG_CHUNKS, r0 = blockIdx.y * per, r1 = min(p.V, r0 + per);
   Best best{-INFINITY, 0x7fffffff};
   for (int i0 = r0 + tid; i0 < r1; i0 += 8 * WG) {
@@ -1173,7 +1177,7 @@ __global__ void __launch_bounds__(WG) k_argmax_b(BatchParams P, unsigned* cnt, i
   static_assert(ARG_CHUNKS == 64, "one chunk per lane");
   best = Best{__hip_atomic_load(&ap->v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), __hip_atomic_load(&ap->i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)};
   wave_best();
-  if (lane == 0) {
+  if (lane == 0 && !gave_up) {
     if (p.token_out) p.token_out[b] = best.i;
     if (advance) p.len[b] += 1;
   }

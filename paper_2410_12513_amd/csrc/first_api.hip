@@ -737,6 +737,7 @@ void enqueue_batch_step(first_ctx* c, const int* tokens, float* logits, int* tok
   P.xh = c->d_xh; P.xl = c->d_xl; P.rinv = c->d_rinv; P.xpitch = c->xpitch; P.ssq_part = c->d_ssq;
   P.logits_all = logits ? logits : c->d_logits_all;
   P.t_head = c->t_head;
+  P.err = c->d_err;
   for (int b = 0; b < c->B; ++b) P.seqs.id[P.seqs.n++] = b;
   hipLaunchKernelGGL(k_embed_b, dim3(c->B, 2), dim3(WG), 0, c->stream, P, (const float*)nullptr);
   BatchStep S{};
@@ -878,16 +879,17 @@ int launch_gemm(first_ctx* c, hipStream_t st, int dtype, const void* A, const vo
 // The top-k draw on n_seq rows of logits: one workgroup a row, or lists of parts of the row and a second launch that merges them
 // (part: room for n_seq * ceil(vocab / SMP_PART) * k candidates).  Parts are twice as long where there would be more of them than
 // run at a time (two on each of 256 compute units).
+template <typename... Draw>
 void launch_sample(hipStream_t st, const float* logits, int n_seq, int vocab, const float* uniforms, float temperature, int k, Cand* part,
-                   int* token_out, int* candidates_out) {
+                   int* token_out, int* candidates_out, Draw... draw) {
   if (vocab <= SMP_ROW_MAX) {
-    hipLaunchKernelGGL(k_topk<true>, dim3(1, n_seq), dim3(SMP_THREADS), 0, st, logits, vocab, vocab, k, temperature, uniforms, part, token_out, candidates_out);
+    hipLaunchKernelGGL((k_topk<true, Draw...>), dim3(1, n_seq), dim3(SMP_THREADS), 0, st, logits, vocab, vocab, k, temperature, uniforms, part, token_out, candidates_out, draw...);
     return;
   }
   auto parts = [&](int len) { return (vocab - 1) / len + 1; };
   const int len = (long long)n_seq * parts(SMP_PART) > 512 ? 2 * SMP_PART : SMP_PART;
   hipLaunchKernelGGL(k_topk<false>, dim3(parts(len), n_seq), dim3(SMP_THREADS), 0, st, logits, vocab, len, k, temperature, uniforms, part, token_out, candidates_out);
-  hipLaunchKernelGGL(k_topk_draw, dim3(n_seq), dim3(SMP_THREADS), 0, st, part, parts(len) * k, k, temperature, uniforms, token_out, candidates_out);
+  hipLaunchKernelGGL(k_topk_draw<Draw...>, dim3(n_seq), dim3(SMP_THREADS), 0, st, part, parts(len) * k, k, temperature, uniforms, token_out, candidates_out, draw...);
 }
 
 // Tile and number of K slices of a k_pgemm launch.  The estimate (in us) is a fixed cost + K steps of 64 times the time of a step, summed
@@ -1657,9 +1659,14 @@ int decode_step_impl(first_ctx* c, const int32_t* last_tokens, float* logits_out
     else if (small) enqueue_small_steps(c, last_tokens, logits_out, token_out);
     else if (bf) enqueue_decode_ops<bf16>(c, last_tokens, logits_out, token_out, S);
     else enqueue_decode_ops<float>(c, last_tokens, logits_out, token_out, S);
-    if (smp && !fused)
-      launch_sample(c->stream, logits_out, c->B, c->d.vocab, smp->uniforms, smp->temperature, smp->top_k, c->d_topk_part, token_out,
-                    smp->candidates_out);
+    if (smp && !fused) {
+      auto sample = [&](auto... draw) {
+        launch_sample(c->stream, logits_out, c->B, c->d.vocab, smp->uniforms, smp->temperature, smp->top_k, c->d_topk_part, token_out,
+                      smp->candidates_out, draw...);
+      };
+      if (persistent || whole || small) sample(DrawUnlessGivenUp{c->d_err});
+      else sample();
+    }
   };
   // A small model's step of one launch goes out as one: 6.7 us between two of them, against 13 between replays of a graph with one node.
   const bool one_launch = small && c->B == 1 && !smp;

@@ -93,6 +93,13 @@ __device__ __forceinline__ void rank_keys(const unsigned long long* keys, int n,
   }
 }
 
+// What a draw asks before it writes behind the kernel of a whole decode step: whether a wait of that gave up (bit 0 of *err), so that its logits are none.  Other
+// draws have no such argument.
+struct DrawUnlessGivenUp {
+  const int* err;
+  __device__ __forceinline__ bool operator()() const { return (*err & 1) == 0; }
+};
+
 // The first k of a row (FINAL: and the draw; one launch, no scratch memory), or of part_len logits of it.  grid (parts, rows).
 //
 // First pass: a thread takes every 1024th piece of four logits (of one where they are few) and keeps the largest value and the LAST index of
@@ -109,10 +116,10 @@ constexpr int SMP_PART = 16384;
 constexpr int SMP_ROW_MAX = 65536;                       // longer rows in parts (16 rows of 65536, k = 10: 11.2 us in one launch, 10.1 in parts; 50257: 10.1)
 struct __align__(4) Logits4 { float v[4]; };            // (a row starts on 4 bytes)
 
-template <bool FINAL>
+template <bool FINAL, typename... Draw>
 __global__ void __launch_bounds__(SMP_THREADS) k_topk(const float* __restrict__ logits, int V, int part_len, int k, float temperature,
                                                      const float* __restrict__ uniforms, Cand* __restrict__ part,
-                                                     int* __restrict__ token_out, int* __restrict__ cand_out) {
+                                                     int* __restrict__ token_out, int* __restrict__ cand_out, Draw... draw) {
   __shared__ __align__(16) unsigned long long list[SMP_LIST];
   __shared__ unsigned long long groups[64], top[SMP_KMAX], bound;
   __shared__ int found;
@@ -188,7 +195,7 @@ __global__ void __launch_bounds__(SMP_THREADS) k_topk(const float* __restrict__ 
   const unsigned long long t = bound;
   auto finish = [&]() __attribute__((always_inline)) {   // wave 0: the draw, or the part's list
     if constexpr (FINAL) {
-      smp_draw_wave(top, k, temperature, u, token_out + seq, cand_out ? cand_out + (size_t)seq * k : nullptr);
+      if ((draw() && ...)) smp_draw_wave(top, k, temperature, u, token_out + seq, cand_out ? cand_out + (size_t)seq * k : nullptr);
     } else if (lane < k) {
       Cand c = cand_of(top[lane]);
       if (c.i != SMP_NONE) c.i += c0;
@@ -256,9 +263,10 @@ __global__ void __launch_bounds__(SMP_THREADS) k_topk(const float* __restrict__ 
 }
 
 // Stage 2: grid (rows).  n candidates of the row, 1024 at a time beside the first k of those before them.
+template <typename... Draw>
 __global__ void __launch_bounds__(SMP_THREADS) k_topk_draw(const Cand* __restrict__ part, int n, int k, float temperature,
                                                           const float* __restrict__ uniforms, int* __restrict__ token_out,
-                                                          int* __restrict__ cand_out) {
+                                                          int* __restrict__ cand_out, Draw... draw) {
   __shared__ __align__(16) unsigned long long list[SMP_THREADS + SMP_KMAX], top[SMP_KMAX];
   const int tid = threadIdx.x, seq = blockIdx.x;
   const Cand* c = part + (size_t)seq * n;
@@ -279,7 +287,7 @@ __global__ void __launch_bounds__(SMP_THREADS) k_topk_draw(const Cand* __restric
     rank_keys(list, now + (base > 0 ? k : 0), k, top);
   }
   __syncthreads();
-  if (tid < 64) smp_draw_wave(top, k, temperature, u, token_out + seq, cand_out ? cand_out + (size_t)seq * k : nullptr);
+  if (tid < 64 && (draw() && ...)) smp_draw_wave(top, k, temperature, u, token_out + seq, cand_out ? cand_out + (size_t)seq * k : nullptr);
 }
 
 }  // namespace first

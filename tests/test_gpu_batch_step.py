@@ -132,3 +132,56 @@ def test_a_captured_step_takes_the_launches_per_op():
         out.append(torch.stack(hist))
         ctx.close()
     assert torch.equal(*out)
+
+
+@pytest.mark.parametrize("sampled", [False, True])
+@pytest.mark.parametrize("shape,lens", [((3, 256, 4, 1, 64, 512), [5, 900, 40]), ((2, 768, 6, 2, 128, 1280), [15, 700, 33, 64, 1400])], ids=str)
+def test_a_wait_that_gives_up_stops_everything_until_it_is_reported(shape, lens, sampled):
+    """A poll limit of 0, set from the host: every first unsuccessful poll gives up and every workgroup leaves.  Until the error has been reported, once, later steps
+    change no logits, no tokens and no lengths; after a new prompt the context has the bits of an untouched twin."""
+    desc, B = ModelDesc(*shape, 1003, dtype="bf16"), len(lens)
+    w, r = to_device(make_weights(desc, 6), "cuda"), make_router(desc, 6).cuda()
+    ids = torch.cat([make_prompt(desc.vocab, k, 6 + b) for b, k in enumerate(lens)]).cuda()
+    u = torch.linspace(0.1, 0.9, B, device="cuda")
+    hist = []
+    for provoke in (False, True):
+        ctx = P.FirstContext(desc, w, r, max_batch=B, max_seq_len=max(lens) + 20)
+        lg, tk, tin = torch.zeros(B, desc.vocab, device="cuda"), torch.zeros(B, dtype=torch.int32, device="cuda"), torch.full((B,), 9, dtype=torch.int32, device="cuda")
+
+        def step():
+            if sampled:
+                ctx.decode_step_sampled(tin, u, 1.0, 10, lg, tk)
+            else:
+                ctx.decode_step(tin, lg, tk)
+
+        def prompt():
+            ctx.prefill_route(ids, lens)
+            for b in range(B):
+                ctx.set_mask(b, [1] * desc.n_layers)
+        prompt()
+        for graph in (1, 0) if provoke else ():
+            ctx.set_option(1, graph)
+            for _ in range(3):                                   # (an odd number: the next launch takes the other set of words)
+                step()
+            ctx.sync()
+            lg.fill_(-77.)
+            tk.fill_(-7)
+            ctx.set_option(10, 0)
+            for _ in range(3):
+                step()
+            torch.cuda.synchronize()
+            assert bool((lg == -77.).all()) and bool((tk == -7).all())
+            with pytest.raises(P.FirstError) as e:
+                ctx.sync()
+            assert e.value.code == -4 and "gave up" in str(e.value)
+            assert [ctx.seq_len(b) for b in range(B)] == [k + 3 for k in lens]
+            prompt()
+        ctx.set_option(1, 1)
+        hist.append([])
+        for _ in range(6):
+            step()
+            ctx.sync()
+            hist[-1].append((lg.clone(), tk.clone()))
+        ctx.close()
+    for (la, ta), (lb, tb) in zip(*hist):
+        assert torch.equal(la, lb) and torch.equal(ta, tb)
