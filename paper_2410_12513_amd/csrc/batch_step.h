@@ -705,8 +705,9 @@ __global__ void __launch_bounds__(BS_THREADS) k_batch_step(BatchStep) {
                 }
               }
           }
-          // (a workgroup without a share of the coming phase tells the others' workgroups nothing else: its words are empty before these are out)
-          if (splits > 1 && P.phase[BG_O].units < ncu) vm_wait_all();
+          // What tells the producers to come back is what this workgroup stores in the coming phase, behind weights that this wave has requested since and
+          // waited for.  A workgroup without a share of that phase, or a wave without a share of its K (rows of fewer than 1024), waits here.
+          if (splits > 1 && (P.phase[BG_O].units < ncu || P.phase[BG_O].ksteps < BS_PASS)) vm_wait_all();
 #pragma unroll
           for (int d = 0; d < HD; d += 64) {
             const int row = (g * G + hq) * HD + d + lane;

@@ -42,6 +42,7 @@ def _steps(ctx, desc, masks, n, first):
     ((2, 512, 8, 2, 128, 2304), [3 + 11 * b for b in range(16)]),
     ((2, 1536, 12, 4, 64, 2560), [2047, 40, 9]),
     ((2, 2048, 8, 4, 128, 2048), [30] * 8),
+    ((3, 2048, 4, 1, 64, 512), [1000, 30, 700]),              # (waves that merge splits and have no share of the output projection's K)
 ], ids=str)
 @pytest.mark.parametrize("graph", [1, 0])
 def test_one_kernel_agrees_with_launches_per_op(shape, lens, graph):
