@@ -1694,7 +1694,7 @@ int decode_step_impl(first_ctx* c, const int32_t* last_tokens, float* logits_out
       }
     auto it = c->graphs.find(key);
     if (it == c->graphs.end()) {
-      if (c->graphs.size() >= 32) {
+      if (c->graphs.size() >= (whole ? 2 : 1) * 32u) {       // (32 of the caller's sets of buffers: a whole batched step has a graph for either set of its words)
         // make room for one: the least recently used entry goes (it may still be running: wait first)
         auto old = c->graphs.begin();
         for (auto g = c->graphs.begin(); g != c->graphs.end(); ++g)

@@ -186,3 +186,30 @@ def test_a_wait_that_gives_up_stops_everything_until_it_is_reported(shape, lens,
         ctx.close()
     for (la, ta), (lb, tb) in zip(*hist):
         assert torch.equal(la, lb) and torch.equal(ta, tb)
+
+
+def test_as_many_sets_of_buffers_as_before_keep_their_graphs():
+    """Seventeen output buffers in turn, which meet both sets of exchange words: once each has been through both, a step neither captures nor waits for
+    the stream.  The stream is busy when the steps are enqueued, and still is when they have been."""
+    desc, lens, stream, n = ModelDesc(2, 256, 4, 2, 64, 512, 1003, dtype="bf16"), [20, 33, 7], torch.cuda.Stream(), 17
+    w, r = to_device(make_weights(desc, 7), "cuda"), make_router(desc, 7).cuda()
+    ctx = P.FirstContext(desc, w, r, max_batch=3, max_seq_len=120, stream=stream)
+    torch.cuda.synchronize()
+    ctx.prefill_route(torch.cat([make_prompt(desc.vocab, k, b) for b, k in enumerate(lens)]).cuda(), lens)
+    for b in range(3):
+        ctx.set_mask(b, [1] * desc.n_layers)
+    tok, lg, out = torch.full((3,), 9, dtype=torch.int32, device="cuda"), torch.zeros(n, 3, desc.vocab, device="cuda"), torch.zeros(n, 3, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    for i in range(2 * n):
+        ctx.decode_step(tok, lg[i % n], out[i % n])
+    ctx.sync()
+    busy = torch.cuda.Event()
+    with torch.cuda.stream(stream):
+        torch.cuda._sleep(200_000_000)
+        busy.record(stream)
+    for i in range(n):
+        ctx.decode_step(tok, lg[i], out[i])
+    assert not busy.query()
+    ctx.sync()
+    assert ctx.seq_len(0) == lens[0] + 3 * n
+    ctx.close()
