@@ -182,8 +182,10 @@ __device__ __forceinline__ bool bs_inside(int* bad, int* err, F there) {
   return end == WaitEnd::THERE;
 }
 
-__global__ void __launch_bounds__(WG) k_fill_words(unsigned* p, size_t n, unsigned v) {
-  for (size_t i = (size_t)blockIdx.x * WG + threadIdx.x; i < n; i += (size_t)gridDim.x * WG) p[i] = v;
+// Empties the first n words of both sets and attention's.
+__global__ void __launch_bounds__(WG) k_empty_words(unsigned* ex, unsigned* ex2, size_t n, unsigned* att, size_t n_att) {
+  for (size_t i = (size_t)blockIdx.x * WG + threadIdx.x; i < n; i += (size_t)gridDim.x * WG) { ex[i] = BS_EMPTY; ex2[i] = BS_EMPTY; }
+  for (size_t i = (size_t)blockIdx.x * WG + threadIdx.x; i < n_att; i += (size_t)gridDim.x * WG) att[i] = BS_EMPTY;
 }
 
 // A workgroup's share of a phase: units [u0, u1) and the 16-row tiles they lie in (gate/up: a unit is a tile, eight rows of each matrix).

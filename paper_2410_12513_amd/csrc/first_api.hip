@@ -677,13 +677,18 @@ const void* batch_step_fn(const first_ctx* c) {
 int bs_x_bytes(const first_ctx* c) { return (int)std::max((size_t)BS_X_LDS, (bs_attn_lds(c->G, c->d.head_dim) + 15) / 16 * 16); }
 int bs_own(const first_ctx* c) { return (c->d.d_model / 8 + c->num_cu - 1) / c->num_cu * 8; }
 
+// Words of a set in which a step of so many layers and sequences writes: its first ones.
+size_t bs_words_used(const first_ctx* c, int layers, int sequences) {
+  return (size_t)layers * bs_words(c->d.d_model, c->nq, c->nkv, c->d.d_ffn, bs_slots(sequences), c->num_cu).all;
+}
+
 // Everything the one-kernel batched step needs, where the geometry admits it and memory is plentiful.  Which geometries: those of the attention walk it
 // shares (G, page size), whole MFMA chunks of K (widths in 256s), and what its tables and LDS hold.  Of those it is the faster one from the smallest
 // (1B heads and widths, four sequences: 502 us a step as launches per op, 439 so) to the largest (8B, sixteen: 1167 / 1120 with eight layers).
 hipError_t make_batch_step(first_ctx* c) {
   const first_model_desc& d = c->d;
   if (!c->tiled || c->G < 2 || c->G > 4 || d.kv_page_tokens != 16 || d.d_model % 256 || c->nq % 256 || d.d_ffn % 256 || d.n_layers > BS_MAX_L) return hipSuccess;
-  const int ncu = c->num_cu, slots = bs_slots(std::min(d.max_batch, BATCH_SLOTS));
+  const int ncu = c->num_cu;
   if (bs_own(c) > BS_OWN || ncu < d.n_kv_heads || ncu > BS_MAX_WGS) return hipSuccess;
   const int tiles = (d.max_seq_len + 63) / 64, splits = (4 * tiles + AS_PT - 1) / AS_PT;       // (a split's page ids fit its LDS table)
   if (splits > 1 && splits * std::min(d.max_batch, BATCH_SLOTS) > std::min(BS_WORKS, ncu / d.n_kv_heads)) return hipSuccess;
@@ -697,7 +702,7 @@ hipError_t make_batch_step(first_ctx* c) {
   for (int k = 0; k < 4; ++k) c->bs_acc_tiles = std::max(c->bs_acc_tiles, bs_tiles(c->bs_phase[k], ncu, k == BG_GU));
   const size_t lds = bs_lds(bs_x_bytes(c), c->bs_acc_tiles, bs_own(c));
   if (lds > 160 * 1024) return hipSuccess;
-  c->bs_ex_words = (size_t)2 * d.n_layers * bs_words(d.d_model, c->nq, c->nkv, d.d_ffn, slots, ncu).all;
+  c->bs_ex_words = 2 * bs_words_used(c, d.n_layers, std::min(d.max_batch, BATCH_SLOTS));
   c->bs_att_words = (size_t)bs_items(d.n_kv_heads, ncu) * c->G * (d.head_dim + 4);
   if (!memory_to_spare(c->p_least + (c->bs_ex_words + c->bs_att_words) * sizeof(unsigned))) return hipSuccess;
   const void* fn = batch_step_fn(c);
@@ -747,7 +752,7 @@ void enqueue_batch_step(first_ctx* c, const int* tokens, float* logits, int* tok
   for (int k = 0; k < 4; ++k) S.phase[k] = c->bs_phase[k];
   S.up_offset = (unsigned)((const char*)c->layers[0].t_u - (const char*)c->layers[0].t_g);
   S.w = bs_words(d.d_model, c->nq, c->nkv, d.d_ffn, slots, c->num_cu);
-  const size_t set = (size_t)d.n_layers * S.w.all;
+  const size_t set = c->bs_ex_words / 2;
   S.ex = c->bs_ex + c->bs_set * set; S.ex_next = c->bs_ex + (c->bs_set ^ 1) * set; S.att = c->bs_att;
   S.x_bytes = bs_x_bytes(c); S.own = bs_own(c); S.acc_tiles = c->bs_acc_tiles; S.g_final = c->g_final;
   S.xh = c->d_xh; S.xl = c->d_xl; S.ssq_part = c->d_ssq; S.err = c->d_err;
@@ -1734,8 +1739,9 @@ int decode_step_impl(first_ctx* c, const int32_t* last_tokens, float* logits_out
   if (whole) {
     // (a launch empties what the next one will fill, for the layers and sequences it has itself)
     if (c->bs_layers != layers_kept || c->bs_slots != c->B) {
-      hipLaunchKernelGGL(k_fill_words, dim3(2048), dim3(WG), 0, c->stream, c->bs_ex, c->bs_ex_words, BS_EMPTY);
-      hipLaunchKernelGGL(k_fill_words, dim3(256), dim3(WG), 0, c->stream, c->bs_att, c->bs_att_words, BS_EMPTY);
+      // (what launches have written since all words were emptied last)
+      const size_t set = c->bs_ex_words / 2, used = c->bs_layers < 0 ? set : bs_words_used(c, c->bs_layers, c->bs_slots);
+      hipLaunchKernelGGL(k_empty_words, dim3(2048), dim3(WG), 0, c->stream, c->bs_ex, c->bs_ex + set, used, c->bs_att, c->bs_att_words);
       HIPCHK(c, hipGetLastError());
       c->bs_layers = layers_kept; c->bs_slots = c->B;
     }

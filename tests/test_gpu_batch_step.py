@@ -213,3 +213,23 @@ def test_as_many_sets_of_buffers_as_before_keep_their_graphs():
     ctx.sync()
     assert ctx.seq_len(0) == lens[0] + 3 * n
     ctx.close()
+
+
+def test_sequences_and_layers_that_come_and_go():
+    """Sixteen sequences, three, nine, sixteen again in one context, with more and with fewer layers kept than before: the exchange lies elsewhere every time, and
+    only what was written is emptied in between."""
+    desc, steps = ModelDesc(6, 512, 8, 4, 64, 768, 1003, dtype="bf16"), 5
+    w, r = to_device(make_weights(desc, 8), "cuda"), make_router(desc, 8).cuda()
+    out = []
+    for path in (0, -1):
+        ctx = P.FirstContext(desc, w, r, max_batch=16, max_seq_len=420)
+        ctx.set_option(3, path)
+        for turn, B in enumerate((16, 3, 9, 16, 2)):
+            lens = [5 + 37 * ((b + turn) % 11) for b in range(B)]
+            ctx.prefill_route(torch.cat([make_prompt(desc.vocab, k, turn + b) for b, k in enumerate(lens)]).cuda(), lens)
+            kept = ((2, 1), (6, 4), (5, 3), (3, 3), (6, 1))[turn]  # layers that somebody keeps, at first and later
+            masks = [[[int(i < k and (b == 0 or i == 0 or (i + b) % 3 != 1)) for i in range(6)] for b in range(B)] for k in kept]
+            out.append(_steps(ctx, desc, masks, steps, 11 * turn))
+        ctx.close()
+    for a, b in zip(out[:5], out[5:]):
+        assert float((a - b).abs().max()) <= TOLERANCE and not torch.equal(a, b)

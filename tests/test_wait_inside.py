@@ -20,7 +20,7 @@ def test_no_wait_of_the_batched_step_goes_on_without_what_it_waits_for():
     turns."""
     with open(os.path.join(CSRC, "batch_step.h")) as fh:
         code = re.sub(r"//.*", "", fh.read())
-    body = code[code.index("k_fill_words("):]                              # (behind the waits' own definitions)
+    body = code[code.index("k_empty_words("):]                              # (behind the waits' own definitions)
     assert not re.search(r"SK_SPIN_LIMIT|INSIDE_LIMIT|wait_inside|while \(bs_count", body)
     calls = [m.start() for m in re.finditer(r"\bbs_(?:poll|inside)\(", body)]
     assert len(calls) >= 8
