@@ -84,9 +84,12 @@ extern "C" {
                                       else one pass per sequence; 0: always one pass per sequence; 1: shared pass or error.
                                       Up to 16 sequences of a bf16 model whose widths are multiples of 256, with 2 to 4 query
                                       heads a KV head, 16-token pages and memory for the exchange, take all layers in one
-                                      persistent kernel; it needs every compute unit and is ordered like the persistent step
+                                      persistent kernel where that is the faster way (by an estimate from the widths, the
+                                      sequences, their lengths and the layers they keep); it needs every compute unit and is ordered like the persistent step
                                       above.  FIRST_OPT_DECODE_PATH 0, a fixed number of splits or a stream under capture get
                                       launches per op. */
+#define FIRST_OPT_BATCH_STEP   12  /* test tap: 1 = batched steps take the one persistent kernel wherever it can run; 0 (default): where
+                                      it is the faster way */
 
 typedef struct first_ctx first_ctx;
 

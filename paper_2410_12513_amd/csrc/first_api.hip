@@ -149,6 +149,7 @@ struct first_ctx {
   float *d_rinv = nullptr, *d_logits_all = nullptr;
   int xpitch = 0;
   int batch_path = -1;                    // FIRST_OPT_BATCH_PATH
+  int batch_step = 0;                     // FIRST_OPT_BATCH_STEP
   bf16* t_head = nullptr;                 // tile-order copy of the LM head
   bool tiled = false;                     // tile-order copies of all matrices exist
   // all layers of a batched step as one kernel (batch_step.h): its layer table, two sets of exchange words, and attention's partial results
@@ -683,8 +684,7 @@ size_t bs_words_used(const first_ctx* c, int layers, int sequences) {
 }
 
 // Everything the one-kernel batched step needs, where the geometry admits it and memory is plentiful.  Which geometries: those of the attention walk it
-// shares (G, page size), whole MFMA chunks of K (widths in 256s), and what its tables and LDS hold.  Of those it is the faster one from the smallest
-// (1B heads and widths, four sequences: 502 us a step as launches per op, 439 so) to the largest (8B, sixteen: 1167 / 1120 with eight layers).
+// shares (G, page size), whole MFMA chunks of K (widths in 256s), and what its tables and LDS hold.
 hipError_t make_batch_step(first_ctx* c) {
   const first_model_desc& d = c->d;
   if (!c->tiled || c->G < 2 || c->G > 4 || d.kv_page_tokens != 16 || d.d_model % 256 || c->nq % 256 || d.d_ffn % 256 || d.n_layers > BS_MAX_L) return hipSuccess;
@@ -731,6 +731,22 @@ int kept_by_somebody(const first_ctx* c) {
     kept += any;
   }
   return kept;
+}
+
+// Is the one kernel the faster way for a step of so many layers?  It costs some 13 us a step (its tables, the first exchange of a chip that is empty) and gains
+// `gain` a layer.  The gain is smaller where the rows of the output and down projection do not come out even over the compute units (D 2560: 320 units of eight for 256 of
+// them), and where the activations that every workgroup fetches in a layer are many; it is larger where sequences are split.  us a layer, from steps of one to eight layers of 40
+// keys, at most eight sequences / more: 1B shape 8 to 9.5 / 8, 3B 4 to 5.5 / 3, 8B 8 to 10 / 2 to 2.7, D 2560 1.7 / 2, D 5120 5 to 10 / 2, D 256 to 1536 4 to 9.
+// Launches per op / the one kernel, us a step: 1B shape, 16 sequences, one layer 104 / 110, two 160 / 156; 3B shape, four sequences, two layers 268 / 273, three
+// 338 / 338, four 406 / 400; 8B shape, 16 sequences of 500 keys, four layers 639 / 644, of 1000 663 / 654, eight of 300 1060 / 1055; D 2560, three
+// sequences, four layers 270 / 271, eight 489 / 484.
+bool batch_step_pays(const first_ctx* c, int layers) {
+  const double units = c->d.d_model / 8, uneven = units <= c->num_cu ? 0. : bs_own(c) / 8 * c->num_cu / units - 1.;
+  const double mb = 4e-6 * bs_slots(c->B) * (2 * c->d.d_model + c->nq + c->d.d_ffn);
+  long long keys = 0;
+  for (int b = 0; b < c->B; ++b) keys += c->hlen[b];
+  const double gain = std::max(2., 9. - 12. * uneven - 7. * std::max(0., mb - 0.9)) + (keys > 640ll * c->B ? 3. : 0.);      // (a sequence is split from 10 tiles of 64 keys on)
+  return layers * gain >= 14.;
 }
 
 // One decode token for up to BATCH_SLOTS live sequences: the embedding, one kernel for all layers, the LM head and the argmax.
@@ -1629,10 +1645,11 @@ int decode_step_impl(first_ctx* c, const int32_t* last_tokens, float* logits_out
                                     "multiples of 256, 16-token pages and exactly one live sequence");
   const bool batch_ok = bf && c->B > 1 && c->d_xh && d_batch_fits(c);
   const bool batched = !persistent && batch_ok && c->batch_path != 0;
-  // all layers in one kernel, unless the caller asked for launches per op or a number of splits, or is capturing (its replays would neither be ordered
-  // against other steps nor take the two sets of words in turn), or has more sequences than a tile has rows
+  // all layers in one kernel where that is the faster way, unless the caller asked for launches per op or a number of splits, or is capturing (its replays would neither
+  // be ordered against other steps nor take the two sets of words in turn), or has more sequences than a tile has rows
   const int layers_kept = batched && c->bs_ok ? kept_by_somebody(c) : 0;
-  const bool whole = layers_kept > 0 && c->tiled && c->B <= BATCH_SLOTS && c->decode_path != 0 && c->attn_splits <= 0 && !HipOrderApi::capturing(c->stream);
+  const bool whole = layers_kept > 0 && c->tiled && c->B <= BATCH_SLOTS && c->decode_path != 0 && c->attn_splits <= 0 &&
+                     (c->batch_step || batch_step_pays(c, layers_kept)) && !HipOrderApi::capturing(c->stream);
   // (the persistent kernel merges the workgroups' candidate lists in LDS: a large top_k may not fit there)
   const bool fused = smp && persistent && smp->top_k <= sk_sample_kmax(c->d.d_model, c->nq, c->d.d_ffn, c->num_cu);
   if (smp && !fused && !logits_out) logits_out = c->d_logits_own;
@@ -1857,6 +1874,7 @@ int first_set_option(first_ctx* c, int32_t option, int32_t value) {
     case FIRST_OPT_BATCH_PATH:
       if (value < -1 || value > 1) return fail(c, FIRST_ERR_ARG, "first_set_option: unknown batch path");
       c->batch_path = value; return FIRST_OK;
+    case FIRST_OPT_BATCH_STEP: c->batch_step = value ? 1 : 0; return FIRST_OK;
     case FIRST_OPT_STEP_POLL_LIMIT: {
       if (value < -1 || value > (1 << 29)) return fail(c, FIRST_ERR_ARG, "first_set_option: poll limit out of range");
       HIPCHK(c, hipStreamSynchronize(c->stream));

@@ -14,6 +14,7 @@ torch.set_grad_enabled(False)
 # then a key or value falls on the other side of its bf16 rounding: 2^-8 of one element, which reaches a logit as one of hundreds of terms of
 # its size (logits of size 4: 2^-8 * 4 / sqrt(256) = 1e-3 a flip at most; a few of them at a time).
 TOLERANCE = 3e-3
+OPT_BATCH_STEP = 12                                              # 1: the one kernel wherever it can run, also where it is not the faster way
 
 
 def _steps(ctx, desc, masks, n, first):
@@ -58,6 +59,7 @@ def test_one_kernel_agrees_with_launches_per_op(shape, lens, graph):
         ctx = P.FirstContext(desc, w, r, max_batch=B, max_seq_len=max(lens) + n + 1)
         ctx.set_option(1, graph)
         ctx.set_option(3, path)
+        ctx.set_option(OPT_BATCH_STEP, 1)
         for first in (3, 400):                                   # (a new prompt: every layer again)
             ctx.prefill_route(ids, lens)
             out.append(_steps(ctx, desc, masks, n, first))
@@ -77,6 +79,7 @@ def test_batched_and_single_steps_on_streams_of_their_own():
         out = []
         for model, lens in (("step_hd128", [40, 21, 300]), ("step_hd64", [70]), ("step_g2", [90] * 5)):
             desc, _, _, ctx = build(model, 11, max_batch=len(lens), max_seq_len=400)
+            ctx.set_option(OPT_BATCH_STEP, 1)
             ctx.prefill_route(torch.cat([make_prompt(desc.vocab, k, 5 + b) for b, k in enumerate(lens)]).cuda(), lens)
             for b in range(len(lens)):
                 ctx.set_mask(b, [1] * desc.n_layers)
@@ -107,6 +110,7 @@ def test_a_captured_step_takes_the_launches_per_op():
     for captured in (False, True):
         ctx = P.FirstContext(desc, w, r, max_batch=3, max_seq_len=100, stream=stream)
         ctx.set_option(1, 0)
+        ctx.set_option(OPT_BATCH_STEP, 1)
         torch.cuda.synchronize()
         ctx.prefill_route(ids, lens)
         for b in range(3):
@@ -147,6 +151,7 @@ def test_a_wait_that_gives_up_stops_everything_until_it_is_reported(shape, lens,
     hist = []
     for provoke in (False, True):
         ctx = P.FirstContext(desc, w, r, max_batch=B, max_seq_len=max(lens) + 20)
+        ctx.set_option(OPT_BATCH_STEP, 1)
         lg, tk, tin = torch.zeros(B, desc.vocab, device="cuda"), torch.zeros(B, dtype=torch.int32, device="cuda"), torch.full((B,), 9, dtype=torch.int32, device="cuda")
 
         def step():
@@ -194,6 +199,7 @@ def test_as_many_sets_of_buffers_as_before_keep_their_graphs():
     desc, lens, stream, n = ModelDesc(2, 256, 4, 2, 64, 512, 1003, dtype="bf16"), [20, 33, 7], torch.cuda.Stream(), 17
     w, r = to_device(make_weights(desc, 7), "cuda"), make_router(desc, 7).cuda()
     ctx = P.FirstContext(desc, w, r, max_batch=3, max_seq_len=120, stream=stream)
+    ctx.set_option(OPT_BATCH_STEP, 1)
     torch.cuda.synchronize()
     ctx.prefill_route(torch.cat([make_prompt(desc.vocab, k, b) for b, k in enumerate(lens)]).cuda(), lens)
     for b in range(3):
@@ -224,6 +230,7 @@ def test_sequences_and_layers_that_come_and_go():
     for path in (0, -1):
         ctx = P.FirstContext(desc, w, r, max_batch=16, max_seq_len=420)
         ctx.set_option(3, path)
+        ctx.set_option(OPT_BATCH_STEP, 1)
         for turn, B in enumerate((16, 3, 9, 16, 2)):
             lens = [5 + 37 * ((b + turn) % 11) for b in range(B)]
             ctx.prefill_route(torch.cat([make_prompt(desc.vocab, k, turn + b) for b, k in enumerate(lens)]).cuda(), lens)
@@ -233,3 +240,31 @@ def test_sequences_and_layers_that_come_and_go():
         ctx.close()
     for a, b in zip(out[:5], out[5:]):
         assert float((a - b).abs().max()) <= TOLERANCE and not torch.equal(a, b)
+
+
+@pytest.mark.parametrize("width,ffn,heads,lens,first", [
+    (512, 1536, 8, [40, 300, 9], 2),                             # 14 us to gain, 9 a layer
+    (2560, 1024, 20, [40, 300, 9], 7),                           # 320 units of rows on 256 compute units: 2 a layer
+    (2560, 1024, 20, [900, 700, 800], 3),                        # ... and 3 more where sequences are split
+], ids=str)
+def test_few_layers_take_the_launches(width, ffn, heads, lens, first):
+    """From `first` kept layers on a step has the bits of the one kernel, with fewer those of the launches per op."""
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the numbers of layers are those of 256 compute units")
+    desc, B = ModelDesc(8, width, heads, heads // 4, 64, ffn, 1003, dtype="bf16"), len(lens)
+    w, r = to_device(make_weights(desc, 9), "cuda"), make_router(desc, 9).cuda()
+    ids = torch.cat([make_prompt(desc.vocab, k, 9 + b) for b, k in enumerate(lens)]).cuda()
+    masks, out = [[[int(i < k) for i in range(8)]] * B for k in (8, first, first - 1)], []
+    for path, force in ((0, 0), (-1, 0), (-1, 1)):
+        ctx = P.FirstContext(desc, w, r, max_batch=B, max_seq_len=max(lens) + 10)
+        ctx.set_option(3, path)
+        ctx.set_option(OPT_BATCH_STEP, force)
+        kept = []
+        for m in masks:
+            ctx.prefill_route(ids, lens)
+            kept.append(_steps(ctx, desc, [m], 3, 5))
+        out.append(kept)
+        ctx.close()
+    launches, auto, one = out
+    assert all(not torch.equal(a, b) for a, b in zip(launches, one))
+    assert [torch.equal(a, b) for a, b in zip(auto, one)] == [True, True, False] and torch.equal(auto[2], launches[2])
