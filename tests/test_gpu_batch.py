@@ -15,7 +15,9 @@ from tests.test_gpu_path import _decode, _prefill
 pytestmark = pytest.mark.gpu
 torch.set_grad_enabled(False)
 
-OPT_BATCH_PATH = 6
+OPT_DECODE_PATH, OPT_BATCH_PATH, OPT_BATCH_STEP = 3, 6, 12
+# Models whose widths are multiples of 256 have their steps in one kernel too: the oracle tests run both ways.
+both_ways = pytest.mark.parametrize("one_kernel", [False, True], ids=["launches", "one kernel"])
 
 
 def _masks(L, B, seed):
@@ -27,12 +29,14 @@ def _masks(L, B, seed):
     return out
 
 
-def _run(model, lens, n_steps, seed, page=16, splits=0, masks=None):
+def _run(model, lens, n_steps, seed, page=16, splits=0, masks=None, one_kernel=None):
     desc = CONFIGS[model]
     B = len(lens)
     prompts = [make_prompt(desc.vocab, n, seed + 10 * b) for b, n in enumerate(lens)]
     desc, w, router, ctx = build(model, seed, max_batch=B, max_seq_len=max(lens) + n_steps + 8, page=page)
     ctx.set_option(OPT_BATCH_PATH, 1)
+    if one_kernel is not None:
+        ctx.set_option(OPT_BATCH_STEP if one_kernel else OPT_DECODE_PATH, int(one_kernel))
     ctx.set_option(2, splits)
     _prefill(ctx, desc, prompts)
     masks = masks or _masks(desc.n_layers, B, seed)
@@ -72,8 +76,9 @@ def test_batch16_mixed_masks_matches_oracle_per_sequence():
     _run("mini_bf16", lens, 6, 61)                               # d_ffn = 1416: ragged last MFMA step
 
 
-def test_batch16_wide_model_matches_oracle():
-    _run("step_hd128", [40 + 3 * b for b in range(16)], 4, 63)  # widths 2048 / 4096, K split over waves
+@both_ways
+def test_batch16_wide_model_matches_oracle(one_kernel):
+    _run("step_hd128", [40 + 3 * b for b in range(16)], 4, 63, one_kernel=one_kernel)  # widths 2048 / 4096, K split over waves
 
 
 def test_batch4_long_context_matches_oracle():
@@ -84,15 +89,17 @@ def test_few_attention_splits_walk_several_key_tiles_per_wave():
     _run("mini_hd128", [1500, 700, 90], 3, 66, splits=2)
 
 
-def test_attention_work_list_with_very_different_lengths():
+@both_ways
+def test_attention_work_list_with_very_different_lengths(one_kernel):
     # one to a dozen splits per sequence in the same launch (splits in proportion to the lengths)
-    _run("step_hd128", [20, 300, 1500, 64, 700], 3, 75)
+    _run("step_hd128", [20, 300, 1500, 64, 700], 3, 75, one_kernel=one_kernel)
 
 
-def test_long_batched_run_keeps_its_graph_while_the_sequences_grow():
+@both_ways
+def test_long_batched_run_keeps_its_graph_while_the_sequences_grow(one_kernel):
     # 140 steps on one cached graph: every sequence crosses key-tile and page boundaries several times, so the splits
     # of the attention work list (fixed when the graph was built) get longer, and new pages enter the tables
-    _run("step_hd128", [60, 130, 20], 140, 77)
+    _run("step_hd128", [60, 130, 20], 140, 77, one_kernel=one_kernel)
 
 
 def test_attention_without_a_work_list_when_the_batch_needs_too_many_items():
@@ -210,6 +217,7 @@ def test_a_short_sequence_that_outgrows_its_one_workgroup_beside_a_long_one(mode
     for drop in (False, True):
         _, _, _, ctx = build(model, 98, max_batch=2, max_seq_len=4000)
         ctx.set_option(OPT_BATCH_PATH, 1)
+        ctx.set_option(OPT_DECODE_PATH, 0)                         # (a step in one kernel looks at the lengths itself)
         _prefill(ctx, desc, prompts)
         ctx.set_mask(0, [1] + [0] * (desc.n_layers - 1))          # the other layers are the short sequence's alone
         ctx.set_mask(1, [1] * desc.n_layers)

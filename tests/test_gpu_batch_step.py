@@ -1,4 +1,4 @@
-"""All layers of a batched decode step in one kernel against the launches per op (option 3 = 0), which the oracle tests of the batched path pin."""
+"""All layers of a batched decode step in one kernel against the launches per op (option 3 = 0).  The oracle tests of the batched path run both."""
 import pytest
 import torch
 
@@ -34,7 +34,8 @@ def _steps(ctx, desc, masks, n, first):
 
 # (layers, width, heads, KV heads, head dimension, FFN width), contexts.  Workgroups without a row (32 units for 256 of them), with one or two units and with half
 # tiles (288, 544), pairs of waves without a share of K, a last pass that is not whole (2304, 4352); 4, 8 and 16 slots, all used or not; one and several splits;
-# contexts at the edges of pages and tiles.
+# contexts at the edges of pages and tiles; a split of more tiles than page ids are fetched ahead for; more items of attention than compute units; contexts that
+# need two splits whatever else there is.
 @pytest.mark.parametrize("shape,lens", [
     ((3, 256, 4, 2, 64, 256), [1, 16, 63, 64]),
     ((3, 256, 4, 1, 64, 512), [5, 900]),
@@ -44,6 +45,9 @@ def _steps(ctx, desc, masks, n, first):
     ((2, 1536, 12, 4, 64, 2560), [2047, 40, 9]),
     ((2, 2048, 8, 4, 128, 2048), [30] * 8),
     ((3, 2048, 4, 1, 64, 512), [1000, 30, 700]),              # (waves that merge splits and have no share of the output projection's K)
+    ((2, 512, 32, 16, 64, 512), [4310] + [20 + b for b in range(15)]),      # (16 items a KV head: one split each, the first of 68 tiles)
+    ((2, 512, 64, 32, 64, 512), [33 + 9 * b for b in range(16)]),           # (512 items)
+    ((2, 256, 4, 2, 64, 256), [16390, 50]),
 ], ids=str)
 @pytest.mark.parametrize("graph", [1, 0])
 def test_one_kernel_agrees_with_launches_per_op(shape, lens, graph):
@@ -74,10 +78,11 @@ def test_one_kernel_agrees_with_launches_per_op(shape, lens, graph):
 
 
 def test_batched_and_single_steps_on_streams_of_their_own():
-    """Two kernels that each need the whole chip, a few microseconds behind each other: each context has the bits that it has alone."""
+    """Kernels that each need the whole chip, and small fp32 models' between them, which then have no room, a few microseconds behind each other: each context has
+    the bits that it has alone."""
     def contexts():
         out = []
-        for model, lens in (("step_hd128", [40, 21, 300]), ("step_hd64", [70]), ("step_g2", [90] * 5)):
+        for model, lens in (("step_hd128", [40, 21, 300]), ("step_hd64", [70]), ("mini_fp32", [60]), ("step_g2", [90] * 5), ("mini_fp32", [31])):
             desc, _, _, ctx = build(model, 11, max_batch=len(lens), max_seq_len=400)
             ctx.set_option(OPT_BATCH_STEP, 1)
             ctx.prefill_route(torch.cat([make_prompt(desc.vocab, k, 5 + b) for b, k in enumerate(lens)]).cuda(), lens)
@@ -268,3 +273,29 @@ def test_few_layers_take_the_launches(width, ffn, heads, lens, first):
     launches, auto, one = out
     assert all(not torch.equal(a, b) for a, b in zip(launches, one))
     assert [torch.equal(a, b) for a, b in zip(auto, one)] == [True, True, False] and torch.equal(auto[2], launches[2])
+
+
+def test_sampled_steps_draw_from_the_logits_of_the_one_kernel():
+    desc, lens = ModelDesc(3, 512, 8, 2, 64, 768, 1003, dtype="bf16"), [40, 300, 9, 65, 20]
+    w, r, B = to_device(make_weights(desc, 10), "cuda"), make_router(desc, 10).cuda(), len(lens)
+    ids = torch.cat([make_prompt(desc.vocab, k, 10 + b) for b, k in enumerate(lens)]).cuda()
+    u, out = torch.linspace(0.05, 0.95, B, device="cuda"), []
+    for path in (0, -1):
+        ctx = P.FirstContext(desc, w, r, max_batch=B, max_seq_len=320)
+        ctx.set_option(3, path)
+        ctx.set_option(OPT_BATCH_STEP, 1)
+        ctx.prefill_route(ids, lens)
+        for b in range(B):
+            ctx.set_mask(b, [1] * desc.n_layers)
+        lg, cand, drawn = torch.zeros(B, desc.vocab, device="cuda"), torch.zeros(B, 10, dtype=torch.int32, device="cuda"), torch.zeros(B, 10, dtype=torch.int32, device="cuda")
+        tk, again = torch.zeros(B, dtype=torch.int32, device="cuda"), torch.zeros(B, dtype=torch.int32, device="cuda")
+        for s in range(6):
+            fed = torch.tensor([(3 + 7 * s + 13 * b) % desc.vocab for b in range(B)], dtype=torch.int32, device="cuda")
+            ctx.decode_step_sampled(fed, u, 0.8, 10, lg, tk, cand)
+            ctx.sync()
+            P.sample_top_k_static(lg, u, 0.8, 10, again, drawn)
+            torch.cuda.synchronize()
+            assert torch.equal(tk, again) and torch.equal(cand, drawn)
+            out.append(lg.clone())
+        ctx.close()
+    assert float((torch.stack(out[:6]) - torch.stack(out[6:])).abs().max()) <= TOLERANCE and not torch.equal(out[0], out[6])

@@ -15,6 +15,7 @@ torch.set_grad_enabled(False)
 
 OPT_DECODE_PATH = 3
 OPT_BATCH_PATH = 6
+OPT_BATCH_STEP = 12
 
 
 def _setup(model, n_layers, lens, want, seed):
@@ -94,8 +95,8 @@ def test_more_kept_layers_than_slots_is_a_capacity_error():
     ctx.close()
 
 
-@pytest.mark.parametrize("batch_path", [1, 0])
-def test_batch_shares_slices_per_layer_and_a_new_prefill_starts_over(batch_path):
+@pytest.mark.parametrize("batch_path,option", [(1, (OPT_DECODE_PATH, 0)), (1, (OPT_BATCH_STEP, 1)), (0, (OPT_BATCH_STEP, 0))], ids=["launches", "one kernel", "one by one"])
+def test_batch_shares_slices_per_layer_and_a_new_prefill_starts_over(batch_path, option):
     """Three sequences with different masks: slices = union of the kept layers.  Then a second
     prefill in the same context with other prompts (other masks): the slices are handed out anew."""
     want = [[1, 0, 0, 1, 0], [1, 1, 0, 0, 0], [0, 0, 0, 1, 0]]
@@ -105,6 +106,7 @@ def test_batch_shares_slices_per_layer_and_a_new_prefill_starts_over(batch_path)
     _, _, _, full = build("step_hd128", 85, max_batch=3, max_seq_len=128, router=router, desc=desc)
     for c in (ctx, full):
         c.set_option(OPT_BATCH_PATH, batch_path)
+        c.set_option(*option)
     for round_, order in enumerate(([0, 1, 2], [2, 0])):
         ps = [prompts[b] for b in order]
         states = [O.prefill_route(desc, w, router, p, elide_kv=True) for p in ps]
