@@ -21,7 +21,7 @@ import tempfile
 
 from .build import FLAGS, SRC
 
-KERNELS = ("k_step", "k_attn_tiles_b", "k_attn_mfma_b", "k_bgemv", "k_gemm_nt_bf16_hl")
+KERNELS = ("k_step", "k_attn_tiles_b", "k_attn_mfma_b", "k_batch_step", "k_bgemv", "k_gemm_nt_bf16_hl", "k_pgemm", "k_attn_prompt")
 
 
 def _regs(tok: str):
@@ -114,6 +114,8 @@ def touched_in_flight(asm: str, keys=KERNELS):
                     events.append(seq)
                     returns = m.group(2) == "load" or (m.group(2) == "atomic" and m.group(3).rstrip(",").startswith("v") and
                                                        (" sc0" in t or " glc" in t))
+                    if re.search(r"\blds\b", t):         # (its registers are an address: the data goes to LDS)
+                        continue
                     if returns and in_asm:               # (the compiler waits for the loads it issues itself before it reuses their registers)
                         for r in _regs(m.group(3).rstrip(",")):
                             inflight[r] = seq

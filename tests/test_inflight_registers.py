@@ -84,6 +84,25 @@ _ZN5first6k_stepILi128EEEvNS_10StepParamsE:
     assert not asm_check.touched_in_flight(managed)
 
 
+def test_scan_counts_a_load_into_lds_but_has_no_destination_for_it():
+    text = """
+_ZN5first12k_batch_stepILi128ELi4EEEvNS_9BatchStepE:
+	;;#ASMSTART
+	global_load_dwordx4 v[2:5], v[10:11], off
+	;;#ASMEND
+	;;#ASMSTART
+	buffer_load_dwordx4 v12, s[4:7], s8 offen lds
+	;;#ASMEND
+	v_add_u32_e32 v12, 16, v12
+	s_waitcnt vmcnt(1)
+	v_add_f32_e32 v20, v2, v3
+	s_endpgm
+"""
+    assert asm_check.touched_in_flight(text) == []
+    hits = asm_check.touched_in_flight(text.replace("vmcnt(1)", "vmcnt(2)"))
+    assert len(hits) == 1 and hits[0][3] == [2, 3]       # the load into LDS is the younger of the two
+
+
 def test_no_kernel_of_the_library_touches_a_load_destination_in_flight():
     asm = asm_check.assembly()
     seen = asm_check.kernels_seen(asm)
