@@ -31,11 +31,12 @@
 // not come: a streaming wave without its activations does not count itself done, a serving wave without all sums stores none.
 //
 // us a step, launches per op / this kernel, bf16, embedding and head included: 8B shape, eight layers, 16 sequences of 256 to 2048 keys 1165 / 1120 (436 MB of
-// weights a layer: 61 us at the 7.1 TB/s of a large read, 112 here); four of 16384 keys, four layers 782 / 746; 3B shape, six layers, three
+// weights a layer: 61 us at the 7.1 TB/s of a large read, 112 here); four of 16384 keys, three layers 633 / 608; 3B shape, six layers, three
 // sequences 572 / 540; 1B shape, four layers, 16 of 1000 keys 338 / 297; eight layers, four of 300 keys 502 / 439.  What is left above
 // the bytes: about 7 us at each of a layer's five exchanges (the slowest workgroup, 3 to 5 us behind the median; the sums over the pairs; the poll; the first
-// activations into LDS).  Variants that were slower: K cut across the workgroups, with partial sums to add up (four of 16384 keys 2 % slower than launches
-// per op); squares of the norms polled together with the activations (b16 2 % slower: four times the words a poll reads).
+// activations into LDS), each workgroup's own copy of the activations among it (at sixteen slots 1.7 MB a layer of the 8B shape, as many bytes as its weights).  Variants that
+// were slower: K cut across the workgroups, with partial sums to add up (four of 16384 keys 2 % slower than launches per op, sixteen sequences 1.4 % faster
+// where this is 3.9); squares of the norms polled together with the activations (b16 2 % slower: four times the words a poll reads).
 #pragma once
 #include "decode_batch_kernels.h"
 
@@ -96,7 +97,7 @@ __host__ __device__ inline int bs_tiles(const BsPhase& p, int ncu, bool two) {
 }
 constexpr int BS_X_LDS = BS_PAIRS * 32 * 1024;        // every pair: 32 / slots passes of 1 KB a slot
 __host__ __device__ inline size_t bs_lds(int x_bytes, int acc_tiles, int own) {
-  return (size_t)x_bytes + (size_t)BS_PAIRS * acc_tiles * 1024 + sizeof(float) * (own * 16 + BS_MAX_L + BS_PAGES + 16 + BS_WORKS + 16 + 16 + 16 + 4 * 16 + 16);
+  return (size_t)x_bytes + (size_t)BS_PAIRS * acc_tiles * 1024 + sizeof(float) * (own * 16 + BS_MAX_L + BS_PAGES + 16 + BS_WORKS + 16 + 16 + 16);
 }
 
 __device__ __forceinline__ BatchStep bs_params() { return sk_const<BatchStep>(sk_args()); }
@@ -364,10 +365,9 @@ __global__ void __launch_bounds__(BS_THREADS) k_batch_step(BatchStep) {
   int* pages = kept + BS_MAX_L;                                 // of this workgroup's item of attention
   int* pos = pages + BS_PAGES;
   int* works = pos + 16;                                        // attention: slot | split << 8, in the order of the slots
-  int *wbeg = works + BS_WORKS, *wcnt = wbeg + 16;              // a slot's first one, its number (= its splits)
+  int* wcnt = works + BS_WORKS;                                 // a slot's splits
   float* rinv = reinterpret_cast<float*>(wcnt + 16);
-  float* sqs = rinv + 16;                                       // [serving wave][16] squares
-  int* ctl = reinterpret_cast<int*>(sqs + 4 * 16);
+  int* ctl = reinterpret_cast<int*>(rinv + 16);
   int *bad = ctl, *done = ctl + 1, *n_works = ctl + 2, *n_kept = ctl + 3, *staged = ctl + 4, *consumed = ctl + 8;
   if (wave == 0) {                                              // layers that somebody keeps
     const BatchStep P = bs_params();
@@ -576,7 +576,7 @@ __global__ void __launch_bounds__(BS_THREADS) k_batch_step(BatchStep) {
 #pragma unroll
     for (int o = 1; o < 16; o <<= 1) { const int v = __shfl_up(before, o, 64); if (lane >= o) before += v; }
     if (lane < 16) {
-      wbeg[lane] = before - mine; wcnt[lane] = mine;
+      wcnt[lane] = mine;
       for (int q = 0; q < mine; ++q) works[before - mine + q] = lane | (q << 8);
       if (lane == 15) *n_works = before;
     }
