@@ -28,7 +28,8 @@ SCRATCH_LIMITS = {"k_step": 0, "k_attn_tiles_b": 32, "k_attn_mfma_b": 0, "k_bgem
 
 # Registers a lane (vector and accumulation ones together) of the two kernels whose workgroups wait for each other: a SIMD has 512, and two
 # waves of k_step and one of k_small_step have to fit on it together.  With more, a step of each on two streams could hold what the other
-# waits for.  (k_small_step loads nothing through inline asm; its scratch limit is what it took at first, 84 to 104 now, so that more is noticed.)
+# waits for.  (k_small_step loads nothing through inline asm; its scratch limit bounds its speed alone: it takes 84 to 104 bytes, and the 228 to 236 of an
+# earlier form were no fault.)
 REGISTER_LIMITS = {"k_step": 192, "k_small_step": 128}
 
 

@@ -234,9 +234,10 @@ __global__ void __launch_bounds__(AT_THREADS, 4) k_attn_tiles_b(BatchParams P) {
 // hardware and their request ahead of the page ids 6.5 us less a launch at 40 keys).  The host sizes the grid to about one workgroup per
 // compute unit.  Sixteen sequences of 4000 keys, us a layer less than k_attn_tiles_b: 3B heads 64, 1B heads 51.
 // Short contexts are bound by the serial chain in front of and behind the walk (16 sequences of 1000 keys with the 8B heads: some 15 us a launch
-// for 65 MB).  What belongs to it is kept short: pages that do not exist are not requested, and the subgroups' sums meet in 24 or 28 exchanges (us a
-// step before and after, eight launches: 8B heads, 16 sequences of 256 .. 2048 keys 9335 / 9225; 1B heads, four of 300 4020 / 3920; four of 16384 keys
-// 6275 / 6280: there HBM is the bound).
+// for 65 MB).  What belongs to it is kept short: pages that do not exist are not requested, and the subgroups' sums meet in 24 or 28 exchanges (us
+// before and after, eight steps as launches per op: 8B shape, eight layers, 16 sequences of 256 .. 2048 keys 9302 / 9210; 1B shape, eight layers, four of 300 4024 / 3925;
+// 8B shape, three layers, four of 16384 keys 5066 / 5071: there HBM is the bound.  112 geometries and lengths, 1024-wide models of six layers: 3 % less on average;
+// two sequences of 700 keys 1 to 2 % more).
 // (An earlier version relayed 64-key tiles through 128 KB of LDS with a workgroup barrier per
 // pair of tiles: 0.4 % slower steps at 16 k keys.)
 constexpr int AS_THREADS = SK_WAVES * 64;

@@ -13,10 +13,11 @@
 // launch that follows.  No vector ever has epoch 0: a launch whose epochs would not all lie below 2^32 begins again at 1 (after hours of
 // steps; every word then carries an epoch of the launches just before, far from 1, or a layer's has not been written in that whole cycle).
 //
-// A word is never overwritten before everyone has read it: each vector is written again one layer later, by workgroups that have
-// seen complete vectors since to which EVERY workgroup contributed after reading this one (each owns at least one row
-// of each mat-vec, see small_step_wgs).  The residual h is written twice a layer; the MLP's activation lies between, and attention's
-// output before.
+// A word is never overwritten before everyone has read it: whoever writes it again has seen a complete vector since to which EVERY workgroup contributed
+// after reading it (each owns at least one row of each mat-vec, see small_step_wgs).  Where attention's output goes round, the residual h is written twice a
+// layer, behind the projections and attention's output and behind the MLP's activation.  Where the heads' shares of the output projection go round (BY_HEAD), h is
+// written once a layer, behind the MLP's activation, which every workgroup stores after it has read h and the shares; the shares are written again by workgroups that have seen the
+// next layer's projections of their head, stored by workgroups that had seen the whole h of the layer before.
 //
 // Weights of a wave's first rows are requested before it waits for the vector they are multiplied with; the keys and values of a wave's
 // first tile before it waits for the queries.  The waits are bounded as in the persistent kernel (sk_poll_give_up).

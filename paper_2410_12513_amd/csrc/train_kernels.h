@@ -94,10 +94,13 @@ constexpr int LM_COLS = 1024;      // columns per workgroup: 128 threads x 8 col
 constexpr int LM_RMAX = 32;        // largest rank (LDS: r * LM_COLS floats + the Bm rows)
 constexpr int LM_RG = 4;           // rows per thread and iteration
 
-// A matrix that the caches would not hold until it is next used goes past them (NT): what it would push out is written back meanwhile.  us of all matrices of an
-// 8B layer, bf16 (436 MB, rank 8): 205 / 190 with and without its small ones; matrices of a layer that the 256 MB memory-side cache holds are up to 15 %
-// slower that way (two of 117 MB in turn 41 / 48), fp32 ones of any size 5 to 12 %.  Ranks above 8, where W waits for the sums, gain from
-// 32 MB on: 4096 x 4096 rank 16 bf16 44.6 / 32.0, fp32 65.0 / 45.6; 14336 x 4096 rank 32 242 / 169 and 288 / 185; 1024 x 4096 fp32 17.3 / 18.2.
+// A matrix that the caches would not hold until it is next used goes past them (NT): what it would push out is written back meanwhile.  A program merges the
+// matrices of a model once each; us through the caches / past them, bf16 of rank 8, matrices of a size in turn, 1.2 GB in all: 64 MB 31.1 / 29.6, 80 MB 37.5 / 35.6,
+// 96 MB 43.3 / 41.8, 112 MB 50.4 / 48.8, 192 MB 80.7 / 78.8; rank 1 the same gains; all matrices of an 8B layer 208 / 192, of four layers 839 / 808.  The line lies at 64 MB because
+// the 32 and 48 MB ones of the 8B and 3B shapes were left as they are.  What is slower past the caches is a matrix, or two, merged again at once while the 256 MB
+// memory-side cache holds them: 112 MB 41 / 48, two of 64 MB in turn 24.0 / 29.3, one of 192 MB 64 / 77.  fp32 of rank 8 is 5 to 12 % slower past them at any size.
+// Ranks above 8, where W waits for the sums, gain from 32 MB on, again at once or in turn: 4096 x 4096 rank 16 bf16 44.0 / 31.8, fp32 65.4 / 45.7; 14336 x 4096
+// rank 32 234 / 171 and 286 / 189; only 14336 x 4096 fp32 rank 16 is slower if merged again at once (106 / 112; in turn 120 / 114).
 __host__ inline bool lora_past_caches(size_t bytes, bool is_bf16, int r) { return r > 8 ? bytes >= (32u << 20) : is_bf16 && bytes >= (64u << 20); }
 template <bool NT> __device__ __forceinline__ u32x4_t lora_ld(const void* p) {
   return NT ? __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(p)) : *reinterpret_cast<const u32x4_t*>(p);
