@@ -9,7 +9,7 @@
 // tile is multiplied with both halves, accumulating in fp32.  RMSNorm's gain is applied before
 // the split and its 1/rms after the product (it is one scalar per sequence).
 //
-// batch_step.h runs all of a step's layers in one kernel where it can; the launches below serve the rest: other geometries, more than sixteen sequences, fixed
+// batch_step.h runs all of a step's layers in one kernel where it can; the launches below serve the rest: other geometries, more than sixteen sequences, few kept layers, fixed
 // numbers of splits, steps under capture.
 #pragma once
 #include "decode_kernels.h"
